@@ -139,10 +139,19 @@ __device__ __forceinline__ float4 load_w4_rows(const float* base, int row, int d
 }
 
 // Weight access mode of a kernel instance.  kWGeneric checks every element against the row end
-// (any d_out, any alignment).  The other two are for layers whose rows are 16-byte aligned and a
+// (any d_out, any alignment).  kWVector* are for layers whose rows are 16-byte aligned and a
 // multiple of 64 columns long: every access is one unconditional 16-byte instruction, which lets
 // the compiler issue a trip's loads back to back with no control flow between them.
-constexpr int kWGeneric = 0, kWVector = 1, kWVectorStream = 2;
+// kWRagged* do the same for every other layer of at least 64 columns.  A load is one unconditional
+// 16-byte instruction at 4-byte alignment (which global memory instructions take); in the last
+// column chunk it may run over the end of the row, by at most 62 columns: into the next row, or
+// behind the last row into the layer's biases, of which there are at least 64 -- always inside the
+// replica's own parameters.  What it finds there is never used: the kernels zero those columns
+// where they are an operand of a sum, and the stores stop at the row end.
+constexpr int kWGeneric = 0, kWVector = 1, kWVectorStream = 2, kWRagged = 3, kWRaggedStream = 4;
+constexpr bool weight_ragged(int wm) { return wm == kWRagged || wm == kWRaggedStream; }
+constexpr bool weight_streams(int wm) { return wm == kWVectorStream || wm == kWRaggedStream; }
+typedef f32x4 f32x4_u __attribute__((aligned(4)));   // four floats at any float address
 
 template <int WM>
 __device__ __forceinline__ float4 load_wm(const float* row, int c, int d_out, bool vec) {
@@ -150,6 +159,12 @@ __device__ __forceinline__ float4 load_wm(const float* row, int c, int d_out, bo
         return *reinterpret_cast<const float4*>(row + c);
     } else if constexpr (WM == kWVectorStream) {
         const f32x4 t = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(row + c));
+        return make_float4(t[0], t[1], t[2], t[3]);
+    } else if constexpr (WM == kWRagged) {
+        const f32x4 t = *reinterpret_cast<const f32x4_u*>(row + c);
+        return make_float4(t[0], t[1], t[2], t[3]);
+    } else if constexpr (WM == kWRaggedStream) {
+        const f32x4 t = __builtin_nontemporal_load(reinterpret_cast<const f32x4_u*>(row + c));
         return make_float4(t[0], t[1], t[2], t[3]);
     } else {
         return load_w4(row, c, d_out, vec, false);
@@ -161,6 +176,16 @@ __device__ __forceinline__ void store_wm(float* row, int c, int d_out, bool vec,
         *reinterpret_cast<float4*>(row + c) = v;
     } else if constexpr (WM == kWVectorStream) {
         __builtin_nontemporal_store(f32x4{v.x, v.y, v.z, v.w}, reinterpret_cast<f32x4*>(row + c));
+    } else if constexpr (weight_ragged(WM)) {
+        if (c + 3 < d_out) {
+            const f32x4 t{v.x, v.y, v.z, v.w};
+            if constexpr (WM == kWRaggedStream) __builtin_nontemporal_store(t, reinterpret_cast<f32x4_u*>(row + c));
+            else *reinterpret_cast<f32x4_u*>(row + c) = t;
+        } else {
+            if (c < d_out) row[c] = v.x;
+            if (c + 1 < d_out) row[c + 1] = v.y;
+            if (c + 2 < d_out) row[c + 2] = v.z;
+        }
     } else {
         store_w4(row, c, d_out, vec, false, v);
     }
