@@ -549,41 +549,80 @@ struct SoftmaxArgs {
     int eval;               // 1: loss[g] = sum over valid samples; 0: mean over B
 };
 
-// One block per group, one thread per sample.
+// One block per group and 16 samples, one wavefront per sample (4 samples each, one after the
+// other), the classes over its lanes; the deltas pass through LDS for the feature-major copy.  Every
+// block leaves one partial loss.  (One thread per sample walking its classes, one block per group,
+// took 53 us at 16 groups of 100 samples and 100 classes: a serial chain of three passes over
+// uncoalesced rows.  This form: 12 us, the launch and three dependent round trips.)
+constexpr int kSoftmaxRows = 16;
+constexpr int kMaxClasses = 1024;   // (the library refuses more)
 template <typename OT>
-__global__ __launch_bounds__(128) void softmax_kernel(SoftmaxArgs a) {
-    __shared__ float red[128];
-    const int g = blockIdx.x, b = threadIdx.x;
-    float nll = 0.f;
-    if (b < a.B) {
-        const int y = a.labels[static_cast<int64_t>(g) * a.Bp + b];
+__global__ __launch_bounds__(256) void softmax_kernel(SoftmaxArgs a) {
+    __shared__ OT dl[kSoftmaxRows][kMaxClasses + 2];
+    __shared__ float nll_s[kSoftmaxRows];
+    const int g = blockIdx.x, b0 = blockIdx.y * kSoftmaxRows;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int kPerLane = kMaxClasses / 64;
+    for (int i = 0; i < kSoftmaxRows / 4; ++i) {
+        const int r = wave + 4 * i, b = b0 + r;   // uniform over the wavefront
+        float nll = 0.f;
+        const int y = b < a.B ? a.labels[static_cast<int64_t>(g) * a.Bp + b] : -1;
         if (y >= 0) {
             const float* z = a.logits + (static_cast<int64_t>(g) * a.Bp + b) * a.dpL;
-            float zmax = z[0];
-            for (int c = 1; c < a.C; ++c) zmax = fmaxf(zmax, z[c]);
-            float s_other = 0.f;
-            for (int c = 0; c < a.C; ++c) s_other += c == y ? 0.f : expf(z[c] - zmax);
-            const float e_y = expf(z[y] - zmax);
+            float zc[kPerLane], zmax = z[0];
+#pragma unroll
+            for (int u = 0; u < kPerLane; ++u) {
+                const int c = lane + 64 * u;
+                if (64 * u < a.C) {   // uniform
+                    zc[u] = c < a.C ? z[c] : z[0];
+                    zmax = fmaxf(zmax, zc[u]);
+                }
+            }
+            for (int w = 32; w > 0; w >>= 1) zmax = fmaxf(zmax, __shfl_xor(zmax, w));
+            float s_other = 0.f, e_y = 0.f;
+#pragma unroll
+            for (int u = 0; u < kPerLane; ++u) {
+                const int c = lane + 64 * u;
+                if (c >= a.C) continue;
+                const float e = expf(zc[u] - zmax);
+                if (c == y) e_y = e;
+                else s_other += e;
+                zc[u] = e;
+            }
+            for (int w = 32; w > 0; w >>= 1) {
+                s_other += __shfl_xor(s_other, w);
+                e_y += __shfl_xor(e_y, w);
+            }
             nll = xent_loss(s_other, e_y, z[y] - zmax);
             if (a.dz_bm) {
                 OT* dbm = static_cast<OT*>(a.dz_bm) + (static_cast<int64_t>(g) * a.Bp + b) * a.dpL;
-                OT* dfm = static_cast<OT*>(a.dz_fm) + static_cast<int64_t>(g) * a.dpL * a.Bp + b;
                 const float inv = 1.f / (s_other + e_y), invB = 1.f / static_cast<float>(a.B);
-                for (int c = 0; c < a.C; ++c) {
-                    const OT d = static_cast<OT>(xent_delta(expf(z[c] - zmax), c == y, s_other, inv) * invB);
+#pragma unroll
+                for (int u = 0; u < kPerLane; ++u) {
+                    const int c = lane + 64 * u;
+                    if (c >= a.C) continue;
+                    const OT d = static_cast<OT>(xent_delta(zc[u], c == y, s_other, inv) * invB);
                     dbm[c] = d;
-                    dfm[static_cast<int64_t>(c) * a.Bp] = d;
+                    dl[r][c] = d;
                 }
             }
         }
+        if (lane == 0) nll_s[r] = nll;
     }
-    red[b] = nll;
     __syncthreads();
-    for (int w = 64; w > 0; w >>= 1) {
-        if (b < w) red[b] += red[b + w];
-        __syncthreads();
+    if (a.dz_bm) {
+        // (a sample without a label leaves its deltas as they are; with training labels there is none)
+        for (int e = tid; e < a.C * kSoftmaxRows; e += 256) {
+            const int c = e / kSoftmaxRows, r = e % kSoftmaxRows, b = b0 + r;
+            if (b < a.B && a.labels[static_cast<int64_t>(g) * a.Bp + b] >= 0)
+                static_cast<OT*>(a.dz_fm)[(static_cast<int64_t>(g) * a.dpL + c) * a.Bp + b] = dl[r][c];
+        }
     }
-    if (b == 0) a.loss[static_cast<int64_t>(g) * kLossParts] = a.eval ? red[0] : red[0] / static_cast<float>(a.B);
+    if (tid == 0) {
+        float sum = 0.f;
+        for (int r = 0; r < kSoftmaxRows; ++r) sum += nll_s[r];
+        a.loss[static_cast<int64_t>(g) * kLossParts + blockIdx.y] = a.eval ? sum : sum / static_cast<float>(a.B);
+    }
 }
 
 // ------------------------------------------------------------------- backward
@@ -1486,14 +1525,16 @@ hipError_t launch_softmax(lc_handle* h, bool eval, int loss_offset) {
     a.dz_bm = eval ? nullptr : S.dz_bm[h->L];
     a.dz_fm = eval ? nullptr : S.dz_fm[h->L];
     a.loss = S.loss + static_cast<int64_t>(loss_offset) * kLossParts;
-    (eval ? h->loss_parts_eval : h->loss_parts_train) = 1;
+    const int parts = (S.B + kSoftmaxRows - 1) / kSoftmaxRows;
+    static_assert(128 / kSoftmaxRows <= kLossParts, "one partial loss per block");
+    (eval ? h->loss_parts_eval : h->loss_parts_train) = parts;
     a.C = h->layer[h->L].d_out;
     a.dpL = h->layer[h->L].dp_out;
     a.B = S.B;
     a.Bp = S.Bp;
     a.eval = eval ? 1 : 0;
-    if (bf16) hipLaunchKernelGGL((softmax_kernel<bf16_t>), dim3(S.G), dim3(128), 0, h->stream, a);
-    else hipLaunchKernelGGL((softmax_kernel<float>), dim3(S.G), dim3(128), 0, h->stream, a);
+    if (bf16) hipLaunchKernelGGL((softmax_kernel<bf16_t>), dim3(S.G, parts), dim3(256), 0, h->stream, a);
+    else hipLaunchKernelGGL((softmax_kernel<float>), dim3(S.G, parts), dim3(256), 0, h->stream, a);
     return hipGetLastError();
 }
 

@@ -35,3 +35,21 @@ def test_one_step_with_ragged_rows(pkg, orc, dims, m, B, bf16):
     # what lies beyond a row's end belongs to others: the padding of every replica is still zero
     assert not run.X[:, run.P:].any() and not run.V[:, run.P:].any()
     run.close()
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("C,B", [(65, 1), (66, 16), (128, 17), (130, 128), (1024, 20)])
+def test_softmax_over_many_classes(pkg, orc, C, B, bf16):
+    _say(f"softmax C={C} B={B} bf16={bf16}")
+    dims, m = [24, C], 2
+    ref, run = _problem(pkg, orc, dims, m, B, bf16=bf16)
+    tol = TOL16 if bf16 else TOL32
+    masks = UnitMasks()
+    _ref_steps(orc, ref, 11, 1, masks)
+    run.local_steps(1)
+    _check_workers(run, ref, dims, tol, "one step", masks)
+    _check_losses(run, ref, tol, "local losses")
+    ref.average()
+    run.average()
+    assert abs(run.loss() - ref.loss()) < TOL32 * ref.loss()
+    run.close()
