@@ -693,7 +693,8 @@ int lc_loss(lc_handle* h, double* out) {
         hipError_t e = hipSuccess;
         for (int p = 0; p < passes && e == hipSuccess; ++p) {
             e = launch_gather(h, true, static_cast<int64_t>(p) * per_pass, 1);
-            for (int l = 1; l <= h->L && e == hipSuccess; ++l) e = launch_forward(h, true, l, p * h->eval.G);
+            for (int l = 1; l <= h->L && e == hipSuccess; ++l)
+                e = eval_layer_ok(h, l) ? launch_eval_layer(h, l) : launch_forward(h, true, l, p * h->eval.G);
             if (e == hipSuccess && !forward_fuses_softmax(h)) e = launch_softmax(h, true, p * h->eval.G);
         }
         if (e == hipSuccess) e = hipMemcpyAsync(host, h->eval.loss, sizeof(float) * n, hipMemcpyDeviceToHost, h->stream);

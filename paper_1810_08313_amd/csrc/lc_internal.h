@@ -164,6 +164,8 @@ hipError_t launch_quad_loss(lc_handle* h, int* n_partial);
 
 hipError_t launch_gather(lc_handle* h, bool eval, int64_t k_or_base, int n_steps);
 hipError_t launch_forward(lc_handle* h, bool eval, int l, int loss_offset);
+bool eval_layer_ok(const lc_handle* h, int l);   // hidden layer of the evaluation pass as one dense product
+hipError_t launch_eval_layer(lc_handle* h, int l);
 bool forward_fuses_softmax(const lc_handle* h);  // last layer's kernel also does a3
 hipError_t launch_softmax(lc_handle* h, bool eval, int loss_offset);
 hipError_t launch_backward(lc_handle* h, int l, bool da_only = false);   // da_only: dZ_{l-1} only, no update
