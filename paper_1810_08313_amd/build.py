@@ -10,7 +10,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblocalcomm.so")
 SOURCES = ["lc_api.hip", "lc_stream_kernels.hip", "lc_mlp_kernels.hip", "lc_resident_kernels.hip", "lc_first_layer_kernels.hip",
-           "lc_sync_kernels.hip", "lc_eval_kernels.hip"]
+           "lc_sync_kernels.hip", "lc_eval_kernels.hip", "lc_net_kernels.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

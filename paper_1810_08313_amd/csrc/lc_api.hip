@@ -148,7 +148,7 @@ size_t carve(lc_handle* h, char* base) {
         const int passes = eval ? (h->md.E + per_pass - 1) / per_pass : 1;
         S.loss = static_cast<float*>(c.take(sizeof(float) * static_cast<size_t>(S.G) * passes * kLossParts));
     }
-    if (resident_shape_ok(h)) {
+    if (resident_shape_ok(h) || net_shape_ok(h)) {
         h->res_a1x = static_cast<float*>(c.take(sizeof(float) * resident_exchange_floats(h)));
         h->res_ctr = static_cast<unsigned*>(c.take(sizeof(unsigned) * 384));
         h->res_avx = static_cast<float*>(c.take(sizeof(float) * 2 * static_cast<size_t>(h->m) * h->Ps));
@@ -511,10 +511,14 @@ int lc_local_periods(lc_handle* h, int tau, int n_periods) {
     if (tau < 1 || n_periods < 1) return LC_ERR_ARG;
     // In-kernel averaging pays while the m copies a workgroup has to read from the other replicas
     // (other XCDs) are small: measured on the 784-256-10 model at m = 8, 400 KB per workgroup take
-    // 15 us, more than ending the launch and running the averaging kernel costs.
-    const bool small = h->L == 1 || static_cast<int64_t>(h->m) * h->layer[1].dp_in * 64 <= 200 * 1024;
-    const bool fused = h->md.kind == LC_KIND_MLP && h->res_on && h->res_a1x && h->res_avx && !h->bm_on &&
-                       tau <= h->train.slots && (small || h->res_fuse_always);
+    // 15 us, more than ending the launch and running the averaging kernel costs.  (net_kernel: one
+    // workgroup reads m whole models.)
+    const bool mlp = h->md.kind == LC_KIND_MLP;
+    const int64_t copies = !mlp ? 0 : resident_shape_ok(h) ? static_cast<int64_t>(h->m) * h->layer[1].dp_in * 64
+                                                           : static_cast<int64_t>(h->m) * h->P * 4;
+    const bool small = (h->L == 1 && resident_shape_ok(h)) || copies <= 200 * 1024;
+    const bool fused = mlp && h->res_on && h->res_a1x && h->res_avx && !h->bm_on && tau <= h->train.slots &&
+                       h->m <= resident_workgroup_budget() && (small || h->res_fuse_always);
     if (!fused) return run_periods(h, tau, n_periods, true);
     // weights resident on chip: as many whole periods per launch as one gather launch has inputs
     // for, the averaging steps taken inside the kernel

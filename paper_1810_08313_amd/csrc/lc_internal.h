@@ -183,6 +183,10 @@ hipError_t launch_head(lc_handle* h);
 
 // resident path (weights stay in LDS over a run of local steps)
 bool resident_shape_ok(const lc_handle* h);
+int resident_workgroup_budget();   // workgroups of a whole compute unit each that are on the chip together
+// small networks of any depth, one compute unit per replica (shapes the resident kernels do not take)
+bool net_shape_ok(const lc_handle* h);
+hipError_t launch_net(lc_handle* h, int slot0, int n_steps, int period);
 size_t resident_exchange_floats(const lc_handle* h);
 hipError_t probe_block_placement(lc_handle* h);   // synchronises the stream once
 hipError_t launch_resident(lc_handle* h, int slot0, int n_steps, int period);  // the steps gathered into slots slot0 .. slot0+n_steps-1

@@ -68,6 +68,44 @@ __device__ __forceinline__ f32x4 mma8(const Frag<bf16_t>& a, const Frag<bf16_t>&
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b.v, c, 0, 0, 0);
 }
 
+// operand fragments of the 16-deep product: 4 consecutive reduction indices per lane
+template <typename OT>
+struct Frag4;
+template <>
+struct Frag4<float> {
+    float v[4];
+};
+template <>
+struct Frag4<bf16_t> {
+    bf16x4 v;
+};
+__device__ __forceinline__ Frag4<float> load4(const float* p) {
+    const float4 a = *reinterpret_cast<const float4*>(p);
+    return Frag4<float>{{a.x, a.y, a.z, a.w}};
+}
+__device__ __forceinline__ Frag4<bf16_t> load4(const bf16_t* p) {
+    Frag4<bf16_t> f;
+    f.v = *reinterpret_cast<const bf16x4*>(p);
+    return f;
+}
+__device__ __forceinline__ void pack4(Frag4<float>& f, float a, float b, float c, float d) {
+    f.v[0] = a; f.v[1] = b; f.v[2] = c; f.v[3] = d;
+}
+__device__ __forceinline__ void pack4(Frag4<bf16_t>& f, float a, float b, float c, float d) {
+    f.v[0] = static_cast<bf16_t>(a); f.v[1] = static_cast<bf16_t>(b);
+    f.v[2] = static_cast<bf16_t>(c); f.v[3] = static_cast<bf16_t>(d);
+}
+__device__ __forceinline__ f32x4 mma4(const Frag4<float>& a, const Frag4<float>& b, f32x4 c) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v[e], b.v[e], c, 0, 0, 0);
+    return c;
+}
+__device__ __forceinline__ f32x4 mma4(const Frag4<bf16_t>& a, const Frag4<bf16_t>& b, f32x4 c) {
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, a.v), __builtin_bit_cast(s16x4, b.v), c,
+                                                     0, 0, 0);
+}
+
 __device__ __forceinline__ float to_f32(float x) { return x; }
 __device__ __forceinline__ float to_f32(bf16_t x) { return static_cast<float>(x); }
 
