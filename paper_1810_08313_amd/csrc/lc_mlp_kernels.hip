@@ -773,8 +773,8 @@ __global__ __launch_bounds__(256) void backward_kernel(BwdArgs a) {
                 // weights are zeroed when used and they are never stored
                 const int rr = row < a.d_in ? row : a.d_in - 1;
                 // (weights that all replicas share are wanted in the L2 by the neighbouring blocks)
-                if (weight_streams(WM) && a.shared_w)
-                    ww[r] = load_wm<weight_ragged(WM) ? kWRagged : kWVector>(Wr + static_cast<int64_t>(rr) * a.d_out, c0 + 4 * j, a.d_out, vec);
+                if (WM == kWVectorStream && a.shared_w)
+                    ww[r] = load_wm<kWVector>(Wr + static_cast<int64_t>(rr) * a.d_out, c0 + 4 * j, a.d_out, vec);
                 else
                     ww[r] = load_wm<WM>(Wr + static_cast<int64_t>(rr) * a.d_out, c0 + 4 * j, a.d_out, vec);
                 if constexpr (!DAO) vv[r] = load_wm<WM>(Va + static_cast<int64_t>(rr) * a.d_out, c0 + 4 * j, a.d_out, vec);
@@ -861,7 +861,7 @@ __global__ __launch_bounds__(256) void backward_kernel(BwdArgs a) {
             for (int r = 0; r < 4; ++r) {
                 const bool in = WM == kWGeneric || k0 + 4 * q + r < a.d_in;
                 // (columns past the row end: what a ragged load found there)
-                const int left = weight_ragged(WM) ? a.d_out - (c0 + 4 * j) : 4;
+                const int left = WM == kWRagged ? a.d_out - (c0 + 4 * j) : 4;
                 store4<OT>(&wlds[wave][4 * q + r][4 * j], in && left > 0 ? w[r].x : 0.f, in && left > 1 ? w[r].y : 0.f,
                            in && left > 2 ? w[r].z : 0.f, in && left > 3 ? w[r].w : 0.f);
             }
@@ -1190,11 +1190,11 @@ __global__ __launch_bounds__(512) void head_kernel(HeadArgs a) {
 // checks, other rows of at least one chunk only where they end.  (A narrower row may be the last
 // thing in the buffer, and a load over its end could leave the replica.)  Checked element by element
 // a row costs four masked loads per lane instead of one: 3072-1500-1000-100, 16 workers of 100
-// samples, bf16 operands: first-layer backward 480 -> 285 us, forward 240 -> 99 us, forward of the
+// samples, bf16 operands: first-layer backward 480 -> 260 us, forward 240 -> 99 us, forward of the
 // 1500x1000 layer 60 -> 31 us; 784-500-300 fp32 forward 33 -> 30 and 30 -> 22 us.
 int weight_mode(bool vec, bool stream, int d_out) {
     if (vec && d_out % kColChunk == 0) return stream ? kWVectorStream : kWVector;
-    if (d_out >= kColChunk) return stream ? kWRaggedStream : kWRagged;
+    if (d_out >= kColChunk) return kWRagged;
     return kWGeneric;
 }
 
@@ -1221,7 +1221,6 @@ hipError_t launch_fwd_wm(const FwdArgs& a, int mt, bool wide, bool afm, unsigned
         case kWVector: return launch_fwd_cfg<OT, kWVector>(a, mt, wide, afm, grid, s);
         case kWVectorStream: return launch_fwd_cfg<OT, kWVectorStream>(a, mt, wide, afm, grid, s);
         case kWRagged: return launch_fwd_cfg<OT, kWRagged>(a, mt, wide, afm, grid, s);
-        case kWRaggedStream: return launch_fwd_cfg<OT, kWRaggedStream>(a, mt, wide, afm, grid, s);
         default: return launch_fwd_cfg<OT, kWGeneric>(a, mt, wide, afm, grid, s);
     }
 }
@@ -1253,7 +1252,6 @@ hipError_t launch_bwd_wm(const BwdArgs& a, int nt, unsigned grid, hipStream_t s)
         case kWVector: return launch_bwd_nt<OT, kWVector>(a, nt, grid, s);
         case kWVectorStream: return launch_bwd_nt<OT, kWVectorStream>(a, nt, grid, s);
         case kWRagged: return launch_bwd_nt<OT, kWRagged>(a, nt, grid, s);
-        case kWRaggedStream: return launch_bwd_nt<OT, kWRaggedStream>(a, nt, grid, s);
         default: return launch_bwd_nt<OT, kWGeneric>(a, nt, grid, s);
     }
 }

@@ -180,15 +180,16 @@ __device__ __forceinline__ float4 load_w4_rows(const float* base, int row, int d
 // (any d_out, any alignment).  kWVector* are for layers whose rows are 16-byte aligned and a
 // multiple of 64 columns long: every access is one unconditional 16-byte instruction, which lets
 // the compiler issue a trip's loads back to back with no control flow between them.
-// kWRagged* do the same for every other layer of at least 64 columns.  A load is one unconditional
+// kWRagged does the same for every other layer of at least 64 columns.  A load is one unconditional
 // 16-byte instruction at 4-byte alignment (which global memory instructions take); in the last
 // column chunk it may run over the end of the row, by at most 62 columns: into the next row, or
 // behind the last row into the layer's biases, of which there are at least 64 -- always inside the
 // replica's own parameters.  What it finds there is never used: the kernels zero those columns
-// where they are an operand of a sum, and the stores stop at the row end.
-constexpr int kWGeneric = 0, kWVector = 1, kWVectorStream = 2, kWRagged = 3, kWRaggedStream = 4;
-constexpr bool weight_ragged(int wm) { return wm == kWRagged || wm == kWRaggedStream; }
-constexpr bool weight_streams(int wm) { return wm == kWVectorStream || wm == kWRaggedStream; }
+// where they are an operand of a sum, and the stores stop at the row end.  Such rows share cache
+// lines with their neighbours, so they are never accessed with the streaming hint (with it:
+// 3072-1500-1000-100, 16 workers, batch 100: 2887 instead of 2671 us for 5 steps; 3072-2000x3-10, 32
+// workers, batch 32: 9286 instead of 8784).
+constexpr int kWGeneric = 0, kWVector = 1, kWVectorStream = 2, kWRagged = 3;
 typedef f32x4 f32x4_u __attribute__((aligned(4)));   // four floats at any float address
 
 template <int WM>
@@ -201,9 +202,6 @@ __device__ __forceinline__ float4 load_wm(const float* row, int c, int d_out, bo
     } else if constexpr (WM == kWRagged) {
         const f32x4 t = *reinterpret_cast<const f32x4_u*>(row + c);
         return make_float4(t[0], t[1], t[2], t[3]);
-    } else if constexpr (WM == kWRaggedStream) {
-        const f32x4 t = __builtin_nontemporal_load(reinterpret_cast<const f32x4_u*>(row + c));
-        return make_float4(t[0], t[1], t[2], t[3]);
     } else {
         return load_w4(row, c, d_out, vec, false);
     }
@@ -214,11 +212,9 @@ __device__ __forceinline__ void store_wm(float* row, int c, int d_out, bool vec,
         *reinterpret_cast<float4*>(row + c) = v;
     } else if constexpr (WM == kWVectorStream) {
         __builtin_nontemporal_store(f32x4{v.x, v.y, v.z, v.w}, reinterpret_cast<f32x4*>(row + c));
-    } else if constexpr (weight_ragged(WM)) {
+    } else if constexpr (WM == kWRagged) {
         if (c + 3 < d_out) {
-            const f32x4 t{v.x, v.y, v.z, v.w};
-            if constexpr (WM == kWRaggedStream) __builtin_nontemporal_store(t, reinterpret_cast<f32x4_u*>(row + c));
-            else *reinterpret_cast<f32x4_u*>(row + c) = t;
+            *reinterpret_cast<f32x4_u*>(row + c) = f32x4{v.x, v.y, v.z, v.w};
         } else {
             if (c < d_out) row[c] = v.x;
             if (c + 1 < d_out) row[c + 1] = v.y;
