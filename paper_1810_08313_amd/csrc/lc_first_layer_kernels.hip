@@ -73,8 +73,11 @@ struct FlBudget {
 // steps are in flight while it works on the current one (PD + 1 register sets, addressed
 // statically); a step is small enough (about 20 memory instructions with its stores) that the
 // steps in flight stay below the 64 outstanding memory instructions a wavefront can have.
-// Rows are 16-byte aligned and a multiple of 64 columns long and d_in is a multiple of 16 (the
-// launcher checks), so every weight access is one unconditional 16-byte instruction.
+// Every weight access is one unconditional 16-byte instruction: of aligned rows that are a multiple of
+// 64 columns long and a d_in that is a multiple of 16, or (WM == kWRagged, see lc_mma.h) of any rows
+// of at least 64 columns and any d_in.  In those instances the last steps read the last row in place of
+// rows that do not exist, the stores leave out what does not exist, and such rows enter the
+// forward product as zeros.
 // WM is the access mode of the state that streams (momentum or older model, all stores), WMR that of
 // the weights read: cached where all replicas read one model, which the neighbouring blocks want in
 // the L2.  (A template parameter, not a run-time flag: with the choice made per load the compiler
@@ -109,7 +112,9 @@ __global__ __launch_bounds__(256, (FlBudget<OT, NT>::kWavesPerSimd)) void first_
     const float* Va = a.Aux + g * a.aux_stride + a.w_off;
     const OT* AT = static_cast<const OT*>(a.a_fm) + static_cast<int64_t>(g) * a.dp_in * Bp;
     const OT* AN = static_cast<const OT*>(a.an_bm) + static_cast<int64_t>(g) * Bp * a.dp_in;
-    const int n_steps = a.d_in / 16;
+    constexpr bool RAG = WM == kWRagged;
+    const int n_steps = RAG ? (a.d_in + 15) / 16 : a.d_in / 16;
+    const int left = RAG ? a.d_out - (c0 + 4 * j) : 4;   // columns that exist from this lane's first one on
 
     struct Set {
         float4 w[4], v[4];      // rows k0 + 4 q + r, columns c0 + 4 j ..
@@ -132,6 +137,7 @@ __global__ __launch_bounds__(256, (FlBudget<OT, NT>::kWavesPerSimd)) void first_
         return reinterpret_cast<T*>(reinterpret_cast<C*>(base) + off);
     };
 
+    auto past_end = [&](int row) { return row < a.d_in ? 0 : row - (a.d_in - 1); };   // rows back to the last one
     auto load_step = [&](int s, Set& x) {
         // steps past the end are never used: a valid step is read for them, so that no branch
         // sits between the loads
@@ -140,8 +146,10 @@ __global__ __launch_bounds__(256, (FlBudget<OT, NT>::kWavesPerSimd)) void first_
         const float* vb = Va + static_cast<int64_t>(k0) * a.d_out;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            x.w[r] = load_wm<WMR>(at_byte(wb, woff[r]), 0, a.d_out, true);
-            x.v[r] = load_wm<WM>(at_byte(vb, woff[r]), 0, a.d_out, true);
+            unsigned at = woff[r];
+            if constexpr (RAG) at -= 4u * static_cast<unsigned>(a.d_out) * static_cast<unsigned>(past_end(k0 + 4 * q + r));
+            x.w[r] = load_wm<WMR>(at_byte(wb, at), 0, a.d_out, true);
+            x.v[r] = load_wm<WM>(at_byte(vb, at), 0, a.d_out, true);
         }
         const OT* ab = AT + static_cast<int64_t>(k0) * Bp;
 #pragma unroll
@@ -163,7 +171,7 @@ __global__ __launch_bounds__(256, (FlBudget<OT, NT>::kWavesPerSimd)) void first_
     }
     __syncthreads();
     // bias of these columns: db_1 = sum_b dZ_1, the same update; kept for the forward epilogue
-    if (tid < kColChunk) {
+    if (tid < kColChunk && (WM != kWRagged || c0 + tid < a.d_out)) {
         float* bx = a.X + g * a.x_stride + a.b_off + c0 + tid;
         const float x = a.Xr[g * a.xr_stride + a.b_off + c0 + tid];
         float vb0 = a.Aux[g * a.aux_stride + a.b_off + c0 + tid];
@@ -215,8 +223,13 @@ __global__ __launch_bounds__(256, (FlBudget<OT, NT>::kWavesPerSimd)) void first_
             x.w[r].y -= a.lr * x.v[r].y;
             x.w[r].z -= a.lr * x.v[r].z;
             x.w[r].w -= a.lr * x.v[r].w;
-            if (vs) store_wm<WM>(at_byte(vs, woff[r]), 0, a.d_out, true, x.v[r]);
-            store_wm<WM>(at_byte(ws, woff[r]), 0, a.d_out, true, x.w[r]);
+            const bool in = !RAG || 16 * s + 4 * q + r < a.d_in;
+            if (in) {
+                if (vs) store_wm<WM>(at_byte(vs, woff[r]), 0, left, true, x.v[r]);
+                store_wm<WM>(at_byte(ws, woff[r]), 0, left, true, x.w[r]);
+            } else {
+                x.w[r] = make_float4(0.f, 0.f, 0.f, 0.f);
+            }
         }
         // Z_1' += A_0'[:, k0 .. k0+15] W_1[k0 .. k0+15, :] with the tile just updated
         Frag4<OT> bf;
@@ -284,14 +297,14 @@ __global__ __launch_bounds__(256, (FlBudget<OT, NT>::kWavesPerSimd)) void first_
     for (int e = tid; e < Bp * (kColChunk / 8); e += 256) {
         const int b = e / (kColChunk / 8), cl = (e % (kColChunk / 8)) * 8;
         if (b >= a.B) continue;
-        float y[8];
+        float y[8];   // (columns that do not exist keep the zeros of the padding)
 #pragma unroll
-        for (int i = 0; i < 8; ++i) y[i] = value(b, cl + i);
+        for (int i = 0; i < 8; ++i) y[i] = (!RAG || c0 + cl + i < a.d_out) ? value(b, cl + i) : 0.f;
         store8(obm + static_cast<int64_t>(b) * a.dp_out + c0 + cl, y);
     }
     for (int e = tid; e < kColChunk * (Bp / 8); e += 256) {
         const int c = e / (Bp / 8), bl = (e % (Bp / 8)) * 8;
-        if (bl >= a.B) continue;
+        if (bl >= a.B || (RAG && c0 + c >= a.d_out)) continue;
         float y[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) y[i] = bl + i < a.B ? value(bl + i, c) : 0.f;
@@ -350,7 +363,10 @@ __global__ __launch_bounds__(64 * kWideWaves) void first_layer_wide_kernel(First
     const OT* AT = static_cast<const OT*>(a.a_fm) + static_cast<int64_t>(g) * a.dp_in * Bp;
     // this wavefront's 16 samples of the next step's input
     const OT* AN = static_cast<const OT*>(a.an_bm) + (static_cast<int64_t>(g) * Bp + 16 * wave) * a.dp_in;
-    const int n_rounds = a.d_in / (16 * kWideWaves);   // the launcher checks that this divides
+    constexpr bool RAG = WM == kWRagged;
+    const int n_rounds = (a.d_in + 16 * kWideWaves - 1) / (16 * kWideWaves);   // (divides unless RAG)
+    const int left = RAG ? a.d_out - (c0 + 4 * j) : 4;   // columns that exist from this lane's first one on
+    auto past_end = [&](int row) { return row < a.d_in ? 0 : row - (a.d_in - 1); };   // rows back to the last one
 
     struct Set {
         float4 w[4], v[4];            // rows k0 + 4 q + r, columns c0 + 4 j ..
@@ -378,15 +394,28 @@ __global__ __launch_bounds__(64 * kWideWaves) void first_layer_wide_kernel(First
         const float* vb = Va + static_cast<int64_t>(k0) * a.d_out;
 #pragma unroll
         for (int r4 = 0; r4 < 4; ++r4) {
-            x.w[r4] = load_wm<WMR>(at_byte(wb, woff[r4]), 0, a.d_out, true);
-            x.v[r4] = load_wm<WM>(at_byte(vb, woff[r4]), 0, a.d_out, true);
+            // (a row's distance from this step's first row may be negative: 64-bit, sign-extended)
+            if constexpr (RAG) {
+                const int64_t back = static_cast<int64_t>(past_end(k0 + 4 * q + r4)) * a.d_out;
+                x.w[r4] = load_wm<WMR>(at_byte(wb, woff[r4]) - back, 0, a.d_out, true);
+                x.v[r4] = load_wm<WM>(at_byte(vb, woff[r4]) - back, 0, a.d_out, true);
+            } else {
+                x.w[r4] = load_wm<WMR>(at_byte(wb, woff[r4]), 0, a.d_out, true);
+                x.v[r4] = load_wm<WM>(at_byte(vb, woff[r4]), 0, a.d_out, true);
+            }
         }
-        const OT* ab = AT + static_cast<int64_t>(k0) * Bp;
+        // (inputs have dp_in rows and columns; a step beyond them reads the last 16 instead, for rows
+        // of the tile that are not stored and enter the forward product as zeros)
+        const int ka = RAG && k0 > a.dp_in - 16 ? a.dp_in - 16 : k0;
+        const OT* ab = AT + static_cast<int64_t>(ka) * Bp;
 #pragma unroll
         for (int st = 0; st < NS; ++st) x.af[st] = load8(at_byte(ab + 32 * st, atoff));
-        const OT* nb = AN + 16 * kWideWaves * rr;
+        const int kn = 16 * kWideWaves * rr;
 #pragma unroll
-        for (int u = 0; u < kWideWaves; ++u) x.an[u] = load4(at_byte(nb + 16 * u, anoff));
+        for (int u = 0; u < kWideWaves; ++u) {
+            const int kc = RAG && kn + 16 * u > a.dp_in - 16 ? a.dp_in - 16 : kn + 16 * u;
+            x.an[u] = load4(at_byte(AN + kc, anoff));
+        }
     };
 
 #pragma unroll
@@ -399,7 +428,7 @@ __global__ __launch_bounds__(64 * kWideWaves) void first_layer_wide_kernel(First
         }
     }
     __syncthreads();
-    if (tid < kColChunk) {
+    if (tid < kColChunk && (WM != kWRagged || c0 + tid < a.d_out)) {
         float* bx = a.X + g * a.x_stride + a.b_off + c0 + tid;
         const float x = a.Xr[g * a.xr_stride + a.b_off + c0 + tid];
         float vb0 = a.Aux[g * a.aux_stride + a.b_off + c0 + tid];
@@ -449,8 +478,12 @@ __global__ __launch_bounds__(64 * kWideWaves) void first_layer_wide_kernel(First
             x.w[r4].y -= a.lr * x.v[r4].y;
             x.w[r4].z -= a.lr * x.v[r4].z;
             x.w[r4].w -= a.lr * x.v[r4].w;
-            if (vs) store_wm<WM>(at_byte(vs, woff[r4]), 0, a.d_out, true, x.v[r4]);
-            store_wm<WM>(at_byte(ws, woff[r4]), 0, a.d_out, true, x.w[r4]);
+            if (!RAG || 16 * (kWideWaves * r + wave) + 4 * q + r4 < a.d_in) {
+                if (vs) store_wm<WM>(at_byte(vs, woff[r4]), 0, left, true, x.v[r4]);
+                store_wm<WM>(at_byte(ws, woff[r4]), 0, left, true, x.w[r4]);
+            } else {
+                x.w[r4] = make_float4(0.f, 0.f, 0.f, 0.f);
+            }
         }
         // the updated tile, as the 4 operand fragments of this lane
         Frag4<OT> b0, b1, b2, b3;
@@ -516,12 +549,12 @@ __global__ __launch_bounds__(64 * kWideWaves) void first_layer_wide_kernel(First
         if (b >= a.B) continue;
         float y[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) y[i] = part[b][cl + i];
+        for (int i = 0; i < 8; ++i) y[i] = (!RAG || c0 + cl + i < a.d_out) ? part[b][cl + i] : 0.f;
         store8(obm + static_cast<int64_t>(b) * a.dp_out + c0 + cl, y);
     }
     for (int e = tid; e < kColChunk * (Bp / 8); e += NTH) {
         const int c = e / (Bp / 8), bl = (e % (Bp / 8)) * 8;
-        if (bl >= a.B) continue;
+        if (bl >= a.B || (RAG && c0 + c >= a.d_out)) continue;
         float y[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) y[i] = bl + i < a.B ? part[bl + i][c] : 0.f;
@@ -533,9 +566,13 @@ __global__ __launch_bounds__(64 * kWideWaves) void first_layer_wide_kernel(First
     }
 }
 
+// whole 64-column chunks of 16-byte aligned rows, and whole 16-row steps
+bool whole_tiles(const FirstArgs& a) { return a.d_out % kColChunk == 0 && a.w_off % 4 == 0 && a.d_in % 16 == 0; }
+
 template <typename OT, int NT>
 void launch_fl_wm(const FirstArgs& a, bool stream_w, unsigned grid, hipStream_t st) {
-    if (stream_w && !a.shared_w)
+    if (!whole_tiles(a)) hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWRagged, kWRagged>), dim3(grid), dim3(256), 0, st, a);
+    else if (stream_w && !a.shared_w)
         hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWVectorStream, kWVectorStream>), dim3(grid), dim3(256), 0, st, a);
     else if (stream_w) hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWVectorStream, kWVector>), dim3(grid), dim3(256), 0, st, a);
     else hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWVector, kWVector>), dim3(grid), dim3(256), 0, st, a);
@@ -544,9 +581,11 @@ void launch_fl_wm(const FirstArgs& a, bool stream_w, unsigned grid, hipStream_t 
 template <typename OT>
 hipError_t launch_fl(const FirstArgs& a, int nt, bool stream_w, unsigned grid, hipStream_t st) {
     if constexpr (sizeof(OT) == 2) {
-        if (nt == 8 && a.d_in % (16 * kWideWaves) == 0) {
+        const bool rounds = a.d_in % (16 * kWideWaves) == 0;
+        if (nt == 8 && (rounds || !whole_tiles(a))) {
             const dim3 block(64 * kWideWaves);
-            if (stream_w && !a.shared_w)
+            if (!whole_tiles(a)) hipLaunchKernelGGL((first_layer_wide_kernel<OT, kWRagged, kWRagged>), dim3(grid), block, 0, st, a);
+            else if (stream_w && !a.shared_w)
                 hipLaunchKernelGGL((first_layer_wide_kernel<OT, kWVectorStream, kWVectorStream>), dim3(grid), block, 0, st, a);
             else if (stream_w) hipLaunchKernelGGL((first_layer_wide_kernel<OT, kWVectorStream, kWVector>), dim3(grid), block, 0, st, a);
             else hipLaunchKernelGGL((first_layer_wide_kernel<OT, kWVector, kWVector>), dim3(grid), block, 0, st, a);
@@ -561,21 +600,25 @@ hipError_t launch_fl(const FirstArgs& a, int nt, bool stream_w, unsigned grid, h
 
 }  // namespace
 
-// The kernel serves layer 1 of models with at least two layers whose first-layer rows are 16-byte
-// aligned and a multiple of 64 columns long and whose input width is a multiple of 16, when there
-// are enough (replica, column chunk) pairs to fill the chip; everything else keeps the row-owner
-// backward kernel and the separate forward launch.
+// The kernel serves layer 1 of models with at least two layers whose first-layer rows are at least one
+// column chunk long, when there are enough (replica, column chunk) pairs to fill the chip; everything
+// else keeps the row-owner backward kernel and the separate forward launch.
 bool first_layer_kernel_ok(const lc_handle* h) {
     if (h->md.kind != LC_KIND_MLP || h->L < 2) return false;
     const LayerGeom& g = h->layer[1];
     const ActSet& S = h->train;
-    if (g.d_out % kColChunk != 0 || g.w_off % 4 != 0 || h->Ps % 4 != 0) return false;
+    if (g.d_out < kColChunk) return false;
     if (S.Bp != 32 && S.Bp != 64 && S.Bp != 128) return false;
-    if (g.d_in % 16 != 0 || g.d_in < 16 * kFlWaves) return false;
+    if (g.d_in < 16 * kFlWaves) return false;
     // fp32 operands at 128 samples: the operand fragments of two steps and the 32 accumulator tiles
     // do not fit the register file
     if (h->md.gemm != LC_GEMM_BF16 && S.Bp == 128) return false;
-    return static_cast<int64_t>(S.G) * (g.d_out / kColChunk) >= 192;
+    // Every workgroup walks a whole column chunk, so a last round of few workgroups takes as long as a
+    // full one (3072x1024, batch 128: 147 us a step with 16 replicas = 256 workgroups, 250 with 20, 288
+    // with 32).  Fused against separate, whole runs: 1.02 rounds 0.88 .. 0.98 times as fast, 1.25 rounds
+    // 0.97 at batch 128 and 1.00 .. 1.09 below, 1.0, 1.5 and 1.8 rounds 1.01 .. 1.16, 4 rounds 1.08 .. 1.16.
+    const int64_t blocks = static_cast<int64_t>(S.G) * (g.dp_out / kColChunk), rounds = (blocks + 255) / 256;
+    return blocks >= 192 && 100 * blocks >= (S.Bp == 128 ? 70 : 60) * 256 * rounds;
 }
 
 // Backward pass and update of layer 1 for the step in slot train.cur_slot, and A_1 of the step in
@@ -615,7 +658,7 @@ hipError_t launch_first_layer(lc_handle* h) {
     a.an_bm = static_cast<const char*>(S.a_bm[0]) + static_cast<size_t>(S.cur_slot + 1) * slot_bytes;
     a.out_bm = S.a_bm[1];
     a.out_fm = S.a_fm[1];
-    a.n_chunks = g.d_out / kColChunk;
+    a.n_chunks = g.dp_out / kColChunk;
     a.total_blocks = static_cast<int64_t>(S.G) * a.n_chunks;
     const unsigned grid = static_cast<unsigned>((a.total_blocks + kXcds - 1) / kXcds * kXcds);
     timing_start(h, kTimeBwd, 1, kBwdFirstLayer);
