@@ -148,6 +148,8 @@ size_t carve(lc_handle* h, char* base) {
         const int passes = eval ? (h->md.E + per_pass - 1) / per_pass : 1;
         S.loss = static_cast<float*>(c.take(sizeof(float) * static_cast<size_t>(S.G) * passes * kLossParts));
     }
+    const size_t shares = backward_share_floats(h);
+    h->da_part = shares ? static_cast<float*>(c.take(sizeof(float) * shares)) : nullptr;
     if (resident_shape_ok(h) || net_shape_ok(h)) {
         h->res_a1x = static_cast<float*>(c.take(sizeof(float) * resident_exchange_floats(h)));
         h->res_ctr = static_cast<unsigned*>(c.take(sizeof(unsigned) * 384));
@@ -414,6 +416,7 @@ int lc_init(int m, int64_t P, const lc_model* md, uint64_t seed, lc_handle** out
     h->last_hip = 0;
     h->res_a1x = nullptr;
     h->res_ctr = nullptr;
+    h->da_part = nullptr;
     h->res_on = true;
     h->res_fuse_always = false;
     h->fl_on = true;

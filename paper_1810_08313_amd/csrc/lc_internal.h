@@ -126,6 +126,7 @@ struct lc_handle {
     float* res_a1x;         // [2 parities][m][dp1/16][Bp][16] exchange buffer of the resident kernel, null when the shape does not qualify
     unsigned* res_ctr;      // [0..63] arrival counters per replica, [64] error flag, [65] all-replica counter, [128..383] placement probe
     unsigned res_arrivals;  // value of every counter once the queued launches have run (zeroed with the scratch at attach)
+    float* da_part;         // shares of dA of the largest layer whose columns are shared out (see BwdArgs), or null
     float* res_avx;         // [2 parities][m][Ps] models handed over at averaging steps inside a launch
     unsigned res_garrivals; // the same for the all-replica counter of those averaging steps (res_ctr[65])
     bool res_on;            // lc_set_resident
@@ -169,6 +170,7 @@ hipError_t launch_eval_layer(lc_handle* h, int l);
 bool forward_fuses_softmax(const lc_handle* h);  // last layer's kernel also does a3
 hipError_t launch_softmax(lc_handle* h, bool eval, int loss_offset);
 hipError_t launch_backward(lc_handle* h, int l, bool da_only = false);   // da_only: dZ_{l-1} only, no update
+size_t backward_share_floats(const lc_handle* h);   // scratch for the shares of dA of layers whose columns are shared out
 bool first_layer_kernel_ok(const lc_handle* h);   // layer 1: backward kernel that also runs the next step's forward
 hipError_t launch_first_layer(lc_handle* h);
 bool implicit_layer_ok(const lc_handle* h, int l);   // layer l may keep its momentum implicitly inside a period

@@ -659,6 +659,9 @@ struct BwdArgs {
                          // the same rows of W for different replicas, in sets of this many (see FwdArgs)
     int fm_Bp;           // DAO instances: padded batch of ONE replica when a block takes the batches of several
                          // (see FwdArgs::fm_Bp); the feature-major buffers are laid out by it.  Else = Bp
+    float* da_part;      // columns shared out although dZ_{l-1} is wanted: this workgroup's share of dA goes to
+    int64_t part_stride; // da_part + (its share) part_stride, [G][dp_in][Bp] fp32, and combine_da_kernel
+                         // adds the shares up.  Null: the workgroup walks all columns and writes dZ_{l-1} itself
     int skip_x;          // V is updated, X is left unwritten: the averaging step that follows forms
                          // every replica's new weights from Xr and V itself (tau = 1, deferred update)
     int64_t total_blocks;
@@ -678,19 +681,22 @@ struct BwdArgs {
 // W and V cross HBM exactly once in each direction; the gradient never exists
 // in memory; dA is complete when the wavefront has walked its rows, so nothing
 // is reduced across workgroups.  When dA is not needed (first layer) the
-// columns may additionally be split over several workgroups.
+// columns may additionally be split over several workgroups, and where there are too few row blocks
+// for the chip also when it is needed: the shares of dA then go through memory (BwdArgs::da_part).
 // DAO instances (tau = 1, layers whose update and averaging a tile-owner kernel does afterwards)
 // form dZ_{l-1} only: the same walk over W_l without V, dW, the update or any store to X and V.
-template <typename OT, int NT, int WM, bool DAO = false>
-__global__ __launch_bounds__(256) void backward_kernel(BwdArgs a) {
+// NDA instances (first layer) form no dZ_{l-1}: without the two tiles that product needs in LDS, 2 to 4
+// workgroups share a CU where one did (784x500 with 16 replicas of 100 samples, fp32: 43 -> 36 us).
+template <typename OT, int NT, int WM, bool DAO = false, bool NDA = false>
+__global__ __launch_bounds__(256, NT == 8 && !NDA && !DAO ? 1 : 2) void backward_kernel(BwdArgs a) {
     constexpr int kPad = sizeof(OT) == 2 ? 8 : 4;
     constexpr int Bp = 16 * NT;
     constexpr int NS = NT / 2;                 // 32-wide steps over the batch; also staging pieces per thread
     // dZ^T slice: row (c % 4) * 16 + c / 4 holds column c0 + c, so that the 16 lanes
     // of a B-operand read (columns 4 j + t) hit 16 consecutive LDS rows
     __shared__ __attribute__((aligned(16))) OT dzt_lds[kColChunk][Bp + kPad];
-    __shared__ __attribute__((aligned(16))) OT dz_lds[Bp][kColChunk + kPad];
-    __shared__ __attribute__((aligned(16))) OT wlds[4][kRowsPerWave][kColChunk + kPad];
+    __shared__ __attribute__((aligned(16))) OT dz_lds[NDA ? 1 : Bp][kColChunk + kPad];
+    __shared__ __attribute__((aligned(16))) OT wlds[NDA ? 1 : 4][kRowsPerWave][kColChunk + kPad];
 
     const int64_t logical = xcd_logical_block(a.total_blocks);
     if (logical < 0) return;
@@ -702,7 +708,7 @@ __global__ __launch_bounds__(256) void backward_kernel(BwdArgs a) {
     const int j = lane & 15, q = lane >> 4;
     const int k0 = (rb * 4 + wave) * kRowsPerWave;   // < dp_in: the grid covers dp_in / 64 row blocks exactly
     const bool vec = a.vec != 0;
-    const bool need_da = a.dzp_bm != nullptr;
+    constexpr bool need_da = !NDA;
 
     float* W = a.X + g * a.x_stride + a.w_off;
     const float* Wr = a.Xr + g * a.xr_stride + a.w_off;
@@ -749,7 +755,7 @@ __global__ __launch_bounds__(256) void backward_kernel(BwdArgs a) {
         else return static_cast<int64_t>(row) * Bp + b;
     };
     uint32_t gate = 0;
-    if (need_da) {
+    if (need_da) {   // (not wanted when the shares of dA go through memory, but a branch here costs registers)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
@@ -915,6 +921,14 @@ __global__ __launch_bounds__(256) void backward_kernel(BwdArgs a) {
         }
     }
 
+    if (!DAO && !NDA && WM != kWVectorStream && a.da_part) {   // (a state that streams has no shares)
+        float* part = a.da_part + cs * a.part_stride + static_cast<int64_t>(g) * a.dp_in * Bp;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) part[static_cast<int64_t>(k0 + 4 * q + r) * Bp + 16 * nt + j] = dacc[nt][r];
+        return;
+    }
     if (need_da) {
         // dZ_{l-1} = dA .* [A_{l-1} > 0], both layouts.  Rows beyond d_in and batch
         // entries beyond B come out as exact zeros (zero operands), which is what
@@ -934,6 +948,46 @@ __global__ __launch_bounds__(256) void backward_kernel(BwdArgs a) {
             store4<OT>(pbm + static_cast<int64_t>(b) * a.dp_in + k0 + 4 * q, d[0], d[1], d[2], d[3]);
         }
     }
+}
+
+// dZ_{l-1} = (sum of the column shares of dA, in order) .* [A_{l-1} > 0], both layouts: one block = 64 rows
+// (units of layer l-1) x 32 samples of one replica, through LDS as in gather_kernel.
+struct CombineArgs {
+    const float* part;   // [shares][G][dp_in][Bp]
+    int64_t part_stride;
+    int shares;
+    int dp_in, Bp;
+    const void* a_fm;    // A_{l-1} feature-major [G][dp_in][Bp]
+    void* dzp_bm;        // [G][Bp][dp_in]
+    void* dzp_fm;        // [G][dp_in][Bp]
+};
+template <typename OT>
+__global__ __launch_bounds__(256) void combine_da_kernel(CombineArgs a) {
+    __shared__ float tile[32][65];
+    const int g = blockIdx.z, b0 = blockIdx.y * 32, k0 = blockIdx.x * 64, t = threadIdx.x;
+    {
+        const int kk = t >> 2, seg = (t & 3) * 8;
+        const int64_t at = (static_cast<int64_t>(g) * a.dp_in + k0 + kk) * a.Bp + b0 + seg;
+        const Frag<OT> act = load8(static_cast<const OT*>(a.a_fm) + at);
+        float y[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        for (int c = 0; c < a.shares; ++c) {
+            const Frag<float> f = load8(a.part + c * a.part_stride + at);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) y[e] += f.v[e];
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            y[e] = to_f32(act.v[e]) > 0.f ? y[e] : 0.f;
+            tile[seg + e][kk] = y[e];
+        }
+        store8(static_cast<OT*>(a.dzp_fm) + at, y);
+    }
+    __syncthreads();
+    const int r = t >> 3, seg = (t & 7) * 8;
+    float x[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = tile[r][seg + e];
+    store8(static_cast<OT*>(a.dzp_bm) + (static_cast<int64_t>(g) * a.Bp + b0 + r) * a.dp_in + k0 + seg, x);
 }
 
 // ----------------------------------------------------------------------- head
@@ -1227,6 +1281,17 @@ hipError_t launch_fwd_wm(const FwdArgs& a, int mt, bool wide, bool afm, unsigned
 
 template <typename OT, int WM>
 hipError_t launch_bwd_nt(const BwdArgs& a, int nt, unsigned grid, hipStream_t s) {
+    if (!a.dzp_bm) {
+        // (where the weights stream a third workgroup per CU costs more than it hides: the unused LDS keeps it out)
+        const unsigned pad = a.stream ? 55u * 1024 : 0;
+        switch (nt) {
+            case 2: hipLaunchKernelGGL((backward_kernel<OT, 2, WM, false, true>), dim3(grid), dim3(256), pad, s, a); break;
+            case 4: hipLaunchKernelGGL((backward_kernel<OT, 4, WM, false, true>), dim3(grid), dim3(256), 0, s, a); break;
+            case 8: hipLaunchKernelGGL((backward_kernel<OT, 8, WM, false, true>), dim3(grid), dim3(256), 0, s, a); break;
+            default: return hipErrorInvalidValue;
+        }
+        return hipGetLastError();
+    }
     switch (nt) {
         case 2: hipLaunchKernelGGL((backward_kernel<OT, 2, WM>), dim3(grid), dim3(256), 0, s, a); break;
         case 4: hipLaunchKernelGGL((backward_kernel<OT, 4, WM>), dim3(grid), dim3(256), 0, s, a); break;
@@ -1445,8 +1510,13 @@ hipError_t launch_forward(lc_handle* h, bool eval, int l, int loss_offset) {
     if (a.fuse_softmax) (eval ? h->loss_parts_eval : h->loss_parts_train) = a.m_split;
     a.total_blocks = static_cast<int64_t>(n_groups) * a.n_chunks * a.m_split;
     const unsigned grid = xcd_grid(a.total_blocks);
-    // few blocks: split the reduction over more wavefronts per block
-    const bool wide = a.total_blocks * 4 < 2048 && g.dp_in >= 512;
+    // few blocks: split the reduction over more wavefronts per block.  (Where the state is cached and there
+    // is a block per CU 4 wavefronts, two blocks of which fit a CU's LDS where 8 leave room for one, are
+    // faster: 784x500, 16 replicas of 100 samples, fp32, 256 blocks:
+    // 32 us with 8, 26 with 4; 500x300, 320 blocks: 22 and 20; bf16 at 208 blocks:
+    // 6.4 and 6.9, at 256: 7.8 and 7.4.)
+    const int64_t few = h->stream_weights || eval || mt < 2 ? 512 : bf16 ? 256 : 192;
+    const bool wide = a.total_blocks < few && g.dp_in >= 512;
     if (!eval) timing_start(h, kTimeFwd);
     hipError_t e;
     // whole padded batch in one block and a feature-major copy of the input at hand
@@ -1536,6 +1606,30 @@ hipError_t launch_softmax(lc_handle* h, bool eval, int loss_offset) {
     return hipGetLastError();
 }
 
+// Workgroups that share the columns of a row block of layer l > 1: one, unless the row blocks of all
+// replicas leave CUs without work; then as many as fill the places there are, each with at least one chunk.  A state that streams from memory keeps the one pass with long walks.  (340x704,
+// 13 replicas of 90 samples, fp32: 78 workgroups of 11 chunks took 80 us; 768x768, 4 replicas of 64: 46 us.)
+int backward_shares(const lc_handle* h, int l) {
+    if (h->stream_weights || l < 2) return 1;
+    const LayerGeom& g = h->layer[l];
+    const int n_cc = g.dp_out / kColChunk;
+    const int64_t base = static_cast<int64_t>(h->m) * (g.dp_in / 64);
+    if (base >= 256 || n_cc < 3) return 1;
+    const int64_t slots = h->train.Bp == 128 ? 256 : 512;   // (at 128 samples the kernel's tiles leave room for one per CU)
+    const int64_t want = (slots + base - 1) / base;
+    const int per = static_cast<int>((n_cc + want - 1) / want);   // chunks per workgroup
+    return (n_cc + per - 1) / per;
+}
+size_t backward_share_floats(const lc_handle* h) {
+    size_t most = 0;
+    for (int l = 2; l <= h->L; ++l) {
+        const int s = backward_shares(h, l);
+        const size_t n = static_cast<size_t>(s) * h->m * h->layer[l].dp_in * h->train.Bp;
+        if (s > 1 && n > most) most = n;
+    }
+    return most;
+}
+
 hipError_t launch_backward(lc_handle* h, int l, bool da_only) {
     const ActSet& S = h->train;
     const LayerGeom& g = h->layer[l];
@@ -1605,6 +1699,14 @@ hipError_t launch_backward(lc_handle* h, int l, bool da_only) {
         // 155 us with 4 or 8 per row block, 191 us with 16)
         if (h->stream_weights && a.col_split < n_cc * 32 / S.Bp) a.col_split = n_cc * 32 / S.Bp;
     }
+    a.da_part = nullptr;
+    a.part_stride = static_cast<int64_t>(S.G) * g.dp_in * S.Bp;
+    const int shares = da_only ? 1 : backward_shares(h, l);
+    if (shares > 1) {
+        if (!h->da_part) return hipErrorInvalidValue;
+        a.col_split = shares;
+        a.da_part = h->da_part;
+    }
     a.total_blocks = static_cast<int64_t>(n_groups) * a.n_row_blocks * a.col_split;
     const unsigned grid = xcd_grid(a.total_blocks);
     // (same conditions as the tile-owner kernel that follows; the columns are not shared out here)
@@ -1617,6 +1719,13 @@ hipError_t launch_backward(lc_handle* h, int l, bool da_only) {
     } else {
         e = bf16 ? launch_bwd_wm<bf16_t>(a, S.Bp / 16, grid, h->stream)
                  : launch_bwd_wm<float>(a, S.Bp / 16, grid, h->stream);
+    }
+    if (e == hipSuccess && shares > 1) {
+        const CombineArgs c{a.da_part, a.part_stride, shares, g.dp_in, S.Bp, a.a_fm, a.dzp_bm, a.dzp_fm};
+        const dim3 cgrid(g.dp_in / 64, S.Bp / 32, S.G);
+        if (bf16) hipLaunchKernelGGL((combine_da_kernel<bf16_t>), cgrid, dim3(256), 0, h->stream, c);
+        else hipLaunchKernelGGL((combine_da_kernel<float>), cgrid, dim3(256), 0, h->stream, c);
+        e = hipGetLastError();
     }
     timing_stop(h, kTimeBwd, l, kBwdRowOwner);
     if (e == hipSuccess && !da_only) h->imp[l] = sb.next;
