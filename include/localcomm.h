@@ -155,8 +155,10 @@ int lc_average(lc_handle* h);
  * over n_periods communication periods of length tau).  The result is that of calling
  * lc_local_steps(h, tau); lc_average(h) n_periods times, and that is what happens for most
  * shapes.  Where the resident step kernel applies (see lc_set_resident), tau is at most the
- * number of steps it takes per launch, and the model is small (one layer; or two layers with
- * m * ceil64(d0) * 64 bytes <= 200 KB, the amount a workgroup then reads from the other replicas),
+ * number of steps it takes per launch, m is at most the number of compute units, and the model is
+ * small (softmax regression; two layers split over workgroups with m * ceil64(d0) * 64 bytes <= 200 KB,
+ * the amount a workgroup then reads from the other replicas; one workgroup per replica with
+ * 4 m P bytes <= 200 KB),
  * several whole periods are ONE launch: at an averaging step every workgroup hands over its part
  * of the model, all workgroups of all replicas meet at a barrier in device memory (bounded wait,
  * LC_ERR_SYNC as described at lc_set_resident), and each forms the mean of its own part -- same
@@ -188,7 +190,9 @@ int lc_materialize(lc_handle* h);
  * workgroups of a replica meet once per step at a barrier in device memory to exchange their shares
  * of the logits.  One-layer models (softmax
  * regression) with at most 16 classes, B <= 64 and padded d0 <= 256 take the same route with one
- * workgroup per replica and no barrier.  Same arithmetic as the
+ * workgroup per replica and no barrier.  Other models of any depth with at most 64 classes do too
+ * where one replica's weights (widths padded to multiples of 16), one batch's activations and its
+ * deltas fit 159 KB together, and the weights are at most 128 tiles of 16 x 16.  Same arithmetic as the
  * launch-per-layer path up to the summation order (results agree to rounding, not bit for bit).
  * on = 0 selects the launch-per-layer path for every shape; the default is on (1); on = 2
  * additionally makes lc_local_periods() take the averaging steps inside the launch at every
@@ -215,7 +219,8 @@ int lc_set_xcd_local_exchange(lc_handle* h, int on);
 /* First-layer fusion across steps (Sec. 2: between two averaging steps a worker's updates touch
  * only its own model, so the first layer's weights after step k are what step k+1 multiplies its
  * mini-batch with).  Inside one lc_local_steps() call, for LC_KIND_MLP models with at least two
- * layers, first-layer rows that are a multiple of 64 columns long and m * d1 / 64 >= 192, the
+ * layers, at least 64 inputs and 64 first-layer columns, n = m * ceil(d1 / 64) >= 192, and n / 256
+ * rounds of workgroups that are at least 60 % full (70 % above 64 samples), the
  * first layer's backward kernel of a step also computes the first hidden activations of the
  * next step from the weight tile it has just updated, and that step's first-layer forward launch
  * is dropped: W_1 then moves 16 instead of 20 bytes per parameter and step.  The first step of a
