@@ -32,8 +32,9 @@ struct EvalArgs {
 };
 
 // x = p1 + p2 + p3.  The clamps keep a number that would round to infinity finite (its rest then goes
-// to the next part) and send an infinity to the last part, with finite parts before it: infinities and
-// NaN come out of the products as they do in fp32.
+// to the next part) and send an infinity to the last part, with finite parts before it.  An infinity
+// still meets parts of the other operand that are zero or of the other sign, so a sum that is not
+// finite is formed again from the operands themselves (see the end of eval_layer_kernel).
 constexpr float kMaxBf16 = 3.38953139e38f;
 __device__ __forceinline__ void split3(const float (&x)[8], bf16x8& p1, bf16x8& p2, bf16x8& p3) {
 #pragma unroll
@@ -160,6 +161,8 @@ __global__ __launch_bounds__(256, 2) void eval_layer_kernel(EvalArgs a) {
     }
 
     // bias, ReLU; register r of a 32 x 32 tile holds row 8 (r / 4) + 4 q + r % 4, column j
+    static_assert(TM * TN * 16 <= 64, "one bit per output of a lane");
+    unsigned long long redo = 0;   // outputs whose sum is not finite
 #pragma unroll
     for (int n = 0; n < TN; ++n) {
         const int c = c0 + wn * BN / 2 + 32 * n + j;
@@ -171,8 +174,24 @@ __global__ __launch_bounds__(256, 2) void eval_layer_kernel(EvalArgs a) {
             for (int r = 0; r < 16; ++r) {
                 const int64_t row = row0 + wm * BM / 2 + 32 * m + 8 * (r / 4) + 4 * q + r % 4;
                 const float z = (hi[m][n][r] + lo[m][n][r]) + bias;
+                if (!isfinite(z)) redo |= 1ull << ((m * TN + n) * 16 + r);
                 a.out[row * a.dp_out + c] = z > 0.f ? z : 0.f;
             }
+    }
+    // Infinities, NaN and overflows: the products of the parts can turn an infinite sum into NaN (infinity
+    // times a part that is zero, or infinite parts of both signs; a zero of A past d_in times the row
+    // read in place of one that does not exist), never into a finite one.  Models that diverged only.
+    while (redo) {
+        const int bit = __builtin_ctzll(redo), r = bit & 15, m = bit / (16 * TN), n = bit / 16 % TN;
+        redo &= redo - 1;
+        const int c = c0 + wn * BN / 2 + 32 * n + j;
+        const int64_t row = row0 + wm * BM / 2 + 32 * m + 8 * (r / 4) + 4 * q + r % 4;
+        const float* x = a.A + row * a.dp_in;
+        float z = 0.f;
+#pragma unroll 1
+        for (int k = 0; k < a.d_in; ++k) z = fmaf(x[k], W[static_cast<int64_t>(k) * a.d_out + c], z);
+        z += a.X[a.b_off + c];
+        a.out[row * a.dp_out + c] = z > 0.f ? z : 0.f;
     }
 }
 
