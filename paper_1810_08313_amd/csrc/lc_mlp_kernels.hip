@@ -290,8 +290,9 @@ __global__ __launch_bounds__(NW * 64) void forward_kernel(FwdArgs a) {
                 for (int e = 0; e < 8; ++e) w[e] = load_w4_rows(W, k0 + e, a.d_in, c0 + 4 * j, a.d_out, vec, false);
             }
         } else {
-            // Rows past d_in meet activation columns that are zero, and steps past the end are
-            // never used: both are redirected to valid rows instead of being branched around.
+            // Rows past d_in meet activation columns that are zero (and are zeroed where rows are
+            // ragged, see multiply_step), and steps past the end are never used: both are redirected
+            // to valid rows instead of being branched around.
             const int k0 = (s < n_steps ? s : n_steps - 1) * 32 + 8 * q;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
@@ -344,11 +345,23 @@ __global__ __launch_bounds__(NW * 64) void forward_kernel(FwdArgs a) {
     static_assert((PF + 1) % 2 == 0, "the activation double buffer needs an even trip count");
     float4 wq[PF + 1][8];
     Frag<OT> af[2][MT];
-    auto multiply_step = [&](Frag<OT> (&f)[MT], float4 (&w)[8]) {
+    auto multiply_step = [&](int s, Frag<OT> (&f)[MT], float4 (&w)[8]) {
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) consume_here(f[mt]);
 #pragma unroll
         for (int e = 0; e < 8; ++e) consume_here(w[e]);
+        if constexpr (WM == kWRagged) {
+            // an infinity in the last row must not meet the zeros past it (selects, not a branch: the
+            // later rows stay in flight)
+            const int left = a.d_in - (32 * s + 8 * q);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                w[e].x = e < left ? w[e].x : 0.f;
+                w[e].y = e < left ? w[e].y : 0.f;
+                w[e].z = e < left ? w[e].z : 0.f;
+                w[e].w = e < left ? w[e].w : 0.f;
+            }
+        }
         transpose_a_step(f);
         Frag<OT> bf;
         float x[8];
@@ -386,7 +399,7 @@ __global__ __launch_bounds__(NW * 64) void forward_kernel(FwdArgs a) {
             const int s = s0 + u * NW;
             load_a_step(s + NW, af[(u + 1) & 1]);
             load_w_step(s + PF * NW, wq[(u + PF) % (PF + 1)]);
-            multiply_step(af[u & 1], wq[u]);
+            multiply_step(s, af[u & 1], wq[u]);
             __builtin_amdgcn_sched_barrier(0);   // keep the next step's loads below this step's products
         }
     }
@@ -395,7 +408,7 @@ __global__ __launch_bounds__(NW * 64) void forward_kernel(FwdArgs a) {
         const int s = s0 + u * NW;
         if (s < n_steps) {   // uniform over the wavefront
             load_a_step(s + NW, af[(u + 1) & 1]);
-            multiply_step(af[u & 1], wq[u]);
+            multiply_step(s, af[u & 1], wq[u]);
         }
     }
 

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import synth
-from test_gpu_parity import _blocks, _say, pkg  # noqa: F401
+from test_gpu_parity import _blocks, _problem, _say, pkg  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
@@ -42,7 +42,7 @@ def test_infinite_data_reach_the_loss(pkg, dims, E, bf16):
 
 
 @pytest.mark.parametrize("bf16", [False, True])
-@pytest.mark.parametrize("dims,E", [([70, 768, 10], 8192), ([33, 256, 10], 8192)])
+@pytest.mark.parametrize("dims,E", [([70, 768, 10], 8192), ([70, 130, 10], 500), ([33, 256, 10], 8192)])
 def test_infinite_last_weight_row_reaches_the_loss(pkg, dims, E, bf16):
     """The padding of the reduction reads a row that exists in place of rows that do not."""
     _say(f"infinite last row, evaluation, dims={dims} bf16={bf16}")
@@ -53,4 +53,20 @@ def test_infinite_last_weight_row_reaches_the_loss(pkg, dims, E, bf16):
     with pytest.raises(pkg.LcError) as e:
         run.loss()
     assert e.value.status == -7
+    run.close()
+
+
+@pytest.mark.parametrize("resident", [True, False])
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("dims,B", [([70, 130, 10], 16), ([70, 130, 33, 10], 100), ([33, 65, 5], 48)])
+def test_infinite_last_weight_row_reaches_the_local_losses(pkg, orc, dims, B, bf16, resident):
+    _say(f"infinite last row, step, dims={dims} B={B} bf16={bf16} resident={resident}")
+    _, run = _problem(pkg, orc, dims, 2, B, bf16=bf16, resident=resident)
+    for l in range(1, len(dims)):   # every unit positive, so that the infinity is passed on
+        _weights(run, dims, l)[:] = 0.01
+    run.X[:, dict(_blocks(dims))["b1"]] = 100.0
+    _weights(run, dims, 1)[:, -1, 3] = np.inf
+    run.local_steps(1)
+    losses = run.local_losses()
+    assert not np.isfinite(losses).any(), losses
     run.close()
