@@ -154,11 +154,10 @@ int lc_average(lc_handle* h);
 /* n_periods times { tau local iterations; averaging step } (Sec. 2: the PASGD update rule run
  * over n_periods communication periods of length tau).  The result is that of calling
  * lc_local_steps(h, tau); lc_average(h) n_periods times, and that is what happens for most
- * shapes.  Where the resident step kernel applies (see lc_set_resident), tau is at most the
- * number of steps it takes per launch, m is at most the number of compute units, and the model is
- * small (softmax regression; two layers split over workgroups with m * ceil64(d0) * 64 bytes <= 200 KB,
- * the amount a workgroup then reads from the other replicas; one workgroup per replica with
- * 4 m P bytes <= 200 KB),
+ * shapes.  Where the resident step kernel applies (see lc_set_resident: one and two layers within its
+ * limits), tau is at most the number of steps it takes per launch, m is at most the number of compute
+ * units, and the model is small (softmax regression, or m * ceil64(d0) * 64 bytes <= 200 KB, the amount
+ * a workgroup then reads from the other replicas),
  * several whole periods are ONE launch: at an averaging step every workgroup hands over its part
  * of the model, all workgroups of all replicas meet at a barrier in device memory (bounded wait,
  * LC_ERR_SYNC as described at lc_set_resident), and each forms the mean of its own part -- same

@@ -150,7 +150,7 @@ size_t carve(lc_handle* h, char* base) {
     }
     const size_t shares = backward_share_floats(h);
     h->da_part = shares ? static_cast<float*>(c.take(sizeof(float) * shares)) : nullptr;
-    if (resident_shape_ok(h) || net_shape_ok(h)) {
+    if (resident_shape_ok(h)) {
         h->res_a1x = static_cast<float*>(c.take(sizeof(float) * resident_exchange_floats(h)));
         h->res_ctr = static_cast<unsigned*>(c.take(sizeof(unsigned) * 384));
         h->res_avx = static_cast<float*>(c.take(sizeof(float) * 2 * static_cast<size_t>(h->m) * h->Ps));
@@ -231,6 +231,9 @@ int one_local_step(lc_handle* h, bool next_gathered, bool implicit_out = false) 
     return LC_OK;
 }
 
+// Local steps run with the models on chip: the resident step kernels, or one compute unit per replica.
+bool on_chip(const lc_handle* h) { return h->res_on && (h->res_a1x || h->net_ok); }
+
 // Reads and clears the error flag of the resident step kernel.  Call after a stream synchronise.
 int check_resident(lc_handle* h) {
     if (!h->res_used || !h->res_ctr) return LC_OK;
@@ -264,7 +267,7 @@ int whole_periods(int64_t k, int tau, int64_t lim, int64_t k_end) {
 int run_periods(lc_handle* h, int tau, int n_periods, bool average) {
     const bool mlp = h->md.kind == LC_KIND_MLP;
     const int slots = mlp ? h->train.slots : kGatherSlots;
-    const bool resident = mlp && h->res_on && h->res_a1x;
+    const bool resident = mlp && on_chip(h);
     const bool defer_ok = mlp && !resident && average && tau == 1 && h->defer_x_on && h->lazy_enabled &&
                           !h->bm_on && !head_is_fused(h);
     const bool fuse_ok = mlp && !resident && average && tau > 1 && h->fuse_avg_on && h->lazy_enabled && !h->bm_on &&
@@ -279,7 +282,7 @@ int run_periods(lc_handle* h, int tau, int n_periods, bool average) {
         for (int t = 0; t < n;) {
             const int in_period = tau - pos < n - t ? tau - pos : static_cast<int>(n - t);
             if (resident) {
-                LC_HIP(h, launch_resident(h, t, in_period, 0));
+                LC_HIP(h, h->net_ok ? launch_net(h, t, in_period) : launch_resident(h, t, in_period, 0));
                 t += in_period;
                 h->train.cur_slot = t - 1;
                 h->k += in_period;
@@ -417,6 +420,7 @@ int lc_init(int m, int64_t P, const lc_model* md, uint64_t seed, lc_handle** out
     h->res_a1x = nullptr;
     h->res_ctr = nullptr;
     h->da_part = nullptr;
+    h->net_ok = net_shape_ok(h);
     h->res_on = true;
     h->res_fuse_always = false;
     h->fl_on = true;
@@ -514,14 +518,10 @@ int lc_local_periods(lc_handle* h, int tau, int n_periods) {
     if (tau < 1 || n_periods < 1) return LC_ERR_ARG;
     // In-kernel averaging pays while the m copies a workgroup has to read from the other replicas
     // (other XCDs) are small: measured on the 784-256-10 model at m = 8, 400 KB per workgroup take
-    // 15 us, more than ending the launch and running the averaging kernel costs.  (net_kernel: one
-    // workgroup reads m whole models.)
-    const bool mlp = h->md.kind == LC_KIND_MLP;
-    const int64_t copies = !mlp ? 0 : resident_shape_ok(h) ? static_cast<int64_t>(h->m) * h->layer[1].dp_in * 64
-                                                           : static_cast<int64_t>(h->m) * h->P * 4;
-    const bool small = (h->L == 1 && resident_shape_ok(h)) || copies <= 200 * 1024;
-    const bool fused = mlp && h->res_on && h->res_a1x && h->res_avx && !h->bm_on && tau <= h->train.slots &&
-                       h->m <= resident_workgroup_budget() && (small || h->res_fuse_always);
+    // 15 us, more than ending the launch and running the averaging kernel costs.
+    const bool small = h->L == 1 || static_cast<int64_t>(h->m) * h->layer[1].dp_in * 64 <= 200 * 1024;
+    const bool fused = h->md.kind == LC_KIND_MLP && h->res_on && h->res_a1x && h->res_avx && !h->bm_on &&
+                       tau <= h->train.slots && h->m <= resident_workgroup_budget() && (small || h->res_fuse_always);
     if (!fused) return run_periods(h, tau, n_periods, true);
     // weights resident on chip: as many whole periods per launch as one gather launch has inputs
     // for, the averaging steps taken inside the kernel
@@ -607,7 +607,7 @@ int lc_set_fused_averaging(lc_handle* h, int mode) {
 int lc_implicit_momentum_layers(const lc_handle* h) {
     if (!h) return LC_ERR_ARG;
     if (!h->attached) return LC_ERR_STATE;
-    if (h->res_on && h->res_a1x) return 0;
+    if (on_chip(h)) return 0;
     int n = 0;
     for (int l = 1; l <= h->L; ++l) n += implicit_layer_ok(h, l) ? 1 : 0;
     return n;
@@ -622,7 +622,7 @@ int lc_set_deferred_update(lc_handle* h, int on) {
 int lc_resident_active(const lc_handle* h) {
     if (!h) return LC_ERR_ARG;
     if (!h->attached) return LC_ERR_STATE;
-    return (h->res_on && h->res_a1x) ? 1 : 0;
+    return on_chip(h) ? 1 : 0;
 }
 
 int lc_set_barrier_polls(lc_handle* h, int polls) {

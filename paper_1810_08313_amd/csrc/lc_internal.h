@@ -126,6 +126,7 @@ struct lc_handle {
     float* res_a1x;         // [2 parities][m][dp1/16][Bp][16] exchange buffer of the resident kernel, null when the shape does not qualify
     unsigned* res_ctr;      // [0..63] arrival counters per replica, [64] error flag, [65] all-replica counter, [128..383] placement probe
     unsigned res_arrivals;  // value of every counter once the queued launches have run (zeroed with the scratch at attach)
+    bool net_ok;            // the model runs whole local steps on one compute unit per replica (net_kernel)
     float* da_part;         // shares of dA of the largest layer whose columns are shared out (see BwdArgs), or null
     float* res_avx;         // [2 parities][m][Ps] models handed over at averaging steps inside a launch
     unsigned res_garrivals; // the same for the all-replica counter of those averaging steps (res_ctr[65])
@@ -188,7 +189,7 @@ bool resident_shape_ok(const lc_handle* h);
 int resident_workgroup_budget();   // workgroups of a whole compute unit each that are on the chip together
 // small networks of any depth, one compute unit per replica (shapes the resident kernels do not take)
 bool net_shape_ok(const lc_handle* h);
-hipError_t launch_net(lc_handle* h, int slot0, int n_steps, int period);
+hipError_t launch_net(lc_handle* h, int slot0, int n_steps);  // as launch_resident, one period or less
 size_t resident_exchange_floats(const lc_handle* h);
 hipError_t probe_block_placement(lc_handle* h);   // synchronises the stream once
 hipError_t launch_resident(lc_handle* h, int slot0, int n_steps, int period);  // the steps gathered into slots slot0 .. slot0+n_steps-1

@@ -7,7 +7,7 @@
 // Those kernels need 2 L launches per step of 6 to 20 us each at this size, nearly all of it launch
 // and dependent memory round trips; here a step is 2 L + 1 phases between workgroup barriers, bound
 // by the matrix instructions of one compute unit (fp32) and by LDS (bf16).
-// (130-70-33-7, 3 workers, batch 48, fp32, two periods of 3 steps: 348 -> 142 us, 17 us a step.)
+// (130-70-33-7, 3 workers, batch 48, fp32, two periods of 3 steps: 346 -> 134 us, 17 us a step.)
 //
 // One step, 16 wavefronts sharing out 16 x 16 tiles of every product:
 //   A_l = ReLU(A_{l-1} W_l + b_l) for l = 1 .. L (the last one without ReLU)
@@ -19,11 +19,11 @@
 // [unit][sample].  With that every store of a result tile is one 16-byte access, and of the six
 // operand reads three are (the others are four 4-byte reads of 16 consecutive lanes each).
 //
-// A launch may hold several communication periods, as resident_kernel's: at an averaging step every
-// workgroup hands over its model, waits for all of them, and forms the mean of the m copies.
+// No workgroup waits for another: a launch ends with its period, and the averaging step is a launch
+// of its own.  (Averaging inside the launch, behind a barrier of all replicas, can time out where other
+// streams keep workgroups of the launch off the chip; the case above took 142 us with it.)
 #include "lc_internal.h"
 #include "lc_mma.h"
-#include "lc_barrier.h"
 
 namespace lc {
 
@@ -62,12 +62,6 @@ struct NetArgs {
     int slot0, n_steps;
     float lr, beta_first, beta, wd;
     float* loss;             // [G][kLossParts], slot 0 written
-    int period;              // averaging step after every `period` steps inside the launch; 0: none
-    float* avx;              // [2][G][x_stride] models handed over at an averaging step, by parity of the period
-    unsigned* gctr;          // arrivals of all workgroups at averaging steps since attach
-    unsigned gctr_base;
-    unsigned* err;
-    int spin_limit;
 };
 
 __device__ __forceinline__ float net_round(float x, bf16_t) { return static_cast<float>(static_cast<bf16_t>(x)); }
@@ -149,66 +143,6 @@ __global__ __launch_bounds__(kNetThreads) void net_kernel(NetArgs a) {
         stage(static_cast<const OT*>(a.a0_fm) + a.slot0 * a.a0_slot + static_cast<int64_t>(g) * a.dp0 * a.Bp);
         __syncthreads();
     }
-
-    bool gave_up = false;   // thread 0: a barrier wait ran out of polls
-    // The averaging step (see the step loop); pi: period inside this launch.
-    auto average = [&](const NetLayer* layer, int tid, int pi) {
-        const int lane = tid & 63, j = lane & 15, q = lane >> 4;
-        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-        float* all = a.avx + static_cast<int64_t>(pi & 1) * a.G * a.x_stride;
-        float* mine = all + g * a.x_stride;
-        for (int t = wave; t < a.n_tiles; t += kNetWaves) {
-            const int e = __builtin_amdgcn_readfirstlane(tiles[t]);
-            const NetLayer& y = layer[e >> 16];
-            const int k0 = 16 * (e >> 8 & 255) + 4 * q, n = 16 * (e & 255) + j;
-            const f32x4 w = *reinterpret_cast<const f32x4*>(s + y.w + n * y.ws + k0);
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                if (k0 + r < y.d_in && n < y.d_out) mine[y.w_off + static_cast<int64_t>(k0 + r) * y.d_out + n] = w[r];
-        }
-        for (int l = 0; l < a.L; ++l)
-            for (int n = tid; n < layer[l].d_out; n += kNetThreads) mine[layer[l].b_off + n] = s[layer[l].bias + n];
-        __builtin_amdgcn_s_waitcnt(0);   // this wavefront's stores have left before the workgroup arrives
-        __syncthreads();
-        if (tid == 0)
-            arrive_and_wait(a.gctr, a.gctr_base + static_cast<unsigned>(pi + 1) * static_cast<unsigned>(a.G), a.spin_limit,
-                            a.err, gave_up);
-        __syncthreads();
-        const double dm = static_cast<double>(a.G);
-        for (int t = wave; t < a.n_tiles; t += kNetWaves) {
-            const int e = __builtin_amdgcn_readfirstlane(tiles[t]);
-            const NetLayer& y = layer[e >> 16];
-            const int k0 = 16 * (e >> 8 & 255) + 4 * q, n = 16 * (e & 255) + j;
-            double sum[4] = {0.0, 0.0, 0.0, 0.0};
-            int64_t at[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                at[r] = y.w_off + ((k0 + r < y.d_in && n < y.d_out) ? static_cast<int64_t>(k0 + r) * y.d_out + n : 0);
-            for (int g0 = 0; g0 < a.G; g0 += 2) {   // eight loads in flight, added in replica order
-                float x[2][4];
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
-                    if (g0 + u < a.G) {
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) x[u][r] = all[(g0 + u) * a.x_stride + at[r]];
-                    }
-#pragma unroll
-                for (int u = 0; u < 2; ++u)
-                    if (g0 + u < a.G) {
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) sum[r] += static_cast<double>(x[u][r]);
-                    }
-            }
-            f32x4 w;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) w[r] = (k0 + r < y.d_in && n < y.d_out) ? static_cast<float>(sum[r] / dm) : 0.f;
-            *reinterpret_cast<f32x4*>(s + y.w + n * y.ws + k0) = w;
-        }
-        for (int l = 0; l < a.L; ++l)
-            for (int n = tid; n < layer[l].d_out; n += kNetThreads)
-                s[layer[l].bias + n] = mean_of_replicas(all + layer[l].b_off + n, a.x_stride, a.G);
-        __syncthreads();
-    };
 
     for (int step = 0; step < a.n_steps; ++step) {
         // What a step derives from the thread's id and from the layer table is derived afresh from
@@ -449,14 +383,6 @@ __global__ __launch_bounds__(kNetThreads) void net_kernel(NetArgs a) {
             stage(A0T + a.a0_slot);
             __syncthreads();
         }
-        if (a.period == 0 || (step + 1) % a.period != 0) continue;
-        // ---- averaging step: hand over the model, wait for all replicas, take the mean of the copies
-        // (two buffers by parity of the period, see average_resident; opaque copies as above)
-        int tid_v = threadIdx.x, zero_v = 0;
-        asm volatile("" : "+v"(tid_v));
-        asm volatile("" : "+s"(zero_v));
-        const NetLayer* const layer_v = a.layer + zero_v;
-        average(layer_v, tid_v, (step + 1) / a.period - 1);
     }
     // ---- write the state back
 #pragma unroll
@@ -532,11 +458,12 @@ bool net_layout(const lc_handle* h, NetArgs& a) {
 }  // namespace
 
 bool net_shape_ok(const lc_handle* h) {
+    if (resident_shape_ok(h)) return false;
     NetArgs a;
     return net_layout(h, a);
 }
 
-hipError_t launch_net(lc_handle* h, int slot0, int n_steps, int period) {
+hipError_t launch_net(lc_handle* h, int slot0, int n_steps) {
     const ActSet& S = h->train;
     NetArgs a;
     if (!net_layout(h, a)) return hipErrorInvalidValue;
@@ -559,14 +486,7 @@ hipError_t launch_net(lc_handle* h, int slot0, int n_steps, int period) {
     a.beta = h->md.beta;
     a.wd = h->md.wd;
     a.loss = S.loss;
-    a.period = period;
-    a.avx = h->res_avx;
-    a.gctr = h->res_ctr + 65;
-    a.gctr_base = h->res_garrivals;
-    a.err = h->res_ctr + 64;
-    a.spin_limit = h->res_spin_limit;
     if (slot0 < 0 || n_steps < 1 || slot0 + n_steps > S.slots || a.Bq > S.Bp) return hipErrorInvalidValue;
-    if (period < 0 || (period > 0 && (n_steps % period != 0 || !h->res_avx || S.G > resident_workgroup_budget()))) return hipErrorInvalidValue;
     timing_start(h, kTimeBwd, 0, kBwdResident);
     const dim3 grid(S.G), block(kNetThreads);
     if (h->md.gemm == LC_GEMM_BF16) {
@@ -577,7 +497,6 @@ hipError_t launch_net(lc_handle* h, int slot0, int n_steps, int period) {
         else hipLaunchKernelGGL((net_kernel<float, false>), grid, block, 0, h->stream, a);
     }
     h->loss_parts_train = 1;
-    if (period > 0) h->res_garrivals += static_cast<unsigned>(n_steps / period) * static_cast<unsigned>(S.G);
     timing_stop(h, kTimeBwd, 0, kBwdResident);
     return hipGetLastError();
 }

@@ -44,7 +44,6 @@
 // all workgroups of all replicas, always at agent scope.
 #include "lc_internal.h"
 #include "lc_mma.h"
-#include "lc_barrier.h"
 
 namespace lc {
 
@@ -88,6 +87,27 @@ struct ResArgs {
     unsigned gctr_base;   // its value when this launch starts
 };
 
+// Barrier among the workgroups that add to *ctr, called by one thread per workgroup after a
+// workgroup barrier: what the workgroup wrote before is visible to every workgroup that leaves
+// the wait.  The wait is bounded; a workgroup that runs out of polls raises the error flag and
+// never waits again (it still arrives, so the counts stay right), so the grid always drains.
+__device__ __forceinline__ void arrive_and_wait(unsigned* ctr, unsigned target, int spin_limit, unsigned* err,
+                                                bool& gave_up) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int polls = 0;
+    while (!gave_up) {
+        if (polls++ >= spin_limit) {   // a limit of 0 gives up without looking: the host's way to force this path
+            gave_up = true;
+            atomicOr(err, 1u);
+            break;
+        }
+        const unsigned seen = __hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (static_cast<int>(seen - target) >= 0) break;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+}
+
 // The same barrier for workgroups that all run on one XCD, i.e. behind one L2: counter and data
 // need not leave that L2.  Read-modify-write atomics without the device-scope bit are performed
 // in the L2, so the counter is added to and polled there (the poll is a compare-and-swap that
@@ -122,6 +142,22 @@ __device__ __forceinline__ unsigned this_xcd() { return __builtin_amdgcn_s_getre
 
 __global__ void xcd_probe_kernel(unsigned* out) {
     if (threadIdx.x == 0) out[blockIdx.x] = this_xcd();
+}
+
+// x_bar = (1/m) sum_i x^(i) of one entry (Sec. 2, the averaging step), summed in double in
+// replica order and rounded once: the same arithmetic, bit for bit, as the averaging kernels.
+__device__ __forceinline__ float mean_of_replicas(const float* p, int64_t stride, int G) {
+    double s = 0.0;
+    for (int i0 = 0; i0 < G; i0 += 4) {   // four loads in flight, added in replica order
+        float r[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (i0 + u < G) r[u] = p[(i0 + u) * stride];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (i0 + u < G) s += static_cast<double>(r[u]);
+    }
+    return static_cast<float>(s / static_cast<double>(G));
 }
 
 __device__ __forceinline__ float round_operand(float x, bf16_t) { return static_cast<float>(static_cast<bf16_t>(x)); }
@@ -689,7 +725,7 @@ __global__ __launch_bounds__(kResThreads) void resident1_kernel(Res1Args a) {
 size_t resident_exchange_floats(const lc_handle* h) {
     // two step parities x (replicas x padded batch x padded hidden width); the single-layer form
     // exchanges nothing (a token amount keeps the buffer pointer non-null)
-    if (h->L == 1 || !resident_shape_ok(h)) return 64;
+    if (h->L == 1) return 64;
     return 2 * static_cast<size_t>(h->m) * h->train.Bp * h->layer[1].dp_out;
 }
 
@@ -776,7 +812,6 @@ hipError_t launch_resident1(lc_handle* h, int slot0, int n_steps, int period) {
 }  // namespace
 
 hipError_t launch_resident(lc_handle* h, int slot0, int n_steps, int period) {
-    if (!resident_shape_ok(h)) return launch_net(h, slot0, n_steps, period);
     if (h->L == 1) return launch_resident1(h, slot0, n_steps, period);
     const ActSet& S = h->train;
     const bool bf16 = h->md.gemm == LC_GEMM_BF16;
@@ -854,7 +889,7 @@ hipError_t launch_resident(lc_handle* h, int slot0, int n_steps, int period) {
 hipError_t probe_block_placement(lc_handle* h) {
     h->res_xcc_known = false;
     h->res_xcc_of = 0;
-    if (!h->res_ctr || h->L != 2 || !resident_shape_ok(h)) return hipSuccess;   // (no exchange between workgroups)
+    if (!h->res_ctr) return hipSuccess;
     unsigned* dev = h->res_ctr + 128;
     unsigned host[256];
     hipLaunchKernelGGL(xcd_probe_kernel, dim3(256), dim3(64), 0, h->stream, dev);

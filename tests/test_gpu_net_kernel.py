@@ -1,6 +1,6 @@
 """Small networks of any depth with the whole model on one compute unit (net_kernel): against the
-oracle at the edges of its shapes, its averaging steps inside the launch against the call-by-call
-form bit for bit, and the forced time-out of their barrier.  The bars are those of test_gpu_parity.py."""
+oracle at the edges of its shapes, whole periods against the call-by-call form bit for bit, and that
+they need no barrier.  The bars are those of test_gpu_parity.py."""
 import numpy as np
 import pytest
 
@@ -52,8 +52,8 @@ def test_steps_and_average(pkg, orc, dims, m, B, bf16):
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("dims,m,B,tau,periods", [([130, 70, 33, 7], 3, 48, 3, 2), ([64, 20, 17], 5, 70, 1, 9),
                                                   ([40, 24, 16, 10], 9, 16, 5, 13)])
-def test_periods_in_one_launch(pkg, orc, dims, m, B, tau, periods, bf16):
-    _say(f"net kernel, periods in one launch dims={dims} tau={tau} n={periods} bf16={bf16}")
+def test_periods_against_call_by_call(pkg, orc, dims, m, B, tau, periods, bf16):
+    _say(f"net kernel, periods dims={dims} tau={tau} n={periods} bf16={bf16}")
     _, run = _problem(pkg, orc, dims, m, B, wd=5e-4, bf16=bf16, lr=0.05)
     _, sep = _problem(pkg, orc, dims, m, B, wd=5e-4, bf16=bf16, lr=0.05)
     assert run.resident_active()
@@ -74,21 +74,23 @@ def test_periods_in_one_launch(pkg, orc, dims, m, B, tau, periods, bf16):
     sep.close()
 
 
-def test_forced_time_out_is_reported(pkg, orc):
-    dims, m, B = [20, 12, 8, 5], 4, 24
-    ref, run = _problem(pkg, orc, dims, m, B)
-    x1 = ref.X.copy()
-    run.set_barrier_polls(0)
-    run.local_periods(2, 3)
-    with pytest.raises(pkg.LcError) as e:
-        run.get_state()
-    assert e.value.status == -9
-    run.set_barrier_polls(400000)
-    run.set_state(x1, np.zeros_like(x1), 0)
-    run.local_periods(2, 3)
-    for _ in range(3):
-        ref.local_steps(2)
-        ref.average()
-    X, _, _ = run.get_state()
-    _assert_close(X, ref.X, dims, 1e-3, "after recovery")   # (six unforced steps: that it works again, not how exactly)
-    run.close()
+def test_periods_wait_for_no_other_workgroup(pkg, orc):
+    """Whole periods without a barrier among the replicas: with no polls allowed (a barrier would give up
+    at once and report it) they run as ever.  300 replicas cannot all be on the chip together."""
+    dims, B = [20, 12, 8, 5], 24
+    for m in (4, 300):
+        ref, run = _problem(pkg, orc, dims, m, B)
+        assert run.resident_active()
+        for on in (1, 2):
+            run.set_resident(on)
+            run.set_barrier_polls(0)
+            masks = UnitMasks()
+            run.local_periods(1, 2)
+            for j in range(2):
+                _ref_steps(orc, ref, 11, 1, masks, fresh=j == 0)
+                ref.average()
+            X, _, k = run.get_state()
+            assert k == ref.k
+            _assert_close(X[0], ref.X[0], dims, TOL32, "mean", _xmask(ref, masks.union(range(m))), over="skip")
+            _force(run, ref)
+        run.close()
