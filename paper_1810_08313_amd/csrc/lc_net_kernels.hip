@@ -7,7 +7,7 @@
 // Those kernels need 2 L launches per step of 6 to 20 us each at this size, nearly all of it launch
 // and dependent memory round trips; here a step is 2 L + 1 phases between workgroup barriers, bound
 // by the matrix instructions of one compute unit (fp32) and by LDS (bf16).
-// (130-70-33-7, 3 workers, batch 48, fp32, two periods of 3 steps: 346 -> 134 us, 17 us a step.)
+// (130-70-33-7, 3 workers, batch 48, fp32, two periods of 3 steps: 346 -> 136 us, 17 us a step.)
 //
 // One step, 16 wavefronts sharing out 16 x 16 tiles of every product:
 //   A_l = ReLU(A_{l-1} W_l + b_l) for l = 1 .. L (the last one without ReLU)
@@ -167,7 +167,11 @@ __global__ __launch_bounds__(kNetThreads) void net_kernel(NetArgs a) {
             for (int t = wave; t < n_t; t += kNetWaves) {
                 const int b0 = 16 * (t % nbt), n = 16 * (t / nbt) + j;
                 const float* wt = s + y.w + n * y.ws + 4 * q;
-                f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+                // sums of 32 products, added up: one accumulator over the whole reduction is off by 1.23
+                // times (up to 1.95) as much in the gradients as the launches per layer, whose
+                // wavefronts share out the reduction
+                const f32x4 zeros = f32x4{0.f, 0.f, 0.f, 0.f};
+                f32x4 acc = zeros;
                 if (!IN_LDS && l == 0) {
                     // the input rows come from memory: four steps' operands in flight
                     const OT* ar = A0 + static_cast<int64_t>(b0 + j) * a.dp0 + 4 * q;
@@ -181,27 +185,33 @@ __global__ __launch_bounds__(kNetThreads) void net_kernel(NetArgs a) {
                             const int st = s0 + kF + u;
                             nxt[u] = load4(ar + 16 * (st < n_s ? st : 0));
                         }
+                        f32x4 part = zeros;
 #pragma unroll
-                        for (int u = 0; u < kF; ++u)
+                        for (int u = 0; u < kF; ++u) {
                             if (s0 + u < n_s) {   // uniform
                                 const float4 w = *reinterpret_cast<const float4*>(wt + 16 * (s0 + u));
                                 Frag4<OT> bf;
                                 pack4(bf, w.x, w.y, w.z, w.w);
-                                acc = mma4(cur[u], bf, acc);
+                                part = mma4(cur[u], bf, u % 2 == 0 ? zeros : part);
+                                if (u % 2 == 1 || s0 + u + 1 == n_s) acc += part;
                             }
+                        }
 #pragma unroll
                         for (int u = 0; u < kF; ++u) cur[u] = nxt[u];
                     }
                 } else {
                     const float* ap = s + (l == 0 ? a.a0 : layer[l - 1].act) + 4 * q * BS + b0 + j;
-#pragma unroll 1
-                    for (int st = 0; st < n_s; ++st, ap += 16 * BS, wt += 16) {
-                        const float4 w = *reinterpret_cast<const float4*>(wt);
+                    auto product = [&](const float* x, const float* wr, f32x4 c) {
+                        const float4 w = *reinterpret_cast<const float4*>(wr);
                         Frag4<OT> af, bf;
-                        pack4(af, ap[0], ap[BS], ap[2 * BS], ap[3 * BS]);
+                        pack4(af, x[0], x[BS], x[2 * BS], x[3 * BS]);
                         pack4(bf, w.x, w.y, w.z, w.w);
-                        acc = mma4(af, bf, acc);
-                    }
+                        return mma4(af, bf, c);
+                    };
+#pragma unroll 1
+                    for (int st = 1; st < n_s; st += 2, ap += 32 * BS, wt += 32)
+                        acc += product(ap + 16 * BS, wt + 16, product(ap, wt, zeros));
+                    if (n_s & 1) acc += product(ap, wt, zeros);
                 }
                 const float bias = s[y.bias + n];
                 f32x4 o;

@@ -1,0 +1,52 @@
+"""How far fp32 gradients are from 64 bits must not depend on the route a shape takes: the kernels share
+out their reductions differently, but none may add up in longer chains than the others."""
+import numpy as np
+import pytest
+
+import synth
+from test_gpu_parity import _blocks, _say, pkg  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def _error(pkg, dims, m, B, workers, **switches):
+    """rms over the layers of the relative 2-norm error of one step's weight gradients (the momentum after
+    the first step), median over some of the workers, so that a gate that opens on one side only does not count."""
+    N = 1000
+    data, labels = synth.gaussian_mixture(9, N, dims[0], dims[-1], mean_sd=1.0)
+    x1 = synth.init_params(9, dims)
+    run = pkg.LocalSGD(m, pkg.make_model(pkg.KIND_MLP, dims, B=B, N=N, E=64, lr=0.01, beta=0.0), 9, x1, data, labels)
+    for name, value in switches.items():
+        getattr(run, name)(value)
+    run.local_steps(1)
+    idx, V, x = run.last_indices(), run.get_state()[1].astype(np.float64), x1.astype(np.float64)
+    run.close()
+    sl, errors = dict(_blocks(dims)), []
+    for i in range(workers):
+        a, W = [data[idx[i]].astype(np.float64)], []
+        for l, (d, e) in enumerate(zip(dims, dims[1:]), 1):
+            W.append(x[sl[f"W{l}"]].reshape(d, e))
+            z = a[-1] @ W[-1] + x[sl[f"b{l}"]]
+            a.append(z if l == len(dims) - 1 else np.maximum(z, 0.0))
+        p = np.exp(a[-1] - a[-1].max(1, keepdims=True))
+        dz = p / p.sum(1, keepdims=True)
+        dz[np.arange(B), labels[idx[i]]] -= 1.0
+        dz /= B
+        row = []
+        for l in range(len(dims) - 1, 0, -1):
+            g = a[l - 1].T @ dz
+            row.append(np.linalg.norm(V[i, sl[f"W{l}"]].reshape(g.shape) - g) / np.linalg.norm(g))
+            dz = (dz @ W[l - 1].T) * (a[l - 1] > 0)
+        errors.append(row)
+    return float(np.sqrt(np.mean(np.median(errors, axis=0) ** 2)))
+
+
+@pytest.mark.parametrize("dims,B", [([324, 16, 16, 10], 48), ([400, 16, 10, 3], 16), ([196, 20], 66), ([130, 70, 33, 7], 48),
+                                    ([64, 40, 84, 20, 11], 62)])
+def test_models_on_one_compute_unit(pkg, dims, B):
+    """Against the launches per layer.  Both are sums of the same products; a tenth is left for chance."""
+    on = _error(pkg, dims, 5, B, 5, set_resident=True)
+    off = _error(pkg, dims, 5, B, 5, set_resident=False)
+    _say(f"error dims={dims} B={B}: on one compute unit {on:.3e}, launches per layer {off:.3e}")
+    assert on != off   # (two routes)
+    assert on < 1.1 * off
