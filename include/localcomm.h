@@ -191,7 +191,11 @@ int lc_materialize(lc_handle* h);
  * regression) with at most 16 classes, B <= 64 and padded d0 <= 256 take the same route with one
  * workgroup per replica and no barrier.  Other models of any depth with at most 64 classes do too
  * where one replica's weights (widths padded to multiples of 16), one batch's activations and its
- * deltas fit 159 KB together, and the weights are at most 128 tiles of 16 x 16.  Same arithmetic as the
+ * deltas fit 159 KB together, the weights are at most 128 tiles of 16 x 16, and one compute unit per
+ * replica is the faster way at any number of steps per call: four layers and more; fewer where the
+ * batch's inputs fit as well (two layers of a first hidden width of 64 and more: below 88 tiles; one
+ * layer of at most 16 classes: below 24); otherwise two layers below 40 tiles and three below 80 (64 and
+ * 112 with a first hidden width below 64).  lc_resident_active() tells.  Same arithmetic as the
  * launch-per-layer path up to the summation order (results agree to rounding, not bit for bit).
  * on = 0 selects the launch-per-layer path for every shape; the default is on (1); on = 2
  * additionally makes lc_local_periods() take the averaging steps inside the launch at every

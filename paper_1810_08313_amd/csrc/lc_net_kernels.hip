@@ -467,10 +467,25 @@ bool net_layout(const lc_handle* h, NetArgs& a) {
 
 }  // namespace
 
+// A model that fits takes this route where one compute unit per replica is the faster way at any number of
+// steps per call.  Measured against the launches per layer on 1493 models (inputs 16 .. 640, up to three
+// hidden layers of 16 .. 256, 2 .. 512 replicas of 8 .. 128 samples; calls of 1, 5 and 16 steps; the figures
+// are the slowest of the three):
+//   A_0 kept in LDS: 1.03 .. 5.8 times as fast, except one layer of few classes (launches of 12 us a
+//   step) and two layers with many weight tiles, where loading the state costs a call of one step: 0.95 on.
+//   A_0 read from memory, twice per step, at 0.2 (bf16) to 0.4 us per row of 16 x 16 tiles in the first
+//   layer where LDS takes 0.04 to 0.1: one layer 0.61 on; two layers of few tiles 1.07 on, of more from
+//   0.58 (limit twice as high, 1.16 on, below 0.71 on, where the first hidden layer is narrower than a
+//   column chunk, whose rows the launches read element by element); three layers of few tiles 1.01 on,
+//   of more 0.83; more layers 1.07 on.
 bool net_shape_ok(const lc_handle* h) {
     if (resident_shape_ok(h)) return false;
     NetArgs a;
-    return net_layout(h, a);
+    if (!net_layout(h, a)) return false;
+    if (a.L >= 4) return true;
+    const bool narrow = a.layer[0].d_out < kColChunk;
+    if (a.a0 >= 0) return a.L == 3 || (a.L == 2 ? narrow || a.n_tiles < 88 : a.layer[0].d_out > 16 || a.n_tiles < 24);
+    return (a.L == 2 && a.n_tiles < (narrow ? 64 : 40)) || (a.L == 3 && a.n_tiles < (narrow ? 112 : 80));
 }
 
 hipError_t launch_net(lc_handle* h, int slot0, int n_steps) {

@@ -94,3 +94,23 @@ def test_periods_wait_for_no_other_workgroup(pkg, orc):
             _assert_close(X[0], ref.X[0], dims, TOL32, "mean", _xmask(ref, masks.union(range(m))), over="skip")
             _force(run, ref)
         run.close()
+
+
+@pytest.mark.parametrize("dims,m,B,takes", [
+    ([448, 38], 8, 112, False),            # inputs of one layer read from memory
+    ([196, 20], 8, 60, True),              # ... kept in LDS
+    ([320, 64, 26], 2, 64, False),         # two layers, 88 weight tiles, inputs from memory
+    ([300, 64, 26], 2, 16, True),          # ... 84, kept in LDS
+    ([320, 64, 26], 2, 16, False),         # 88
+    ([384, 10], 4, 32, False),             # one layer, few classes
+    ([128, 64, 3], 14, 128, True),         # 36 tiles, from memory
+    ([468, 64, 30], 11, 24, False),
+    ([607, 24, 32], 12, 32, False),        # 80 tiles, first hidden layer narrower than a column chunk
+    ([304, 64, 64, 13], 4, 48, False),     # three layers, 96 tiles
+    ([64, 40, 84, 20, 11], 11, 62, True),  # four layers
+])
+def test_shapes_that_take_one_compute_unit(pkg, orc, dims, m, B, takes):
+    """The route is taken where it was measured to be the faster one (see net_shape_ok)."""
+    _, run = _problem(pkg, orc, dims, m, B)
+    assert run.resident_active() == takes
+    run.close()
