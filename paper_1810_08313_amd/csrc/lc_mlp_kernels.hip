@@ -1523,12 +1523,12 @@ hipError_t launch_forward(lc_handle* h, bool eval, int l, int loss_offset) {
     if (a.fuse_softmax) (eval ? h->loss_parts_eval : h->loss_parts_train) = a.m_split;
     a.total_blocks = static_cast<int64_t>(n_groups) * a.n_chunks * a.m_split;
     const unsigned grid = xcd_grid(a.total_blocks);
-    // few blocks: split the reduction over more wavefronts per block.  (Where the state is cached and there
-    // is a block per CU 4 wavefronts, two blocks of which fit a CU's LDS where 8 leave room for one, are
-    // faster: 784x500, 16 replicas of 100 samples, fp32, 256 blocks:
-    // 32 us with 8, 26 with 4; 500x300, 320 blocks: 22 and 20; bf16 at 208 blocks:
-    // 6.4 and 6.9, at 256: 7.8 and 7.4.)
-    const int64_t few = h->stream_weights || eval || mt < 2 ? 512 : bf16 ? 256 : 192;
+    // few blocks: split the reduction over more wavefronts per block.  (bf16 operands where the state is
+    // cached and there is a block per CU: 4 wavefronts, two blocks of which fit a CU's LDS where 8
+    // leave room for one, are faster.  784x500, 100 samples, at 208 blocks: 6.4 us with 8 wavefronts
+    // and 6.9 with 4, at 256: 7.8 and 7.4.  With fp32 operands sums twice as long would be 1.2 to 1.3
+    // times as far from 64 bits; bf16 results are rounded to 2^-9 anyway.)
+    const int64_t few = h->stream_weights || !bf16 || mt < 2 ? 512 : 256;
     const bool wide = a.total_blocks < few && g.dp_in >= 512;
     if (!eval) timing_start(h, kTimeFwd);
     hipError_t e;

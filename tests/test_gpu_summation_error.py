@@ -50,3 +50,12 @@ def test_models_on_one_compute_unit(pkg, dims, B):
     _say(f"error dims={dims} B={B}: on one compute unit {on:.3e}, launches per layer {off:.3e}")
     assert on != off   # (two routes)
     assert on < 1.1 * off
+
+
+@pytest.mark.parametrize("dims,m,B", [([2048, 500, 10], 24, 33), ([1024, 704, 10], 23, 64), ([784, 640, 10], 20, 100)])
+def test_forward_products_of_many_workers(pkg, dims, m, B):
+    """The same four workers among few and among many: with more column chunks in the launch a product may
+    be shared out differently among wavefronts, but not be summed up in longer chains."""
+    few, many = _error(pkg, dims, 4, B, 4, set_resident=False), _error(pkg, dims, m, B, 4, set_resident=False)
+    _say(f"error dims={dims} B={B}: 4 workers {few:.3e}, {m} workers {many:.3e}")
+    assert many < 1.1 * few
