@@ -1620,8 +1620,17 @@ hipError_t launch_softmax(lc_handle* h, bool eval, int loss_offset) {
 }
 
 // Workgroups that share the columns of a row block of layer l > 1: one, unless the row blocks of all
-// replicas leave CUs without work; then as many as fill the places there are, each with at least one chunk.  A state that streams from memory keeps the one pass with long walks.  (340x704,
-// 13 replicas of 90 samples, fp32: 78 workgroups of 11 chunks took 80 us; 768x768, 4 replicas of 64: 46 us.)
+// replicas leave CUs without work; then as many as fill the places there are, each with at least one
+// chunk.  A state that streams from memory keeps the one pass with long walks.  (340x704, 13 replicas
+// of 90 samples, fp32: 78 workgroups of 11 chunks took 80 us; 768x768, 4 replicas of 64: 46 us.)
+// What that saves is the chunks by which the longest walk gets shorter, counting a second round of
+// workgroups like the first.  What it costs is the launch that adds up the shares and their way
+// through memory.  In chunks, from 170 layers of 3 .. 16 chunks and 3 .. 240 row blocks: with bf16
+// operands 2 (1 at 128 samples, whose chunks take twice as long) and 2 more per 256 workgroups, with
+// fp32 operands 0.6 and 1.3.  Where less is saved the shares made whole steps up to 15 us slower:
+// 128-512-192-10, 24 replicas of 100, fp32: 103 -> 118 us; 64-448-192-10, 16 of 64, bf16: 40 -> 43;
+// 64-768-300-10, 13 of 128, bf16: 69 -> 79.  Where more is saved: 64-256-1024-10, 16 of 16, bf16:
+// 60 -> 50; 128-256-1024-10, 16 of 100, fp32: 178 -> 108.
 int backward_shares(const lc_handle* h, int l) {
     if (h->stream_weights || l < 2) return 1;
     const LayerGeom& g = h->layer[l];
@@ -1630,8 +1639,12 @@ int backward_shares(const lc_handle* h, int l) {
     if (base >= 256 || n_cc < 3) return 1;
     const int64_t slots = h->train.Bp == 128 ? 256 : 512;   // (at 128 samples the kernel's tiles leave room for one per CU)
     const int64_t want = (slots + base - 1) / base;
-    const int per = static_cast<int>((n_cc + want - 1) / want);   // chunks per workgroup
-    return (n_cc + per - 1) / per;
+    const int64_t per = (n_cc + want - 1) / want;   // chunks per workgroup
+    const int64_t shares = (n_cc + per - 1) / per, blocks = base * shares;
+    const double saved = static_cast<double>(n_cc - (blocks + slots - 1) / slots * per);
+    const double cost = h->md.gemm == LC_GEMM_BF16 ? (h->train.Bp == 128 ? 1.0 : 2.0) + 2.0 * static_cast<double>(blocks) / 256
+                                                   : 0.6 + 1.3 * static_cast<double>(blocks) / 256;
+    return saved > cost ? static_cast<int>(shares) : 1;
 }
 size_t backward_share_floats(const lc_handle* h) {
     size_t most = 0;
