@@ -222,8 +222,9 @@ int lc_set_xcd_local_exchange(lc_handle* h, int on);
 /* First-layer fusion across steps (Sec. 2: between two averaging steps a worker's updates touch
  * only its own model, so the first layer's weights after step k are what step k+1 multiplies its
  * mini-batch with).  Inside one lc_local_steps() call, for LC_KIND_MLP models with at least two
- * layers, at least 64 inputs and 64 first-layer columns, n = m * ceil(d1 / 64) >= 192, and n / 256
- * rounds of workgroups that are at least 60 % full (70 % above 64 samples), the
+ * layers, at least 64 inputs and 64 first-layer columns, n = m * ceil(d1 / 64) >= 192, and, where n / 256
+ * rounds of workgroups are more than one, rounds that are full enough (75 to 80 % above 64 samples, 70 to
+ * 85 % for ragged rows of a state above 256 MB, else any), the
  * first layer's backward kernel of a step also computes the first hidden activations of the
  * next step from the weight tile it has just updated, and that step's first-layer forward launch
  * is dropped: W_1 then moves 16 instead of 20 bytes per parameter and step.  The first step of a

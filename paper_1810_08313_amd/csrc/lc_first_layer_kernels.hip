@@ -615,10 +615,22 @@ bool first_layer_kernel_ok(const lc_handle* h) {
     if (h->md.gemm != LC_GEMM_BF16 && S.Bp == 128) return false;
     // Every workgroup walks a whole column chunk, so a last round of few workgroups takes as long as a
     // full one (3072x1024, batch 128: 147 us a step with 16 replicas = 256 workgroups, 250 with 20, 288
-    // with 32).  Fused against separate, whole runs: 1.02 rounds 0.88 .. 0.98 times as fast, 1.25 rounds
-    // 0.97 at batch 128 and 1.00 .. 1.09 below, 1.0, 1.5 and 1.8 rounds 1.01 .. 1.16, 4 rounds 1.08 .. 1.16.
+    // with 32).  How many times as fast whole runs are than with the separate launches, median (least)
+    // of 1709 models of d0 = 128 .. 3072, d1 = 256 .. 2048, by how full the rounds are on average:
+    //   one round (192 workgroups and more) 1.02 .. 1.17 everywhere
+    //   up to 64 samples, state cached or whole tiles: 50 .. 60 % 0.98 .. 1.10 (0.94), 60 .. 100 % 1.01 .. 1.17
+    //   up to 64 samples, ragged rows that stream: fp32 operands 0.86 .. 0.99 (0.85) below 80 %, 1.01 up to
+    //   90 %; bf16 0.90 .. 1.01 (0.89) below 70 %, 1.04 up to 80 %
+    //   128 samples: below 70 % 0.84 .. 1.01 (0.84), to 75 % 0.95 .. 1.02, to 80 % 0.97 .. 1.03 (ragged
+    //   and cached 0.97), above 0.99 .. 1.11
     const int64_t blocks = static_cast<int64_t>(S.G) * (g.dp_out / kColChunk), rounds = (blocks + 255) / 256;
-    return blocks >= 192 && 100 * blocks >= (S.Bp == 128 ? 70 : 60) * 256 * rounds;
+    if (blocks < 192) return false;
+    if (rounds == 1) return true;
+    const bool whole = g.d_out % kColChunk == 0 && g.w_off % 4 == 0 && g.d_in % 16 == 0;
+    int full = 0;   // per cent
+    if (S.Bp == 128) full = whole || h->stream_weights ? 75 : 80;
+    else if (!whole && h->stream_weights) full = h->md.gemm == LC_GEMM_BF16 ? 70 : 85;
+    return 100 * blocks >= full * 256 * rounds;
 }
 
 // Backward pass and update of layer 1 for the step in slot train.cur_slot, and A_1 of the step in
