@@ -521,7 +521,7 @@ int lc_local_periods(lc_handle* h, int tau, int n_periods) {
     // 15 us, more than ending the launch and running the averaging kernel costs.
     const bool small = h->L == 1 || static_cast<int64_t>(h->m) * h->layer[1].dp_in * 64 <= 200 * 1024;
     const bool fused = h->md.kind == LC_KIND_MLP && h->res_on && h->res_a1x && h->res_avx && !h->bm_on &&
-                       tau <= h->train.slots && h->m <= resident_workgroup_budget() && (small || h->res_fuse_always);
+                       tau <= h->train.slots && h->m <= compute_units() && (small || h->res_fuse_always);
     if (!fused) return run_periods(h, tau, n_periods, true);
     // weights resident on chip: as many whole periods per launch as one gather launch has inputs
     // for, the averaging steps taken inside the kernel

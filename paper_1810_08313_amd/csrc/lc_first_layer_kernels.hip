@@ -623,14 +623,15 @@ bool first_layer_kernel_ok(const lc_handle* h) {
     //   90 %; bf16 0.90 .. 1.01 (0.89) below 70 %, 1.04 up to 80 %
     //   128 samples: below 70 % 0.84 .. 1.01 (0.84), to 75 % 0.95 .. 1.02, to 80 % 0.97 .. 1.03 (ragged
     //   and cached 0.97), above 0.99 .. 1.11
-    const int64_t blocks = static_cast<int64_t>(S.G) * (g.dp_out / kColChunk), rounds = (blocks + 255) / 256;
+    const int64_t blocks = static_cast<int64_t>(S.G) * (g.dp_out / kColChunk);
+    const int64_t cus = compute_units(), rounds = (blocks + cus - 1) / cus;
     if (blocks < 192) return false;
     if (rounds == 1) return true;
     const bool whole = g.d_out % kColChunk == 0 && g.w_off % 4 == 0 && g.d_in % 16 == 0;
     int full = 0;   // per cent
     if (S.Bp == 128) full = whole || h->stream_weights ? 75 : 80;
     else if (!whole && h->stream_weights) full = h->md.gemm == LC_GEMM_BF16 ? 70 : 85;
-    return 100 * blocks >= full * 256 * rounds;
+    return 100 * blocks >= full * cus * rounds;
 }
 
 // Backward pass and update of layer 1 for the step in slot train.cur_slot, and A_1 of the step in

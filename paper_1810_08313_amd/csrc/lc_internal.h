@@ -186,7 +186,7 @@ hipError_t launch_head(lc_handle* h);
 
 // resident path (weights stay in LDS over a run of local steps)
 bool resident_shape_ok(const lc_handle* h);
-int resident_workgroup_budget();   // workgroups of a whole compute unit each that are on the chip together
+int compute_units();   // of the current device: workgroups of a whole compute unit each that are on the chip together
 // small networks of any depth, one compute unit per replica (shapes the resident kernels do not take)
 bool net_shape_ok(const lc_handle* h);
 hipError_t launch_net(lc_handle* h, int slot0, int n_steps);  // as launch_resident, one period or less

@@ -1626,7 +1626,7 @@ hipError_t launch_softmax(lc_handle* h, bool eval, int loss_offset) {
 // What that saves is the chunks by which the longest walk gets shorter, counting a second round of
 // workgroups like the first.  What it costs is the launch that adds up the shares and their way
 // through memory.  In chunks, from 170 layers of 3 .. 16 chunks and 3 .. 240 row blocks: with bf16
-// operands 2 (1 at 128 samples, whose chunks take twice as long) and 2 more per 256 workgroups, with
+// operands 2 (1 at 128 samples, whose chunks take twice as long) and 2 more per workgroup and CU, with
 // fp32 operands 0.6 and 1.3.  Where less is saved the shares made whole steps up to 15 us slower:
 // 128-512-192-10, 24 replicas of 100, fp32: 103 -> 118 us; 64-448-192-10, 16 of 64, bf16: 40 -> 43;
 // 64-768-300-10, 13 of 128, bf16: 69 -> 79.  Where more is saved: 64-256-1024-10, 16 of 16, bf16:
@@ -1636,14 +1636,15 @@ int backward_shares(const lc_handle* h, int l) {
     const LayerGeom& g = h->layer[l];
     const int n_cc = g.dp_out / kColChunk;
     const int64_t base = static_cast<int64_t>(h->m) * (g.dp_in / 64);
-    if (base >= 256 || n_cc < 3) return 1;
-    const int64_t slots = h->train.Bp == 128 ? 256 : 512;   // (at 128 samples the kernel's tiles leave room for one per CU)
+    const int64_t cus = compute_units();
+    if (base >= cus || n_cc < 3) return 1;
+    const int64_t slots = h->train.Bp == 128 ? cus : 2 * cus;   // (at 128 samples the kernel's tiles leave room for one per CU)
     const int64_t want = (slots + base - 1) / base;
     const int64_t per = (n_cc + want - 1) / want;   // chunks per workgroup
     const int64_t shares = (n_cc + per - 1) / per, blocks = base * shares;
     const double saved = static_cast<double>(n_cc - (blocks + slots - 1) / slots * per);
-    const double cost = h->md.gemm == LC_GEMM_BF16 ? (h->train.Bp == 128 ? 1.0 : 2.0) + 2.0 * static_cast<double>(blocks) / 256
-                                                   : 0.6 + 1.3 * static_cast<double>(blocks) / 256;
+    const double per_cu = static_cast<double>(blocks) / static_cast<double>(cus);
+    const double cost = h->md.gemm == LC_GEMM_BF16 ? (h->train.Bp == 128 ? 1.0 : 2.0) + 2.0 * per_cu : 0.6 + 1.3 * per_cu;
     return saved > cost ? static_cast<int>(shares) : 1;
 }
 size_t backward_share_floats(const lc_handle* h) {
