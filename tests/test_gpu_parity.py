@@ -390,10 +390,13 @@ def _resident_shape(dims, m, B):
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("dims,m,B", SHAPES)
 def test_one_local_step(pkg, orc, dims, m, B, bf16, resident):
-    if not resident and not _resident_shape(dims, m, B):
-        pytest.skip("only one engine handles this shape")
     _say(f"one step dims={dims} m={m} B={B} bf16={bf16} resident={resident}")
-    ref, run = _problem(pkg, orc, dims, m, B, wd=1e-3, bf16=bf16, resident=resident)
+    ref, run = _problem(pkg, orc, dims, m, B, wd=1e-3, bf16=bf16)
+    if not resident and not run.resident_active():
+        run.close()
+        pytest.skip("only one engine handles this shape")
+    run.set_resident(resident)
+    assert not _resident_shape(dims, m, B) or run.resident_active() == resident
     tol = TOL16 if bf16 else TOL32
     masks = UnitMasks()
     _ref_steps(orc, ref, 11, 1, masks)
@@ -405,11 +408,13 @@ def test_one_local_step(pkg, orc, dims, m, B, bf16, resident):
     run.close()
 
 
+@pytest.mark.parametrize("resident", [True, False])   # one compute unit per replica; launches per layer
 @pytest.mark.parametrize("bf16", [False, True])
-def test_round_of_local_steps_then_average(pkg, orc, bf16):
+def test_round_of_local_steps_then_average(pkg, orc, bf16, resident):
     dims, m, B, tau = [130, 70, 33, 7], 4, 48, 5
-    _say(f"round dims={dims} bf16={bf16}")
-    ref, run = _problem(pkg, orc, dims, m, B, wd=5e-4, bf16=bf16, lr=0.03)
+    _say(f"round dims={dims} bf16={bf16} resident={resident}")
+    ref, run = _problem(pkg, orc, dims, m, B, wd=5e-4, bf16=bf16, lr=0.03, resident=resident)
+    assert run.resident_active() == resident
     tol = TOL16 if bf16 else TOL32
     for r in range(2):
         masks = UnitMasks()
@@ -633,12 +638,14 @@ def test_resident_exchange_inside_one_xcd_is_bit_identical(pkg, orc, dims, m, B)
 PERIOD_CASES = [
     # dims, m, B, tau, periods: one launch holds several periods (32 steps at most); 7 periods of 5
     # need two launches; one period per launch at tau=20; tau=1 (an averaging step after every step);
-    # a shape outside the resident kernel's limits (call-by-call fallback)
+    # a shape that runs on one compute unit per replica, and one that no kernel keeps on chip (both end a
+    # launch with its period)
     ([70, 7], 5, 20, 4, 5),
     ([67, 129, 10], 3, 33, 5, 7),
     ([96, 64, 16], 5, 64, 1, 9),
     ([784, 256, 10], 8, 64, 20, 2),
     ([130, 70, 33, 7], 3, 16, 3, 2),
+    ([300, 200, 33, 7], 3, 16, 3, 2),
     ([96, 64, 16], 5, 64, 40, 1),   # a period longer than one gather launch prepares: two resident launches
 ]
 
@@ -657,6 +664,7 @@ def test_periods_in_one_launch(pkg, orc, dims, m, B, tau, periods, bf16):
     ref, run = _problem(pkg, orc, dims, m, B, wd=5e-4, bf16=bf16, lr=0.05)
     _, sep = _problem(pkg, orc, dims, m, B, wd=5e-4, bf16=bf16, lr=0.05)
     run.set_resident(2)   # in-kernel averaging also at the size where ending the launch is faster
+    assert run.resident_active() == (dims[0] != 300)
     for lazy in (False, True):   # the second batch starts from a deferred broadcast
         run.set_lazy_broadcast(lazy)
         sep.set_lazy_broadcast(lazy)
@@ -802,14 +810,16 @@ def test_adaptive_schedule_bit_exact(pkg, orc):
     run.close()
 
 
-@pytest.mark.parametrize("dims,m,B", [([64, 10], 4, 32), ([64, 32, 10], 4, 32), ([130, 70, 33, 7], 3, 16)])
-def test_grid_search_for_tau0(pkg, orc, dims, m, B):
+@pytest.mark.parametrize("dims,m,B,resident", [([64, 10], 4, 32, True), ([64, 32, 10], 4, 32, True),
+                                               ([130, 70, 33, 7], 3, 16, True), ([130, 70, 33, 7], 3, 16, False)])
+def test_grid_search_for_tau0(pkg, orc, dims, m, B, resident):
     """The tau_0 helper: every candidate's loss is the loss of K iterations with that fixed
     period from the same start (against the oracle's own runs), the state is back where it
     was afterwards, bit for bit, and the index returned is the largest loss decrease per second
     of the two arrays it hands back."""
-    _say(f"grid search dims={dims} m={m}")
-    ref, run = _problem(pkg, orc, dims, m, B, N=2000, lr=0.05, beta=0.9, E=512, mean_sd=2.0)
+    _say(f"grid search dims={dims} m={m} resident={resident}")
+    ref, run = _problem(pkg, orc, dims, m, B, N=2000, lr=0.05, beta=0.9, E=512, mean_sd=2.0, resident=resident)
+    assert run.resident_active() == resident
     run.local_steps(3)
     run.average()
     ref.local_steps(3)
@@ -906,14 +916,16 @@ def test_refined_schedule_bit_exact(pkg, orc):
     run.close()
 
 
-@pytest.mark.parametrize("dims", [[130, 70, 33, 7], [96, 64, 10]])   # per-layer kernels; resident kernel
+@pytest.mark.parametrize("resident", [True, False])   # both models: on chip; launches per layer
+@pytest.mark.parametrize("dims", [[130, 70, 33, 7], [96, 64, 10]])   # one compute unit per replica; resident kernel
 @pytest.mark.parametrize("bf16", [False, True])
-def test_block_momentum_rounds(pkg, orc, bf16, dims):
+def test_block_momentum_rounds(pkg, orc, bf16, dims, resident):
     """Block momentum (global factor 0.3, local 0.9, local buffers restarted at every
     averaging step) over several periods against the oracle."""
     m, B, tau = 4, 48, 3
-    _say(f"block momentum bf16={bf16} dims={dims}")
-    ref, run = _problem(pkg, orc, dims, m, B, lr=0.05, beta=0.9, bf16=bf16)
+    _say(f"block momentum bf16={bf16} dims={dims} resident={resident}")
+    ref, run = _problem(pkg, orc, dims, m, B, lr=0.05, beta=0.9, bf16=bf16, resident=resident)
+    assert run.resident_active() == resident
     tol = TOL16 if bf16 else TOL32
     ref.block_begin(0.3)
     run.block_momentum_begin(0.3)
@@ -973,14 +985,16 @@ def test_block_momentum_quadratic_closed_form_and_driver(pkg, orc):
     run.close()
 
 
+@pytest.mark.parametrize("resident", [True, False])   # one compute unit per replica; launches per layer
 @pytest.mark.parametrize("bf16", [False, True])
-def test_lazy_broadcast_is_bit_identical_to_eager(pkg, orc, bf16):
+def test_lazy_broadcast_is_bit_identical_to_eager(pkg, orc, bf16, resident):
     """Deferred broadcast: the averaging step only reduces, the next local step reads
     the one averaged model.  Same bits as the eager form at every observable point."""
     dims, m, B = [130, 70, 33, 7], 4, 48
-    _say(f"lazy broadcast bf16={bf16}")
-    _, eager = _problem(pkg, orc, dims, m, B, wd=5e-4, bf16=bf16)
-    ref, lazy = _problem(pkg, orc, dims, m, B, wd=5e-4, bf16=bf16)
+    _say(f"lazy broadcast bf16={bf16} resident={resident}")
+    _, eager = _problem(pkg, orc, dims, m, B, wd=5e-4, bf16=bf16, resident=resident)
+    ref, lazy = _problem(pkg, orc, dims, m, B, wd=5e-4, bf16=bf16, resident=resident)
+    assert lazy.resident_active() == resident
     lazy.set_lazy_broadcast(True)
     for tau in (1, 1, 3, 2):
         for r in (eager, lazy):
