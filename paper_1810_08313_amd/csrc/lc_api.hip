@@ -71,7 +71,7 @@ int model_ok(const lc_model* md) {
     if (md->n_layers < 1 || md->n_layers > LC_MAX_LAYERS) return LC_ERR_MODEL;
     for (int l = 0; l <= md->n_layers; ++l)
         if (md->dims[l] < 1) return LC_ERR_MODEL;
-    if (md->dims[md->n_layers] > 1024) return LC_ERR_UNSUPPORTED;  // classes per sample handled by one thread
+    if (md->dims[md->n_layers] > 1024) return LC_ERR_UNSUPPORTED;  // softmax_kernel's LDS rows
     if (md->B < 1 || md->B > 128) return LC_ERR_MODEL;
     if (md->N < 1 || md->N > 2147483647LL) return LC_ERR_MODEL;
     if (md->E < 1 || md->E > md->N) return LC_ERR_MODEL;

@@ -4,7 +4,9 @@
 // The fp32 matrix instructions run at a sixteenth of the bf16 rate, and this pass is bound by them.
 // An fp32 number is the sum of three bf16 numbers exactly (8 + 8 + 8 of its 24 significant bits, each
 // part rounded to nearest), products of bf16 numbers are exact in fp32, and of the nine products of
-// two such sums the three smallest are below 2^-26 of the whole, a quarter of an fp32 rounding.
+// two such sums the three smallest reach 2^-24 of the whole together (the second part is at most 2^-8,
+// the third 2^-17 of the number's power of two), 2^-27.4 in the mean square: once per product, one fp32
+// rounding at most.
 // So x w = x1 w1 + (x1 w2 + x2 w1 + x1 w3 + x2 w2 + x3 w1): six bf16 instructions in place of
 // the fp32 ones' sixteenfold cost.  x1 w1 is added up in an accumulator of its own and the rest, 2^-8
 // as large, in a second one, so that only one rounding per 16 products is of the size of the result:

@@ -182,7 +182,7 @@ __device__ __forceinline__ float4 load_w4_rows(const float* base, int row, int d
 // the compiler issue a trip's loads back to back with no control flow between them.
 // kWRagged does the same for every other layer of at least 64 columns.  A load is one unconditional
 // 16-byte instruction at 4-byte alignment (which global memory instructions take); in the last
-// column chunk it may run over the end of the row, by at most 62 columns: into the next row, or
+// column chunk it may run over the end of the row, by at most 63 columns: into the next row, or
 // behind the last row into the layer's biases, of which there are at least 64 -- always inside the
 // replica's own parameters.  What it finds there is never used: the kernels zero those columns
 // where they are an operand of a sum, and the stores stop at the row end.  Such rows share cache
