@@ -5,8 +5,9 @@
 // one workgroup takes a whole run of local steps: the weights stay in LDS, the momentum in
 // registers, and what the launch-per-layer kernels hand each other through memory stays in LDS.
 // Those kernels need 2 L launches per step of 6 to 20 us each at this size, nearly all of it launch
-// and dependent memory round trips; here a step is 2 L + 1 phases between workgroup barriers, bound
-// by the matrix instructions of one compute unit (fp32) and by LDS (bf16).
+// and dependent memory round trips; here a step is 2 L + 1 phases between workgroup barriers, each a
+// chain of LDS reads and matrix instructions (in the case below the compute unit's matrix cores are
+// busy a quarter of the time, LDS bank conflicts take a tenth).
 // (130-70-33-7, 3 workers, batch 48, fp32, two periods of 3 steps: 346 -> 136 us, 17 us a step.)
 //
 // One step, 16 wavefronts sharing out 16 x 16 tiles of every product:
