@@ -199,7 +199,7 @@ int lc_materialize(lc_handle* h);
  * launch-per-layer path up to the summation order (results agree to rounding, not bit for bit).
  * on = 0 selects the launch-per-layer path for every shape; the default is on (1); on = 2
  * additionally makes lc_local_periods() take the averaging steps inside the launch at every
- * shape the kernel handles, also where ending the launch is the faster way.  Shapes outside
+ * shape the one- and two-layer kernels handle, also where ending the launch is the faster way.  Shapes outside
  * the limits always take the launch-per-layer path.  The barrier wait is bounded: if it ever
  * times out the kernel still terminates, and the next synchronising call (lc_loss,
  * lc_get_state, lc_get_local_losses) returns LC_ERR_SYNC; the state is then undefined.  The
