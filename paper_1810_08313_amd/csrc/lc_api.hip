@@ -152,7 +152,7 @@ size_t carve(lc_handle* h, char* base) {
     h->da_part = shares ? static_cast<float*>(c.take(sizeof(float) * shares)) : nullptr;
     if (resident_shape_ok(h)) {
         h->res_a1x = static_cast<float*>(c.take(sizeof(float) * resident_exchange_floats(h)));
-        h->res_ctr = static_cast<unsigned*>(c.take(sizeof(unsigned) * 384));
+        h->res_ctr = static_cast<unsigned*>(c.take(sizeof(unsigned) * kCtrTotal));
         h->res_avx = static_cast<float*>(c.take(sizeof(float) * 2 * static_cast<size_t>(h->m) * h->Ps));
     } else {
         h->res_a1x = nullptr;
@@ -238,11 +238,11 @@ bool on_chip(const lc_handle* h) { return h->res_on && (h->res_a1x || h->net_ok)
 int check_resident(lc_handle* h) {
     if (!h->res_used || !h->res_ctr) return LC_OK;
     unsigned flag = 0;
-    LC_HIP(h, hipMemcpyAsync(&flag, h->res_ctr + 64, sizeof(unsigned), hipMemcpyDeviceToHost, h->stream));
+    LC_HIP(h, hipMemcpyAsync(&flag, h->res_ctr + kCtrErr, sizeof(unsigned), hipMemcpyDeviceToHost, h->stream));
     LC_HIP(h, hipStreamSynchronize(h->stream));
     h->res_used = false;
     if (flag == 0) return LC_OK;
-    LC_HIP(h, hipMemsetAsync(h->res_ctr + 64, 0, sizeof(unsigned), h->stream));
+    LC_HIP(h, hipMemsetAsync(h->res_ctr + kCtrErr, 0, sizeof(unsigned), h->stream));
     return (flag & 2u) ? LC_ERR_PLACEMENT : LC_ERR_SYNC;
 }
 

@@ -26,6 +26,19 @@ constexpr int kLossParts = 8;    // partial loss sums per group (one per block t
 
 inline int64_t round_up(int64_t a, int64_t b) { return (a + b - 1) / b * b; }
 
+// Fragment order of a matrix that is an MFMA operand: 16 rows x 32 reduction indices after each other,
+// one wavefront's operand of one step, 512 values.  bf16: lane l's 8 values at 8 l, so that one load
+// instruction takes 1 KB in one piece; fp32: the first four of each lane at 4 l, the last four at
+// 256 + 4 l, two such instructions.  Fragments of one row tile follow each other (row-major tiles).
+// The same operand read from plain rows, 16 rows at a stride and 64 or 128 bytes of each, moves 15.5 B per
+// clock and compute unit whatever the stride; in fragment order it moves 45 to 58 (208 KB out of the L2,
+// 4 to 16 wavefronts, on 128 or all 256 compute units: 5.7 against 1.5 to 1.9 us).
+constexpr int kFragElems = 512;
+
+// lc_handle::res_ctr: error flag, arrivals at averaging steps, placement probe, and per replica one arrival
+// counter per batch tile, 256 bytes apart (polls of counters in one cache line hold each other up).
+constexpr int kCtrErr = 0, kCtrAll = 1, kCtrProbe = 64, kCtrReplica = 320, kCtrTile = 64, kCtrTotal = kCtrReplica + 64 * 4 * kCtrTile;
+
 // Kernel classes for lc_timing_begin().
 enum TimedKernel { kTimeBwd = 0, kTimeFwd = 1, kTimeAvg = 2, kTimeUpd = 3, kTimeUpdAvg = 4, kTimeNone = -1 };
 // Kernels of the backward class, for lc_timing_select().
@@ -124,12 +137,12 @@ struct lc_handle {
     int share_w_set;          // ... replicas per set
     // resident local steps (small two-layer models): exchange buffer, barrier counters, switches
     float* res_a1x;         // [2 parities][m][dp1/16][Bp][16] exchange buffer of the resident kernel, null when the shape does not qualify
-    unsigned* res_ctr;      // [0..63] arrival counters per replica, [64] error flag, [65] all-replica counter, [128..383] placement probe
+    unsigned* res_ctr;      // error flag, counters and placement probe of the resident kernels, see kCtr* below
     unsigned res_arrivals;  // value of every counter once the queued launches have run (zeroed with the scratch at attach)
     bool net_ok;            // the model runs whole local steps on one compute unit per replica (net_kernel)
     float* da_part;         // shares of dA of the largest layer whose columns are shared out (see BwdArgs), or null
     float* res_avx;         // [2 parities][m][Ps] models handed over at averaging steps inside a launch
-    unsigned res_garrivals; // the same for the all-replica counter of those averaging steps (res_ctr[65])
+    unsigned res_garrivals; // the same for the all-replica counter of those averaging steps (res_ctr[kCtrAll])
     bool res_on;            // lc_set_resident
     bool res_local_on;      // lc_set_xcd_local_exchange
     bool res_xcc_known;     // the probe found blocks dealt to the XCDs by id mod 8
@@ -192,6 +205,7 @@ bool net_shape_ok(const lc_handle* h);
 hipError_t launch_net(lc_handle* h, int slot0, int n_steps);  // as launch_resident, one period or less
 size_t resident_exchange_floats(const lc_handle* h);
 hipError_t probe_block_placement(lc_handle* h);   // synchronises the stream once
+inline bool inputs_in_fragments(const lc_handle* h) { return h->res_on && h->res_a1x && h->L == 2; }   // how the gather kernel leaves A_0
 hipError_t launch_resident(lc_handle* h, int slot0, int n_steps, int period);  // the steps gathered into slots slot0 .. slot0+n_steps-1
 
 // timing helpers used by the launchers

@@ -99,6 +99,7 @@ struct GatherArgs {
     int sampler, m;         // training: lc_sampler and the number of workers
     int G;                  // groups per step; blockIdx.z = step * G + group
     int64_t a_slot, lab_slot;  // elements between the buffers of consecutive steps
+    int frags;              // both layouts in fragment order (tiles of 16 rows: samples in a_bm, features in a_fm)
 };
 
 // One block copies a 32-sample x 64-feature tile through LDS and writes it in
@@ -154,9 +155,23 @@ __global__ __launch_bounds__(256) void gather_kernel(GatherArgs a) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) tile[r][seg + e] = x[e];
         OT* bm = static_cast<OT*>(a.a_bm) + step * a.a_slot + static_cast<int64_t>(g) * a.Bp * a.dp0;
-        store8(bm + static_cast<int64_t>(b0 + r) * a.dp0 + kk0, x);
+        if (!a.frags) store8(bm + static_cast<int64_t>(b0 + r) * a.dp0 + kk0, x);
     }
     __syncthreads();
+    if (a.frags) {
+        // the 32 x 64 tile holds four fragments of either kind; every wavefront writes one of each
+        const int lane = t & 63, w = t >> 6, j = lane & 15, q = lane >> 4;
+        OT* bm = static_cast<OT*>(a.a_bm) + step * a.a_slot + static_cast<int64_t>(g) * a.Bp * a.dp0;
+        OT* fm = static_cast<OT*>(a.a_fm) + step * a.a_slot + static_cast<int64_t>(g) * a.Bp * a.dp0;
+        float y[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) y[e] = tile[16 * (w >> 1) + j][32 * (w & 1) + 8 * q + e];
+        store_frag(bm + static_cast<int64_t>((b0 / 16 + (w >> 1)) * (a.dp0 / 32) + k0 / 32 + (w & 1)) * kFragElems, lane, y);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) y[e] = tile[8 * q + e][16 * w + j];
+        store_frag(fm + static_cast<int64_t>((k0 / 16 + w) * (a.Bp / 32) + b0 / 32) * kFragElems, lane, y);
+        return;
+    }
     if (a.a_fm) {
         OT* fm = static_cast<OT*>(a.a_fm) + step * a.a_slot + static_cast<int64_t>(g) * a.dp0 * a.Bp;
         const int kk = t >> 2, seg = (t & 3) * 8;
@@ -1376,6 +1391,7 @@ hipError_t launch_gather(lc_handle* h, bool eval, int64_t k_or_base, int n_steps
     a.G = S.G;
     a.a_slot = static_cast<int64_t>(a0_slot_elems(h, S));
     a.lab_slot = static_cast<int64_t>(S.G) * S.Bp;
+    a.frags = !eval && inputs_in_fragments(h) ? 1 : 0;
     const dim3 grid(a.dp0 / 64, a.Bp / 32, S.G * n_steps);
     if (eval) {
         if (bf16) hipLaunchKernelGGL((gather_kernel<bf16_t, float>), grid, dim3(256), 0, h->stream, a);

@@ -34,6 +34,17 @@ __device__ __forceinline__ Frag<bf16_t> load8(const bf16_t* p) {
     return f;
 }
 
+// A lane's 8 values of a fragment that is laid out in fragment order (see kFragElems).
+__device__ __forceinline__ Frag<float> load_frag(const float* p, int lane) {
+    Frag<float> f;
+    const float4 a = *reinterpret_cast<const float4*>(p + 4 * lane);
+    const float4 b = *reinterpret_cast<const float4*>(p + 256 + 4 * lane);
+    f.v[0] = a.x; f.v[1] = a.y; f.v[2] = a.z; f.v[3] = a.w;
+    f.v[4] = b.x; f.v[5] = b.y; f.v[6] = b.z; f.v[7] = b.w;
+    return f;
+}
+__device__ __forceinline__ Frag<bf16_t> load_frag(const bf16_t* p, int lane) { return load8(p + 8 * lane); }
+
 // Marks the point where prefetched registers are consumed.  Without it the compiler moves the
 // conversion of a prefetched weight row up to its load, which makes every trip wait for the loads
 // it has just issued (loads retire in order) and turns the prefetch queue into a plain load.
@@ -134,6 +145,12 @@ __device__ __forceinline__ void store8(bf16_t* p, const float (&y)[8]) {
     for (int i = 0; i < 8; ++i) v[i] = static_cast<bf16_t>(y[i]);
     *reinterpret_cast<bf16x8*>(p) = v;
 }
+
+__device__ __forceinline__ void store_frag(float* p, int lane, const float (&y)[8]) {
+    *reinterpret_cast<float4*>(p + 4 * lane) = make_float4(y[0], y[1], y[2], y[3]);
+    *reinterpret_cast<float4*>(p + 256 + 4 * lane) = make_float4(y[4], y[5], y[6], y[7]);
+}
+__device__ __forceinline__ void store_frag(bf16_t* p, int lane, const float (&y)[8]) { store8(p + 8 * lane, y); }
 
 // Four consecutive floats of a weight row, zero outside [0, d_out).  When the
 // state of all replicas is far larger than the caches, each weight is touched
@@ -245,6 +262,40 @@ __device__ __forceinline__ float momentum_update(float beta, float v, float g, f
     return __builtin_fmaf(beta, v, __builtin_fmaf(wd, w, g));
 }
 __device__ __forceinline__ float weight_update(float w, float lr, float v) { return __builtin_fmaf(-lr, v, w); }
+
+// Sums and maxima across a wavefront without going through LDS.  Quarters: over the four lanes j, j + 16,
+// j + 32, j + 48; row: over the 16 lanes of a quarter.  Every lane receives the same value.
+// (The two swaps exchange the odd rows of one register with the even rows of the other, and its upper half
+// with the other's lower half; the wait states stand for a register that the instruction before has written.
+// In inline asm because the builtins' second result comes out as the first here.)
+__device__ __forceinline__ void swap_rows(float& x, float& y) { asm("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(x), "+v"(y)); }
+__device__ __forceinline__ void swap_halves(float& x, float& y) { asm("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(x), "+v"(y)); }
+__device__ __forceinline__ float sum_over_quarters(float x) {
+    float y = x;
+    swap_rows(x, y);
+    x += y;
+    y = x;
+    swap_halves(x, y);
+    return x + y;
+}
+__device__ __forceinline__ float max_over_quarters(float x) {
+    float y = x;
+    swap_rows(x, y);
+    x = fmaxf(x, y);
+    y = x;
+    swap_halves(x, y);
+    return fmaxf(x, y);
+}
+template <int N>
+__device__ __forceinline__ float rotated_in_row(float x) {   // DPP row_ror:N
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x120 + N, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float sum_over_row(float x) {
+    x += rotated_in_row<8>(x);
+    x += rotated_in_row<4>(x);
+    x += rotated_in_row<2>(x);
+    return x + rotated_in_row<1>(x);
+}
 
 __device__ __forceinline__ void wave_sync_lds() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

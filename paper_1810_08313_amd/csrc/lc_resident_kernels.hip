@@ -13,31 +13,40 @@
 //          matching ROWS C of W_2, V_2 -- every weight of the model has exactly one owner;
 //   keeps  a private copy of b_2 (d2 values), updated identically by every workgroup.
 // One step:
-//   (1) A_1[:, C] = ReLU(A_0 W_1[:, C] + b_1[C])          MFMA; the 16 wavefronts split batch tiles and K
-//   (2) this slice's share of the logits, A_1[:, C] W_2[C, :] (Bp x 16 values), handed to the
-//       replica; replica-wide barrier
+//   (1) A_0 W_1[:, C]                                      MFMA; the 16 wavefronts split batch tiles and K
+//   then one wavefront per tile of 16 samples, in registers from here to dZ_1:
+//   (2) A_1[:, C] = ReLU(. + b_1[C]) and this slice's share of the logits, A_1[:, C] W_2[C, :] (16 x 16
+//       values), handed to the replica; barrier with the same tile's wavefronts of the other slices
 //   (3) Z_2 = sum of the NB shares in slice order + b_2, softmax cross-entropy, dZ_2
 //       (redundantly in every workgroup: a few hundred values)
 //   (4) dZ_1[:, C] = (dZ_2 W_2[C, :]^T) .* [A_1[:, C] > 0]  with the weights of before the update
-//   (5) dW_2[C, :] = A_1[:, C]^T dZ_2, db_2 and their momentum updates
+//   and with all wavefronts again
+//   (5) dW_2[C, :] = A_1[:, C]^T dZ_2, db_2 and their momentum updates (one wavefront each)
 //   (6) dW_1[:, C] = A_0^T dZ_1[:, C], db_1[C] and the momentum update of the slice
-// The only communication is the share of the logits (Bp x 16 values per workgroup and step),
-// double buffered by step parity so that a fast workgroup never overwrites what a slow one still
-// reads.  (Exchanging the logit shares instead of the activations is what lets W_2 be
+// The only communication is the share of the logits (Bp x 16 values per workgroup and step), into a
+// region of the step's own.  (Exchanging the logit shares instead of the activations is what lets W_2 be
 // partitioned: with the activations exchanged every workgroup had to keep and update a full
 // copy of W_2, and the second layer's products, done 16 times over, were a quarter of the step.)
 //
-// The barrier is a counter per replica in device memory: arrive with an agent-scope release,
+// What bounds it is the chain of phases.  784-256-10, 8 replicas, batch 64, fp32, in clocks of a step of
+// 30000 (12.5 us): (1) 10000, of which 6300 are matrix instructions, (2) 1500, barrier 2500, (3) 4500,
+// (4) 900, (5) and (6) 10500, of which 6300 matrix instructions.  It was 42000 with the phases (2) to (5)
+// spread over all threads and LDS (a 64-term sum per thread for dW_2 alone made the step wait for 8000,
+// the shuffles of the softmax and an L2 invalidation per barrier for 3000) and the inputs in plain rows:
+// 461 us for 4 periods of 5 steps then, 341 us now.
+//
+// The barrier is a counter per replica and batch tile in device memory: arrive with an agent-scope release,
 // poll with relaxed loads, then an agent-scope acquire.  The shares are published with
 // agent-scope (write-through) stores, so the release has no dirty cache lines to write back;
 // the counters are never reset, each launch is told their value at its start.  All workgroups of a launch are
 // co-resident (the launcher refuses grids above one workgroup per compute unit), and the
-// poll loop is bounded: a workgroup that runs out of polls raises the error flag, stops
+// poll loop is bounded: a wavefront that runs out of polls raises the error flag, stops
 // waiting for good and finishes its steps, so the grid always drains.  (A cooperative launch
 // would have the runtime vouch for the co-residency, but costs 18 us more per launch here, a
 // tenth of the throughput at five steps per launch; the bounded wait covers the same case.)
-// Where the block numbering puts all workgroups of a replica on one XCD, slices and counter stay
-// in that XCD's L2 (arrive_and_wait_same_xcd).
+// Where an XCD has compute units for an eighth of the replicas, a replica's workgroups all go to one
+// XCD, and slices and counters stay in its L2 (arrive_and_wait_same_xcd): up to 64 replicas of 64 hidden
+// units, 16 of 256.
 //
 // A launch may also hold several whole communication periods: after every `period` steps the
 // averaging step of Sec. 2 is taken inside the kernel (average_resident), with one barrier over
@@ -66,15 +75,15 @@ struct ResArgs {
     int64_t w1_off, b1_off, w2_off, b2_off;
     int d0, d1, d2, dp0, dp1;
     int B, G, NB;
-    const void* a0_bm;    // [slots][G][Bp][dp0] of OT
-    const void* a0_fm;    // [slots][G][dp0][Bp] of OT
+    const void* a0_bm;    // [slots][G] A_0 in fragment order, tiles of 16 samples
+    const void* a0_fm;    // [slots][G] A_0^T in fragment order, tiles of 16 features
     int64_t a0_slot;      // elements per slot
     const int32_t* labels;  // [slots][G][Bp]
     int slot0, n_steps;
     float lr, beta_first, beta, wd;
     int vec;              // rows of W_1 may be accessed 16 bytes at a time
-    float* zx;            // [2][G][NB][Bp][16] exchange buffer: the slices' shares of the logits, by step parity
-    unsigned* ctr;        // [G] arrivals since attach (every workgroup arrives once per step, whatever happens)
+    float* zx;            // [steps][G][NB][Bp][16] exchange buffer: the slices' shares of the logits, by step of the launch
+    unsigned* ctr;        // [G][MT][kCtrTile] arrivals since attach, by batch tile (every workgroup arrives once per step, whatever happens)
     unsigned ctr_base;    // their value when this launch starts
     unsigned* err;        // set to 1 when a barrier wait ran out of polls
     int spin_limit;       // polls one barrier wait may take
@@ -87,9 +96,9 @@ struct ResArgs {
     unsigned gctr_base;   // its value when this launch starts
 };
 
-// Barrier among the workgroups that add to *ctr, called by one thread per workgroup after a
-// workgroup barrier: what the workgroup wrote before is visible to every workgroup that leaves
-// the wait.  The wait is bounded; a workgroup that runs out of polls raises the error flag and
+// Barrier among the workgroups (or one wavefront of each) that add to *ctr, called by one thread once
+// the stores of those it speaks for have arrived: what they wrote before is visible to everyone who leaves
+// the wait.  The wait is bounded; a caller that runs out of polls raises the error flag and
 // never waits again (it still arrives, so the counts stay right), so the grid always drains.
 __device__ __forceinline__ void arrive_and_wait(unsigned* ctr, unsigned target, int spin_limit, unsigned* err,
                                                 bool& gave_up) {
@@ -113,10 +122,12 @@ __device__ __forceinline__ void arrive_and_wait(unsigned* ctr, unsigned target, 
 // in the L2, so the counter is added to and polled there (the poll is a compare-and-swap that
 // never matches: a workgroup-scope LOAD may be served by the compute unit's L1 and then never sees
 // the count move -- measured).  The slices were written through to the L2 and stay there as
-// dirty lines; after the L1 has been invalidated (the agent-scope acquire does that) loads find
-// them in the L2, where the agent-scope form sends data and counter to the memory side and
-// back.  Valid only while the participants really share an L2: the launcher checks the placement
-// rule once with a probe kernel, and every workgroup checks its own XCD id against it.
+// dirty lines, where the agent-scope form sends data and counter to the memory side and back.  The
+// readers' L1 cannot hold an older copy: every step of a launch has an exchange region of its own, and
+// a launch begins with an empty L1.  (An invalidation by the agent-scope acquire reaches the L2 as well;
+// one per workgroup and step was a third of the time between the arrival and the logits, one per
+// wavefront took 10000 clocks.)  Valid only while the participants really share an L2: the launcher checks
+// the placement rule once with a probe kernel, and every workgroup checks its own XCD id against it.
 __device__ __forceinline__ void arrive_and_wait_same_xcd(unsigned* ctr, unsigned target, int spin_limit, unsigned* err,
                                                          bool& gave_up) {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -133,7 +144,7 @@ __device__ __forceinline__ void arrive_and_wait_same_xcd(unsigned* ctr, unsigned
                                              __HIP_MEMORY_SCOPE_WORKGROUP);
         if (static_cast<int>(seen - target) >= 0) break;
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
 // The XCD this wavefront runs on: hardware register XCC_ID (number 20), bits 3:0.  The operand
@@ -235,23 +246,35 @@ __device__ __forceinline__ void average_resident(const ResArgs& a, int tid, int 
 }
 
 template <typename OT, int MT>
-__global__ __launch_bounds__(kResThreads) void resident_kernel(ResArgs a) {
+__global__ __launch_bounds__(kResThreads) void resident_kernel(ResArgs args) {
+    const ResArgs& a = args;
     constexpr int Bp = 16 * MT;
     constexpr int NS = Bp / 32;   // 32-wide steps over the batch
     constexpr int KP = kResWaves / MT;   // wavefronts that share one batch tile and split the reduction
     __shared__ __attribute__((aligned(16))) float w1s[16][kResK1P];    // W_1[:, C]^T
     __shared__ float w2s[16][17], v2s[16][17];                          // W_2[C, :]^T, V_2[C, :]^T: [class][own hidden unit]
-    __shared__ __attribute__((aligned(16))) float part[KP][Bp][17];
+    __shared__ __attribute__((aligned(16))) float part[KP - 1][Bp][20];
     __shared__ float a1s[Bp][17];                                       // own slice of A_1
-    __shared__ float z2s[Bp][17];                                       // logits, then dZ_2
+    __shared__ float z2s[Bp][17];                                       // dZ_2
     __shared__ __attribute__((aligned(16))) OT dz1t[16][Bp + 8];        // dZ_1[:, C]^T
     __shared__ float b1s[16], vb1s[16], b2s[16], vb2s[16];
     __shared__ float lred[Bp];
-    __shared__ float colsum1[kResWaves][16], colsum2[kResWaves][16];
+    __shared__ float colsum1[MT][16], colsum2[MT][16];
 
-    const int64_t logical = xcd_logical_block(static_cast<int64_t>(a.G) * a.NB);
-    if (logical < 0) return;
-    const int g = static_cast<int>(logical / a.NB), cb = static_cast<int>(logical % a.NB);
+    // Blocks are dealt to the XCDs round-robin.  Replica g has its blocks on XCD g mod 8 where each XCD has
+    // compute units enough for that; else the replicas' blocks simply follow each other.
+    int g, cb;
+    if (a.local_xcd) {
+        const int i = blockIdx.x / kXcds;
+        g = blockIdx.x % kXcds + kXcds * (i / a.NB);
+        cb = i % a.NB;
+        if (g >= a.G) return;
+    } else {
+        const int64_t logical = xcd_logical_block(static_cast<int64_t>(a.G) * a.NB);
+        if (logical < 0) return;
+        g = static_cast<int>(logical / a.NB);
+        cb = static_cast<int>(logical % a.NB);
+    }
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int j = lane & 15, q = lane >> 4;
     const int c_base = 16 * cb;
@@ -312,169 +335,212 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResArgs a) {
         vb2s[tid] = in2 ? Vg[a.b2_off + tid] : 0.f;
     }
     __syncthreads();
-    bool gave_up = false;   // thread 0: a barrier wait ran out of polls
+    bool gave_up = false;   // first lane of a wavefront: one of its barrier waits ran out of polls
     if (a.local_xcd && threadIdx.x == 0 && this_xcd() != ((a.xcc_of >> (4 * (blockIdx.x % kXcds))) & 15u))
         atomicOr(a.err, 2u);   // not where the probe saw such blocks run: the exchange cannot be trusted
+    // the input rows of batch tile mt, and where a wavefront's share of their fragments begins
+    auto input_tile = [&](const ResArgs& a, int slot, int mt) {
+        return static_cast<const OT*>(a.a0_bm) + slot * a.a0_slot + (static_cast<int64_t>(g) * MT + mt) * (a.dp0 / 32) * kFragElems;
+    };
+    const int uwave = __builtin_amdgcn_readfirstlane(wave);
+    const int first_st = uwave / MT < (a.d0 + 31) / 32 ? uwave / MT : 0;
     for (int s = 0; s < a.n_steps;) {
-    // One period (the whole launch when it has no averaging steps).  What the steps derive from
-    // the thread's id is derived afresh from an opaque copy per period, so that none of it is
-    // held in registers across the averaging step, which needs them for its own loads.
-    int tid_p = threadIdx.x;
-    asm volatile("" : "+v"(tid_p));
-    const int tid = tid_p, lane = tid & 63, wave = tid >> 6, j = lane & 15, q = lane >> 4;
+    // One period (the whole launch when it has no averaging steps).
     const int s_end = a.period > 0 ? s + a.period : a.n_steps;
+    const int s_begin = s;
+    Frag<OT> af;
     for (; s < s_end; ++s) {
-        const float beta = s == 0 ? a.beta_first : a.beta;
+        // What a step derives from the thread's id is derived afresh from an opaque copy, so that none of
+        // it is held in registers across the steps and the averaging step, which need them for their loads.
+        int tid_o = threadIdx.x;
+        asm volatile("" : "+v"(tid_o));
+        const int tid = tid_o, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), j = lane & 15, q = lane >> 4;
+        int zero = 0;   // ... and what it takes from the arguments is read afresh, for the scalar registers' sake
+        asm volatile("" : "+s"(zero));
+        const ResArgs& a = (&args)[zero];
+        const float beta = s == 0 ? a.beta_first : a.beta, lr = a.lr, wd = a.wd;
+        const int d1 = a.d1, d2 = a.d2, NB = a.NB;
         const int slot = a.slot0 + s;
-        const OT* A0 = static_cast<const OT*>(a.a0_bm) + slot * a.a0_slot + static_cast<int64_t>(g) * Bp * a.dp0;
         const OT* A0T = static_cast<const OT*>(a.a0_fm) + slot * a.a0_slot + static_cast<int64_t>(g) * a.dp0 * Bp;
         const int32_t* lab = a.labels + (static_cast<int64_t>(slot) * a.G + g) * Bp;
-        const int par = s & 1;
-        float* xp = a.zx + (static_cast<int64_t>(par) * a.G + g) * Bp * a.dp1;   // [NB][Bp][16]
-        // ---- (1) Z_1[:, C]: wavefront (mt, kpart) takes batch tile mt and the 32-wide k steps
-        //      kpart, kpart + KP, ...
+        float* xp = a.zx + (static_cast<int64_t>(s) * a.G + g) * Bp * a.dp1;   // [NB][Bp][16]
+        // ---- (1) Z_1[:, C]^T: wavefront (mt, kpart) takes batch tile mt and the 32-wide k steps
+        //      kpart, kpart + KP, ...  A lane ends up with hidden units 4 q .. 4 q + 3 of sample 16 mt + j.
         const int mt = wave % MT, kpart = wave / MT;
+        f32x4 z1 = f32x4{0.f, 0.f, 0.f, 0.f};
+        const int y = kpart == 0 && 16 * mt + j < a.B ? lab[16 * mt + j] : -1;
         {
-            f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
-            const OT* arow = A0 + static_cast<int64_t>(16 * mt + j) * a.dp0 + 8 * q;
+            const OT* atile = input_tile(a, slot, mt);
+            if (s == s_begin) af = load_frag(atile + kFragElems * first_st, lane);
             const int n_st = (a.d0 + 31) / 32;   // (steps that hold only padding rows are skipped)
-            Frag<OT> af = load8(arow + 32 * (kpart < n_st ? kpart : 0));
             for (int st = kpart; st < n_st; st += KP) {
                 const int k0 = 32 * st + 8 * q;
                 const int nx = st + KP < n_st ? st + KP : st;
-                const Frag<OT> af_next = load8(arow + 32 * nx);   // next step's operand in flight
+                const Frag<OT> af_next = load_frag(atile + kFragElems * nx, lane);   // next step's operand in flight
                 const float4 x0 = *reinterpret_cast<const float4*>(&w1s[j][k0]);
                 const float4 x1 = *reinterpret_cast<const float4*>(&w1s[j][k0 + 4]);
                 const float x[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
                 Frag<OT> bf;
                 pack8(bf, x);
-                acc = mma8(af, bf, acc);
+                z1 = mma8(bf, af, z1);
                 af = af_next;
             }
+        }
+        if (kpart > 0) *reinterpret_cast<f32x4*>(&part[kpart - 1][16 * mt + j][4 * q]) = z1;
+        // (operands of what follows the barrier)
+        float w2a[4];   // W_2[own unit 4 q + i, class j]
+        if (wave < MT) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) part[kpart][16 * mt + 4 * q + r][j] = acc[r];
+            for (int i = 0; i < 4; ++i) w2a[i] = round_operand(w2s[j][4 * q + i], OT());
         }
         __syncthreads();
-        for (int e = tid; e < Bp * 16; e += kResThreads) {
-            const int b = e / 16, c = e % 16;
-            float z = part[0][b][c];
+        // ---- (2) to (4): wavefront mt takes batch tile mt from the partial sums to dZ_1 in registers.  The
+        //      16 x 16 products have their reduction index in the order the results before them are in:
+        //      instruction i sums over units (classes) 4 q + i, which a lane holds in register i.
+        if (wave < MT) {
+            const int b = 16 * mt + j;
+            f32x4 a1 = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int p = 1; p < KP; ++p) z += part[p][b][c];
-            z += b1s[c];
-            float act = 0.f;
-            if (b < a.B && c_base + c < a.d1) act = round_operand(z > 0.f ? z : 0.f, OT());
-            a1s[b][c] = act;
-        }
-        __syncthreads();
-        // ---- (2) this slice's share of the logits, A_1[:, C] W_2[C, :], handed to the replica
-        if (tid < Bp * 16) {
-            const int b = tid >> 4, c2 = tid & 15;
-            float zp = 0.f;
+            for (int p = 1; p < KP; ++p) z1 += *reinterpret_cast<const f32x4*>(&part[p - 1][b][4 * q]);
 #pragma unroll
-            for (int kk = 0; kk < 16; ++kk) zp += a1s[b][kk] * round_operand(w2s[c2][kk], OT());
-            float* px = xp + static_cast<int64_t>(cb) * (Bp * 16) + tid;
-            if (a.local_xcd) __hip_atomic_store(px, zp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);   // as far as the XCD's L2
-            else __hip_atomic_store(px, zp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // written through to device scope
-        }
-        // every wavefront's stores have arrived before the workgroup does
-        __builtin_amdgcn_s_waitcnt(0);
-
-        // ---- (2) replica-wide barrier
-        __syncthreads();
-        if (tid == 0 && a.NB > 1) {
-            const unsigned target = a.ctr_base + static_cast<unsigned>(s + 1) * static_cast<unsigned>(a.NB);
-            if (a.local_xcd) arrive_and_wait_same_xcd(&a.ctr[g], target, a.spin_limit, a.err, gave_up);
-            else arrive_and_wait(&a.ctr[g], target, a.spin_limit, a.err, gave_up);
-        }
-        __syncthreads();
-        // ---- (3) logits = sum of the slices' shares in slice order + b_2; softmax cross-entropy and
-        //      dZ_2 (redundantly in every workgroup: a few hundred values)
-        // one thread per (sample, class): 16-lane groups hold a sample's logits
-        if (tid < Bp * 16) {
-            const int b = tid >> 4, c = tid & 15;
-            float z = 0.f;
-            for (int o0 = 0; o0 < a.NB; o0 += 8) {   // eight loads in flight, added in slice order
-                float r[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    if (o0 + u < a.NB) r[u] = xp[static_cast<int64_t>(o0 + u) * (Bp * 16) + tid];
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    if (o0 + u < a.NB) z += r[u];
+            for (int r = 0; r < 4; ++r) {
+                const float z = z1[r] + b1s[4 * q + r];
+                if (b < a.B && c_base + 4 * q + r < d1) a1[r] = round_operand(z > 0.f ? z : 0.f, OT());
+                a1s[b][4 * q + r] = a1[r];
             }
-            z += b2s[c];
-            const int y = b < a.B ? lab[b] : -1;
-            const bool valid = c < a.d2;
-            float zmax = valid ? z : -INFINITY;
+            // ---- (2) this slice's share of the logits, (A_1[:, C] W_2[C, :])^T, handed to the replica
+            f32x4 zp = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int o = 8; o > 0; o >>= 1) zmax = fmaxf(zmax, __shfl_xor(zmax, o, 16));
-            const float ex = valid ? expf(z - zmax) : 0.f;
-            float s_other = c == y ? 0.f : ex;   // over the classes other than the label (see xent_loss)
+            for (int i = 0; i < 4; ++i)
+                zp = __builtin_amdgcn_mfma_f32_16x16x4f32(w2a[i], a1[i], zp, 0, 0, 0);
+            float* px = xp + static_cast<int64_t>(cb) * (Bp * 16) + b * 16 + 4 * q;
 #pragma unroll
-            for (int o = 8; o > 0; o >>= 1) s_other += __shfl_xor(s_other, o, 16);
-            const float zy = __shfl(z, y >= 0 ? y : 0, 16), sum = s_other + __shfl(ex, y >= 0 ? y : 0, 16);
-            float dz = 0.f;
-            if (y >= 0 && valid)
-                dz = round_operand(xent_delta(ex, c == y, s_other, 1.f / sum) * (1.f / static_cast<float>(a.B)), OT());
-            z2s[b][c] = dz;
-            // (the step's own loss is a by-product here: the plain form, without the log1p of xent_loss)
-            if (c == 0) lred[b] = y >= 0 ? -(zy - zmax - logf(sum)) : 0.f;
+            for (int r = 0; r < 4; ++r) {
+                if (a.local_xcd) __hip_atomic_store(px + r, zp[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);   // as far as the XCD's L2
+                else __hip_atomic_store(px + r, zp[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // written through to device scope
+            }
+            // ---- replica-wide barrier of the wavefronts of this batch tile: nothing else is exchanged
+            if (NB > 1) {
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                __builtin_amdgcn_s_waitcnt(0);   // the whole wavefront's stores have arrived before it does
+                if (lane == 0) {
+                    const unsigned target = a.ctr_base + static_cast<unsigned>(s + 1) * static_cast<unsigned>(NB);
+                    unsigned* ctr = a.ctr + (g * MT + mt) * kCtrTile;
+                    if (a.local_xcd) arrive_and_wait_same_xcd(ctr, target, a.spin_limit, a.err, gave_up);
+                    else arrive_and_wait(ctr, target, a.spin_limit, a.err, gave_up);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+            } else {
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                __builtin_amdgcn_s_waitcnt(0);
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+            }
+            // ---- (3) logits = sum of the slices' shares in slice order + b_2; softmax cross-entropy and
+            //      dZ_2 (redundantly in every workgroup: a few hundred values).  Classes 4 q .. 4 q + 3 of
+            //      sample b in a lane; all shares are requested at once.
+            f32x4 z = f32x4{0.f, 0.f, 0.f, 0.f};
+            {
+                const float* sx = xp + b * 16 + 4 * q;
+                f32x4 r[16];
+#pragma unroll
+                for (int o = 0; o < 16; ++o) r[o] = *reinterpret_cast<const f32x4*>(sx + (o < NB ? o : 0) * (Bp * 16));
+#pragma unroll
+                for (int o = 0; o < 16; ++o) z += o < NB ? r[o] : f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+            float zmax = -INFINITY;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                z[r] += b2s[4 * q + r];
+                if (4 * q + r < d2) zmax = fmaxf(zmax, z[r]);
+            }
+            zmax = max_over_quarters(zmax);
+            f32x4 ex;
+            float s_other = 0.f, e_y = 0.f, z_y = 0.f;   // (over the classes other than the label, see xent_loss)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int c = 4 * q + r;
+                ex[r] = c < d2 ? expf(z[r] - zmax) : 0.f;
+                s_other += c == y ? 0.f : ex[r];
+                e_y += c == y ? ex[r] : 0.f;
+                z_y += c == y ? z[r] : 0.f;
+            }
+            s_other = sum_over_quarters(s_other);
+            const float sum = s_other + sum_over_quarters(e_y), inv = 1.f / sum, invB = 1.f / static_cast<float>(a.B);
+            f32x4 dz2, dz1 = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int c = 4 * q + r;
+                dz2[r] = y >= 0 && c < d2 ? round_operand(xent_delta(ex[r], c == y, s_other, inv) * invB, OT()) : 0.f;
+                z2s[b][c] = dz2[r];
+            }
+            if (cb == 0) {   // (the step's own loss is a by-product here: the plain form, without the log1p of xent_loss)
+                z_y = sum_over_quarters(z_y);
+                if (q == 0) lred[b] = y >= 0 ? -(z_y - zmax - logf(sum)) : 0.f;
+            }
+            // ---- (4) dZ_1[:, C]^T from the second layer's weights of before this step's update, and this
+            //      tile's sums of dZ_1[:, C] and dZ_2 (bias gradients)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) dz1 = __builtin_amdgcn_mfma_f32_16x16x4f32(round_operand(w2s[4 * q + i][j], OT()), dz2[i], dz1, 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const OT d = static_cast<OT>(a1[r] > 0.f ? dz1[r] : 0.f);   // rounds in bf16 mode
+                dz1t[4 * q + r][b] = d;
+                const float s1 = sum_over_row(to_f32(d)), s2 = sum_over_row(dz2[r]);
+                if (j == 0) {
+                    colsum1[mt][4 * q + r] = s1;
+                    colsum2[mt][4 * q + r] = s2;
+                }
+            }
         }
         __syncthreads();
-        if (cb == 0 && wave == 0) {
+        // ---- the step's loss and the bias updates.  These small jobs go to the last wavefronts: when the
+        //      tiles of step (6) do not divide evenly, those have one tile less to do
+        if (cb == 0 && wave == kResWaves - 3) {
             float v = lane < Bp ? lred[lane] : 0.f;
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
             if (lane == 0) a.loss[static_cast<int64_t>(g) * kLossParts] = v / static_cast<float>(a.B);
         }
-        // ---- (4) dZ_1[:, C] from the second layer's weights of before this step's update, and the
-        //      column sums of dZ_1[:, C] and dZ_2 (bias gradients): first over each wavefront's
-        //      four samples, then over the wavefronts
-        if (tid < Bp * 16) {
-            const int b = tid >> 4, c = tid & 15;
-            float sum = 0.f;
-            for (int c2 = 0; c2 < a.d2; ++c2) sum += z2s[b][c2] * round_operand(w2s[c2][c], OT());
-            const OT d = static_cast<OT>(a1s[b][c] > 0.f ? sum : 0.f);   // rounds in bf16 mode
-            dz1t[c][b] = d;
-            float s1 = to_f32(d), s2 = z2s[b][c];
-            s1 += __shfl_xor(s1, 16, 64); s1 += __shfl_xor(s1, 32, 64);
-            s2 += __shfl_xor(s2, 16, 64); s2 += __shfl_xor(s2, 32, 64);
-            if (lane < 16) {
-                colsum1[wave][lane] = s1;
-                colsum2[wave][lane] = s2;
-            }
-        }
-        __syncthreads();
-        // ---- bias updates (one thread per entry).  These small jobs go to the last wavefronts:
-        //      when the tiles of step (6) do not divide evenly, those have one tile less to do
-        if (tid >= kResThreads - 64 && tid < kResThreads - 32) {
-            const int c = tid & 15;
-            const bool first = tid < kResThreads - 48;
+        if (wave == kResWaves - 2 && lane < 32) {
+            const int c = lane & 15;
+            const bool first = lane < 16;
             float db = 0.f;
-            for (int w = 0; w < Bp / 4; ++w) db += first ? colsum1[w][c] : colsum2[w][c];
+#pragma unroll
+            for (int w = 0; w < MT; ++w) db += first ? colsum1[w][c] : colsum2[w][c];
             if (first) {
-                if (c_base + c < a.d1) {
-                    const float vb = momentum_update(beta, vb1s[c], db, a.wd, b1s[c]);
+                if (c_base + c < d1) {
+                    const float vb = momentum_update(beta, vb1s[c], db, wd, b1s[c]);
                     vb1s[c] = vb;
-                    b1s[c] = weight_update(b1s[c], a.lr, vb);
+                    b1s[c] = weight_update(b1s[c], lr, vb);
                 }
-            } else if (c < a.d2) {
-                const float vb = momentum_update(beta, vb2s[c], db, a.wd, b2s[c]);
+            } else if (c < d2) {
+                const float vb = momentum_update(beta, vb2s[c], db, wd, b2s[c]);
                 vb2s[c] = vb;
-                b2s[c] = weight_update(b2s[c], a.lr, vb);
+                b2s[c] = weight_update(b2s[c], lr, vb);
             }
         }
-        // ---- (5) dW_2[C, :] = A_1[:, C]^T dZ_2 and the update of the own rows (16 x 16 values: plain FMAs)
-        if (tid >= kResThreads - 320 && tid < kResThreads - 64) {
-            const int kk = (tid - (kResThreads - 320)) >> 4, c2 = tid & 15;
-            if (c_base + kk < a.d1 && c2 < a.d2) {
-                float gw = 0.f;
-                for (int b = 0; b < Bp; ++b) gw += a1s[b][kk] * z2s[b][c2];
-                const float w = w2s[c2][kk];
-                const float v = momentum_update(beta, v2s[c2][kk], gw, a.wd, w);
-                v2s[c2][kk] = v;
-                w2s[c2][kk] = weight_update(w, a.lr, v);
+        // ---- (5) dW_2[C, :] = A_1[:, C]^T dZ_2 and the update of the own rows
+        if (wave == kResWaves - 1) {
+            __builtin_amdgcn_s_setprio(3);   // (its own tiles wait for this, and the step for them)
+            f32x4 gw = f32x4{0.f, 0.f, 0.f, 0.f};
+            float x[Bp / 4], y[Bp / 4];
+#pragma unroll
+            for (int i = 0; i < Bp / 4; ++i) {
+                x[i] = a1s[4 * i + q][j];
+                y[i] = z2s[4 * i + q][j];
             }
+            __builtin_amdgcn_sched_barrier(0);   // all reads before the chain of products, not one pair after the other
+#pragma unroll
+            for (int i = 0; i < Bp / 4; ++i) gw = __builtin_amdgcn_mfma_f32_16x16x4f32(x[i], y[i], gw, 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int kk = 4 * q + r;   // (entries that do not exist are zero and stay zero)
+                const float w = w2s[j][kk];
+                const float v = momentum_update(beta, v2s[j][kk], c_base + kk < d1 && j < d2 ? gw[r] : 0.f, wd, w);
+                v2s[j][kk] = v;
+                w2s[j][kk] = weight_update(w, lr, v);
+            }
+            __builtin_amdgcn_s_setprio(0);
         }
         // ---- (6) dW_1[:, C] = A_0^T dZ_1[:, C] and the update of the slice
 #pragma unroll
@@ -486,7 +552,7 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResArgs a) {
                 for (int st = 0; st < NS; ++st) {
                     const int b0 = 32 * st + 8 * q;
                     const Frag<OT> af = *reinterpret_cast<const Frag<OT>*>(&dz1t[j][b0]);
-                    const Frag<OT> bf = load8(A0T + static_cast<int64_t>(16 * kt + j) * Bp + b0);
+                    const Frag<OT> bf = load_frag(A0T + static_cast<int64_t>(kt * NS + st) * kFragElems, lane);
                     acc = mma8(af, bf, acc);
                 }
                 const int k = 16 * kt + j;
@@ -495,18 +561,25 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResArgs a) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const float w = w1s[4 * q + r][k];
-                    const float v = momentum_update(beta, v1[i][r], acc[r], a.wd, w);
+                    const float v = momentum_update(beta, v1[i][r], acc[r], wd, w);
                     v1[i][r] = v;
-                    w1s[4 * q + r][k] = weight_update(w, a.lr, v);
+                    w1s[4 * q + r][k] = weight_update(w, lr, v);
                 }
             }
         }
+        if (s + 1 < s_end) af = load_frag(input_tile(a, slot + 1, mt) + kFragElems * first_st, lane);   // on its way across the barrier
         __syncthreads();
     }
-    if (a.period > 0) average_resident(a, tid, s / a.period - 1, g, cb, w1s, w2s, b1s, b2s, gave_up);
+    int tid_a = threadIdx.x;
+    asm volatile("" : "+v"(tid_a));
+    if (a.period > 0) average_resident(a, tid_a, s / a.period - 1, g, cb, w1s, w2s, b1s, b2s, gave_up);
     }
 
     // ---- write the state back
+    int tid_w = threadIdx.x;
+    asm volatile("" : "+v"(tid_w));
+    {
+    const int tid = tid_w, wave = tid >> 6, j = tid & 15, q = (tid >> 4) & 3;
 #pragma unroll
     for (int i = 0; i < kResTiles; ++i) {
         const int kt = wave + kResWaves * i;
@@ -535,6 +608,7 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResArgs a) {
     if (cb == 0 && tid < a.d2) {
         Xg[a.b2_off + tid] = b2s[tid];
         Vg[a.b2_off + tid] = vb2s[tid];
+    }
     }
 }
 
@@ -723,10 +797,10 @@ __global__ __launch_bounds__(kResThreads) void resident1_kernel(Res1Args a) {
 }  // namespace
 
 size_t resident_exchange_floats(const lc_handle* h) {
-    // two step parities x (replicas x padded batch x padded hidden width); the single-layer form
+    // steps of a launch x (replicas x padded batch x padded hidden width); the single-layer form
     // exchanges nothing (a token amount keeps the buffer pointer non-null)
     if (h->L == 1) return 64;
-    return 2 * static_cast<size_t>(h->m) * h->train.Bp * h->layer[1].dp_out;
+    return static_cast<size_t>(h->train.slots) * h->m * h->train.Bp * h->layer[1].dp_out;
 }
 
 // Compute units of the current device: 256 on the MI355X this is written for, fewer on a partition of it.
@@ -786,9 +860,9 @@ hipError_t launch_resident1(lc_handle* h, int slot0, int n_steps, int period) {
     a.loss = S.loss;
     a.period = period;
     a.avx = h->res_avx;
-    a.gctr = h->res_ctr + 65;
+    a.gctr = h->res_ctr + kCtrAll;
     a.gctr_base = h->res_garrivals;
-    a.err = h->res_ctr + 64;
+    a.err = h->res_ctr + kCtrErr;
     a.spin_limit = h->res_spin_limit;
     if (slot0 < 0 || n_steps < 1 || slot0 + n_steps > S.slots) return hipErrorInvalidValue;
     if (period < 0 || (period > 0 && (n_steps % period != 0 || !h->res_avx || S.G > compute_units()))) return hipErrorInvalidValue;
@@ -845,27 +919,27 @@ hipError_t launch_resident(lc_handle* h, int slot0, int n_steps, int period) {
     a.wd = h->md.wd;
     a.vec = (a.d1 % 4 == 0 && a.w1_off % 4 == 0) ? 1 : 0;
     a.zx = h->res_a1x;
-    a.ctr = h->res_ctr;
+    a.ctr = h->res_ctr + kCtrReplica;
     a.ctr_base = h->res_arrivals;
-    a.err = h->res_ctr + 64;
+    a.err = h->res_ctr + kCtrErr;
     a.spin_limit = h->res_spin_limit;
     a.loss = S.loss;
     a.period = period;
     a.avx = h->res_avx;
-    a.gctr = h->res_ctr + 65;
+    a.gctr = h->res_ctr + kCtrAll;
     a.gctr_base = h->res_garrivals;
     {
-        // blocks are numbered so that each XCD works on a contiguous range of logical blocks: a
-        // replica's NB workgroups share an XCD when the ranges are whole multiples of NB
-        const int64_t per = (static_cast<int64_t>(a.G) * a.NB + kXcds - 1) / kXcds;
-        a.local_xcd = (h->res_local_on && h->res_xcc_known && per % a.NB == 0) ? 1 : 0;
+        // a replica's NB workgroups on one XCD, which has room for an eighth of the chip's
+        const int per = (a.G + kXcds - 1) / kXcds * a.NB;
+        a.local_xcd = (h->res_local_on && h->res_xcc_known && per <= compute_units() / kXcds) ? 1 : 0;
         a.xcc_of = h->res_xcc_of;
     }
     if (slot0 < 0 || n_steps < 1 || slot0 + n_steps > S.slots) return hipErrorInvalidValue;
     if (period < 0 || (period > 0 && (n_steps % period != 0 || !h->res_avx))) return hipErrorInvalidValue;
     const int64_t total = static_cast<int64_t>(a.G) * a.NB;
     if (total > compute_units() || a.G > 64 || !h->res_a1x) return hipErrorInvalidValue;
-    const unsigned grid = static_cast<unsigned>((total + kXcds - 1) / kXcds * kXcds);
+    const unsigned grid = static_cast<unsigned>(a.local_xcd ? (a.G + kXcds - 1) / kXcds * kXcds * a.NB
+                                                            : (total + kXcds - 1) / kXcds * kXcds);
     if (S.Bp != 32 && S.Bp != 64) return hipErrorInvalidValue;
     timing_start(h, kTimeBwd, 0, kBwdResident);
     if (S.Bp == 32) {
@@ -890,7 +964,7 @@ hipError_t probe_block_placement(lc_handle* h) {
     h->res_xcc_known = false;
     h->res_xcc_of = 0;
     if (!h->res_ctr) return hipSuccess;
-    unsigned* dev = h->res_ctr + 128;
+    unsigned* dev = h->res_ctr + kCtrProbe;
     unsigned host[256];
     hipLaunchKernelGGL(xcd_probe_kernel, dim3(256), dim3(64), 0, h->stream, dev);
     hipError_t e = hipGetLastError();
