@@ -209,10 +209,9 @@ int lc_materialize(lc_handle* h);
 int lc_set_resident(lc_handle* h, int on);
 /* Exchange inside one XCD.  The resident step kernel's workgroups of one replica exchange their
  * shares of the logits once per step.  Blocks are numbered so that a replica's workgroups run on one XCD
- * (one L2 cache) whenever m * ceil64(d1) / 16 / 8 is a multiple of ceil64(d1) / 16; counter and
+ * (one L2 cache) whenever ceil(m / 8) * ceil(d1 / 16) workgroups fit an XCD's compute units (32); counter and
  * exchanged values then stay in that L2 (workgroup-scope atomics, which the hardware performs in the
- * L2, and an invalidate of the compute unit's L1 only) instead of travelling to the memory side
- * and back.  The placement rule (hardware block id mod 8 selects the XCD) is observed by a probe
+ * L2) instead of travelling to the memory side and back.  The placement rule (hardware block id mod 8 selects the XCD) is observed by a probe
  * kernel at lc_attach(), and every workgroup compares its own XCD id with it when it starts: a
  * mismatch is reported as LC_ERR_PLACEMENT by the next synchronising call (the state is then
  * undefined).  Where the rule does not hold, or with on = 0, the agent-scope exchange is used.

@@ -8,7 +8,7 @@
 // The streaming kernels need four launches per step and move W and V through the memory
 // system in every one of them; at this size those launches, not the arithmetic, are the cost.
 //
-// Work split for a model d0 -> d1 -> d2 (d2 <= 16), replica g, workgroup cb of NB = dp1 / 16:
+// Work split for a model d0 -> d1 -> d2 (d2 <= 16), replica g, workgroup cb of the NB slices of 16 hidden units:
 //   owns   hidden units C = [16 cb, 16 cb + 16): columns C of W_1, V_1, entries C of b_1, and the
 //          matching ROWS C of W_2, V_2 -- every weight of the model has exactly one owner;
 //   keeps  a private copy of b_2 (d2 values), updated identically by every workgroup.
@@ -35,17 +35,15 @@
 // the shuffles of the softmax and an L2 invalidation per barrier for 3000) and the inputs in plain rows:
 // 461 us for 4 periods of 5 steps then, 341 us now.
 //
-// The barrier is a counter per replica and batch tile in device memory: arrive with an agent-scope release,
-// poll with relaxed loads, then an agent-scope acquire.  The shares are published with
-// agent-scope (write-through) stores, so the release has no dirty cache lines to write back;
-// the counters are never reset, each launch is told their value at its start.  All workgroups of a launch are
+// The barrier is a counter per replica and batch tile in device memory (arrive_and_wait_step); the
+// counters are never reset, each launch is told their value at its start.  All workgroups of a launch are
 // co-resident (the launcher refuses grids above one workgroup per compute unit), and the
 // poll loop is bounded: a wavefront that runs out of polls raises the error flag, stops
 // waiting for good and finishes its steps, so the grid always drains.  (A cooperative launch
 // would have the runtime vouch for the co-residency, but costs 18 us more per launch here, a
 // tenth of the throughput at five steps per launch; the bounded wait covers the same case.)
 // Where an XCD has compute units for an eighth of the replicas, a replica's workgroups all go to one
-// XCD, and slices and counters stay in its L2 (arrive_and_wait_same_xcd): up to 64 replicas of 64 hidden
+// XCD, and shares and counters stay in its L2: up to 64 replicas of 64 hidden
 // units, 16 of 256.
 //
 // A launch may also hold several whole communication periods: after every `period` steps the
@@ -96,9 +94,9 @@ struct ResArgs {
     unsigned gctr_base;   // its value when this launch starts
 };
 
-// Barrier among the workgroups (or one wavefront of each) that add to *ctr, called by one thread once
-// the stores of those it speaks for have arrived: what they wrote before is visible to everyone who leaves
-// the wait.  The wait is bounded; a caller that runs out of polls raises the error flag and
+// Barrier among the workgroups that add to *ctr, called by one thread per workgroup after a
+// workgroup barrier: what the workgroup wrote before is visible to every workgroup that leaves
+// the wait.  The wait is bounded; a workgroup that runs out of polls raises the error flag and
 // never waits again (it still arrives, so the counts stay right), so the grid always drains.
 __device__ __forceinline__ void arrive_and_wait(unsigned* ctr, unsigned target, int spin_limit, unsigned* err,
                                                 bool& gave_up) {
@@ -117,21 +115,24 @@ __device__ __forceinline__ void arrive_and_wait(unsigned* ctr, unsigned target, 
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
 }
 
-// The same barrier for workgroups that all run on one XCD, i.e. behind one L2: counter and data
-// need not leave that L2.  Read-modify-write atomics without the device-scope bit are performed
-// in the L2, so the counter is added to and polled there (the poll is a compare-and-swap that
-// never matches: a workgroup-scope LOAD may be served by the compute unit's L1 and then never sees
-// the count move -- measured).  The slices were written through to the L2 and stay there as
-// dirty lines, where the agent-scope form sends data and counter to the memory side and back.  The
-// readers' L1 cannot hold an older copy: every step of a launch has an exchange region of its own, and
-// a launch begins with an empty L1.  (An invalidation by the agent-scope acquire reaches the L2 as well;
-// one per workgroup and step was a third of the time between the arrival and the logits, one per
-// wavefront took 10000 clocks.)  Valid only while the participants really share an L2: the launcher checks
-// the placement rule once with a probe kernel, and every workgroup checks its own XCD id against it.
-__device__ __forceinline__ void arrive_and_wait_same_xcd(unsigned* ctr, unsigned target, int spin_limit, unsigned* err,
-                                                         bool& gave_up) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+// The barrier of a step, among the wavefronts of one batch tile: no cache is written back or invalidated.
+// What it orders are the shares of the logits, and those (a) have been stored through to the scope that the
+// readers share, and have arrived there (the caller waits for its stores), (b) lie in a region of the step's
+// own, whose lines nobody has read before in this launch -- and a launch begins with the caches clean -- so
+// no reader holds an older copy.  (The agent-scope acquire invalidates the L2 as well: 3000 clocks of a step
+// of 42000 with one per workgroup, 10000 with one per wavefront.)
+//
+// local: the wavefronts run on one XCD, i.e. behind one L2, and counter and data need not leave it.
+// Read-modify-write atomics without the device-scope bit are performed in the L2, so the counter is
+// added to and polled there (the poll is a compare-and-swap that never matches: a workgroup-scope LOAD
+// may be served by the compute unit's L1 and then never sees the count move -- measured), where the
+// agent-scope form sends data and counter to the memory side and back.  Valid only while the participants
+// really share an L2: the launcher checks the placement rule once with a probe kernel, and every
+// workgroup checks its own XCD id against it.
+__device__ __forceinline__ void arrive_and_wait_step(unsigned* ctr, unsigned target, int spin_limit, unsigned* err,
+                                                     bool local, bool& gave_up) {
+    if (local) __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    else __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     int polls = 0;
     while (!gave_up) {
         if (polls++ >= spin_limit) {
@@ -140,11 +141,13 @@ __device__ __forceinline__ void arrive_and_wait_same_xcd(unsigned* ctr, unsigned
             break;
         }
         unsigned seen = 0xFFFFFFFFu;   // (were the count ever this, the swap would write the same value back)
-        __hip_atomic_compare_exchange_strong(ctr, &seen, 0xFFFFFFFFu, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (local)
+            __hip_atomic_compare_exchange_strong(ctr, &seen, 0xFFFFFFFFu, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_WORKGROUP);
+        else
+            seen = __hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (static_cast<int>(seen - target) >= 0) break;
     }
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
 // The XCD this wavefront runs on: hardware register XCC_ID (number 20), bits 3:0.  The operand
@@ -363,7 +366,7 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResArgs args) {
         const int slot = a.slot0 + s;
         const OT* A0T = static_cast<const OT*>(a.a0_fm) + slot * a.a0_slot + static_cast<int64_t>(g) * a.dp0 * Bp;
         const int32_t* lab = a.labels + (static_cast<int64_t>(slot) * a.G + g) * Bp;
-        float* xp = a.zx + (static_cast<int64_t>(s) * a.G + g) * Bp * a.dp1;   // [NB][Bp][16]
+        float* xp = a.zx + (static_cast<int64_t>(s) * a.G + g) * Bp * a.dp1;   // [NB][Bp][16] of [dp1 / 16][Bp][16]
         // ---- (1) Z_1[:, C]^T: wavefront (mt, kpart) takes batch tile mt and the 32-wide k steps
         //      kpart, kpart + KP, ...  A lane ends up with hidden units 4 q .. 4 q + 3 of sample 16 mt + j.
         const int mt = wave % MT, kpart = wave / MT;
@@ -382,7 +385,7 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResArgs args) {
                 const float x[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
                 Frag<OT> bf;
                 pack8(bf, x);
-                z1 = mma8(bf, af, z1);
+                z1 += mma8(bf, af, f32x4{0.f, 0.f, 0.f, 0.f});   // (sums of 32, added up: no error of a long chain)
                 af = af_next;
             }
         }
@@ -420,21 +423,13 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResArgs args) {
                 else __hip_atomic_store(px + r, zp[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // written through to device scope
             }
             // ---- replica-wide barrier of the wavefronts of this batch tile: nothing else is exchanged
-            if (NB > 1) {
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-                __builtin_amdgcn_s_waitcnt(0);   // the whole wavefront's stores have arrived before it does
-                if (lane == 0) {
-                    const unsigned target = a.ctr_base + static_cast<unsigned>(s + 1) * static_cast<unsigned>(NB);
-                    unsigned* ctr = a.ctr + (g * MT + mt) * kCtrTile;
-                    if (a.local_xcd) arrive_and_wait_same_xcd(ctr, target, a.spin_limit, a.err, gave_up);
-                    else arrive_and_wait(ctr, target, a.spin_limit, a.err, gave_up);
-                }
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-            } else {
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-                __builtin_amdgcn_s_waitcnt(0);
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            __builtin_amdgcn_s_waitcnt(0);   // the whole wavefront's stores have arrived before it does
+            if (NB > 1 && lane == 0) {
+                const unsigned target = a.ctr_base + static_cast<unsigned>(s + 1) * static_cast<unsigned>(NB);
+                arrive_and_wait_step(a.ctr + (g * MT + mt) * kCtrTile, target, a.spin_limit, a.err, a.local_xcd != 0, gave_up);
             }
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
             // ---- (3) logits = sum of the slices' shares in slice order + b_2; softmax cross-entropy and
             //      dZ_2 (redundantly in every workgroup: a few hundred values).  Classes 4 q .. 4 q + 3 of
             //      sample b in a lane; all shares are requested at once.
@@ -817,6 +812,8 @@ int compute_units() {
     return units;
 }
 
+static int resident_slices(const lc_handle* h) { return (h->layer[1].d_out + 15) / 16; }   // workgroups of a replica
+
 // Two layers, at most 16 classes and 64 samples, widths within the LDS budget, and few enough
 // workgroups that all of them are on the chip at the same time (one per compute unit); or one
 // layer of at most 256 (padded) inputs and 16 classes.
@@ -906,7 +903,7 @@ hipError_t launch_resident(lc_handle* h, int slot0, int n_steps, int period) {
     a.dp1 = h->layer[1].dp_out;
     a.B = S.B;
     a.G = S.G;
-    a.NB = a.dp1 / 16;
+    a.NB = resident_slices(h);
     a.a0_bm = S.a_bm[0];
     a.a0_fm = S.a_fm[0];
     a.a0_slot = static_cast<int64_t>(S.G) * S.Bp * a.dp0;
