@@ -277,7 +277,7 @@ int run_periods(lc_handle* h, int tau, int n_periods, bool average) {
     while (left > 0) {
         int64_t n = (pos == 0 && tau <= slots) ? static_cast<int64_t>(slots / tau) * tau : (tau - pos < slots ? tau - pos : slots);
         if (n > left) n = left;
-        if (mlp) LC_HIP(h, launch_gather(h, false, h->k, static_cast<int>(n)));
+        if (mlp && !fetches_its_inputs(h)) LC_HIP(h, launch_gather(h, false, h->k, static_cast<int>(n)));
         h->a1_ready = false;
         for (int t = 0; t < n;) {
             const int in_period = tau - pos < n - t ? tau - pos : static_cast<int>(n - t);
@@ -528,7 +528,7 @@ int lc_local_periods(lc_handle* h, int tau, int n_periods) {
     const int per_launch = h->train.slots / tau;
     for (int done = 0; done < n_periods; done += per_launch) {
         const int p = n_periods - done < per_launch ? n_periods - done : per_launch;
-        LC_HIP(h, launch_gather(h, false, h->k, p * tau));
+        if (!fetches_its_inputs(h)) LC_HIP(h, launch_gather(h, false, h->k, p * tau));
         LC_HIP(h, launch_resident(h, 0, p * tau, tau));
         h->train.cur_slot = p * tau - 1;
         h->k += static_cast<int64_t>(p) * tau;

@@ -206,6 +206,7 @@ hipError_t launch_net(lc_handle* h, int slot0, int n_steps);  // as launch_resid
 size_t resident_exchange_floats(const lc_handle* h);
 hipError_t probe_block_placement(lc_handle* h);   // synchronises the stream once
 inline bool inputs_in_fragments(const lc_handle* h) { return h->res_on && h->res_a1x && h->L == 2; }   // how the gather kernel leaves A_0
+inline bool fetches_its_inputs(const lc_handle* h) { return h->res_on && h->res_a1x && h->L == 1; }    // ... and where there is none
 hipError_t launch_resident(lc_handle* h, int slot0, int n_steps, int period);  // the steps gathered into slots slot0 .. slot0+n_steps-1
 
 // timing helpers used by the launchers

@@ -35,52 +35,6 @@ namespace lc {
 
 namespace {
 
-// ----------------------------------------------------------------- index hash
-
-__device__ __forceinline__ uint64_t mix64(uint64_t z) {
-    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ULL;
-    z = (z ^ (z >> 27)) * 0x94D049BB133111EBULL;
-    return z ^ (z >> 31);
-}
-__device__ __forceinline__ int64_t batch_index(uint64_t seed, int i, int64_t k, int b, int64_t N) {
-    const uint64_t gamma = 0x9E3779B97F4A7C15ULL;
-    uint64_t hsh = mix64(seed + gamma * (static_cast<uint64_t>(k) + 1));
-    hsh = mix64(hsh + gamma * (static_cast<uint64_t>(i) + 1));
-    hsh = mix64(hsh + gamma * (static_cast<uint64_t>(b) + 1));
-    return static_cast<int64_t>(hsh % static_cast<uint64_t>(N));
-}
-
-// Partition sampler: bijection of [0, n) by a 4-round balanced Feistel network on 2w bits with
-// cycle walking.  The network permutes its 2w-bit domain, so a walk that starts below n returns
-// below n after finitely many rounds (fewer than four on average, as the domain is < 4 n).
-__device__ __forceinline__ uint64_t feistel_permute(uint64_t x, uint64_t n, uint64_t key) {
-    int w = 1;
-    while ((1ULL << (2 * w)) < n) ++w;
-    const uint64_t mask = (1ULL << w) - 1;
-    const uint64_t gamma = 0x9E3779B97F4A7C15ULL;
-    do {
-        uint64_t l = x >> w, r = x & mask;
-#pragma unroll
-        for (int round = 0; round < 4; ++round) {
-            const uint64_t f = mix64(key + gamma * static_cast<uint64_t>(round + 1) + r) & mask;
-            const uint64_t t = l ^ f;
-            l = r;
-            r = t;
-        }
-        x = (l << w) | r;
-    } while (x >= n);
-    return x;
-}
-__device__ __forceinline__ int64_t partition_index(uint64_t seed, int i, int64_t k, int b, int64_t N, int m, int B) {
-    const int64_t lo = static_cast<int64_t>(i) * N / m, hi = static_cast<int64_t>(i + 1) * N / m;
-    const int64_t S = (N / m) / B;   // >= 1, checked by lc_init
-    const int64_t epoch = k / S, pos = (k % S) * B + b;
-    const uint64_t gamma = 0x9E3779B97F4A7C15ULL;
-    uint64_t key = mix64(seed + gamma * (static_cast<uint64_t>(epoch) + 1));
-    key = mix64(key + gamma * (static_cast<uint64_t>(i) + 1));
-    return lo + static_cast<int64_t>(feistel_permute(static_cast<uint64_t>(pos), static_cast<uint64_t>(hi - lo), key));
-}
-
 // --------------------------------------------------------------------- gather
 
 struct GatherArgs {

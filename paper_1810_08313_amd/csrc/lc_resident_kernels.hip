@@ -59,7 +59,6 @@ namespace {
 constexpr int kResMaxD0 = 1024;   // padded input width the LDS slice is sized for
 constexpr int kResMaxD1 = 256;    // padded hidden width (private W_2^T copy)
 constexpr int kResK1P = kResMaxD0 + 4;
-constexpr int kResK2P = kResMaxD1 + 4;
 constexpr int kResWaves = 16;                    // wavefronts per workgroup: four per SIMD hide each other's waits
 constexpr int kResThreads = kResWaves * 64;
 constexpr int kResTiles = kResMaxD0 / 16 / kResWaves;   // 16-row tiles of W_1 per wavefront
@@ -608,9 +607,18 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResArgs args) {
 }
 
 // Softmax regression (one layer, d0 -> d1 with d1 <= 16 classes): the same idea without any
-// exchange.  One workgroup per replica keeps W^T, V^T and the bias in LDS for all the steps of a
-// launch; a step is logits (reduction split over the wavefronts), softmax cross-entropy, and
-// dW = A_0^T dZ with the momentum update applied in place.
+// exchange.  One workgroup per replica takes all the steps of a launch, and selects and fetches the
+// mini-batches itself.  Wavefront w owns the weights and momentum of features 16 w .. 16 w + 15, in registers
+// (class 4 q + r of feature 16 w + j in register r); LDS holds a copy of W^T for the logits and the batch.
+// One step:
+//   logits, the wavefronts sharing out batch tiles and the reduction; every wavefront also takes its operand
+//     of the weight gradient, A_0 of its features, into registers
+//   one wavefront per batch tile: softmax cross-entropy and dZ; all: a batch that was requested a step ago
+//     into LDS, and another one requested
+//   dW = A_0^T dZ and the update of the own tile
+// What bounds it is latency: 64-10, 4 workers, batch 32, one period of 4 steps, 14.2 us -- before the first
+// step 4 us (the indices' hash, one round trip for rows, state and labels), 1.6 us a step, 3 us for the averaging
+// step in the launch.  With a gather kernel before it, W in LDS only and the softmax through LDS it was 18.2 us.
 struct Res1Args {
     float* X;
     float* V;
@@ -620,11 +628,14 @@ struct Res1Args {
     int64_t w_off, b_off;
     int d0, d1, dp0;
     int B, G;
-    const void* a0_bm;      // [slots][G][Bp][dp0] of OT
-    const void* a0_fm;      // [slots][G][dp0][Bp] of OT
-    int64_t a0_slot;
-    const int32_t* labels;  // [slots][G][Bp]
-    int slot0, n_steps;
+    const void* data;       // [N][d0] of OT
+    const int32_t* labels;  // [N]
+    int32_t* idx_out;       // [steps][G][Bp] of the launch
+    int64_t N;
+    uint64_t seed;
+    int64_t k;              // local iteration of the launch's first step
+    int sampler, m;
+    int n_steps, ring;      // batches the ring holds
     float lr, beta_first, beta, wd;
     float* loss;            // [G][kLossParts], slot 0 written
     int period;             // averaging step after every `period` steps inside the launch; 0: none
@@ -635,126 +646,233 @@ struct Res1Args {
     int spin_limit;
 };
 
+constexpr int kRes1Steps = 4 * kGatherSlots;   // most steps of a launch
+constexpr int kRes1Ring = 96 * 1024;           // bytes of the ring of batches
+constexpr int kRes1First = 6;                  // rounds of fetches at the start
+constexpr int kRes1K = 256;                    // padded inputs: 16 features for each of the 16 wavefronts
+
 template <typename OT, int MT>
 __global__ __launch_bounds__(kResThreads) void resident1_kernel(Res1Args a) {
     constexpr int Bp = 16 * MT;
     constexpr int NS = Bp / 32;
     constexpr int KP = kResWaves / MT;
-    __shared__ __attribute__((aligned(16))) float ws[16][kResK2P];    // W^T (row = class)
-    __shared__ __attribute__((aligned(16))) float vs[16][kResK2P];
-    __shared__ __attribute__((aligned(16))) float part[KP][Bp][17];
-    __shared__ float zs[Bp][17];                                       // dZ
-    __shared__ __attribute__((aligned(16))) OT dzt[16][Bp + 8];        // dZ^T
+    constexpr int NP = MT;   // rounds of fetches for a batch: each takes at least a row per wavefront
+    __shared__ __attribute__((aligned(16))) OT ring[kRes1Ring / sizeof(OT)];   // A_0 of several steps
+    __shared__ __attribute__((aligned(16))) float ws[16][kRes1K + 4];   // W^T (row = class)
+    __shared__ __attribute__((aligned(16))) float part[KP - 1][Bp][20];
+    __shared__ __attribute__((aligned(16))) OT dzt[16][Bp + 8];         // dZ^T
+    __shared__ int idxs[kRes1Steps * Bp], labs[kRes1Steps * Bp];        // [step][Bp], -1: no sample
     __shared__ float bs[16], vbs[16];
     __shared__ float lred[Bp];
-    __shared__ float colsum[kResWaves][16];
 
     const int g = blockIdx.x;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane & 15, q = lane >> 4;
     float* Xg = a.X + g * a.x_stride;
     float* Vg = a.V + g * a.x_stride;
     const float* Xrg = a.Xr + g * a.xr_stride;
+    const int d0 = a.d0, d1 = a.d1, dp0 = a.dp0;
+    const float lr = a.lr, wd = a.wd;
 
-    for (int e = tid; e < 16 * a.dp0; e += kResThreads) {
-        const int k = e / 16, c = e % 16;
-        const bool in = k < a.d0 && c < a.d1;
-        ws[c][k] = in ? Xrg[a.w_off + static_cast<int64_t>(k) * a.d1 + c] : 0.f;
-        vs[c][k] = in ? Vg[a.w_off + static_cast<int64_t>(k) * a.d1 + c] : 0.f;
+    // ---- the launch's mini-batches
+    for (int e = tid; e < a.n_steps * Bp; e += kResThreads) {
+        const int s = e / Bp, b = e % Bp;
+        int64_t idx = -1;
+        if (b < a.B)
+            idx = a.sampler ? partition_index(a.seed, g, a.k + s, b, a.N, a.m, a.B) : batch_index(a.seed, g, a.k + s, b, a.N);
+        idxs[e] = static_cast<int>(idx);
+        a.idx_out[(static_cast<int64_t>(s) * a.G + g) * Bp + b] = static_cast<int>(idx);
+    }
+    __syncthreads();
+    // The ring holds R batches.  The first `lead - 1` are fetched together; the one after them is on its way
+    // when the steps begin, and step s places batch s + lead - 1 and requests batch s + lead.
+    const OT* data = static_cast<const OT*>(a.data);
+    const int row = dp0 + 16 / static_cast<int>(sizeof(OT)), R = a.ring, lead = R > 1 ? R : 2;
+    // A lane fetches 4 features; a wavefront takes as many whole rows at a time as it has lanes for.
+    const bool vec = d0 % 4 == 0;   // row pieces are whole and aligned
+    const int per_row = dp0 / 4, rows = 64 / per_row, lane_row = lane / per_row, c = 4 * (lane - per_row * lane_row);
+    const int my_row = lane_row < rows ? wave * rows + lane_row : -(1 << 20);   // of the 16 * rows of a round
+    auto fetch = [&](int idx) {   // features c .. c + 3 of a sample, zero where there are none
+        const bool in = idx >= 0 && c < d0;
+        const OT* p = data + (in ? static_cast<int64_t>(idx) * d0 + c : 0);
+        Frag4<OT> f;
+        if (vec) {
+            f = load4(p);
+            if (!in) pack4(f, 0.f, 0.f, 0.f, 0.f);
+        } else {
+            float x[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[i] = to_f32(p[in && c + i < d0 ? i : 0]);
+            pack4(f, in ? x[0] : 0.f, in && c + 1 < d0 ? x[1] : 0.f, in && c + 2 < d0 ? x[2] : 0.f, in && c + 3 < d0 ? x[3] : 0.f);
+        }
+        return f;
+    };
+    auto put = [&](OT* to, const Frag4<OT>& f) { store4(to, to_f32(f.v[0]), to_f32(f.v[1]), to_f32(f.v[2]), to_f32(f.v[3])); };
+    Frag4<OT> next[NP];
+    auto request = [&](int s) {
+#pragma unroll
+        for (int u = 0; u < NP; ++u) {
+            const int b = my_row + kResWaves * rows * u;
+            if (kResWaves * rows * u < Bp) next[u] = fetch(b >= 0 && b < Bp ? idxs[s * Bp + b] : -1);
+        }
+    };
+    auto place = [&](int s) {
+        OT* to = ring + s % R * (Bp * row) + c;
+#pragma unroll
+        for (int u = 0; u < NP; ++u) {
+            const int b = my_row + kResWaves * rows * u;
+            if (b >= 0 && b < Bp) put(to + b * row, next[u]);
+        }
+    };
+    const int n_first = (lead - 1 < a.n_steps ? lead - 1 : a.n_steps) * Bp;   // rows
+    Frag4<OT> first[kRes1First];
+#pragma unroll
+    for (int u = 0; u < kRes1First; ++u) {
+        const int r = my_row + kResWaves * rows * u;
+        if (kResWaves * rows * u < n_first) first[u] = fetch(r >= 0 && r < n_first ? idxs[r] : -1);
+    }
+    // ---- the own tile of the state (entries that do not exist read the first one and are zeroed), the labels
+    const int k_own = 16 * wave + j;
+    float w[4], v[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const bool in = k_own < d0 && 4 * q + r < d1;
+        const int64_t at = a.w_off + (in ? k_own * d1 + 4 * q + r : 0);
+        w[r] = Xrg[at];
+        v[r] = Vg[at];
+    }
+    const bool has_bias = tid < d1;
+    const float b_in = Xrg[a.b_off + (has_bias ? tid : 0)], vb_in = Vg[a.b_off + (has_bias ? tid : 0)];
+    for (int e = tid; e < a.n_steps * Bp; e += kResThreads) {
+        const int idx = idxs[e], y = a.labels[idx >= 0 ? idx : 0];
+        labs[e] = idx >= 0 ? y : -1;
+    }
+#pragma unroll
+    for (int u = 0; u < kRes1First; ++u) {
+        const int r = my_row + kResWaves * rows * u;
+        if (r >= 0 && r < n_first) put(ring + r * row + c, first[u]);
+    }
+    if (lead - 1 < a.n_steps) request(lead - 1);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const bool in = k_own < d0 && 4 * q + r < d1;
+        w[r] = in ? w[r] : 0.f;
+        v[r] = in ? v[r] : 0.f;
+        ws[4 * q + r][k_own] = w[r];
     }
     if (tid < 16) {
-        bs[tid] = tid < a.d1 ? Xrg[a.b_off + tid] : 0.f;
-        vbs[tid] = tid < a.d1 ? Vg[a.b_off + tid] : 0.f;
+        bs[tid] = has_bias ? b_in : 0.f;
+        vbs[tid] = has_bias ? vb_in : 0.f;
     }
     __syncthreads();
 
     const int mt = wave % MT, kpart = wave / MT;
     bool gave_up = false;   // thread 0: a barrier wait ran out of polls
     for (int s = 0; s < a.n_steps; ++s) {
+        int tid_o = threadIdx.x;   // (addresses are derived afresh in every step instead of held in registers)
+        asm volatile("" : "+v"(tid_o));
+        const int tid = tid_o, lane = tid & 63, j = lane & 15, q = lane >> 4, k_own = 16 * wave + j;
         const float beta = s == 0 ? a.beta_first : a.beta;
-        const int slot = a.slot0 + s;
-        const OT* A0 = static_cast<const OT*>(a.a0_bm) + slot * a.a0_slot + static_cast<int64_t>(g) * Bp * a.dp0;
-        const OT* A0T = static_cast<const OT*>(a.a0_fm) + slot * a.a0_slot + static_cast<int64_t>(g) * a.dp0 * Bp;
-        const int32_t* lab = a.labels + (static_cast<int64_t>(slot) * a.G + g) * Bp;
-
-        // ---- logits, partial over this wavefront's share of d0
-        {
-            f32x4 z = f32x4{0.f, 0.f, 0.f, 0.f};
-            const OT* arow = A0 + static_cast<int64_t>(16 * mt + j) * a.dp0 + 8 * q;
-            for (int st = kpart; st < a.dp0 / 32; st += KP) {
-                const int k0 = 32 * st + 8 * q;
-                const Frag<OT> af = load8(arow + 32 * st);
-                const float4 x0 = *reinterpret_cast<const float4*>(&ws[j][k0]);
-                const float4 x1 = *reinterpret_cast<const float4*>(&ws[j][k0 + 4]);
-                const float x[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
-                Frag<OT> bf;
-                pack8(bf, x);
-                z = mma8(af, bf, z);
+        const OT* as = ring + s % R * (Bp * row);
+        // ---- logits^T, partial over this wavefront's share of d0: class 4 q + r of sample 16 mt + j
+        f32x4 z = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int st = kpart; st < dp0 / 32; st += KP) {
+            const int k0 = 32 * st + 8 * q;
+            const Frag<OT> af = load8(as + (16 * mt + j) * row + k0);
+            const float4 x0 = *reinterpret_cast<const float4*>(&ws[j][k0]);
+            const float4 x1 = *reinterpret_cast<const float4*>(&ws[j][k0 + 4]);
+            const float x[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+            Frag<OT> bf;
+            pack8(bf, x);
+            z = mma8(bf, af, z);
+        }
+        if (kpart > 0) *reinterpret_cast<f32x4*>(&part[kpart - 1][16 * mt + j][4 * q]) = z;
+        // ---- A_0 of the own features, operand of dW
+        Frag<OT> own[NS];
+        if (16 * wave < dp0) {
+#pragma unroll
+            for (int st = 0; st < NS; ++st)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) own[st].v[e] = as[(32 * st + 8 * q + e) * row + k_own];
+        }
+        __syncthreads();
+        // ---- a place of the ring has become free (with R = 1 this step's, else that of the step before)
+        if (s + lead - 1 < a.n_steps) {
+            place(s + lead - 1);
+            if (s + lead < a.n_steps) request(s + lead);
+        }
+        // ---- softmax cross-entropy and dZ, one wavefront per batch tile
+        if (wave < MT) {
+            const int b = 16 * mt + j, y = labs[s * Bp + b];
+#pragma unroll
+            for (int p = 1; p < KP; ++p) z += *reinterpret_cast<const f32x4*>(&part[p - 1][b][4 * q]);
+            float zmax = -INFINITY;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                z[r] += bs[4 * q + r];
+                if (4 * q + r < d1) zmax = fmaxf(zmax, z[r]);
             }
+            zmax = max_over_quarters(zmax);
+            f32x4 ex;
+            float s_other = 0.f, e_y = 0.f, z_y = 0.f;   // (over the classes other than the label, see xent_loss)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) part[kpart][16 * mt + 4 * q + r][j] = z[r];
+            for (int r = 0; r < 4; ++r) {
+                const int c = 4 * q + r;
+                ex[r] = c < d1 ? expf(z[r] - zmax) : 0.f;
+                s_other += c == y ? 0.f : ex[r];
+                e_y += c == y ? ex[r] : 0.f;
+                z_y += c == y ? z[r] : 0.f;
+            }
+            s_other = sum_over_quarters(s_other);
+            const float sum = s_other + sum_over_quarters(e_y), inv = 1.f / sum, invB = 1.f / static_cast<float>(a.B);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int c = 4 * q + r;
+                const OT dz = static_cast<OT>(y >= 0 && c < d1 ? xent_delta(ex[r], c == y, s_other, inv) * invB : 0.f);
+                dzt[c][b] = dz;
+            }
+            if (s + 1 == a.n_steps) {   // (the losses that are kept are those of the last step)
+                z_y = sum_over_quarters(z_y);
+                if (q == 0) lred[b] = y >= 0 ? -(z_y - zmax - logf(sum)) : 0.f;
+            }
         }
         __syncthreads();
-        // ---- softmax cross-entropy and dZ, one thread per (sample, class); column sums of dZ
-        if (tid < Bp * 16) {
-            const int b = tid >> 4, c = tid & 15;
-            float z = part[0][b][c];
+        if (s + 1 == a.n_steps && wave == kResWaves - 1) {
+            float l = lane < Bp ? lred[lane] : 0.f;
 #pragma unroll
-            for (int p = 1; p < KP; ++p) z += part[p][b][c];
-            z += bs[c];
-            const int y = b < a.B ? lab[b] : -1;
-            const bool valid = c < a.d1;
-            float zmax = valid ? z : -INFINITY;
-#pragma unroll
-            for (int o = 8; o > 0; o >>= 1) zmax = fmaxf(zmax, __shfl_xor(zmax, o, 16));
-            const float ex = valid ? expf(z - zmax) : 0.f;
-            float s_other = c == y ? 0.f : ex;   // over the classes other than the label (see xent_loss)
-#pragma unroll
-            for (int o = 8; o > 0; o >>= 1) s_other += __shfl_xor(s_other, o, 16);
-            const float zy = __shfl(z, y >= 0 ? y : 0, 16), sum = s_other + __shfl(ex, y >= 0 ? y : 0, 16);
-            float dz = 0.f;
-            if (y >= 0 && valid)
-                dz = round_operand(xent_delta(ex, c == y, s_other, 1.f / sum) * (1.f / static_cast<float>(a.B)), OT());
-            zs[b][c] = dz;
-            dzt[c][b] = static_cast<OT>(dz);
-            if (c == 0) lred[b] = y >= 0 ? -(zy - zmax - logf(sum)) : 0.f;
-            float cs = dz;
-            cs += __shfl_xor(cs, 16, 64);
-            cs += __shfl_xor(cs, 32, 64);
-            if (lane < 16) colsum[wave][lane] = cs;
+            for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o, 64);
+            if (lane == 0) a.loss[static_cast<int64_t>(g) * kLossParts] = l / static_cast<float>(a.B);
         }
-        __syncthreads();
-        if (wave == 0) {
-            float v = lane < Bp ? lred[lane] : 0.f;
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-            if (lane == 0) a.loss[static_cast<int64_t>(g) * kLossParts] = v / static_cast<float>(a.B);
-        } else if (wave == 1 && lane < a.d1) {
+        if (wave == kResWaves - 2) {   // column sums of dZ, a quarter of the batch per lane
             float db = 0.f;
-            for (int w = 0; w < Bp / 4; ++w) db += colsum[w][lane];
-            const float vb = momentum_update(beta, vbs[lane], db, a.wd, bs[lane]);
-            vbs[lane] = vb;
-            bs[lane] = weight_update(bs[lane], a.lr, vb);
+#pragma unroll
+            for (int i = 0; i < Bp / 32; ++i) {
+                const Frag<OT> f = load8(&dzt[j][32 * i + 8 * q]);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) db += to_f32(f.v[e]);
+            }
+            db = sum_over_quarters(db);
+            if (lane < d1) {
+                const float vb = momentum_update(beta, vbs[lane], db, wd, bs[lane]);
+                vbs[lane] = vb;
+                bs[lane] = weight_update(bs[lane], lr, vb);
+            }
         }
-        // ---- dW = A_0^T dZ and the update; tile kt = 16 rows of W
-        for (int kt = wave; kt < a.dp0 / 16; kt += kResWaves) {
+        // ---- dW^T = dZ^T A_0 of the own features and the update
+        if (16 * wave < dp0) {
             f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int st = 0; st < NS; ++st) {
-                const int b0 = 32 * st + 8 * q;
-                const Frag<OT> af = load8(A0T + static_cast<int64_t>(16 * kt + j) * Bp + b0);
-                const Frag<OT> bf = *reinterpret_cast<const Frag<OT>*>(&dzt[j][b0]);
-                acc = mma8(af, bf, acc);
+                const Frag<OT> zf = *reinterpret_cast<const Frag<OT>*>(&dzt[j][32 * st + 8 * q]);
+                acc = mma8(zf, own[st], acc);
             }
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int k = 16 * kt + 4 * q + r;
-                if (k < a.d0 && j < a.d1) {
-                    const float w = ws[j][k];
-                    const float v = momentum_update(beta, vs[j][k], acc[r], a.wd, w);
-                    vs[j][k] = v;
-                    ws[j][k] = weight_update(w, a.lr, v);
-                }
+                // (an entry that does not exist must stay zero also where its zero operand meets an infinity)
+                const float gw = k_own < d0 && 4 * q + r < d1 ? acc[r] : 0.f;
+                v[r] = momentum_update(beta, v[r], gw, wd, w[r]);
+                w[r] = weight_update(w[r], lr, v[r]);
+                ws[4 * q + r][k_own] = w[r];
             }
         }
         __syncthreads();
@@ -764,26 +882,31 @@ __global__ __launch_bounds__(kResThreads) void resident1_kernel(Res1Args a) {
         const int pi = (s + 1) / a.period - 1;
         float* all = a.avx + static_cast<int64_t>(pi & 1) * a.G * a.x_stride;
         float* mine = all + g * a.x_stride;
-        for (int e = tid; e < a.d0 * a.d1; e += kResThreads) mine[a.w_off + e] = ws[e % a.d1][e / a.d1];
-        if (tid < a.d1) mine[a.b_off + tid] = bs[tid];
+        for (int e = tid; e < d0 * d1; e += kResThreads) mine[a.w_off + e] = ws[e % d1][e / d1];
+        if (tid < d1) mine[a.b_off + tid] = bs[tid];
         __builtin_amdgcn_s_waitcnt(0);   // this wavefront's stores have left before the workgroup arrives
         __syncthreads();
         if (tid == 0)
             arrive_and_wait(a.gctr, a.gctr_base + static_cast<unsigned>(pi + 1) * static_cast<unsigned>(a.G),
                             a.spin_limit, a.err, gave_up);
         __syncthreads();
-        for (int e = tid; e < a.d0 * a.d1; e += kResThreads)
-            ws[e % a.d1][e / a.d1] = mean_of_replicas(all + a.w_off + e, a.x_stride, a.G);
-        if (tid < a.d1) bs[tid] = mean_of_replicas(all + a.b_off + tid, a.x_stride, a.G);
+        for (int e = tid; e < d0 * d1; e += kResThreads)
+            ws[e % d1][e / d1] = mean_of_replicas(all + a.w_off + e, a.x_stride, a.G);
+        if (tid < d1) bs[tid] = mean_of_replicas(all + a.b_off + tid, a.x_stride, a.G);
         __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 4; ++r) w[r] = ws[4 * q + r][k_own];
     }
 
-    for (int e = tid; e < a.d0 * a.d1; e += kResThreads) {
-        const int k = e / a.d1, c = e % a.d1;
-        Xg[a.w_off + e] = ws[c][k];
-        Vg[a.w_off + e] = vs[c][k];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        if (k_own < d0 && 4 * q + r < d1) {
+            const int64_t at = a.w_off + k_own * d1 + 4 * q + r;
+            Xg[at] = w[r];
+            Vg[at] = v[r];
+        }
     }
-    if (tid < a.d1) {
+    if (tid < d1) {
         Xg[a.b_off + tid] = bs[tid];
         Vg[a.b_off + tid] = vbs[tid];
     }
@@ -819,7 +942,7 @@ static int resident_slices(const lc_handle* h) { return (h->layer[1].d_out + 15)
 // layer of at most 256 (padded) inputs and 16 classes.
 bool resident_shape_ok(const lc_handle* h) {
     if (h->md.kind != LC_KIND_MLP || h->md.B > 64) return false;
-    if (h->L == 1) return h->layer[1].d_out <= 16 && h->layer[1].dp_in <= kResMaxD1;
+    if (h->L == 1) return h->layer[1].d_out <= 16 && h->layer[1].dp_in <= kRes1K;
     if (h->L != 2) return false;
     if (h->layer[2].d_out > 16) return false;
     if (h->layer[1].dp_in > kResMaxD0 || h->layer[1].dp_out > kResMaxD1) return false;
@@ -844,12 +967,21 @@ hipError_t launch_resident1(lc_handle* h, int slot0, int n_steps, int period) {
     a.dp0 = h->layer[1].dp_in;
     a.B = S.B;
     a.G = S.G;
-    a.a0_bm = S.a_bm[0];
-    a.a0_fm = S.a_fm[0];
-    a.a0_slot = static_cast<int64_t>(S.G) * S.Bp * a.dp0;
-    a.labels = S.labels;
-    a.slot0 = slot0;
+    a.data = h->data;
+    a.labels = h->labels;
+    a.idx_out = S.idx + static_cast<size_t>(slot0) * S.G * S.Bp;
+    a.N = h->md.N;
+    a.seed = h->seed;
+    a.k = h->k;
+    a.sampler = h->md.sampler;
+    a.m = h->m;
     a.n_steps = n_steps;
+    {
+        const int batch = S.Bp * (a.dp0 * (bf16 ? 2 : 4) + 16), per_round = kResWaves * (64 / (a.dp0 / 4));
+        int ring = kRes1Ring / batch;
+        if (ring > 1 + kRes1First * per_round / S.Bp) ring = 1 + kRes1First * per_round / S.Bp;
+        a.ring = ring < n_steps ? ring : n_steps;
+    }
     a.lr = h->md.lr;
     a.beta_first = effective_beta(h);
     a.beta = h->md.beta;
@@ -861,10 +993,10 @@ hipError_t launch_resident1(lc_handle* h, int slot0, int n_steps, int period) {
     a.gctr_base = h->res_garrivals;
     a.err = h->res_ctr + kCtrErr;
     a.spin_limit = h->res_spin_limit;
-    if (slot0 < 0 || n_steps < 1 || slot0 + n_steps > S.slots) return hipErrorInvalidValue;
+    if (slot0 < 0 || n_steps < 1 || slot0 + n_steps > S.slots || n_steps > kRes1Steps) return hipErrorInvalidValue;
     if (period < 0 || (period > 0 && (n_steps % period != 0 || !h->res_avx || S.G > compute_units()))) return hipErrorInvalidValue;
     if (S.Bp != 32 && S.Bp != 64) return hipErrorInvalidValue;
-    if (a.dp0 > kResMaxD1 || a.d1 > 16) return hipErrorInvalidValue;
+    if (a.dp0 > kRes1K || a.d1 > 16) return hipErrorInvalidValue;
     timing_start(h, kTimeBwd, 0, kBwdResident);
     const dim3 grid(static_cast<unsigned>(S.G)), block(kResThreads);
     if (S.Bp == 32) {
