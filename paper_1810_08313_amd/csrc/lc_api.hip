@@ -231,9 +231,6 @@ int one_local_step(lc_handle* h, bool next_gathered, bool implicit_out = false) 
     return LC_OK;
 }
 
-// Local steps run with the models on chip: the resident step kernels, or one compute unit per replica.
-bool on_chip(const lc_handle* h) { return h->res_on && (h->res_a1x || h->net_ok); }
-
 // Reads and clears the error flag of the resident step kernel.  Call after a stream synchronise.
 int check_resident(lc_handle* h) {
     if (!h->res_used || !h->res_ctr) return LC_OK;

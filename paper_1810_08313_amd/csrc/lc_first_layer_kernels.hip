@@ -43,7 +43,7 @@ struct FirstArgs {
     int64_t w_off, b_off;
     int d_in, d_out, dp_in, dp_out;
     int B;
-    const void* a_fm;     // A_0 of this step, feature-major [G][dp_in][Bp]
+    const void* a_fm;     // A_0^T of this step, tiles of 16 features in fragment order
     const void* dz_fm;    // dZ_1 of this step, feature-major [G][dp_out][Bp]
     float lr, beta, wd;
     const void* an_bm;    // A_0 of the next step, batch-major [G][Bp][dp_in]
@@ -129,8 +129,9 @@ __global__ __launch_bounds__(256, (FlBudget<OT, NT>::kWavesPerSimd)) void first_
     unsigned woff[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) woff[r] = 4u * static_cast<unsigned>((4 * q + r) * a.d_out + c0 + 4 * j);
-    const unsigned atoff = static_cast<unsigned>(sizeof(OT)) * static_cast<unsigned>(j * Bp + 8 * q);
-    const unsigned anoff = static_cast<unsigned>(sizeof(OT)) * static_cast<unsigned>(j * a.dp_in + 4 * q);
+    // fragments of A_0^T; of A_0' one half of a 32-deep fragment per step (see InputLayout)
+    constexpr int kHalf = sizeof(OT) == 4 ? 256 : 4;
+    const unsigned atoff = static_cast<unsigned>(sizeof(OT)) * static_cast<unsigned>((sizeof(OT) == 4 ? 4 : 8) * lane);
     auto at_byte = [](auto* base, unsigned off) {
         using T = std::remove_pointer_t<decltype(base)>;
         using C = std::conditional_t<std::is_const_v<T>, const char, char>;
@@ -153,10 +154,18 @@ __global__ __launch_bounds__(256, (FlBudget<OT, NT>::kWavesPerSimd)) void first_
         }
         const OT* ab = AT + static_cast<int64_t>(k0) * Bp;
 #pragma unroll
-        for (int st = 0; st < NS; ++st) x.af[st] = load8(at_byte(ab + 32 * st, atoff));
-        const OT* nb = AN + k0;
+        for (int st = 0; st < NS; ++st) {
+            if constexpr (sizeof(OT) == 4) {
+                const float4 lo = *reinterpret_cast<const float4*>(at_byte(ab + kFragElems * st, atoff));
+                const float4 hi = *reinterpret_cast<const float4*>(at_byte(ab + kFragElems * st + 256, atoff));
+                x.af[st] = Frag<OT>{{lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w}};
+            } else {
+                x.af[st] = load8(at_byte(ab + kFragElems * st, atoff));
+            }
+        }
+        const OT* nb = AN + (k0 / 32) * kFragElems + (k0 / 16 % 2) * kHalf;
 #pragma unroll
-        for (int mt = 0; mt < NT; ++mt) x.an[mt] = load4(at_byte(nb + static_cast<int64_t>(16 * mt) * a.dp_in, anoff));
+        for (int mt = 0; mt < NT; ++mt) x.an[mt] = load4(at_byte(nb + static_cast<int64_t>(16 * mt) * a.dp_in, atoff));
     };
 
     // first loads, then the staging of the slice (its own round trip overlaps with them)
@@ -371,15 +380,14 @@ __global__ __launch_bounds__(64 * kWideWaves) void first_layer_wide_kernel(First
     struct Set {
         float4 w[4], v[4];            // rows k0 + 4 q + r, columns c0 + 4 j ..
         Frag<OT> af[NS];              // A_0^T tile of this wavefront's 16 rows
-        Frag4<OT> an[kWideWaves];     // A_0' of this wavefront's samples, 4 entries for each tile of the round
+        Frag<OT> an[kWideWaves / 2];  // A_0' of this wavefront's samples, 4 entries for each of two tiles of the round
     };
     Set set[PD + 1];
 
     unsigned woff[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) woff[r] = 4u * static_cast<unsigned>((4 * q + r) * a.d_out + c0 + 4 * j);
-    const unsigned atoff = static_cast<unsigned>(sizeof(OT)) * static_cast<unsigned>(j * Bp + 8 * q);
-    const unsigned anoff = static_cast<unsigned>(sizeof(OT)) * static_cast<unsigned>(j * a.dp_in + 4 * q);
+    const unsigned atoff = static_cast<unsigned>(sizeof(OT)) * static_cast<unsigned>(8 * lane);   // in a fragment
     auto at_byte = [](auto* base, unsigned off) {
         using T = std::remove_pointer_t<decltype(base)>;
         using C = std::conditional_t<std::is_const_v<T>, const char, char>;
@@ -409,12 +417,12 @@ __global__ __launch_bounds__(64 * kWideWaves) void first_layer_wide_kernel(First
         const int ka = RAG && k0 > a.dp_in - 16 ? a.dp_in - 16 : k0;
         const OT* ab = AT + static_cast<int64_t>(ka) * Bp;
 #pragma unroll
-        for (int st = 0; st < NS; ++st) x.af[st] = load8(at_byte(ab + 32 * st, atoff));
-        const int kn = 16 * kWideWaves * rr;
+        for (int st = 0; st < NS; ++st) x.af[st] = load8(at_byte(ab + kFragElems * st, atoff));
+        const int sn = kWideWaves / 2 * rr;
 #pragma unroll
-        for (int u = 0; u < kWideWaves; ++u) {
-            const int kc = RAG && kn + 16 * u > a.dp_in - 16 ? a.dp_in - 16 : kn + 16 * u;
-            x.an[u] = load4(at_byte(AN + kc, anoff));
+        for (int u = 0; u < kWideWaves / 2; ++u) {
+            const int sc = RAG && sn + u >= a.dp_in / 32 ? a.dp_in / 32 - 1 : sn + u;
+            x.an[u] = load8(at_byte(AN + sc * kFragElems, atoff));
         }
     };
 
@@ -504,16 +512,17 @@ __global__ __launch_bounds__(64 * kWideWaves) void first_layer_wide_kernel(First
 #pragma unroll
         for (int u = 0; u < kWideWaves; ++u) {
             const bf16x8 l2 = wt[r & 1][u][0][lane], h2 = wt[r & 1][u][1][lane];
-            Frag4<OT> f0, f1, f2, f3;
+            Frag4<OT> an, f0, f1, f2, f3;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
+                an.v[e] = x.an[u / 2].v[4 * (u % 2) + e];
                 f0.v[e] = l2[e]; f1.v[e] = l2[4 + e];
                 f2.v[e] = h2[e]; f3.v[e] = h2[4 + e];
             }
-            facc[0] = mma4(x.an[u], f0, facc[0]);
-            facc[1] = mma4(x.an[u], f1, facc[1]);
-            facc[2] = mma4(x.an[u], f2, facc[2]);
-            facc[3] = mma4(x.an[u], f3, facc[3]);
+            facc[0] = mma4(an, f0, facc[0]);
+            facc[1] = mma4(an, f1, facc[1]);
+            facc[2] = mma4(an, f2, facc[2]);
+            facc[3] = mma4(an, f3, facc[3]);
         }
     };
 

@@ -205,8 +205,18 @@ bool net_shape_ok(const lc_handle* h);
 hipError_t launch_net(lc_handle* h, int slot0, int n_steps);  // as launch_resident, one period or less
 size_t resident_exchange_floats(const lc_handle* h);
 hipError_t probe_block_placement(lc_handle* h);   // synchronises the stream once
-inline bool inputs_in_fragments(const lc_handle* h) { return h->res_on && h->res_a1x && h->L == 2; }   // how the gather kernel leaves A_0
-inline bool fetches_its_inputs(const lc_handle* h) { return h->res_on && h->res_a1x && h->L == 1; }    // ... and where there is none
+// local steps run with the models on chip: the resident step kernels, or one compute unit per replica
+inline bool on_chip(const lc_handle* h) { return h->res_on && (h->res_a1x || h->net_ok); }
+inline bool fetches_its_inputs(const lc_handle* h) { return h->res_on && h->res_a1x && h->L == 1; }   // no gather launch
+// How the gather kernel leaves the mini-batches.  Plain rows: net_kernel, head_kernel, evaluation.  Fragment
+// order with lane l's 8 reduction indices 8 (l / 16) ..: both layouts for the resident two-layer kernel, and A_0^T
+// for the kernels that take a layer per launch; their A_0 has 4 (l / 16) .. + 3 of either half of the 32, so that
+// a half is the operand of a 16-deep product too (first_layer_kernel).
+enum InputLayout { kInputsPlain = 0, kInputsResident = 1, kInputsLayers = 2 };
+inline InputLayout input_layout(const lc_handle* h) {
+    if (on_chip(h)) return h->res_a1x && h->L == 2 ? kInputsResident : kInputsPlain;
+    return h->L == 1 && head_is_fused(h) ? kInputsPlain : kInputsLayers;
+}
 hipError_t launch_resident(lc_handle* h, int slot0, int n_steps, int period);  // the steps gathered into slots slot0 .. slot0+n_steps-1
 
 // timing helpers used by the launchers

@@ -53,7 +53,7 @@ struct GatherArgs {
     int sampler, m;         // training: lc_sampler and the number of workers
     int G;                  // groups per step; blockIdx.z = step * G + group
     int64_t a_slot, lab_slot;  // elements between the buffers of consecutive steps
-    int frags;              // both layouts in fragment order (tiles of 16 rows: samples in a_bm, features in a_fm)
+    int layout;             // InputLayout: plain rows, or fragment order (tiles of 16 samples in a_bm, 16 features in a_fm)
 };
 
 // One block copies a 32-sample x 64-feature tile through LDS and writes it in
@@ -109,17 +109,20 @@ __global__ __launch_bounds__(256) void gather_kernel(GatherArgs a) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) tile[r][seg + e] = x[e];
         OT* bm = static_cast<OT*>(a.a_bm) + step * a.a_slot + static_cast<int64_t>(g) * a.Bp * a.dp0;
-        if (!a.frags) store8(bm + static_cast<int64_t>(b0 + r) * a.dp0 + kk0, x);
+        if (a.layout == kInputsPlain) store8(bm + static_cast<int64_t>(b0 + r) * a.dp0 + kk0, x);
     }
     __syncthreads();
-    if (a.frags) {
+    if (a.layout != kInputsPlain) {
         // the 32 x 64 tile holds four fragments of either kind; every wavefront writes one of each
         const int lane = t & 63, w = t >> 6, j = lane & 15, q = lane >> 4;
         OT* bm = static_cast<OT*>(a.a_bm) + step * a.a_slot + static_cast<int64_t>(g) * a.Bp * a.dp0;
         OT* fm = static_cast<OT*>(a.a_fm) + step * a.a_slot + static_cast<int64_t>(g) * a.Bp * a.dp0;
         float y[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) y[e] = tile[16 * (w >> 1) + j][32 * (w & 1) + 8 * q + e];
+        for (int e = 0; e < 8; ++e) {
+            const int k = a.layout == kInputsLayers ? 4 * q + e % 4 + 16 * (e / 4) : 8 * q + e;
+            y[e] = tile[16 * (w >> 1) + j][32 * (w & 1) + k];
+        }
         store_frag(bm + static_cast<int64_t>((b0 / 16 + (w >> 1)) * (a.dp0 / 32) + k0 / 32 + (w & 1)) * kFragElems, lane, y);
 #pragma unroll
         for (int e = 0; e < 8; ++e) y[e] = tile[8 * q + e][16 * w + j];
@@ -187,8 +190,12 @@ struct FwdArgs {
 // contiguous bytes, and component t of the 8 vectors (k = 8q .. 8q+7) is the operand of tile t:
 // the same trick as for the weight columns.  Tile VW h + t then holds batch rows
 // 16 VW h + VW i + t (i = 0..15) instead of 16 mt + i; only the epilogue needs to know.
-template <typename OT, int MT, int NW, int PF, int WM, bool AFM>
+//
+// FRAGS instances (layer 1 of a training step) read the activations in fragment order, see InputLayout.
+constexpr int kActRows = 0, kActFeatureMajor = 1, kActFragments = 2;
+template <typename OT, int MT, int NW, int PF, int WM, int AM>
 __global__ __launch_bounds__(NW * 64) void forward_kernel(FwdArgs a) {
+    constexpr bool AFM = AM == kActFeatureMajor, FRAGS = AM == kActFragments;
     constexpr int VW = 16 / sizeof(OT);
     static_assert(!AFM || MT % VW == 0, "AFM needs whole groups of VW tiles");
     // batch row (within the block) of accumulator row i of tile mt, and the inverse as the
@@ -273,9 +280,25 @@ __global__ __launch_bounds__(NW * 64) void forward_kernel(FwdArgs a) {
     // Loads retire in issue order, so the activation fragments of step s are requested before the
     // weight rows of the later steps: waiting for them then leaves those rows in flight.
     const OT* AF = static_cast<const OT*>(a.a_in_fm) + static_cast<int64_t>(g) * a.dp_in * a.Bp;
+    // FRAGS: this lane's reduction indices 8 q .. 8 q + 7 lie in half q / 2 of a fragment, with the lanes
+    // 32 (q % 2) + j and 16 further on (see InputLayout)
+    constexpr int kLane = sizeof(OT) == 4 ? 4 : 8;
+    const int a_lane = kLane * (32 * (q & 1) + j) + (q >> 1) * (sizeof(OT) == 4 ? 256 : 4);
     auto load_a_step = [&](int s, Frag<OT> (&f)[MT]) {
-        const int k0 = (s < n_steps ? s : n_steps - 1) * 32 + 8 * q;   // past the end: any valid step, never used
-        if constexpr (!AFM) {
+        const int sc = s < n_steps ? s : n_steps - 1;   // past the end: any valid step, never used
+        const int k0 = sc * 32 + 8 * q;
+        if constexpr (FRAGS) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                const OT* p = A + static_cast<int64_t>(16 * mt) * a.dp_in + sc * kFragElems + a_lane;
+                const Frag4<OT> lo = load4(p), hi = load4(p + 16 * kLane);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    f[mt].v[e] = lo.v[e];
+                    f[mt].v[4 + e] = hi.v[e];
+                }
+            }
+        } else if constexpr (!AFM) {
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) f[mt] = load8(A + static_cast<int64_t>(16 * mt + j) * a.dp_in + k0);
         } else if constexpr (sizeof(OT) == 4) {
@@ -726,7 +749,9 @@ __global__ __launch_bounds__(256, NT == 8 && !NDA && !DAO ? 1 : 2) void backward
     Frag<OT> af[NS];
     if constexpr (!DAO) {
 #pragma unroll
-        for (int s = 0; s < NS; ++s) af[s] = load8(AT + static_cast<int64_t>(k0 + j) * Bp + 32 * s + 8 * q);
+        for (int s = 0; s < NS; ++s)   // (the first layer's inputs are in fragments)
+            af[s] = NDA ? load_frag(AT + static_cast<int64_t>(k0) * Bp + s * kFragElems, lane)
+                        : load8(AT + static_cast<int64_t>(k0 + j) * Bp + 32 * s + 8 * q);
     }
 
     // ReLU gates of this lane's dA entries, fetched now (one bit each) instead of after the walk
@@ -1238,26 +1263,29 @@ int weight_mode(bool vec, bool stream, int d_out) {
 // The accumulators of a full 128-row batch leave no registers for prefetching at two
 // wavefronts per SIMD, so that case runs four wavefronts per block with a deeper queue.
 template <typename OT, int WM>
-hipError_t launch_fwd_cfg(const FwdArgs& a, int mt, bool wide, bool afm, unsigned grid, hipStream_t s) {
-#define LC_FWD(MT_, NW_, PF_, AFM_) \
-    hipLaunchKernelGGL((forward_kernel<OT, MT_, NW_, PF_, WM, AFM_>), dim3(grid), dim3(NW_ * 64), 0, s, a)
+hipError_t launch_fwd_cfg(const FwdArgs& a, int mt, bool wide, int am, unsigned grid, hipStream_t s) {
+#define LC_FWD(MT_, NW_, PF_, AM_) \
+    hipLaunchKernelGGL((forward_kernel<OT, MT_, NW_, PF_, WM, AM_>), dim3(grid), dim3(NW_ * 64), 0, s, a)
+#define LC_FWD_BOTH(MT_, NW_, PF_) \
+    if (am == kActFragments) LC_FWD(MT_, NW_, PF_, kActFragments); else LC_FWD(MT_, NW_, PF_, kActRows)
     switch (mt) {
-        case 1: if (wide) LC_FWD(1, 8, 3, false); else LC_FWD(1, 4, 3, false); break;
-        case 2: if (wide) LC_FWD(2, 8, 3, false); else LC_FWD(2, 4, 1, false); break;   // many blocks: occupancy 3 beats a deeper queue
-        case 4: if (wide) LC_FWD(4, 8, 1, false); else LC_FWD(4, 4, 3, false); break;
-        case 8: if (afm) LC_FWD(8, 4, 1, true); else LC_FWD(8, 4, 1, false); break;
+        case 1: if (wide) { LC_FWD_BOTH(1, 8, 3); } else { LC_FWD_BOTH(1, 4, 3); } break;
+        case 2: if (wide) { LC_FWD_BOTH(2, 8, 3); } else { LC_FWD_BOTH(2, 4, 1); } break;   // many blocks: occupancy 3 beats a deeper queue
+        case 4: if (wide) { LC_FWD_BOTH(4, 8, 1); } else { LC_FWD_BOTH(4, 4, 3); } break;
+        case 8: if (am == kActFeatureMajor) LC_FWD(8, 4, 1, kActFeatureMajor); else { LC_FWD_BOTH(8, 4, 1); } break;
         default: return hipErrorInvalidValue;
     }
+#undef LC_FWD_BOTH
 #undef LC_FWD
     return hipGetLastError();
 }
 template <typename OT>
-hipError_t launch_fwd_wm(const FwdArgs& a, int mt, bool wide, bool afm, unsigned grid, hipStream_t s) {
+hipError_t launch_fwd_wm(const FwdArgs& a, int mt, bool wide, int am, unsigned grid, hipStream_t s) {
     switch (weight_mode(a.vec != 0, a.stream != 0, a.d_out)) {
-        case kWVector: return launch_fwd_cfg<OT, kWVector>(a, mt, wide, afm, grid, s);
-        case kWVectorStream: return launch_fwd_cfg<OT, kWVectorStream>(a, mt, wide, afm, grid, s);
-        case kWRagged: return launch_fwd_cfg<OT, kWRagged>(a, mt, wide, afm, grid, s);
-        default: return launch_fwd_cfg<OT, kWGeneric>(a, mt, wide, afm, grid, s);
+        case kWVector: return launch_fwd_cfg<OT, kWVector>(a, mt, wide, am, grid, s);
+        case kWVectorStream: return launch_fwd_cfg<OT, kWVectorStream>(a, mt, wide, am, grid, s);
+        case kWRagged: return launch_fwd_cfg<OT, kWRagged>(a, mt, wide, am, grid, s);
+        default: return launch_fwd_cfg<OT, kWGeneric>(a, mt, wide, am, grid, s);
     }
 }
 
@@ -1345,7 +1373,7 @@ hipError_t launch_gather(lc_handle* h, bool eval, int64_t k_or_base, int n_steps
     a.G = S.G;
     a.a_slot = static_cast<int64_t>(a0_slot_elems(h, S));
     a.lab_slot = static_cast<int64_t>(S.G) * S.Bp;
-    a.frags = !eval && inputs_in_fragments(h) ? 1 : 0;
+    a.layout = eval ? kInputsPlain : input_layout(h);
     const dim3 grid(a.dp0 / 64, a.Bp / 32, S.G * n_steps);
     if (eval) {
         if (bf16) hipLaunchKernelGGL((gather_kernel<bf16_t, float>), grid, dim3(256), 0, h->stream, a);
@@ -1503,11 +1531,12 @@ hipError_t launch_forward(lc_handle* h, bool eval, int l, int loss_offset) {
     if (!eval) timing_start(h, kTimeFwd);
     hipError_t e;
     // whole padded batch in one block and a feature-major copy of the input at hand
-    const void* in_fm = eval ? nullptr : (l == 1 ? a0_ptr(h, S, S.a_fm[0], false) : S.a_fm[l - 1]);
+    const void* in_fm = eval || l == 1 ? nullptr : S.a_fm[l - 1];
     const bool afm = in_fm != nullptr && !grouped && a.m_split == 1 && mt * 16 == S.Bp && mt == 8;
+    const int am = !eval && l == 1 ? kActFragments : afm ? kActFeatureMajor : kActRows;   // (the mini-batch comes in fragments)
     a.a_in_fm = in_fm;
-    if (bf16) e = launch_fwd_wm<bf16_t>(a, mt, wide, afm, grid, h->stream);
-    else e = launch_fwd_wm<float>(a, mt, wide, afm, grid, h->stream);
+    if (bf16) e = launch_fwd_wm<bf16_t>(a, mt, wide, am, grid, h->stream);
+    else e = launch_fwd_wm<float>(a, mt, wide, am, grid, h->stream);
     if (!eval) timing_stop(h, kTimeFwd);
     return e;
 }

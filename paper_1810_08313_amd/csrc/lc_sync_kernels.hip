@@ -41,7 +41,8 @@ struct SyncArgs {
     int64_t w_off, b_off;
     int d_in, d_out, dp_in, dp_out;
     int B, G;
-    const void* a_fm;     // A_0^T of this iteration [G][dp_in][Bp]
+    const void* a_fm;     // A_{l-1}^T of this iteration [G][dp_in][Bp]; layer 1: in fragments
+    int frags;
     const void* dz_fm;    // dZ_1^T of this iteration [G][dp_out][Bp]
     float lr, beta, wd;
     int n_row_blocks, n_cc;
@@ -90,7 +91,9 @@ __global__ __launch_bounds__(256) void sync_first_layer_kernel(SyncArgs a) {
     auto load_rows = [&](int g) {   // this lane's A_0^T operands of replica g
         const OT* AT = static_cast<const OT*>(a.a_fm) + static_cast<int64_t>(g) * a.dp_in * Bp;
 #pragma unroll
-        for (int s = 0; s < NS; ++s) af[s] = load8(AT + static_cast<int64_t>(k0 + j) * Bp + 32 * s + 8 * q);
+        for (int s = 0; s < NS; ++s)
+            af[s] = a.frags ? load_frag(AT + static_cast<int64_t>(k0) * Bp + s * kFragElems, lane)
+                            : load8(AT + static_cast<int64_t>(k0 + j) * Bp + 32 * s + 8 * q);
     };
     auto issue_loads = [&](int g, float4 (&vv)[4], float4 (&ww)[4]) {
         if constexpr (OWN) {
@@ -270,6 +273,7 @@ hipError_t launch_sync_layer(lc_handle* h, int l) {
     a.dp_out = g.dp_out;
     a.B = S.B;
     a.G = S.G;
+    a.frags = l == 1 ? 1 : 0;
     if (l == 1) {
         const size_t slot_bytes = static_cast<size_t>(S.G) * S.Bp * g.dp_in * (bf16 ? 2 : 4);
         a.a_fm = static_cast<const char*>(S.a_fm[0]) + static_cast<size_t>(S.cur_slot) * slot_bytes;
