@@ -8,7 +8,8 @@
 // and dependent memory round trips; here a step is 2 L + 1 phases between workgroup barriers, each a
 // chain of LDS reads and matrix instructions (in the case below the compute unit's matrix cores are
 // busy a quarter of the time, LDS bank conflicts take a tenth).
-// (130-70-33-7, 3 workers, batch 48, fp32, two periods of 3 steps: 346 -> 136 us, 17 us a step.)
+// (130-70-33-7, 3 workers, batch 48, fp32, two periods of 3 steps: 346 -> 130 us, 16 us a step; with a memory
+// round trip per tile at the start, the layers' descriptions read in every tile and the loss in every step 136.)
 //
 // One step, 16 wavefronts sharing out 16 x 16 tiles of every product:
 //   A_l = ReLU(A_{l-1} W_l + b_l) for l = 1 .. L (the last one without ReLU)
@@ -34,6 +35,7 @@ constexpr int kNetWaves = 16, kNetThreads = 64 * kNetWaves;
 constexpr int kNetTiles = 8;            // 16 x 16 weight tiles per wavefront (4 momentum registers each)
 constexpr int kNetFloats = 40704;       // LDS of a workgroup (159 KB of 160)
 constexpr int kNetMaxClasses = 64;
+constexpr int kTileBias = 1 << 14;      // in the tile table: first tile of its columns
 constexpr int kNetStage = 4;            // pieces of 4 values of A_0 per thread, where A_0 is kept in LDS
 
 struct NetLayer {
@@ -72,6 +74,9 @@ __device__ __forceinline__ float net_round(float x, float) { return x; }
 template <typename OT, bool IN_LDS>
 __global__ __launch_bounds__(kNetThreads) void net_kernel(NetArgs a) {
     __shared__ __attribute__((aligned(16))) float s[kNetFloats];
+    // of every weight tile: (in s: layer, column tile, kTileBias, rows and columns that exist); LDS offsets of
+    // its operands of dZ and A (of A_0 in memory: its first feature); of its weights, and what lies between columns
+    __shared__ int tile_za[kNetWaves * kNetTiles], tile_w[kNetWaves * kNetTiles];
     const int g = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -81,34 +86,55 @@ __global__ __launch_bounds__(kNetThreads) void net_kernel(NetArgs a) {
     const float* Xrg = a.Xr + g * a.xr_stride;
     const int BS = a.bs, nbt = a.Bq / 16;
 
-    // ---- the tile table: layer, row tile and column tile of every weight tile
+    // ---- the tile table: what the steps need to know of a weight tile, without the layer's description
     int* tiles = reinterpret_cast<int*>(s + a.tiles);
     for (int l = 0; l < a.L; ++l) {
-        const int nt = a.layer[l].np / 16, n = nt * (a.layer[l].kp / 16);
-        for (int t = tid; t < n; t += kNetThreads) tiles[a.layer[l].tile0 + t] = l << 16 | (t / nt) << 8 | t % nt;
+        const NetLayer& y = a.layer[l];
+        const int nt = y.np / 16, n = nt * (y.kp / 16), in_at = l > 0 ? a.layer[l - 1].act : a.a0;
+        for (int i = tid; i < n; i += kNetThreads) {
+            const int kt = i / nt, ct = i % nt, t = y.tile0 + i, rows = y.d_in - 16 * kt, cols = y.d_out - 16 * ct;
+            tiles[t] = l << 16 | ct << 24 | (kt == 0 ? kTileBias : 0) | (rows < 16 ? rows : 16) << 8 | (cols < 16 ? cols : 16);
+            tile_za[t] = (y.dz + 16 * ct * BS) | (!IN_LDS && l == 0 ? 16 * kt : in_at + 16 * kt * BS) << 16;
+            tile_w[t] = (y.w + 16 * ct * y.ws + 16 * kt) | y.ws << 16;
+        }
     }
     __syncthreads();
-    // ---- load the state; entries beyond the layer's sizes are zero and stay zero under the update
+    // ---- load the state; entries beyond the layer's sizes are zero and stay zero under the update.
+    // All tiles' loads first: one memory round trip instead of one per tile (12400 -> 5000 clocks at four).
     f32x4 v[kNetTiles];
+    {
+        f32x4 w[kNetTiles];
 #pragma unroll
-    for (int i = 0; i < kNetTiles; ++i) {
-        const int t = wave + kNetWaves * i;
-        v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (t < a.n_tiles) {
-            const int e = __builtin_amdgcn_readfirstlane(tiles[t]);
-            const NetLayer& y = a.layer[e >> 16];
-            const int k0 = 16 * (e >> 8 & 255) + 4 * q, n = 16 * (e & 255) + j;
-            f32x4 w = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < kNetTiles; ++i) {
+            const int t = wave + kNetWaves * i;
+            v[i] = w[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (t < a.n_tiles) {
+                const int e = __builtin_amdgcn_readfirstlane(tiles[t]), o = __builtin_amdgcn_readfirstlane(tile_w[t]);
+                const NetLayer& y = a.layer[e >> 16 & 15];
+                const int n = 16 * (e >> 24 & 63) + j, k0 = ((o & 0xffff) - y.w) % y.ws + 4 * q;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                // (entries that do not exist read the first one and are zeroed: no branch around the loads)
-                const bool in = k0 + r < y.d_in && n < y.d_out;
-                const int64_t at = y.w_off + (in ? static_cast<int64_t>(k0 + r) * y.d_out + n : 0);
-                const float wx = Xrg[at], vx = Vg[at];
-                w[r] = in ? wx : 0.f;
-                v[i][r] = in ? vx : 0.f;
+                for (int r = 0; r < 4; ++r) {
+                    // (entries that do not exist read the first one and are zeroed: no branch around the loads)
+                    const bool in = 4 * q + r < (e >> 8 & 31) && j < (e & 31);
+                    const int64_t at = y.w_off + (in ? static_cast<int64_t>(k0 + r) * y.d_out + n : 0);
+                    w[i][r] = Xrg[at];
+                    v[i][r] = Vg[at];
+                }
             }
-            *reinterpret_cast<f32x4*>(s + y.w + n * y.ws + k0) = w;
+        }
+#pragma unroll
+        for (int i = 0; i < kNetTiles; ++i) {
+            const int t = wave + kNetWaves * i;
+            if (t < a.n_tiles) {
+                const int e = __builtin_amdgcn_readfirstlane(tiles[t]), o = __builtin_amdgcn_readfirstlane(tile_w[t]);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const bool in = 4 * q + r < (e >> 8 & 31) && j < (e & 31);
+                    w[i][r] = in ? w[i][r] : 0.f;
+                    v[i][r] = in ? v[i][r] : 0.f;
+                }
+                *reinterpret_cast<f32x4*>(s + (o & 0xffff) + j * (o >> 16) + 4 * q) = w[i];
+            }
         }
     }
     for (int l = 0; l < a.L; ++l) {
@@ -119,31 +145,32 @@ __global__ __launch_bounds__(kNetThreads) void net_kernel(NetArgs a) {
             s[y.bias + y.np + n] = in ? Vg[y.b_off + n] : 0.f;
         }
     }
-    __syncthreads();
 
     // A_0 in LDS (where it fits): thread t moves pieces t, t + 1024, ... of 4 samples of one feature
-    const int n_stage = a.layer[0].kp * (a.Bq / 4);
-    auto stage = [&](const OT* from) {
-        int t_o = threadIdx.x;
-        asm volatile("" : "+v"(t_o));
-        Frag4<OT> f[kNetStage];
+    const int n_stage = a.layer[0].kp * (a.Bq / 4), per_k = a.Bq / 4;
+    const unsigned inv_k = ((1u << 20) + per_k - 1) / per_k;   // e / per_k = e inv_k >> 20 for e < 4096, per_k <= 32
+    auto request = [&](const OT* from, int t, Frag4<OT> (&f)[kNetStage]) {
 #pragma unroll
         for (int u = 0; u < kNetStage; ++u) {
-            const int e = t_o + kNetThreads * u, k = e / (a.Bq / 4), b4 = e % (a.Bq / 4) * 4;
-            f[u] = load4(from + (e < n_stage ? static_cast<int64_t>(k) * a.Bp + b4 : 0));
+            const int e = t + kNetThreads * u, k = static_cast<int>(static_cast<unsigned>(e) * inv_k >> 20), b4 = (e - k * per_k) * 4;
+            if (kNetThreads * u < n_stage) f[u] = load4(from + (e < n_stage ? k * a.Bp + b4 : 0));
         }
+    };
+    auto place = [&](int t, const Frag4<OT> (&f)[kNetStage]) {
 #pragma unroll
         for (int u = 0; u < kNetStage; ++u) {
-            const int e = t_o + kNetThreads * u, k = e / (a.Bq / 4), b4 = e % (a.Bq / 4) * 4;
+            const int e = t + kNetThreads * u, k = static_cast<int>(static_cast<unsigned>(e) * inv_k >> 20), b4 = (e - k * per_k) * 4;
             if (e < n_stage)
                 *reinterpret_cast<float4*>(s + a.a0 + k * BS + b4) =
                     make_float4(to_f32(f[u].v[0]), to_f32(f[u].v[1]), to_f32(f[u].v[2]), to_f32(f[u].v[3]));
         }
     };
+    Frag4<OT> next_in[kNetStage];
     if constexpr (IN_LDS) {
-        stage(static_cast<const OT*>(a.a0_fm) + a.slot0 * a.a0_slot + static_cast<int64_t>(g) * a.dp0 * a.Bp);
-        __syncthreads();
+        request(static_cast<const OT*>(a.a0_fm) + a.slot0 * a.a0_slot + static_cast<int64_t>(g) * a.dp0 * a.Bp, tid, next_in);
+        place(tid, next_in);
     }
+    __syncthreads();
 
     for (int step = 0; step < a.n_steps; ++step) {
         // What a step derives from the thread's id and from the layer table is derived afresh from
@@ -154,11 +181,13 @@ __global__ __launch_bounds__(kNetThreads) void net_kernel(NetArgs a) {
         const NetLayer* const layer = a.layer + zero;
         const int tid = tid_o, lane = tid & 63, j = lane & 15, q = lane >> 4;
         const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-        const float beta = step == 0 ? a.beta_first : a.beta;
+        const float beta = step == 0 ? a.beta_first : a.beta, lr = a.lr, wd = a.wd;
         const int slot = a.slot0 + step;
         const OT* A0 = static_cast<const OT*>(a.a0_bm) + slot * a.a0_slot + static_cast<int64_t>(g) * a.Bp * a.dp0;
         const OT* A0T = static_cast<const OT*>(a.a0_fm) + slot * a.a0_slot + static_cast<int64_t>(g) * a.dp0 * a.Bp;
         const int32_t* lab = a.labels + (static_cast<int64_t>(slot) * a.G + g) * a.Bp;
+
+        const int yl = (tid >> 3) < a.B ? lab[tid >> 3] : -1;   // (asked for here: the softmax does not wait for it)
 
         // ---- forward
         for (int l = 0; l < a.L; ++l) {
@@ -227,12 +256,13 @@ __global__ __launch_bounds__(kNetThreads) void net_kernel(NetArgs a) {
             __syncthreads();
         }
 
-        // ---- the next step's inputs into the L2 (the gather kernel left them in other XCDs' memory, two
-        //      microseconds away): one 4-byte load per cache line, behind the loads of the forward
-        //      pass, since loads retire in order
+        // ---- the next step's inputs (the gather kernel left them in other XCDs' memory, two microseconds
+        //      away): into registers where A_0 is kept in LDS, else into the L2, one 4-byte load per cache
+        //      line.  Behind the loads of the forward pass, since loads retire in order.
         const bool more = step + 1 < a.n_steps;
         float touched[4] = {0.f, 0.f, 0.f, 0.f};
-        if (more) {
+        if (IN_LDS && more) request(A0T + a.a0_slot, tid, next_in);
+        if (!IN_LDS && more) {
             const int n_lines = a.Bp * a.dp0 * static_cast<int>(sizeof(OT)) / 128;
             const float* nt = reinterpret_cast<const float*>(A0T + a.a0_slot);
             const float* nb = reinterpret_cast<const float*>(A0 + a.a0_slot);
@@ -241,7 +271,7 @@ __global__ __launch_bounds__(kNetThreads) void net_kernel(NetArgs a) {
                 const int e = tid + kNetThreads * u;
                 if (e < n_lines) {
                     touched[u] = nt[32 * e];
-                    if (!IN_LDS) touched[2 + u] = nb[32 * e];
+                    touched[2 + u] = nb[32 * e];
                 }
             }
         }
@@ -252,7 +282,6 @@ __global__ __launch_bounds__(kNetThreads) void net_kernel(NetArgs a) {
             const int b = tid >> 3, u8 = tid & 7;
             if (b < a.Bq) {   // (whole groups of 8 lanes)
                 float* z = s + y.dz + b;
-                const int yl = b < a.B ? lab[b] : -1;
                 float zc[kNetMaxClasses / 8], zmax = -INFINITY;
 #pragma unroll
                 for (int u = 0; u < kNetMaxClasses / 8; ++u) {
@@ -289,7 +318,7 @@ __global__ __launch_bounds__(kNetThreads) void net_kernel(NetArgs a) {
                     if (c < y.np)
                         z[c * BS] = (c < y.d_out && yl >= 0) ? net_round(xent_delta(zc[u], c == yl, s_other, inv) * invB, OT()) : 0.f;
                 }
-                if (u8 == 0) s[a.lred + b] = yl >= 0 ? xent_loss(s_other, e_y, z_y) : 0.f;
+                if (!more && u8 == 0) s[a.lred + b] = yl >= 0 ? xent_loss(s_other, e_y, z_y) : 0.f;
             }
         }
         __syncthreads();
@@ -326,15 +355,14 @@ __global__ __launch_bounds__(kNetThreads) void net_kernel(NetArgs a) {
             const int t = wave + kNetWaves * i;
             if (t < a.n_tiles) {
                 const int e = __builtin_amdgcn_readfirstlane(tiles[t]);
-                const int l = e >> 16;
-                const NetLayer& y = layer[l];
-                const int kt = e >> 8 & 255, n = 16 * (e & 255) + j;
-                const float* zt = s + y.dz + n * BS + 4 * q;
-                const float* at = s + (l == 0 ? a.a0 : layer[l - 1].act) + (16 * kt + j) * BS + 4 * q;
+                const unsigned za = __builtin_amdgcn_readfirstlane(tile_za[t]);
+                const int ow = __builtin_amdgcn_readfirstlane(tile_w[t]);
+                const float* zt = s + (za & 0xffffu) + j * BS + 4 * q;
+                const float* at = s + (za >> 16) + j * BS + 4 * q;
                 f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
                 float db = 0.f;   // column sum of dZ_l over this lane's samples
-                if (!IN_LDS && l == 0) {
-                    const OT* ar = A0T + static_cast<int64_t>(16 * kt + j) * a.Bp + 4 * q;
+                if (!IN_LDS && (e >> 16 & 15) == 0) {
+                    const OT* ar = A0T + (static_cast<int>(za >> 16) + j) * a.Bp + 4 * q;
                     Frag4<OT> af[8];
 #pragma unroll
                     for (int st = 0; st < 8; ++st) af[st] = load4(ar + 16 * (st < nbt ? st : 0));
@@ -359,29 +387,30 @@ __global__ __launch_bounds__(kNetThreads) void net_kernel(NetArgs a) {
                         acc = mma4(af, bf, acc);
                     }
                 }
-                if (kt == 0) {   // the bias of these columns, by the wavefront of their first tile
+                if (e & kTileBias) {   // the bias of these columns, by the wavefront of their first tile
+                    const NetLayer& y = layer[e >> 16 & 15];
                     db += __shfl_xor(db, 16, 64);
                     db += __shfl_xor(db, 32, 64);
-                    if (q == 0 && n < y.d_out) {
-                        const float x = s[y.bias + n];
-                        const float vb = momentum_update(beta, s[y.bias + y.np + n], db, a.wd, x);
-                        s[y.bias + y.np + n] = vb;
-                        s[y.bias + n] = weight_update(x, a.lr, vb);
+                    if (q == 0 && j < (e & 31)) {
+                        float* bp = s + y.bias + 16 * (e >> 24 & 63) + j;
+                        const float vb = momentum_update(beta, bp[y.np], db, wd, *bp);
+                        bp[y.np] = vb;
+                        *bp = weight_update(*bp, lr, vb);
                     }
                 }
-                f32x4* wp = reinterpret_cast<f32x4*>(s + y.w + n * y.ws + 16 * kt + 4 * q);
+                f32x4* wp = reinterpret_cast<f32x4*>(s + (ow & 0xffff) + j * (ow >> 16) + 4 * q);
                 f32x4 w = *wp;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     // (an entry that does not exist must stay zero also where its zero operand meets an infinity)
-                    if (16 * kt + 4 * q + r >= y.d_in || n >= y.d_out) acc[r] = 0.f;
-                    v[i][r] = momentum_update(beta, v[i][r], acc[r], a.wd, w[r]);
-                    w[r] = weight_update(w[r], a.lr, v[i][r]);
+                    const float gw = 4 * q + r < (e >> 8 & 31) && j < (e & 31) ? acc[r] : 0.f;
+                    v[i][r] = momentum_update(beta, v[i][r], gw, wd, w[r]);
+                    w[r] = weight_update(w[r], lr, v[i][r]);
                 }
                 *wp = w;
             }
         }
-        if (wave == 0) {
+        if (!more && wave == 0) {   // (the losses that are kept are those of the last step)
             float sum = (lane < a.Bq ? s[a.lred + lane] : 0.f) + (lane + 64 < a.Bq ? s[a.lred + lane + 64] : 0.f);
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
@@ -391,7 +420,7 @@ __global__ __launch_bounds__(kNetThreads) void net_kernel(NetArgs a) {
 
         asm volatile("" : : "v"(touched[0]), "v"(touched[1]), "v"(touched[2]), "v"(touched[3]));
         if (IN_LDS && more) {
-            stage(A0T + a.a0_slot);
+            place(tid, next_in);
             __syncthreads();
         }
     }
@@ -400,13 +429,13 @@ __global__ __launch_bounds__(kNetThreads) void net_kernel(NetArgs a) {
     for (int i = 0; i < kNetTiles; ++i) {
         const int t = wave + kNetWaves * i;
         if (t < a.n_tiles) {
-            const int e = __builtin_amdgcn_readfirstlane(tiles[t]);
-            const NetLayer& y = a.layer[e >> 16];
-            const int k0 = 16 * (e >> 8 & 255) + 4 * q, n = 16 * (e & 255) + j;
-            const f32x4 w = *reinterpret_cast<const f32x4*>(s + y.w + n * y.ws + k0);
+            const int e = __builtin_amdgcn_readfirstlane(tiles[t]), o = __builtin_amdgcn_readfirstlane(tile_w[t]);
+            const NetLayer& y = a.layer[e >> 16 & 15];
+            const int n = 16 * (e >> 24 & 63) + j, k0 = ((o & 0xffff) - y.w) % y.ws + 4 * q;
+            const f32x4 w = *reinterpret_cast<const f32x4*>(s + (o & 0xffff) + j * y.ws + 4 * q);
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                if (k0 + r < y.d_in && n < y.d_out) {
+                if (4 * q + r < (e >> 8 & 31) && j < (e & 31)) {
                     const int64_t at = y.w_off + static_cast<int64_t>(k0 + r) * y.d_out + n;
                     Xg[at] = w[r];
                     Vg[at] = v[i][r];
