@@ -228,12 +228,6 @@ __global__ __launch_bounds__(NW * 64) void forward_kernel(FwdArgs a) {
         const int c = c0 + threadIdx.x;
         bias_s[threadIdx.x] = c < a.d_out ? a.X[g * a.x_stride + a.b_off + c] : 0.f;
     }
-    int my_label = -1;
-    if (a.fuse_softmax && threadIdx.x < MT * 16) {
-        const int b = row0 + batch_row(threadIdx.x / 16, threadIdx.x % 16);
-        if (b < a.B) my_label = a.labels[static_cast<int64_t>(g) * a.Bp + b];
-    }
-
     f32x4 acc[MT][4];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
@@ -446,39 +440,59 @@ __global__ __launch_bounds__(NW * 64) void forward_kernel(FwdArgs a) {
         }
         if (a.fuse_softmax) {
             // all classes of a sample sit in this block's tile: loss and dZ_L here, for the
-            // block's own samples; the loss is left as one partial sum per block
+            // block's own samples; the loss is left as one partial sum per block.  16 lanes per sample, class
+            // u + 16 i in lane u; the sum over the classes is taken in class order by each of them.  (One
+            // thread per sample, walking the classes twice: 1024-10, 100 samples, fp32, 14.4 us the launch.)
             __shared__ float lred[128];
             __syncthreads();
-            const int t = threadIdx.x;
-            float nll = 0.f;
-            if (t < 128) {
-                const int b = row0 + batch_row(t / 16, t % 16);
-                if (t < MT * 16 && b < a.B && my_label >= 0) {
-                    const int y = my_label;
-                    const float* z = red[t];
-                    float zmax = z[0];
-                    for (int c = 1; c < a.d_out; ++c) zmax = fmaxf(zmax, z[c]);
-                    float s_other = 0.f;
-                    for (int c = 0; c < a.d_out; ++c) s_other += c == y ? 0.f : expf(z[c] - zmax);
-                    const float e_y = expf(z[y] - zmax);
-                    nll = xent_loss(s_other, e_y, z[y] - zmax);
-                    if (a.dz_bm) {
-                        OT* dbm = static_cast<OT*>(a.dz_bm) + (static_cast<int64_t>(g) * a.Bp + b) * a.dp_out;
-                        OT* dfm = static_cast<OT*>(a.dz_fm) + static_cast<int64_t>(g) * a.dp_out * a.Bp + b;
-                        const float inv = 1.f / (s_other + e_y), invB = 1.f / static_cast<float>(a.B);
-                        for (int c = 0; c < a.d_out; ++c) {
-                            const OT d = static_cast<OT>(xent_delta(expf(z[c] - zmax), c == y, s_other, inv) * invB);
+            const int t = threadIdx.x, u = t & 15;
+            if (t < 128) lred[t] = 0.f;
+            __syncthreads();
+            for (int bl = t >> 4; bl < MT * 16; bl += NW * 4) {   // (whole 16-lane rows; NW * 4 divides or exceeds MT * 16)
+                const int b = row0 + batch_row(bl / 16, bl % 16);
+                const int y = b < a.B ? a.labels[static_cast<int64_t>(g) * a.Bp + b] : -1;
+                if (y < 0) continue;
+                float (&z)[kColChunk + 4] = red[bl];
+                float zc[4], zmax = -INFINITY;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    zc[i] = u + 16 * i < a.d_out ? z[u + 16 * i] : -INFINITY;
+                    zmax = fmaxf(zmax, zc[i]);
+                }
+                zmax = max_over_row(zmax);
+                const float zy = z[y] - zmax;
+                wave_sync_lds();   // (z[y] is read before it is overwritten)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    zc[i] = expf(zc[i] - zmax);
+                    if (u + 16 * i < a.d_out) z[u + 16 * i] = zc[i];
+                }
+                wave_sync_lds();
+                float s_other = 0.f;
+                for (int c = 0; c < a.d_out; ++c) s_other += c == y ? 0.f : z[c];
+                const float e_y = z[y];
+                if (u == 0) lred[bl] = xent_loss(s_other, e_y, zy);
+                if (a.dz_bm) {
+                    OT* dbm = static_cast<OT*>(a.dz_bm) + (static_cast<int64_t>(g) * a.Bp + b) * a.dp_out;
+                    OT* dfm = static_cast<OT*>(a.dz_fm) + static_cast<int64_t>(g) * a.dp_out * a.Bp + b;
+                    const float inv = 1.f / (s_other + e_y), invB = 1.f / static_cast<float>(a.B);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int c = u + 16 * i;
+                        if (c < a.d_out) {
+                            const OT d = static_cast<OT>(xent_delta(zc[i], c == y, s_other, inv) * invB);
                             dbm[c] = d;
                             dfm[static_cast<int64_t>(c) * a.Bp] = d;
                         }
                     }
                 }
-                lred[t] = nll;
             }
             __syncthreads();
-            for (int w = 64; w > 0; w >>= 1) {
-                if (t < w) lred[t] += lred[t + w];
-                __syncthreads();
+            if (t < 64) {
+                float l = lred[t] + lred[t + 64];
+#pragma unroll
+                for (int w = 32; w > 0; w >>= 1) l += __shfl_xor(l, w, 64);
+                lred[t] = l;
             }
             if (t == 0)
                 a.loss[static_cast<int64_t>(g) * kLossParts + rem % a.m_split] =
@@ -1122,37 +1136,53 @@ __global__ __launch_bounds__(512) void head_kernel(HeadArgs a) {
     }
     __syncthreads();
 
-    // ---- phase 2: softmax cross-entropy; dZ_L = (p - onehot) / B goes to the LDS tiles
+    // ---- phase 2: softmax cross-entropy; dZ_L = (p - onehot) / B goes to the LDS tiles.  16 lanes per sample,
+    // as in the forward kernel's epilogue
     {
-        const int b = tid;
-        float nll = 0.f;
-        if (b < 128) {
-            if (b < a.B) {
-                const int y = a.labels[static_cast<int64_t>(g) * Bp + b];
-                if (y >= 0) {
-                    const float* z = red[b];
-                    float zmax = z[0];
-                    for (int c = 1; c < a.d_out; ++c) zmax = fmaxf(zmax, z[c]);
-                    float s_other = 0.f;
-                    for (int c = 0; c < a.d_out; ++c) s_other += c == y ? 0.f : expf(z[c] - zmax);
-                    const float e_y = expf(z[y] - zmax);
-                    nll = xent_loss(s_other, e_y, z[y] - zmax);
-                    const float inv = 1.f / (s_other + e_y), invB = 1.f / static_cast<float>(a.B);
-                    for (int c = 0; c < a.d_out; ++c) {
-                        const OT d = static_cast<OT>(xent_delta(expf(z[c] - zmax), c == y, s_other, inv) * invB);
-                        dz_lds[b][c] = d;
-                        dzt_lds[(c & 3) * 16 + (c >> 2)][b] = d;
-                    }
+        const int u = tid & 15;
+        if (tid < 128) lred[tid] = 0.f;
+        __syncthreads();
+        for (int b = tid >> 4; b < Bp; b += NW * 4) {
+            const int y = b < a.B ? a.labels[static_cast<int64_t>(g) * Bp + b] : -1;
+            if (y < 0) continue;
+            float (&z)[kColChunk + 4] = red[b];
+            float zc[4], zmax = -INFINITY;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                zc[i] = u + 16 * i < a.d_out ? z[u + 16 * i] : -INFINITY;
+                zmax = fmaxf(zmax, zc[i]);
+            }
+            zmax = max_over_row(zmax);
+            const float zy = z[y] - zmax;
+            wave_sync_lds();   // (z[y] is read before it is overwritten)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                zc[i] = expf(zc[i] - zmax);
+                if (u + 16 * i < a.d_out) z[u + 16 * i] = zc[i];
+            }
+            wave_sync_lds();
+            float s_other = 0.f;
+            for (int c = 0; c < a.d_out; ++c) s_other += c == y ? 0.f : z[c];
+            const float e_y = z[y];
+            if (u == 0) lred[b] = xent_loss(s_other, e_y, zy);
+            const float inv = 1.f / (s_other + e_y), invB = 1.f / static_cast<float>(a.B);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int c = u + 16 * i;
+                if (c < a.d_out) {
+                    const OT d = static_cast<OT>(xent_delta(zc[i], c == y, s_other, inv) * invB);
+                    dz_lds[b][c] = d;
+                    dzt_lds[(c & 3) * 16 + (c >> 2)][b] = d;
                 }
             }
-            lred[b] = nll;
         }
         __syncthreads();
-        for (int w = 64; w > 0; w >>= 1) {
-            if (b < w) lred[b] += lred[b + w];
-            __syncthreads();
+        if (tid < 64) {
+            float l = lred[tid] + lred[tid + 64];
+#pragma unroll
+            for (int w = 32; w > 0; w >>= 1) l += __shfl_xor(l, w, 64);
+            if (tid == 0) a.loss[static_cast<int64_t>(g) * kLossParts] = l / static_cast<float>(a.B);
         }
-        if (b == 0) a.loss[static_cast<int64_t>(g) * kLossParts] = lred[0] / static_cast<float>(a.B);
     }
 
     // ---- phase 3: backward of the layer.  Bias first (one thread per class) ...

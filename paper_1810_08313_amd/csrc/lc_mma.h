@@ -297,6 +297,13 @@ __device__ __forceinline__ float sum_over_row(float x) {
     return x + rotated_in_row<1>(x);
 }
 
+__device__ __forceinline__ float max_over_row(float x) {
+    x = fmaxf(x, rotated_in_row<8>(x));
+    x = fmaxf(x, rotated_in_row<4>(x));
+    x = fmaxf(x, rotated_in_row<2>(x));
+    return fmaxf(x, rotated_in_row<1>(x));
+}
+
 __device__ __forceinline__ void wave_sync_lds() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
