@@ -136,7 +136,7 @@ struct lc_handle {
     bool group_shared_on;     // ... and several replicas' batches per block in them (see FwdArgs::fm_Bp)
     int share_w_set;          // ... replicas per set
     // resident local steps (small two-layer models): exchange buffer, barrier counters, switches
-    float* res_a1x;         // [2 parities][m][dp1/16][Bp][16] exchange buffer of the resident kernel, null when the shape does not qualify
+    float* res_a1x;         // [slots][m][dp1/16][Bp][16] exchange buffer of the resident kernel, by step of a launch; null when the shape does not qualify
     unsigned* res_ctr;      // error flag, counters and placement probe of the resident kernels, see kCtr* below
     unsigned res_arrivals;  // value of every counter once the queued launches have run (zeroed with the scratch at attach)
     bool net_ok;            // the model runs whole local steps on one compute unit per replica (net_kernel)
