@@ -1075,9 +1075,17 @@ __global__ __launch_bounds__(512) void head_kernel(HeadArgs a) {
     const OT* AT = static_cast<const OT*>(a.a_fm) + static_cast<int64_t>(g) * a.dp_in * Bp;
 
     const bool class_in = lane < a.d_out;   // lane = class, for the bias
-    const int my_label = tid < a.B ? a.labels[static_cast<int64_t>(g) * Bp + tid] : -1;
-    const float bias = class_in ? a.Xr[g * a.xr_stride + a.b_off + lane] : 0.f;
-    const float bias_v = class_in ? a.V[g * a.x_stride + a.b_off + lane] : 0.f;
+    constexpr bool kAhead = sizeof(OT) == 2 || NT < 8;   // (128 samples in fp32: phase 1 has no registers left for these)
+    int my_label = -1;
+    float bias = 0.f, bias_v = 0.f;
+    auto request_small = [&]() {
+        if (tid < a.B) my_label = a.labels[static_cast<int64_t>(g) * Bp + tid];
+        if (class_in) {
+            bias = a.Xr[g * a.xr_stride + a.b_off + lane];
+            bias_v = a.V[g * a.x_stride + a.b_off + lane];
+        }
+    };
+    if constexpr (kAhead) request_small();
 
     // ---- phase 1: logits = A_{L-1} W_L + b_L (reduction over d_in split over the wavefronts)
     {
@@ -1138,6 +1146,7 @@ __global__ __launch_bounds__(512) void head_kernel(HeadArgs a) {
             __syncthreads();
         }
     }
+    if constexpr (!kAhead) request_small();
     // what phase 3 needs: weight rows k0 .. k0 + 15 are this wavefront's (dp_in <= 16 NW, see head_is_fused)
     const int k0 = wave * kRowsPerWave;
     const bool has_rows = k0 < a.dp_in;
