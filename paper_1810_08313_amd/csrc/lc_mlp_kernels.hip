@@ -31,6 +31,8 @@
 #include "lc_internal.h"
 #include "lc_mma.h"
 
+#include <type_traits>
+
 namespace lc {
 
 namespace {
@@ -137,6 +139,60 @@ __global__ __launch_bounds__(256) void gather_kernel(GatherArgs a) {
         for (int e = 0; e < 8; ++e) y[e] = tile[seg + e][kk];
         store8(fm + static_cast<int64_t>(k0 + kk) * a.Bp + b0 + seg, y);
     }
+}
+
+// ------------------------------------------- softmax of a sample, logits in LDS
+
+// Classes u + LANES i (i < 4) of one sample in lane u of LANES neighbouring lanes; z holds its logits.  Leaves
+// exp(z - max) of the lane's classes in e, that of the label in e_y, and returns the sample's loss.  The sum over
+// the classes other than the label is taken in class order whatever LANES is.
+template <int LANES>
+__device__ __forceinline__ float softmax_of_sample(float* z, int u, int d_out, int y, float (&e)[4], float& s_other, float& e_y) {
+    float zmax = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float x = z[u + LANES * i];   // (rows have kColChunk places)
+        e[i] = u + LANES * i < d_out ? x : -INFINITY;
+        zmax = fmaxf(zmax, e[i]);
+    }
+    if constexpr (LANES == 4) zmax = max_over_quad(zmax);
+    if constexpr (LANES == 16) zmax = max_over_row(zmax);
+    const float z_y = z[y] - zmax;
+    s_other = 0.f;
+    if constexpr (LANES == 1) {
+        e_y = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            e[i] = expf(e[i] - zmax);
+            if (i < d_out) {
+                s_other += i == y ? 0.f : e[i];
+                e_y = i == y ? e[i] : e_y;
+            }
+        }
+    } else {
+        wave_sync_lds();   // (z[y] is read before it is overwritten)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            e[i] = expf(e[i] - zmax);
+            if (u + LANES * i < d_out) z[u + LANES * i] = e[i];
+        }
+        wave_sync_lds();
+        for (int c = 0; c < d_out; ++c) s_other += c == y ? 0.f : z[c];
+        e_y = z[y];
+    }
+    return xent_loss(s_other, e_y, z_y);
+}
+
+// Four classes a lane: 1, 4 or 16 lanes per sample, f(integral_constant<lanes>) with what d_out asks for.  More lanes
+// than that sit idle and make more passes over the samples; fewer walk the classes one after the other.  Whole
+// steps, bf16, with one thread per sample at any number of classes / 16 lanes / this: 1024-2, 64 workers of 128 samples,
+// 30.8 / 31.6 / 29.9 us; 1024-10 35.7 / 35.1 / 33.6; 100-2, 4 workers (head_kernel) 21.0 / 18.7 / 14.2; 100-10 22.6 /
+// 20.5 / 16.3; 17 classes and more take 16 lanes (1024-64 18 to 30 % faster than one thread).
+template <typename F>
+__device__ __forceinline__ void with_lanes_per_sample(int d_out, F&& f) {
+    if (d_out <= 4) f(std::integral_constant<int, 1>{});
+    else if (d_out <= 16) f(std::integral_constant<int, 4>{});
+    else f(std::integral_constant<int, 16>{});
 }
 
 // -------------------------------------------------------------------- forward
@@ -445,56 +501,41 @@ __global__ __launch_bounds__(NW * 64) void forward_kernel(FwdArgs a) {
         }
         if (a.fuse_softmax) {
             // all classes of a sample sit in this block's tile: loss and dZ_L here, for the
-            // block's own samples; the loss is left as one partial sum per block.  16 lanes per sample, class
-            // u + 16 i in lane u; the sum over the classes is taken in class order by each of them.  (One
-            // thread per sample, walking the classes twice: 1024-10, 100 samples, fp32, 14.4 us the launch.)
+            // block's own samples; the loss is left as one partial sum per block.
             __shared__ float lred[128];
             __shared__ int lab_s[128];
-            const int t = threadIdx.x, u = t & 15;
+            const int t = threadIdx.x;
             if (t < 128) {
                 lred[t] = 0.f;
                 lab_s[t] = my_label;
             }
             __syncthreads();
-            for (int bl = t >> 4; bl < MT * 16; bl += NW * 4) {   // (whole 16-lane rows; NW * 4 divides or exceeds MT * 16)
-                const int b = row0 + batch_row(bl / 16, bl % 16);
-                const int y = lab_s[bl];
-                if (y < 0) continue;
-                float (&z)[kColChunk + 4] = red[bl];
-                float zc[4], zmax = -INFINITY;
+            with_lanes_per_sample(a.d_out, [&](auto lanes) {
+                constexpr int LANES = decltype(lanes)::value;
+                const int u = t % LANES;
+                for (int bl = t / LANES; bl < MT * 16; bl += NW * 64 / LANES) {
+                    const int b = row0 + batch_row(bl / 16, bl % 16);
+                    const int y = lab_s[bl];
+                    if (y < 0) continue;
+                    float e[4], s_other, e_y;
+                    const float l = softmax_of_sample<LANES>(red[bl], u, a.d_out, y, e, s_other, e_y);
+                    if (u == 0) lred[bl] = l;
+                    if (a.dz_bm) {
+                        OT* dbm = static_cast<OT*>(a.dz_bm) + (static_cast<int64_t>(g) * a.Bp + b) * a.dp_out;
+                        OT* dfm = static_cast<OT*>(a.dz_fm) + static_cast<int64_t>(g) * a.dp_out * a.Bp + b;
+                        const float inv = 1.f / (s_other + e_y), invB = 1.f / static_cast<float>(a.B);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    zc[i] = u + 16 * i < a.d_out ? z[u + 16 * i] : -INFINITY;
-                    zmax = fmaxf(zmax, zc[i]);
-                }
-                zmax = max_over_row(zmax);
-                const float zy = z[y] - zmax;
-                wave_sync_lds();   // (z[y] is read before it is overwritten)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    zc[i] = expf(zc[i] - zmax);
-                    if (u + 16 * i < a.d_out) z[u + 16 * i] = zc[i];
-                }
-                wave_sync_lds();
-                float s_other = 0.f;
-                for (int c = 0; c < a.d_out; ++c) s_other += c == y ? 0.f : z[c];
-                const float e_y = z[y];
-                if (u == 0) lred[bl] = xent_loss(s_other, e_y, zy);
-                if (a.dz_bm) {
-                    OT* dbm = static_cast<OT*>(a.dz_bm) + (static_cast<int64_t>(g) * a.Bp + b) * a.dp_out;
-                    OT* dfm = static_cast<OT*>(a.dz_fm) + static_cast<int64_t>(g) * a.dp_out * a.Bp + b;
-                    const float inv = 1.f / (s_other + e_y), invB = 1.f / static_cast<float>(a.B);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const int c = u + 16 * i;
-                        if (c < a.d_out) {
-                            const OT d = static_cast<OT>(xent_delta(zc[i], c == y, s_other, inv) * invB);
-                            dbm[c] = d;
-                            dfm[static_cast<int64_t>(c) * a.Bp] = d;
+                        for (int i = 0; i < 4; ++i) {
+                            const int c = u + LANES * i;
+                            if (c < a.d_out) {
+                                const OT d = static_cast<OT>(xent_delta(e[i], c == y, s_other, inv) * invB);
+                                dbm[c] = d;
+                                dfm[static_cast<int64_t>(c) * a.Bp] = d;
+                            }
                         }
                     }
                 }
-            }
+            });
             __syncthreads();
             if (t < 64) {
                 float l = lred[t] + lred[t + 64];
@@ -1030,7 +1071,7 @@ __global__ __launch_bounds__(256) void combine_da_kernel(CombineArgs a) {
 // and its momentum at the start; weights, momentum and activations of the backward pass before
 // the softmax) and LDS is read in whole fragments.
 // (324-99-2, 16 workers, batch 110, bf16: 25.5 us with one thread per sample or class walking LDS and every phase
-// waiting for its own loads, 30.0 with 16 lanes per sample and the labels loaded pass by pass, 21.3 now.)
+// waiting for its own loads, 17.9 now; see with_lanes_per_sample for the softmax.)
 
 struct HeadArgs {
     float* X;
@@ -1186,44 +1227,29 @@ __global__ __launch_bounds__(512) void head_kernel(HeadArgs a) {
     }
     __syncthreads();
 
-    // ---- phase 2: softmax cross-entropy; dZ_L = (p - onehot) / B goes to the LDS tiles.  16 lanes per sample,
-    // as in the forward kernel's epilogue
+    // ---- phase 2: softmax cross-entropy; dZ_L = (p - onehot) / B goes to the LDS tiles
     {
-        const int u = tid & 15;
-        for (int b = tid >> 4; b < Bp; b += NW * 4) {
-            const int y = lab_s[b];
-            if (y < 0) continue;
-            float (&z)[kColChunk + 4] = red[b];
-            float zc[4], zmax = -INFINITY;
+        with_lanes_per_sample(a.d_out, [&](auto lanes) {
+            constexpr int LANES = decltype(lanes)::value;
+            const int u = tid % LANES;
+            for (int b = tid / LANES; b < Bp; b += NW * 64 / LANES) {
+                const int y = lab_s[b];
+                if (y < 0) continue;
+                float e[4], s_other, e_y;
+                const float l = softmax_of_sample<LANES>(red[b], u, a.d_out, y, e, s_other, e_y);
+                if (u == 0) lred[b] = l;
+                const float inv = 1.f / (s_other + e_y), invB = 1.f / static_cast<float>(a.B);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                zc[i] = u + 16 * i < a.d_out ? z[u + 16 * i] : -INFINITY;
-                zmax = fmaxf(zmax, zc[i]);
-            }
-            zmax = max_over_row(zmax);
-            const float zy = z[y] - zmax;
-            wave_sync_lds();   // (z[y] is read before it is overwritten)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                zc[i] = expf(zc[i] - zmax);
-                if (u + 16 * i < a.d_out) z[u + 16 * i] = zc[i];
-            }
-            wave_sync_lds();
-            float s_other = 0.f;
-            for (int c = 0; c < a.d_out; ++c) s_other += c == y ? 0.f : z[c];
-            const float e_y = z[y];
-            if (u == 0) lred[b] = xent_loss(s_other, e_y, zy);
-            const float inv = 1.f / (s_other + e_y), invB = 1.f / static_cast<float>(a.B);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int c = u + 16 * i;
-                if (c < a.d_out) {
-                    const OT d = static_cast<OT>(xent_delta(zc[i], c == y, s_other, inv) * invB);
-                    dz_lds[b][c] = d;
-                    dzt_lds[(c & 3) * 16 + (c >> 2)][b] = d;
+                for (int i = 0; i < 4; ++i) {
+                    const int c = u + LANES * i;
+                    if (c < a.d_out) {
+                        const OT d = static_cast<OT>(xent_delta(e[i], c == y, s_other, inv) * invB);
+                        dz_lds[b][c] = d;
+                        dzt_lds[(c & 3) * 16 + (c >> 2)][b] = d;
+                    }
                 }
             }
-        }
+        });
         __syncthreads();
         if (tid < 64) {
             float l = lred[tid] + lred[tid + 64];

@@ -304,6 +304,16 @@ __device__ __forceinline__ float max_over_row(float x) {
     return fmaxf(x, rotated_in_row<1>(x));
 }
 
+template <int N>
+__device__ __forceinline__ float rotated_in_quad(float x) {   // DPP quad_perm
+    constexpr int kPerm = N | (N + 1) % 4 << 2 | (N + 2) % 4 << 4 | (N + 3) % 4 << 6;
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), kPerm, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float max_over_quad(float x) {   // over 4 neighbouring lanes
+    x = fmaxf(x, rotated_in_quad<2>(x));
+    return fmaxf(x, rotated_in_quad<1>(x));
+}
+
 __device__ __forceinline__ void wave_sync_lds() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();

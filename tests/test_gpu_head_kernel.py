@@ -33,3 +33,20 @@ def test_steps(pkg, orc, dims, m, B, bf16):
         assert not run.X[:, run.P:].any() and not run.V[:, run.P:].any()
         _force(run, ref)
     run.close()
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("hidden", [33, 140])   # the one-workgroup kernel; the forward kernel's epilogue
+@pytest.mark.parametrize("classes", [1, 4, 5, 16, 17])
+def test_classes_per_lane(pkg, orc, classes, hidden, bf16):
+    """Both kernels' softmax at the edges of its split: 1, 4 or 16 lanes per sample."""
+    dims, m, B = [40, hidden, classes], 2, 45
+    _say(f"softmax of {classes} classes, {hidden} hidden units, bf16={bf16}")
+    tol = TOL16 if bf16 else TOL32
+    ref, run = _problem(pkg, orc, dims, m, B, wd=1e-3, bf16=bf16, lr=0.05, resident=False)
+    masks = UnitMasks()
+    _ref_steps(orc, ref, 11, 1, masks)
+    run.local_steps(1)
+    _check_workers(run, ref, dims, tol, "step", masks)
+    _check_losses(run, ref, tol, "local losses")
+    run.close()
