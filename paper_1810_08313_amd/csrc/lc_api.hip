@@ -281,7 +281,8 @@ int run_periods(lc_handle* h, int tau, int n_periods, bool average) {
             h->lazy_enabled = true;
             const int r = run_periods(h, tau, n_periods, average);
             h->lazy_enabled = false;
-            return r == LC_OK ? materialise(h) : r;
+            const int w = materialise(h);   // also where the call failed: its caller reads the rows, not xbar
+            return r != LC_OK ? r : w;
         }
     }
     int64_t left = static_cast<int64_t>(tau) * n_periods;
