@@ -41,8 +41,7 @@ struct SyncArgs {
     int64_t w_off, b_off;
     int d_in, d_out, dp_in, dp_out;
     int B, G;
-    const void* a_fm;     // A_{l-1}^T of this iteration [G][dp_in][Bp]; layer 1: in fragments
-    int frags;
+    const void* a_fm;     // A_{l-1}^T of this iteration [G][dp_in][Bp]; FRAGS instances (layer 1): in fragments
     const void* dz_fm;    // dZ_1^T of this iteration [G][dp_out][Bp]
     float lr, beta, wd;
     int n_row_blocks, n_cc;
@@ -52,7 +51,9 @@ struct SyncArgs {
 // Workgroup (row block rb, column chunk cc), 4 wavefronts of 16 rows each.  The loads of replica
 // g + 1 (momentum tile, A_0^T rows, dZ_1 slice) are in flight while replica g is worked on; the
 // slice is staged in LDS in two buffers, one barrier per replica.
-template <typename OT, int NT, bool OWN = false>
+// FRAGS is a template parameter: chosen per load, the form of the A operands costs the OWN instances 4 to 5 %
+// (3072x2048, 64 workers of 32 samples, bf16: 908 us a launch, 859 so; 2048x2048 596 and 573).
+template <typename OT, int NT, bool OWN, bool FRAGS>
 __global__ __launch_bounds__(256) void sync_first_layer_kernel(SyncArgs a) {
     constexpr int kPad = sizeof(OT) == 2 ? 8 : 4;
     constexpr int Bp = 16 * NT;
@@ -92,8 +93,8 @@ __global__ __launch_bounds__(256) void sync_first_layer_kernel(SyncArgs a) {
         const OT* AT = static_cast<const OT*>(a.a_fm) + static_cast<int64_t>(g) * a.dp_in * Bp;
 #pragma unroll
         for (int s = 0; s < NS; ++s)
-            af[s] = a.frags ? load_frag(AT + static_cast<int64_t>(k0) * Bp + s * kFragElems, lane)
-                            : load8(AT + static_cast<int64_t>(k0 + j) * Bp + 32 * s + 8 * q);
+            af[s] = FRAGS ? load_frag(AT + static_cast<int64_t>(k0) * Bp + s * kFragElems, lane)
+                          : load8(AT + static_cast<int64_t>(k0 + j) * Bp + 32 * s + 8 * q);
     };
     auto issue_loads = [&](int g, float4 (&vv)[4], float4 (&ww)[4]) {
         if constexpr (OWN) {
@@ -215,12 +216,17 @@ __global__ __launch_bounds__(256) void sync_first_layer_kernel(SyncArgs a) {
     }
 }
 
-template <typename OT, bool OWN>
-hipError_t launch_sync1(const SyncArgs& a, int nt, unsigned grid, hipStream_t st) {
-    if (nt == 2) hipLaunchKernelGGL((sync_first_layer_kernel<OT, 2, OWN>), dim3(grid), dim3(256), 0, st, a);
-    else if (nt == 4) hipLaunchKernelGGL((sync_first_layer_kernel<OT, 4, OWN>), dim3(grid), dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((sync_first_layer_kernel<OT, 8, OWN>), dim3(grid), dim3(256), 0, st, a);
+template <typename OT, bool OWN, bool FRAGS>
+hipError_t launch_sync_nt(const SyncArgs& a, int nt, unsigned grid, hipStream_t st) {
+    if (nt == 2) hipLaunchKernelGGL((sync_first_layer_kernel<OT, 2, OWN, FRAGS>), dim3(grid), dim3(256), 0, st, a);
+    else if (nt == 4) hipLaunchKernelGGL((sync_first_layer_kernel<OT, 4, OWN, FRAGS>), dim3(grid), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((sync_first_layer_kernel<OT, 8, OWN, FRAGS>), dim3(grid), dim3(256), 0, st, a);
     return hipGetLastError();
+}
+template <typename OT>
+hipError_t launch_sync1(const SyncArgs& a, bool own, bool frags, int nt, unsigned grid, hipStream_t st) {
+    if (own) return frags ? launch_sync_nt<OT, true, true>(a, nt, grid, st) : launch_sync_nt<OT, true, false>(a, nt, grid, st);
+    return frags ? launch_sync_nt<OT, false, true>(a, nt, grid, st) : launch_sync_nt<OT, false, false>(a, nt, grid, st);
 }
 
 }  // namespace
@@ -273,7 +279,6 @@ hipError_t launch_sync_layer(lc_handle* h, int l) {
     a.dp_out = g.dp_out;
     a.B = S.B;
     a.G = S.G;
-    a.frags = l == 1 ? 1 : 0;
     if (l == 1) {
         const size_t slot_bytes = static_cast<size_t>(S.G) * S.Bp * g.dp_in * (bf16 ? 2 : 4);
         a.a_fm = static_cast<const char*>(S.a_fm[0]) + static_cast<size_t>(S.cur_slot) * slot_bytes;
@@ -289,9 +294,8 @@ hipError_t launch_sync_layer(lc_handle* h, int l) {
     a.total_blocks = static_cast<int64_t>(a.n_row_blocks) * a.n_cc;
     const unsigned grid = static_cast<unsigned>((a.total_blocks + kXcds - 1) / kXcds * kXcds);
     timing_start(h, kTimeBwd, l, kBwdTileOwner);
-    hipError_t e;
-    if (own) e = bf16 ? launch_sync1<bf16_t, true>(a, S.Bp / 16, grid, h->stream) : launch_sync1<float, true>(a, S.Bp / 16, grid, h->stream);
-    else e = bf16 ? launch_sync1<bf16_t, false>(a, S.Bp / 16, grid, h->stream) : launch_sync1<float, false>(a, S.Bp / 16, grid, h->stream);
+    const hipError_t e = bf16 ? launch_sync1<bf16_t>(a, own, l == 1, S.Bp / 16, grid, h->stream)
+                              : launch_sync1<float>(a, own, l == 1, S.Bp / 16, grid, h->stream);
     timing_stop(h, kTimeBwd, l, kBwdTileOwner);
     if (e == hipSuccess && own) h->imp[l] = sb.next;   // (explicit again: v is in V; the rows of X wait for the broadcast)
     return e;
