@@ -265,6 +265,7 @@ int run_periods(lc_handle* h, int tau, int n_periods, bool average) {
     const bool mlp = h->md.kind == LC_KIND_MLP;
     const int slots = mlp ? h->train.slots : kGatherSlots;
     const bool resident = mlp && on_chip(h);
+    if (mlp) h->a0_layout = input_layout(h, tau > 1);
     const bool defer_ok = mlp && !resident && average && tau == 1 && h->defer_x_on && h->lazy_enabled &&
                           !h->bm_on && !head_is_fused(h);
     const bool fuse_ok = mlp && !resident && average && h->fuse_avg_on && h->lazy_enabled && !h->bm_on &&
@@ -434,6 +435,7 @@ int lc_init(int m, int64_t P, const lc_model* md, uint64_t seed, lc_handle** out
     h->res_a1x = nullptr;
     h->res_ctr = nullptr;
     h->da_part = nullptr;
+    h->a0_layout = kInputsPlain;
     h->net_ok = net_shape_ok(h);
     h->res_on = true;
     h->res_fuse_always = false;
@@ -539,6 +541,7 @@ int lc_local_periods(lc_handle* h, int tau, int n_periods) {
     if (!fused) return run_periods(h, tau, n_periods, true);
     // weights resident on chip: as many whole periods per launch as one gather launch has inputs
     // for, the averaging steps taken inside the kernel
+    h->a0_layout = input_layout(h, true);
     const int per_launch = h->train.slots / tau;
     for (int done = 0; done < n_periods; done += per_launch) {
         const int p = n_periods - done < per_launch ? n_periods - done : per_launch;

@@ -658,7 +658,7 @@ hipError_t launch_first_layer(lc_handle* h) {
     const size_t es = bf16 ? 2 : 4;
     const size_t slot_bytes = static_cast<size_t>(S.G) * S.Bp * g.dp_in * es;
     if (!first_layer_kernel_ok(h)) return hipErrorInvalidValue;
-    if (S.cur_slot + 1 >= S.slots) return hipErrorInvalidValue;
+    if (S.cur_slot + 1 >= S.slots || h->a0_layout != kInputsLayers) return hipErrorInvalidValue;
     FirstArgs a;
     const StepBufs sb = plan_step_buffers(h, 1);
     a.X = sb.ox;

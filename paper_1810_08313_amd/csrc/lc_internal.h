@@ -69,6 +69,12 @@ struct LayerGeom {
     int64_t w_off, b_off; // offsets inside a replica row (floats)
 };
 
+// How the gather kernel leaves the mini-batches.  Plain rows: net_kernel, head_kernel, evaluation, and where
+// first_forward_reads_rows().  Fragment order with lane l's 8 reduction indices 8 (l / 16) ..: both layouts for the
+// resident two-layer kernel, and A_0^T for the kernels that take a layer per launch; their A_0 has 4 (l / 16) .. + 3
+// of either half of the 32, so that a half is the operand of a 16-deep product too (first_layer_kernel).
+enum InputLayout { kInputsPlain = 0, kInputsResident = 1, kInputsLayers = 2 };
+
 // Device buffers of one "activation set": either the training set (operand type
 // of the run) or the evaluation set (always fp32).
 struct ActSet {
@@ -107,6 +113,7 @@ struct lc_handle {
     size_t scratch_bytes;
     hipStream_t stream;
     lc::ActSet train, eval;
+    lc::InputLayout a0_layout;   // of the mini-batches of the call in progress, see input_layout()
     float* xbar;            // [Ps]
     // block momentum: global buffer, last synchronised model, and the deferred clearing of V
     float *bm_u, *bm_xs;    // [Ps]
@@ -208,14 +215,21 @@ hipError_t probe_block_placement(lc_handle* h);   // synchronises the stream onc
 // local steps run with the models on chip: the resident step kernels, or one compute unit per replica
 inline bool on_chip(const lc_handle* h) { return h->res_on && (h->res_a1x || h->net_ok); }
 inline bool fetches_its_inputs(const lc_handle* h) { return h->res_on && h->res_a1x && h->L == 1; }   // no gather launch
-// How the gather kernel leaves the mini-batches.  Plain rows: net_kernel, head_kernel, evaluation.  Fragment
-// order with lane l's 8 reduction indices 8 (l / 16) ..: both layouts for the resident two-layer kernel, and A_0^T
-// for the kernels that take a layer per launch; their A_0 has 4 (l / 16) .. + 3 of either half of the 32, so that
-// a half is the operand of a 16-deep product too (first_layer_kernel).
-enum InputLayout { kInputsPlain = 0, kInputsResident = 1, kInputsLayers = 2 };
-inline InputLayout input_layout(const lc_handle* h) {
+// Whole batches of 65 to 128 samples in one block of the forward kernel: it reads the feature-major copy in
+// plain rows faster than fragments.  784-512-512-10, 32 workers of 128, tau = 1: layers 1 and 2, which then also
+// share an instance, 25.0 us of an iteration of 132 and 28.8 of 134 with fragments; 3072-1500-1000-100, 16 of 100,
+// 105 and 109 us for layer 1; fp32, 784-512-512-10: 66.2 and 68.7.
+// (bf16 with 16 bytes of a fragment per load instead of two halves: 27.6.)
+inline bool first_forward_reads_rows(const lc_handle* h) {
+    return h->train.Bp == 128 && static_cast<int64_t>(h->train.G) * (h->layer[1].dp_out / kColChunk) >= 256;
+}
+// The layout of a call's mini-batches; more_steps: its periods have more than one step, so that the first layer's
+// kernel may run the next step's forward pass.
+inline InputLayout input_layout(const lc_handle* h, bool more_steps) {
     if (on_chip(h)) return h->res_a1x && h->L == 2 ? kInputsResident : kInputsPlain;
-    return h->L == 1 && head_is_fused(h) ? kInputsPlain : kInputsLayers;
+    if (h->L == 1 && head_is_fused(h)) return kInputsPlain;
+    if (first_forward_reads_rows(h) && !(more_steps && h->fl_on && first_layer_kernel_ok(h))) return kInputsPlain;
+    return kInputsLayers;
 }
 hipError_t launch_resident(lc_handle* h, int slot0, int n_steps, int period);  // the steps gathered into slots slot0 .. slot0+n_steps-1
 

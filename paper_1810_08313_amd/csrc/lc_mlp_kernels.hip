@@ -247,7 +247,7 @@ struct FwdArgs {
 // the same trick as for the weight columns.  Tile VW h + t then holds batch rows
 // 16 VW h + VW i + t (i = 0..15) instead of 16 mt + i; only the epilogue needs to know.
 //
-// FRAGS instances (layer 1 of a training step) read the activations in fragment order, see InputLayout.
+// FRAGS instances (layer 1 of most training steps, see input_layout) read the activations in fragment order.
 constexpr int kActRows = 0, kActFeatureMajor = 1, kActFragments = 2;
 template <typename OT, int MT, int NW, int PF, int WM, int AM>
 __global__ __launch_bounds__(NW * 64) void forward_kernel(FwdArgs a) {
@@ -730,6 +730,7 @@ struct BwdArgs {
     float* da_part;      // columns shared out although dZ_{l-1} is wanted: this workgroup's share of dA goes to
     int64_t part_stride; // da_part + (its share) part_stride, [G][dp_in][Bp] fp32, and combine_da_kernel
                          // adds the shares up.  Null: the workgroup walks all columns and writes dZ_{l-1} itself
+    int frags;           // layer 1: a_fm comes in fragments
     int skip_x;          // V is updated, X is left unwritten: the averaging step that follows forms
                          // every replica's new weights from Xr and V itself (tau = 1, deferred update)
     int64_t total_blocks;
@@ -755,7 +756,9 @@ struct BwdArgs {
 // form dZ_{l-1} only: the same walk over W_l without V, dW, the update or any store to X and V.
 // NDA instances (first layer) form no dZ_{l-1}: without the two tiles that product needs in LDS, 2 to 4
 // workgroups share a CU where one did (784x500 with 16 replicas of 100 samples, fp32: 43 -> 36 us).
-template <typename OT, int NT, int WM, bool DAO = false, bool NDA = false>
+// FRAGS: they read their inputs in fragments.  (Chosen at run time it costs registers: 784x512, 32 replicas of 128
+// samples, fp32: 62 us instead of 55.)
+template <typename OT, int NT, int WM, bool DAO = false, bool NDA = false, bool FRAGS = NDA>
 __global__ __launch_bounds__(256, NT == 8 && !NDA && !DAO ? 1 : 2) void backward_kernel(BwdArgs a) {
     constexpr int kPad = sizeof(OT) == 2 ? 8 : 4;
     constexpr int Bp = 16 * NT;
@@ -812,9 +815,9 @@ __global__ __launch_bounds__(256, NT == 8 && !NDA && !DAO ? 1 : 2) void backward
     Frag<OT> af[NS];
     if constexpr (!DAO) {
 #pragma unroll
-        for (int s = 0; s < NS; ++s)   // (the first layer's inputs are in fragments)
-            af[s] = NDA ? load_frag(AT + static_cast<int64_t>(k0) * Bp + s * kFragElems, lane)
-                        : load8(AT + static_cast<int64_t>(k0 + j) * Bp + 32 * s + 8 * q);
+        for (int s = 0; s < NS; ++s)
+            af[s] = FRAGS ? load_frag(AT + static_cast<int64_t>(k0) * Bp + s * kFragElems, lane)
+                          : load8(AT + static_cast<int64_t>(k0 + j) * Bp + 32 * s + 8 * q);
     }
 
     // ReLU gates of this lane's dA entries, fetched now (one bit each) instead of after the walk
@@ -1387,12 +1390,16 @@ hipError_t launch_fwd_wm(const FwdArgs& a, int mt, bool wide, int am, unsigned g
 template <typename OT, int WM>
 hipError_t launch_bwd_nt(const BwdArgs& a, int nt, unsigned grid, hipStream_t s) {
     if (!a.dzp_bm) {
+        if (!a.frags && nt != 8) return hipErrorInvalidValue;   // (see first_forward_reads_rows)
         // (where the weights stream a third workgroup per CU costs more than it hides: the unused LDS keeps it out)
         const unsigned pad = a.stream ? 55u * 1024 : 0;
         switch (nt) {
             case 2: hipLaunchKernelGGL((backward_kernel<OT, 2, WM, false, true>), dim3(grid), dim3(256), pad, s, a); break;
             case 4: hipLaunchKernelGGL((backward_kernel<OT, 4, WM, false, true>), dim3(grid), dim3(256), 0, s, a); break;
-            case 8: hipLaunchKernelGGL((backward_kernel<OT, 8, WM, false, true>), dim3(grid), dim3(256), 0, s, a); break;
+            case 8:
+                if (a.frags) hipLaunchKernelGGL((backward_kernel<OT, 8, WM, false, true>), dim3(grid), dim3(256), 0, s, a);
+                else hipLaunchKernelGGL((backward_kernel<OT, 8, WM, false, true, false>), dim3(grid), dim3(256), 0, s, a);
+                break;
             default: return hipErrorInvalidValue;
         }
         return hipGetLastError();
@@ -1468,7 +1475,7 @@ hipError_t launch_gather(lc_handle* h, bool eval, int64_t k_or_base, int n_steps
     a.G = S.G;
     a.a_slot = static_cast<int64_t>(a0_slot_elems(h, S));
     a.lab_slot = static_cast<int64_t>(S.G) * S.Bp;
-    a.layout = eval ? kInputsPlain : input_layout(h);
+    a.layout = eval ? kInputsPlain : h->a0_layout;
     const dim3 grid(a.dp0 / 64, a.Bp / 32, S.G * n_steps);
     if (eval) {
         if (bf16) hipLaunchKernelGGL((gather_kernel<bf16_t, float>), grid, dim3(256), 0, h->stream, a);
@@ -1626,9 +1633,10 @@ hipError_t launch_forward(lc_handle* h, bool eval, int l, int loss_offset) {
     if (!eval) timing_start(h, kTimeFwd);
     hipError_t e;
     // whole padded batch in one block and a feature-major copy of the input at hand
-    const void* in_fm = eval || l == 1 ? nullptr : S.a_fm[l - 1];
+    const bool frags = !eval && l == 1 && h->a0_layout == kInputsLayers;
+    const void* in_fm = eval || frags ? nullptr : l == 1 ? a0_ptr(h, S, S.a_fm[0], false) : S.a_fm[l - 1];
     const bool afm = in_fm != nullptr && !grouped && a.m_split == 1 && mt * 16 == S.Bp && mt == 8;
-    const int am = !eval && l == 1 ? kActFragments : afm ? kActFeatureMajor : kActRows;   // (the mini-batch comes in fragments)
+    const int am = frags ? kActFragments : afm ? kActFeatureMajor : kActRows;
     a.a_in_fm = in_fm;
     if (bf16) e = launch_fwd_wm<bf16_t>(a, mt, wide, am, grid, h->stream);
     else e = launch_fwd_wm<float>(a, mt, wide, am, grid, h->stream);
@@ -1788,6 +1796,7 @@ hipError_t launch_backward(lc_handle* h, int l, bool da_only) {
     a.stream = h->stream_weights ? 1 : 0;
     a.n_row_blocks = g.dp_in / 64;
     a.col_split = 1;
+    a.frags = h->a0_layout == kInputsLayers ? 1 : 0;
     a.skip_x = h->defer_x ? 1 : 0;
     a.fm_Bp = S.Bp;
     // the dA-only pass over one model that all replicas share: sets of replicas as one batch of up

@@ -41,7 +41,7 @@ struct SyncArgs {
     int64_t w_off, b_off;
     int d_in, d_out, dp_in, dp_out;
     int B, G;
-    const void* a_fm;     // A_{l-1}^T of this iteration [G][dp_in][Bp]; FRAGS instances (layer 1): in fragments
+    const void* a_fm;     // A_{l-1}^T of this iteration [G][dp_in][Bp]; FRAGS instances (layer 1, see input_layout): in fragments
     const void* dz_fm;    // dZ_1^T of this iteration [G][dp_out][Bp]
     float lr, beta, wd;
     int n_row_blocks, n_cc;
@@ -293,9 +293,10 @@ hipError_t launch_sync_layer(lc_handle* h, int l) {
     a.n_cc = g.d_out / kColChunk;
     a.total_blocks = static_cast<int64_t>(a.n_row_blocks) * a.n_cc;
     const unsigned grid = static_cast<unsigned>((a.total_blocks + kXcds - 1) / kXcds * kXcds);
+    const bool frags = l == 1 && h->a0_layout == kInputsLayers;
     timing_start(h, kTimeBwd, l, kBwdTileOwner);
-    const hipError_t e = bf16 ? launch_sync1<bf16_t>(a, own, l == 1, S.Bp / 16, grid, h->stream)
-                              : launch_sync1<float>(a, own, l == 1, S.Bp / 16, grid, h->stream);
+    const hipError_t e = bf16 ? launch_sync1<bf16_t>(a, own, frags, S.Bp / 16, grid, h->stream)
+                              : launch_sync1<float>(a, own, frags, S.Bp / 16, grid, h->stream);
     timing_stop(h, kTimeBwd, l, kBwdTileOwner);
     if (e == hipSuccess && own) h->imp[l] = sb.next;   // (explicit again: v is in V; the rows of X wait for the broadcast)
     return e;
