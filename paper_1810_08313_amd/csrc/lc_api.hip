@@ -255,6 +255,26 @@ int whole_periods(int64_t k, int tau, int64_t lim, int64_t k_end) {
     return static_cast<int>(np);
 }
 
+// A caller who wants every row written gets them at the end of the call: in between nobody sees them, and
+// where large layers take their averaging step by tile the broadcast may as well wait (bf16: 8 workers of
+// 3072-1536-1024-10, batch 64, a period of 5, 1078 -> 984 us; 64 of 3072-2048-2048-2048-10, batch 32, 4
+// iterations at tau = 1, 18.6 -> 8.9 ms).  Whether it pays, from 784 calls (4 models of 1 and 2 hidden layers, 2 to 32
+// workers): bf16 always, 1.01 to 2.0 times as fast.  With fp32 operands the pass by tile is bound by its products:
+//   65 to 128 samples: iterations at tau = 1 after the first of a call, 1.07 to 1.17; else 0.95 to 1.05, below 1 for most
+//   33 to 64 samples: a single iteration with a hidden layer by tile 0.97 to 1.01; else 1.00 to 1.43
+//   up to 32 samples: 1.02 to 1.6
+bool rows_may_wait(const lc_handle* h, int tau, int n_periods) {
+    bool any = false, hidden = false;
+    for (int l = 1; l < h->L; ++l) {
+        const bool by_tile = sync_layer_ok(h, l);
+        any = any || by_tile;
+        hidden = hidden || (by_tile && l > 1);
+    }
+    if (!any || h->md.gemm == LC_GEMM_BF16 || h->train.Bp == 32) return any;
+    if (h->train.Bp == 128) return tau == 1 && n_periods > 1;
+    return tau > 1 || n_periods > 1 || !hidden;
+}
+
 // tau local iterations, n_periods times, with the averaging step after each period where asked.
 // Mini-batch selection does not depend on the weights, so one gather launch prepares the inputs
 // of a whole chunk of steps: as many whole periods as it has slots for, or a piece of a period
@@ -270,15 +290,9 @@ int run_periods(lc_handle* h, int tau, int n_periods, bool average) {
                           !h->bm_on && !head_is_fused(h);
     const bool fuse_ok = mlp && !resident && average && h->fuse_avg_on && h->lazy_enabled && !h->bm_on &&
                          h->m >= 2 && !head_is_fused(h);
-    // A caller who wants every row written gets them at the end of the call: in between nobody sees them, and
-    // where large layers take their averaging step by tile the broadcast may as well wait (bf16: 8 workers of
-    // 3072-1536-1024-10, batch 64, a period of 5, 1078 -> 984 us; 64 of 3072-2048-2048-2048-10, batch 32, 4
-    // iterations at tau = 1, 18.6 -> 8.9 ms).
     if (mlp && !resident && average && !h->lazy_enabled && !h->bm_on && h->m >= 2 && !head_is_fused(h) &&
         (h->fuse_avg_on || (tau == 1 && h->defer_x_on))) {
-        bool by_tile = false;
-        for (int l = 1; l < h->L; ++l) by_tile = by_tile || sync_layer_ok(h, l);
-        if (by_tile) {
+        if (rows_may_wait(h, tau, n_periods)) {
             h->lazy_enabled = true;
             const int r = run_periods(h, tau, n_periods, average);
             h->lazy_enabled = false;

@@ -4,6 +4,7 @@ has no pending broadcast to start from."""
 import numpy as np
 import pytest
 
+from paper_1810_08313_amd import binding
 from test_gpu_parity import _problem, _say, pkg  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -32,5 +33,56 @@ def test_periods_against_call_by_call(pkg, orc, tau, periods, lazy, bf16):
     for got, want in zip(runs[0].get_state(), runs[1].get_state()):
         assert np.array_equal(got, want)
     assert np.array_equal(runs[0].local_losses(), runs[1].local_losses())
+    for r in runs:
+        r.close()
+
+
+def _tile_launches(run, tau, periods):
+    """Launches of the tile-owner kernel in one call, by layer."""
+    n = []
+    for layer in (1, 2):
+        run.timing_begin(binding.TIME_BWD)
+        run.timing_select(layer, binding.BWD_TILE_OWNER)
+        run.local_periods(tau, periods)
+        n.append(run.timing_read()[0])
+    run.timing_begin(binding.TIME_NONE)
+    return n
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("lazy", [False, True])
+@pytest.mark.parametrize("tau,periods", [(1, 1), (1, 3), (3, 1)])
+@pytest.mark.parametrize("B", [20, 100])   # fragments and plain rows of the first layer's inputs
+def test_hidden_layer_by_tile(pkg, orc, B, tau, periods, lazy, bf16):
+    """Two layers by tile, both well above the size from which they are; the second needs the deltas of the layer
+    below beforehand, from every worker's own weights where no broadcast is pending.  Against the run that writes the
+    rows in every step and averages them in kernels of their own, bit for bit; which calls go by tile, by rule.  (That
+    run defers its broadcast: where all workers read one model the columns are walked in another order than where
+    each reads its own.)"""
+    dims, m = [2048, 1280, 1792, 10], 16
+    _say(f"hidden layer by tile B={B} tau={tau} n={periods} lazy={lazy} bf16={bf16}")
+    runs = [_problem(pkg, orc, dims, m, B, wd=5e-4, bf16=bf16, lr=0.01)[1] for _ in range(2)]
+    runs[1].set_fused_averaging(0)
+    runs[1].set_deferred_update(False)
+    runs[1].set_lazy_broadcast(True)
+    runs[0].set_lazy_broadcast(lazy)
+    for r in runs:
+        r.local_steps(1)
+        r.average()
+        r.materialize()
+        r.local_periods(tau, periods)
+    F = [r.loss() for r in runs]
+    assert F[0] == F[1]
+    rows = runs[0].X.cpu().numpy()[:, :runs[0].P]
+    for got, want in zip(runs[0].get_state(), runs[1].get_state()):
+        assert np.array_equal(got, want)
+    if not lazy:   # they had been there when the call returned
+        assert np.array_equal(rows, runs[0].get_state()[0])
+    by_tile = _tile_launches(runs[0], tau, periods)
+    if lazy or bf16 or B == 20 or (tau == 1 and periods > 1):
+        assert by_tile == [periods, periods]
+    else:   # fp32, more than 64 samples: not for a single iteration or the end of a longer period
+        assert by_tile == [0, 0]
+    assert _tile_launches(runs[1], tau, periods) == [0, 0]
     for r in runs:
         r.close()
