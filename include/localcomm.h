@@ -108,17 +108,20 @@ int64_t lc_row_stride(int64_t P);
  * mix = SplitMix64 output function, G = 0x9E3779B97F4A7C15 (sampling with
  * replacement from the whole set, an independent stream per worker).
  * The iteration counter starts at k = 0.  No device memory is touched.
- * Four environment variables are read here, for measurement runs only (results are bit-identical
+ * Four environment variables are read here, for measurement runs only (results agree to rounding
  * whatever they say): LC_AVG_CHUNK_MB (1..1024, column chunk of the two-kernel averaging step),
  * LC_AVG_TWO_PHASE (0: one averaging kernel at every size), LC_SHARED_W_ORDER (0: replica-major
  * block order everywhere; n: sets of n replicas, see lc_set_lazy_broadcast), LC_SYNC_FIRST_LAYER
- * (0: no tile-owner kernels at tau = 1, 1: for the first layer only; see lc_set_deferred_update).
+ * (0: no tile-owner kernels, 1: for the first layer only; see lc_set_deferred_update).
  * Errors: LC_ERR_ARG (m < 1, null), LC_ERR_MODEL (P != lc_param_count, bad dims,
  * B outside 1..128, E > N). */
 int lc_init(int m, int64_t P, const lc_model* model, uint64_t seed, lc_handle** out);
 void lc_destroy(lc_handle* h);
 
-/* Bytes of device scratch lc_attach() needs for this run. */
+/* Bytes of device scratch lc_attach() needs for this run.  Two-layer models on the resident step
+ * kernel (lc_set_resident) hand over their shares of the logits in a region per step of a launch:
+ * 32 * m * ceil32(B) * ceil64(d1) * 4 bytes of it, 17 MB for 8 workers of 784-256-10 at 64 samples,
+ * at most 34 MB (ceil32: 32 or 64; fewer steps than 32 where a step's inputs exceed 4 MB). */
 size_t lc_workspace_bytes(const lc_handle* h);
 
 /* Bind caller-owned device memory and the stream.
@@ -175,7 +178,9 @@ int lc_local_periods(lc_handle* h, int tau, int n_periods);
  * every replica -- it is served from cache m-1 times out of m -- and writes every row of X, as it
  * does anyway.  This removes the m row writes of the averaging step and most weight reads of the
  * step after it; at tau = 1 the traffic per iteration falls from about 28 to 16 bytes per
- * parameter.  Results are bit-identical to the eager form.  While a broadcast is pending the rows
+ * parameter.  Results are bit-identical to the eager form, except below a hidden layer of 8 MB
+ * and more in a state above 256 MB: its columns are walked in another order where all replicas read
+ * one model, and the deltas it hands down agree to rounding.  While a broadcast is pending the rows
  * of X in device memory are STALE; every entry point of this library accounts for that, but a
  * caller who reads X directly must call lc_materialize() first.  Turning the mode off materialises.
  * In a step that reads the one model for all replicas, layers of 8 MB and more (in a state above
@@ -236,8 +241,10 @@ int lc_set_xcd_local_exchange(lc_handle* h, int on);
 int lc_set_first_layer_fusion(lc_handle* h, int on);
 
 /* Deferred update at tau = 1 (Sec. 2, the k mod tau = 0 branch taken at every iteration: all
- * workers start each iteration from the same averaged model).  Under the deferred broadcast, in
- * lc_local_periods(h, 1, n) and the schedule drivers while tau is 1, replica i's model after its
+ * workers start each iteration from the same averaged model).  In lc_local_periods(h, 1, n) and the
+ * schedule drivers while tau is 1, in iterations that begin with a broadcast pending -- under the
+ * deferred broadcast, or after the first iteration of a call without it whose rows are written at
+ * its end (see lc_set_fused_averaging) -- replica i's model after its
  * step is x_bar - lr * v_i with v_i the momentum row the step has just written.  The backward
  * kernels then leave the rows of X unwritten, and the averaging step reads the rows of V and
  * forms each replica's weights on the fly (same expression, same rounding) before it adds them
@@ -272,15 +279,18 @@ int lc_set_implicit_momentum(lc_handle* h, int mode);
 
 /* The averaging step of large layers folded into the last local step of a period (Sec. 2: the
  * k mod tau = 0 branch follows that step at once).  Inside lc_local_periods() and the schedule
- * drivers, with tau > 1, the deferred broadcast on and block momentum off, the last step of a
- * period does not write the rows of X for such a layer: one kernel owns the layer's weights by
+ * drivers, with block momentum off, the last step of a period (at tau = 1: an iteration that does
+ * not take the deferred update) does not write the rows of X for such a layer: one kernel owns the layer's weights by
  * tile, walks over the workers, updates each worker's momentum tile from that worker's own weights
  * and adds the worker's new weights to a sum kept in double; after the last worker the tile of the
  * averaged model is written, and the averaging kernels skip the layer's weights (its biases are
  * written to X and averaged as before).  Bit-identical to the step followed by the averaging
  * step; 12 instead of 20-24 bytes per parameter and replica for the two together.  Layers as for
  * the tile-owner kernel of tau = 1 (lc_set_deferred_update): 8 MB or more, rows of a multiple of
- * 64 columns, not the last layer.
+ * 64 columns, not the last layer.  Without the deferred broadcast it applies too: the broadcast then
+ * waits until the call returns, and the rows of X are complete at that point.  (Not with fp32
+ * operands where that is slower: above 64 samples all but calls of several iterations at tau = 1,
+ * above 32 samples single iterations of models with a hidden layer of such a size.)
  *   mode 1: the first layer (it needs no deltas for a layer below);
  *   mode 2 (default): the hidden layers too (after a pass over the old weights that forms the
  *           deltas of the layer below);
@@ -294,6 +304,10 @@ int lc_implicit_momentum_layers(const lc_handle* h);
 
 /* 1 if lc_local_steps() of this (attached) handle takes the resident step kernel, else 0. */
 int lc_resident_active(const lc_handle* h);
+
+/* 1 if the workgroups of a replica exchange inside one XCD under the current switches (see
+ * lc_set_xcd_local_exchange; two-layer models on the resident step kernel only), else 0. */
+int lc_xcd_local_exchange_active(const lc_handle* h);
 
 /* How many times a workgroup of the resident step kernel re-reads a replica's arrival counter
  * before it gives up waiting (default 400000, several hundred milliseconds).  0 makes every

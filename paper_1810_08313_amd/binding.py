@@ -97,6 +97,8 @@ def lib() -> C.CDLL:
     L.lc_implicit_momentum_layers.argtypes = [vp]
     L.lc_resident_active.restype = C.c_int
     L.lc_resident_active.argtypes = [vp]
+    L.lc_xcd_local_exchange_active.restype = C.c_int
+    L.lc_xcd_local_exchange_active.argtypes = [vp]
     L.lc_set_barrier_polls.restype = C.c_int
     L.lc_set_barrier_polls.argtypes = [vp, C.c_int]
     L.lc_materialize.restype = C.c_int
@@ -341,6 +343,11 @@ class LocalSGD:
     def resident_active(self) -> bool:
         rc = self._L.lc_resident_active(self._h)
         self._check(min(rc, 0), "lc_resident_active")
+        return rc == 1
+
+    def xcd_local_exchange_active(self) -> bool:
+        rc = self._L.lc_xcd_local_exchange_active(self._h)
+        self._check(min(rc, 0), "lc_xcd_local_exchange_active")
         return rc == 1
 
     def set_barrier_polls(self, polls: int) -> None:

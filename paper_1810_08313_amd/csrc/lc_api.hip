@@ -656,6 +656,12 @@ int lc_resident_active(const lc_handle* h) {
     return on_chip(h) ? 1 : 0;
 }
 
+int lc_xcd_local_exchange_active(const lc_handle* h) {
+    if (!h) return LC_ERR_ARG;
+    if (!h->attached) return LC_ERR_STATE;
+    return exchange_is_local(h) ? 1 : 0;
+}
+
 int lc_set_barrier_polls(lc_handle* h, int polls) {
     if (!h || polls < 0) return LC_ERR_ARG;
     h->res_spin_limit = polls;

@@ -125,16 +125,16 @@ struct lc_handle {
     bool lazy_enabled, lazy_rows;
     int loss_parts_train, loss_parts_eval;   // how many of the kLossParts slots the last launch wrote
     bool lazy_enabled_step;   // set only while lc_average runs its reduce-only form
-    // deferred update (tau = 1 under the deferred broadcast): every replica starts the iteration
+    // deferred update (tau = 1 while a broadcast is pending): every replica starts the iteration
     // from xbar, so its new weights are xbar - lr V_i; the backward kernels write V only and the
     // averaging step forms the weights from V on the fly.  defer_x is set only while run_periods
     // queues such an iteration and its averaging step.
     bool defer_x_on, defer_x;
-    // tau = 1, first layer: backward pass, update of V and the layer's averaging in one kernel; sync1_done
-    // is set while the averaging step of the iteration still has to skip the layer
+    // large layers: backward pass, update of V and the layer's averaging in one kernel
     bool sync1_on, sync_all_on;   // layer 1 / the layers above it as well
     unsigned sync_done;           // bit l: the iteration in progress has averaged layer l's weights already
-    // Last step of a period of tau > 1 whose averaging step follows with the broadcast deferred: the
+    // Last step of a period whose averaging step follows with the broadcast deferred (by the caller, or until the
+    // call ends: rows_may_wait), at tau = 1 where no broadcast is pending: the
     // large layers' tile-owner kernel forms the step and the layer's average together (the rows of X
     // stay unwritten).  fuse_avg is set only while run_periods takes such a step and its averaging step.
     int fuse_avg_on;              // 0 off, 1 the first layer, 2 the large hidden layers as well
@@ -144,7 +144,7 @@ struct lc_handle {
     int share_w_set;          // ... replicas per set
     // resident local steps (small two-layer models): exchange buffer, barrier counters, switches
     float* res_a1x;         // [slots][m][dp1/16][Bp][16] exchange buffer of the resident kernel, by step of a launch; null when the shape does not qualify
-    unsigned* res_ctr;      // error flag, counters and placement probe of the resident kernels, see kCtr* below
+    unsigned* res_ctr;      // error flag, counters and placement probe of the resident kernels, see kCtr* above
     unsigned res_arrivals;  // value of every counter once the queued launches have run (zeroed with the scratch at attach)
     bool net_ok;            // the model runs whole local steps on one compute unit per replica (net_kernel)
     float* da_part;         // shares of dA of the largest layer whose columns are shared out (see BwdArgs), or null
@@ -212,6 +212,7 @@ bool net_shape_ok(const lc_handle* h);
 hipError_t launch_net(lc_handle* h, int slot0, int n_steps);  // as launch_resident, one period or less
 size_t resident_exchange_floats(const lc_handle* h);
 hipError_t probe_block_placement(lc_handle* h);   // synchronises the stream once
+bool exchange_is_local(const lc_handle* h);       // the resident two-layer kernel's exchange stays in one XCD's L2
 // local steps run with the models on chip: the resident step kernels, or one compute unit per replica
 inline bool on_chip(const lc_handle* h) { return h->res_on && (h->res_a1x || h->net_ok); }
 inline bool fetches_its_inputs(const lc_handle* h) { return h->res_on && h->res_a1x && h->L == 1; }   // no gather launch

@@ -36,6 +36,7 @@ constexpr int kNetTiles = 8;            // 16 x 16 weight tiles per wavefront (4
 constexpr int kNetFloats = 40704;       // LDS of a workgroup (159 KB of 160)
 constexpr int kNetMaxClasses = 64;
 constexpr int kTileBias = 1 << 14;      // in the tile table: first tile of its columns
+static_assert(kNetFloats <= 1 << 16 && LC_MAX_LAYERS <= 16, "the tile table's fields: LDS offsets of 16 bits, layers of 4");
 constexpr int kNetStage = 4;            // pieces of 4 values of A_0 per thread, where A_0 is kept in LDS
 
 struct NetLayer {
@@ -463,7 +464,7 @@ bool net_layout(const lc_handle* h, NetArgs& a) {
     int n_tiles = 0;
     for (int l = 0; l < a.L; ++l) {
         const LayerGeom& g = h->layer[l + 1];
-        if (g.d_in > 1024 || g.d_out > 1024) return false;   // (tile indices have 8 bits, and such layers do not fit anyway)
+        if (g.d_in > 1024 || g.d_out > 1024) return false;   // (column tiles have 6 bits in the tile table, and such layers do not fit anyway)
         NetLayer& y = a.layer[l];
         y.d_in = g.d_in;
         y.d_out = g.d_out;

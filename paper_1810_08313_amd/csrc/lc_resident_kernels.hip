@@ -57,7 +57,11 @@ namespace lc {
 namespace {
 
 constexpr int kResMaxD0 = 1024;   // padded input width the LDS slice is sized for
-constexpr int kResMaxD1 = 256;    // padded hidden width (private W_2^T copy)
+constexpr int kResMaxD1 = 256;    // padded hidden width: at most kResMaxSlices shares of the logits are requested at once
+constexpr int kResMaxSlices = 16;
+static_assert(kResMaxD1 <= 16 * kResMaxSlices, "a slice whose share nobody adds would be missing from the logits");
+constexpr int kResShare = 16 * 16;   // a slice's share of the logits of one batch tile, floats
+static_assert(kResShare * sizeof(float) % 128 == 0, "shares in whole cache lines, see arrive_and_wait_step");
 constexpr int kResK1P = kResMaxD0 + 4;
 constexpr int kResWaves = 16;                    // wavefronts per workgroup: four per SIMD hide each other's waits
 constexpr int kResThreads = kResWaves * 64;
@@ -80,7 +84,8 @@ struct ResArgs {
     float lr, beta_first, beta, wd;
     int vec;              // rows of W_1 may be accessed 16 bytes at a time
     float* zx;            // [steps][G][NB][Bp][16] exchange buffer: the slices' shares of the logits, by step of the launch
-    unsigned* ctr;        // [G][MT][kCtrTile] arrivals since attach, by batch tile (every workgroup arrives once per step, whatever happens)
+    unsigned* ctr;        // [G][MT][kCtrTile] arrivals since attach, by batch tile: every workgroup arrives once per step, whatever
+                          // happens.  (One slice has nobody to wait for: nobody arrives and nobody looks)
     unsigned ctr_base;    // their value when this launch starts
     unsigned* err;        // set to 1 when a barrier wait ran out of polls
     int spin_limit;       // polls one barrier wait may take
@@ -118,7 +123,8 @@ __device__ __forceinline__ void arrive_and_wait(unsigned* ctr, unsigned target, 
 // What it orders are the shares of the logits, and those (a) have been stored through to the scope that the
 // readers share, and have arrived there (the caller waits for its stores), (b) lie in a region of the step's
 // own, whose lines nobody has read before in this launch -- and a launch begins with the caches clean -- so
-// no reader holds an older copy.  (The agent-scope acquire invalidates the L2 as well: 3000 clocks of a step
+// no reader holds an older copy.  (A share is whole cache lines of its own: kResShare, and the buffer is aligned
+// to 256 bytes.  Another layout has to keep that.  The agent-scope acquire invalidates the L2 as well: 3000 clocks of a step
 // of 42000 with one per workgroup, 10000 with one per wavefront.)
 //
 // local: the wavefronts run on one XCD, i.e. behind one L2, and counter and data need not leave it.
@@ -415,7 +421,7 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResArgs args) {
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 zp = __builtin_amdgcn_mfma_f32_16x16x4f32(w2a[i], a1[i], zp, 0, 0, 0);
-            float* px = xp + static_cast<int64_t>(cb) * (Bp * 16) + b * 16 + 4 * q;
+            float* px = xp + static_cast<int64_t>(cb) * (MT * kResShare) + b * 16 + 4 * q;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 if (a.local_xcd) __hip_atomic_store(px + r, zp[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);   // as far as the XCD's L2
@@ -435,11 +441,11 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResArgs args) {
             f32x4 z = f32x4{0.f, 0.f, 0.f, 0.f};
             {
                 const float* sx = xp + b * 16 + 4 * q;
-                f32x4 r[16];
+                f32x4 r[kResMaxSlices];
 #pragma unroll
-                for (int o = 0; o < 16; ++o) r[o] = *reinterpret_cast<const f32x4*>(sx + (o < NB ? o : 0) * (Bp * 16));
+                for (int o = 0; o < kResMaxSlices; ++o) r[o] = *reinterpret_cast<const f32x4*>(sx + (o < NB ? o : 0) * (MT * kResShare));
 #pragma unroll
-                for (int o = 0; o < 16; ++o) z += o < NB ? r[o] : f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int o = 0; o < kResMaxSlices; ++o) z += o < NB ? r[o] : f32x4{0.f, 0.f, 0.f, 0.f};
             }
             float zmax = -INFINITY;
 #pragma unroll
@@ -937,6 +943,12 @@ int compute_units() {
 
 static int resident_slices(const lc_handle* h) { return (h->layer[1].d_out + 15) / 16; }   // workgroups of a replica
 
+bool exchange_is_local(const lc_handle* h) {
+    if (h->L != 2 || !h->res_a1x || !h->res_on || !h->res_local_on || !h->res_xcc_known) return false;
+    // a replica's workgroups on one XCD, which has room for an eighth of the chip's
+    return (h->m + kXcds - 1) / kXcds * resident_slices(h) <= compute_units() / kXcds;
+}
+
 // Two layers, at most 16 classes and 64 samples, widths within the LDS budget, and few enough
 // workgroups that all of them are on the chip at the same time (one per compute unit); or one
 // layer of at most 256 (padded) inputs and 16 classes.
@@ -1057,12 +1069,8 @@ hipError_t launch_resident(lc_handle* h, int slot0, int n_steps, int period) {
     a.avx = h->res_avx;
     a.gctr = h->res_ctr + kCtrAll;
     a.gctr_base = h->res_garrivals;
-    {
-        // a replica's NB workgroups on one XCD, which has room for an eighth of the chip's
-        const int per = (a.G + kXcds - 1) / kXcds * a.NB;
-        a.local_xcd = (h->res_local_on && h->res_xcc_known && per <= compute_units() / kXcds) ? 1 : 0;
-        a.xcc_of = h->res_xcc_of;
-    }
+    a.local_xcd = exchange_is_local(h) ? 1 : 0;
+    a.xcc_of = h->res_xcc_of;
     if (slot0 < 0 || n_steps < 1 || slot0 + n_steps > S.slots) return hipErrorInvalidValue;
     if (period < 0 || (period > 0 && (n_steps % period != 0 || !h->res_avx))) return hipErrorInvalidValue;
     const int64_t total = static_cast<int64_t>(a.G) * a.NB;

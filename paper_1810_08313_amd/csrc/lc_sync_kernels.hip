@@ -13,7 +13,8 @@
 // exist in memory, and the averaging kernels skip the layer: 8 bytes per parameter and replica
 // (v_i in, v_i out) is all that moves.
 //
-// The same decomposition serves the LAST step of a longer period (OWN instances): there every
+// The same decomposition serves the LAST step of a period (OWN instances; at tau = 1 the iterations that do
+// not begin with a pending broadcast): there every
 // worker has weights of its own, so the walk reads worker i's tile of weights and of momentum (or,
 // where the momentum is implicit, of the model one step earlier), writes v_i, and adds the worker's
 // new weights to the sum -- the rows of X are not written, since the averaging step that follows
@@ -248,8 +249,9 @@ bool sync_layer_ok(const lc_handle* h, int l) {
 
 // dW_l of every replica from A_{l-1}^T and dZ_l, the update of V, and the new averaged weights of
 // the layer written over the old ones in xbar.  Inside a tau = 1 iteration whose replicas all
-// start from xbar (lc_handle::defer_x), or as the last step of a longer period whose averaging step
-// follows with the broadcast deferred (lc_handle::fuse_avg: every worker's own weights); for l > 1
+// start from xbar (lc_handle::defer_x), or as the last step of a period whose averaging step
+// follows with the broadcast deferred (lc_handle::fuse_avg: every worker's own weights, or the one
+// model where the deferred update is off); for l > 1
 // after dZ_{l-1} has been formed from the old weights (launch_backward(h, l, true)).
 hipError_t launch_sync_layer(lc_handle* h, int l) {
     const ActSet& S = h->train;

@@ -34,6 +34,7 @@ bool net_shape_ok(const lc_handle*) { return false; }
 hipError_t launch_net(lc_handle*, int, int) { return hipSuccess; }
 size_t resident_exchange_floats(const lc_handle*) { return 0; }
 hipError_t probe_block_placement(lc_handle*) { return hipSuccess; }
+bool exchange_is_local(const lc_handle*) { return false; }
 hipError_t launch_resident(lc_handle*, int, int, int) { return hipSuccess; }
 }  // namespace lc
 

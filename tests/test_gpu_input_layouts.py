@@ -1,6 +1,6 @@
 """Mini-batches in plain rows and in fragment order: a handle whose batches of 65 to 128 samples fill a block each
 takes the one for single steps and the other for periods whose first layer runs a step ahead.  Calls of both kinds
-in turn against the oracle, at the bars of test_gpu_parity.py; the last shape is too small for that and always has
+in turn against the oracle, at the bars of test_gpu_parity.py; 31 workers are too few for that and always have
 fragments."""
 import pytest
 
@@ -16,6 +16,8 @@ pytestmark = pytest.mark.gpu
     ([300, 200, 10], 64, 65),
     ([67, 132, 10], 86, 128),      # ragged rows of both operands; 258 blocks
     ([100, 512, 24, 10], 31, 120),
+    ([40, 200, 512, 10], 32, 100),  # a hidden layer, and below the last layer, read from the feature-major copy
+    ([30, 150, 10], 256, 70),
 ])
 def test_calls_of_both_kinds(pkg, orc, dims, m, B, bf16):
     _say(f"input layouts dims={dims} m={m} B={B} bf16={bf16}")

@@ -26,19 +26,21 @@ def test_steps_and_average(pkg, orc, dims, m, B, bf16):
     _say(f"resident slices dims={dims} m={m} B={B} bf16={bf16}")
     ref, run = _problem(pkg, orc, dims, m, B, wd=1e-3, bf16=bf16, lr=0.05)
     assert run.resident_active()
+    if dims[1] == 190:
+        assert not run.xcd_local_exchange_active()
     run.set_lazy_broadcast(True)
     tol = TOL16 if bf16 else TOL32
     for tau in (1, 3):
         masks = UnitMasks()
         _ref_steps(orc, ref, 11, tau, masks)
         run.local_steps(tau)
-        _check_workers(run, ref, dims, tol, f"call of {tau}", masks, over="skip")
+        _check_workers(run, ref, dims, tol, f"call of {tau}", masks, over="fail" if tau == 1 else "skip")
         _check_losses(run, ref, tol, "local losses")
         ref.average()
         run.average()
         X, _, k = run.get_state()
         assert k == ref.k
-        _assert_close(X[0], ref.X[0], dims, tol, "mean", _xmask(ref, masks.union(range(m))), over="skip")
+        _assert_close(X[0], ref.X[0], dims, tol, "mean", _xmask(ref, masks.union(range(m))), over="fail" if tau == 1 else "skip")
         assert not run.X[:, run.P:].any() and not run.V[:, run.P:].any()
         _force(run, ref)
         run.average()   # identical rows: exact; leaves the broadcast pending
@@ -49,6 +51,9 @@ def test_steps_and_average(pkg, orc, dims, m, B, bf16):
 def test_both_exchanges_give_the_same_bits(pkg, orc, dims, m, B):
     runs = [_problem(pkg, orc, dims, m, B, wd=5e-4, lr=0.05)[1] for _ in range(2)]
     runs[1].set_xcd_local_exchange(False)
+    if not runs[0].xcd_local_exchange_active():
+        pytest.skip("blocks are not dealt to the XCDs in turn here: there is one exchange only")
+    assert not runs[1].xcd_local_exchange_active()
     for r in runs:
         r.local_steps(33)   # two launches
     for got, want in zip(runs[0].get_state(), runs[1].get_state()):

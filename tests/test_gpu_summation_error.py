@@ -52,6 +52,17 @@ def test_models_on_one_compute_unit(pkg, dims, B):
     assert on < 1.1 * off
 
 
+@pytest.mark.parametrize("dims,B", [([784, 256, 10], 64), ([65, 40, 5], 33), ([1024, 130, 16], 17), ([300, 250, 2], 64),
+                                    ([64, 10], 32), ([256, 16], 64), ([100, 3], 20)])
+def test_resident_models(pkg, dims, B):
+    """The same for the two resident kernels, with more workers since a few classes leave much to chance.  (Two
+    layers: 0.8 to 0.9 of what one sum per product gave; softmax regression 0.97 to 1.03 of it.)"""
+    on = _error(pkg, dims, 16, B, 16, set_resident=True)
+    off = _error(pkg, dims, 16, B, 16, set_resident=False)
+    _say(f"error dims={dims} B={B}: resident {on:.3e}, launches per layer {off:.3e}")
+    assert on < 1.1 * off   # (three classes of 100 inputs: the same bits)
+
+
 @pytest.mark.parametrize("dims,m,B", [([2048, 500, 10], 24, 33), ([1024, 704, 10], 23, 64), ([784, 640, 10], 20, 100)])
 def test_forward_products_of_many_workers(pkg, dims, m, B):
     """The same four workers among few and among many: with more column chunks in the launch a product may
