@@ -288,9 +288,10 @@ int lc_set_implicit_momentum(lc_handle* h, int mode);
  * step; 12 instead of 20-24 bytes per parameter and replica for the two together.  Layers as for
  * the tile-owner kernel of tau = 1 (lc_set_deferred_update): 8 MB or more, rows of a multiple of
  * 64 columns, not the last layer.  Without the deferred broadcast it applies too: the broadcast then
- * waits until the call returns, and the rows of X are complete at that point.  (Not with fp32
- * operands where that is slower: above 64 samples all but calls of several iterations at tau = 1,
- * above 32 samples single iterations of models with a hidden layer of such a size.)
+ * waits until the call returns, and the rows of X are complete at that point.  (Only where that is
+ * the faster way: several iterations at tau = 1; or a first layer by tile of at least a third of the model, not with
+ * fp32 operands above 64 samples; or several periods of at least 4 workers with bf16 operands or up to 32
+ * samples.  In a call of one period the hidden layers' rows are written.)
  *   mode 1: the first layer (it needs no deltas for a layer below);
  *   mode 2 (default): the hidden layers too (after a pass over the old weights that forms the
  *           deltas of the layer below);

@@ -215,7 +215,7 @@ int one_local_step(lc_handle* h, bool next_gathered, bool implicit_out = false) 
         for (int l = head_is_fused(h) ? h->L - 1 : h->L; l >= 1; --l) {
             if (l == 1 && first_fused) {
                 LC_HIP(h, launch_first_layer(h));
-            } else if ((h->defer_x || (h->fuse_avg && (l == 1 || h->fuse_avg_on > 1))) && sync_layer_ok(h, l)) {
+            } else if ((h->defer_x || (h->fuse_avg && (l == 1 || (h->fuse_avg_on > 1 && h->fuse_hidden)))) && sync_layer_ok(h, l)) {
                 if (l > 1) LC_HIP(h, launch_backward(h, l, true));   // dZ_{l-1} from the weights of before the update
                 LC_HIP(h, launch_sync_layer(h, l));   // dW_l, V, and the layer's part of the averaging step
                 h->sync_done |= 1u << l;
@@ -258,21 +258,27 @@ int whole_periods(int64_t k, int tau, int64_t lim, int64_t k_end) {
 // A caller who wants every row written gets them at the end of the call: in between nobody sees them, and
 // where large layers take their averaging step by tile the broadcast may as well wait (bf16: 8 workers of
 // 3072-1536-1024-10, batch 64, a period of 5, 1078 -> 984 us; 64 of 3072-2048-2048-2048-10, batch 32, 4
-// iterations at tau = 1, 18.6 -> 8.9 ms).  Whether it pays, from 784 calls (4 models of 1 and 2 hidden layers, 2 to 32
-// workers): bf16 always, 1.01 to 2.0 times as fast.  With fp32 operands the pass by tile is bound by its products:
-//   65 to 128 samples: iterations at tau = 1 after the first of a call, 1.07 to 1.17; else 0.95 to 1.05, below 1 for most
-//   33 to 64 samples: a single iteration with a hidden layer by tile 0.97 to 1.01; else 1.00 to 1.43
-//   up to 32 samples: 1.02 to 1.6
+// iterations at tau = 1, 18.6 -> 8.9 ms).  Whether it pays, from 2200 calls (9 models of 1 to 4 hidden layers, 2 to
+// 32 workers) both ways:
+//   several iterations at tau = 1: 1.00 to 2.0 times as fast (fp32, 33 to 64 samples, only hidden layers by
+//     tile: from three on, two 0.99 to 1.15)
+//   else it is layer 1 that gains, which needs no deltas for a layer below.  At a third of the model and more
+//     0.99 to 1.37, at less 0.96 to 1.15; but with fp32 operands above 64 samples the pass by tile is bound by its
+//     products: 0.95 to 1.04
+//   without that, several periods 1.00 to 1.4 (bf16, or up to 32 samples; 2 workers 0.98), else 0.95 to 1.05; one
+//     period 0.90 to 1.14
+// In calls of one period the hidden layers go the other way (fuse_hidden): by tile they cost such a call up to 11 %
+// with few workers.
 bool rows_may_wait(const lc_handle* h, int tau, int n_periods) {
-    bool any = false, hidden = false;
-    for (int l = 1; l < h->L; ++l) {
-        const bool by_tile = sync_layer_ok(h, l);
-        any = any || by_tile;
-        hidden = hidden || (by_tile && l > 1);
-    }
-    if (!any || h->md.gemm == LC_GEMM_BF16 || h->train.Bp == 32) return any;
-    if (h->train.Bp == 128) return tau == 1 && n_periods > 1;
-    return tau > 1 || n_periods > 1 || !hidden;
+    bool any = false;
+    for (int l = 1; l < h->L; ++l) any = any || sync_layer_ok(h, l);
+    if (!any) return false;
+    const bool first = sync_layer_ok(h, 1) && 3 * static_cast<int64_t>(h->layer[1].d_in) * h->layer[1].d_out >= h->P;
+    const bool fp32 = h->md.gemm != LC_GEMM_BF16;
+    const int Bp = h->train.Bp;
+    if (tau == 1 && n_periods > 1) return !(fp32 && Bp == 64) || first || n_periods > 2;
+    if (first) return !(fp32 && Bp == 128);
+    return n_periods > 1 && h->m >= 4 && !(fp32 && Bp > 32);
 }
 
 // tau local iterations, n_periods times, with the averaging step after each period where asked.
@@ -288,17 +294,17 @@ int run_periods(lc_handle* h, int tau, int n_periods, bool average) {
     if (mlp) h->a0_layout = input_layout(h, tau > 1);
     const bool defer_ok = mlp && !resident && average && tau == 1 && h->defer_x_on && h->lazy_enabled &&
                           !h->bm_on && !head_is_fused(h);
-    const bool fuse_ok = mlp && !resident && average && h->fuse_avg_on && h->lazy_enabled && !h->bm_on &&
-                         h->m >= 2 && !head_is_fused(h);
+    const bool fuse_ok = mlp && !resident && average && h->fuse_avg_on && (tau > 1 || h->defer_x_on) && h->lazy_enabled &&
+                         !h->bm_on && h->m >= 2 && !head_is_fused(h);
     if (mlp && !resident && average && !h->lazy_enabled && !h->bm_on && h->m >= 2 && !head_is_fused(h) &&
-        (h->fuse_avg_on || (tau == 1 && h->defer_x_on))) {
-        if (rows_may_wait(h, tau, n_periods)) {
-            h->lazy_enabled = true;
-            const int r = run_periods(h, tau, n_periods, average);
-            h->lazy_enabled = false;
-            const int w = materialise(h);   // also where the call failed: its caller reads the rows, not xbar
-            return r != LC_OK ? r : w;
-        }
+        (tau == 1 ? h->defer_x_on && (h->fuse_avg_on || n_periods > 1) : h->fuse_avg_on > 0) && rows_may_wait(h, tau, n_periods)) {
+        h->lazy_enabled = true;
+        h->fuse_hidden = n_periods > 1;
+        const int r = run_periods(h, tau, n_periods, average);
+        h->lazy_enabled = false;
+        h->fuse_hidden = true;
+        const int w = materialise(h);   // also where the call failed: its caller reads the rows, not xbar
+        return r != LC_OK ? r : w;
     }
     int64_t left = static_cast<int64_t>(tau) * n_periods;
     int pos = 0;   // steps of the current period already taken
@@ -478,6 +484,7 @@ int lc_init(int m, int64_t P, const lc_model* md, uint64_t seed, lc_handle** out
     h->sync1_on = h->sync_all_on = true;
     h->fuse_avg_on = 2;
     h->fuse_avg = false;
+    h->fuse_hidden = true;
     if (const char* e = getenv("LC_SYNC_FIRST_LAYER")) {   // tuning knob for measurement runs: 0 off, 1 layer 1 only
         h->sync1_on = atoi(e) != 0;
         h->sync_all_on = atoi(e) > 1;

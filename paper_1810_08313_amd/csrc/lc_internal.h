@@ -139,6 +139,7 @@ struct lc_handle {
     // stay unwritten).  fuse_avg is set only while run_periods takes such a step and its averaging step.
     int fuse_avg_on;              // 0 off, 1 the first layer, 2 the large hidden layers as well
     bool fuse_avg;
+    bool fuse_hidden;             // false while a call of one period runs whose rows are written at its end: layer 1 only
     bool share_w_on;          // block order of the steps that read one model for all replicas (see FwdArgs)
     bool group_shared_on;     // ... and several replicas' batches per block in them (see FwdArgs::fm_Bp)
     int share_w_set;          // ... replicas per set

@@ -1208,14 +1208,14 @@ def test_shared_model_block_order_against_oracle(pkg, orc, bf16, m, d0, d1, tau,
 def test_deferred_update_with_chunked_averaging(pkg, orc):
     """The same on a state above 512 MB, where the averaging step is the chunked reduce kernel: against the
     run that writes the rows of every layer and averages them with that kernel, bit for bit (that run is held
-    to the oracle elsewhere).  Third run: every iteration by tile from the one model a pending broadcast left."""
+    to the oracle elsewhere)."""
     dims, m, B = [8192, 8320, 10], 2, 32
     _say("deferred update, chunked averaging")
     data, labels = synth.gaussian_mixture(5, 200, dims[0], dims[-1], mean_sd=1.0)
     data = synth.bf16_representable(data)
     x1 = synth.init_params(5, dims)
     out = []
-    for deferred, fused in ((False, 0), (True, 2), (False, 2)):
+    for deferred, fused in ((False, 0), (True, 2)):
         md = pkg.make_model(pkg.KIND_MLP, dims, B=B, N=200, E=100, lr=0.05, beta=0.9, wd=1e-4, bf16=True)
         run = pkg.LocalSGD(m, md, 5, x1, data, labels)
         run.set_lazy_broadcast(True)

@@ -79,9 +79,11 @@ def test_hidden_layer_by_tile(pkg, orc, B, tau, periods, lazy, bf16):
     if not lazy:   # they had been there when the call returned
         assert np.array_equal(rows, runs[0].get_state()[0])
     by_tile = _tile_launches(runs[0], tau, periods)
-    if lazy or bf16 or B == 20 or (tau == 1 and periods > 1):
+    if lazy or periods > 1:
         assert by_tile == [periods, periods]
-    else:   # fp32, more than 64 samples: not for a single iteration or the end of a longer period
+    elif bf16 or B == 20:   # rows written at the end of the call: one period, layer 1 only
+        assert by_tile == [1, 0]
+    else:                   # fp32, more than 64 samples
         assert by_tile == [0, 0]
     assert _tile_launches(runs[1], tau, periods) == [0, 0]
     for r in runs:
