@@ -169,7 +169,8 @@ int lc_average(lc_handle* h);
  * momentum is on.  Afterwards every row of X holds the averaged model.  Asynchronous.
  * Without the deferred broadcast (lc_set_lazy_broadcast) the rows are nevertheless written only at the
  * end of the call where a large layer takes its averaging step by tile (lc_set_fused_averaging,
- * lc_set_deferred_update); a call that fails half-way writes them too, before it returns.
+ * lc_set_deferred_update); a call that fails half-way writes them too, before it returns.  (Iterations at
+ * tau = 1 then start from one shared model, and agree with separate calls as lc_set_lazy_broadcast says.)
  * Errors: LC_ERR_ARG (tau < 1 or n_periods < 1), LC_ERR_STATE, LC_ERR_HIP. */
 int lc_local_periods(lc_handle* h, int tau, int n_periods);
 

@@ -187,7 +187,7 @@ __device__ __forceinline__ float softmax_of_sample(float* z, int u, int d_out, i
 // than that sit idle and make more passes over the samples; fewer walk the classes one after the other.  Whole
 // steps, bf16, with one thread per sample at any number of classes / 16 lanes / this: 1024-2, 64 workers of 128 samples,
 // 30.8 / 31.6 / 29.9 us; 1024-10 35.7 / 35.1 / 33.6; 100-2, 4 workers (head_kernel) 21.0 / 18.7 / 14.2; 100-10 22.6 /
-// 20.5 / 16.3; 17 classes and more take 16 lanes (1024-64 18 to 30 % faster than one thread).
+// 20.5 / 16.3; 17 classes and more take 16 lanes (1024-64: steps 1.2 to 1.6 times as fast as with one thread).
 template <typename F>
 __device__ __forceinline__ void with_lanes_per_sample(int d_out, F&& f) {
     if (d_out <= 4) f(std::integral_constant<int, 1>{});
