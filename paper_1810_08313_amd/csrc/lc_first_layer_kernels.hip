@@ -27,6 +27,12 @@ namespace lc {
 
 namespace {
 
+// Wavefronts of a workgroup.  Up to 64 samples two workgroups share a CU; where the whole grid is no more than one
+// per CU, fp32 operands at 33 to 64 samples take twice as many, since such a wavefront requests nothing ahead (see
+// FlBudget) and its matrix instructions, 40 % of the time, need another one's loads under way beside them.  Five steps with
+// four and eight: 3072-1024-1024-10, 16 workers of 64, 1894 and 1817 us (the launch 211 and 194); 1500-800-800-10, 16 of 50,
+// 1255 and 1150; 784-1000-300-10, 14 of 64, 670 and 633; 300-1024-10, 12 of 60, 264 and 258; but 128 inputs, one step of the
+// walk per wavefront, 276 and 279.  bf16 operands and up to 32 samples, which have a step ahead: 0.99 to 1.04 times as fast.
 constexpr int kFlWaves = 4;
 
 struct FirstArgs {
@@ -67,8 +73,8 @@ struct FlBudget {
     static constexpr int kAhead = (NT == 4 && sizeof(OT) == 4) ? 0 : 1;
 };
 
-// One workgroup = one replica x 64 columns of W_1; its 4 wavefronts take the 16-row steps
-// wave, wave + 4, ... and never synchronise inside the walk: the dZ_1 slice is staged once, the
+// One workgroup = one replica x 64 columns of W_1; its NW wavefronts take the 16-row steps
+// wave, wave + NW, ... and never synchronise inside the walk: the dZ_1 slice is staged once, the
 // A_0 tiles go from memory straight into operand registers.  The loads of a wavefront's next PD
 // steps are in flight while it works on the current one (PD + 1 register sets, addressed
 // statically); a step is small enough (about 20 memory instructions with its stores) that the
@@ -82,15 +88,15 @@ struct FlBudget {
 // the weights read: cached where all replicas read one model, which the neighbouring blocks want in
 // the L2.  (A template parameter, not a run-time flag: with the choice made per load the compiler
 // waited for each load before it issued the next.)
-template <typename OT, int NT, int WM, int WMR>
-__global__ __launch_bounds__(256, (FlBudget<OT, NT>::kWavesPerSimd)) void first_layer_kernel(FirstArgs a) {
+template <typename OT, int NT, int WM, int WMR, int NW>
+__global__ __launch_bounds__(64 * NW, (FlBudget<OT, NT>::kWavesPerSimd)) void first_layer_kernel(FirstArgs a) {
     constexpr int kPad = sizeof(OT) == 2 ? 8 : 4;
     constexpr int Bp = 16 * NT;
     constexpr int NS = Bp / 32;
     constexpr int PD = FlBudget<OT, NT>::kAhead;
     // the dZ^T slice during the walk; the wavefronts' partial Z_1' tiles after it
     constexpr size_t kSliceBytes = sizeof(OT) * kColChunk * (Bp + kPad);
-    constexpr size_t kPartBytes = sizeof(float) * kFlWaves * Bp * (kColChunk + 4);
+    constexpr size_t kPartBytes = sizeof(float) * NW * Bp * (kColChunk + 4);
     __shared__ __attribute__((aligned(16))) char smem[kSliceBytes > kPartBytes ? kSliceBytes : kPartBytes];
     __shared__ float bias_s[kColChunk];
     // row (c % 4) * 16 + c / 4 holds column c0 + c: the 16 lanes of an operand read (columns
@@ -170,10 +176,10 @@ __global__ __launch_bounds__(256, (FlBudget<OT, NT>::kWavesPerSimd)) void first_
 
     // first loads, then the staging of the slice (its own round trip overlaps with them)
 #pragma unroll
-    for (int p = 0; p < PD; ++p) load_step(wave + p * kFlWaves, set[p]);
+    for (int p = 0; p < PD; ++p) load_step(wave + p * NW, set[p]);
     {
         const OT* ZT = static_cast<const OT*>(a.dz_fm) + (static_cast<int64_t>(g) * a.dp_out + c0) * Bp;
-        for (int p = tid; p < kColChunk * (Bp / 8); p += 256) {
+        for (int p = tid; p < kColChunk * (Bp / 8); p += 64 * NW) {
             const int c = p / (Bp / 8), seg = p % (Bp / 8);
             *reinterpret_cast<Frag<OT>*>(&dzt[(c & 3) * 16 + (c >> 2)][seg * 8]) = load8(ZT + static_cast<int64_t>(p) * 8);
         }
@@ -259,18 +265,18 @@ __global__ __launch_bounds__(256, (FlBudget<OT, NT>::kWavesPerSimd)) void first_
     // groups of PD + 1 steps without control flow in between (a branch would make the compiler
     // drain the loads in flight where the paths meet), then the steps whose loads are under way
     int s0 = wave;
-    for (; s0 + PD * kFlWaves < n_steps; s0 += kFlWaves * (PD + 1)) {
+    for (; s0 + PD * NW < n_steps; s0 += NW * (PD + 1)) {
 #pragma unroll
         for (int u = 0; u <= PD; ++u) {
-            const int s = s0 + u * kFlWaves;
-            load_step(s + PD * kFlWaves, set[(u + PD) % (PD + 1)]);
+            const int s = s0 + u * NW;
+            load_step(s + PD * NW, set[(u + PD) % (PD + 1)]);
             process(s, set[u]);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
 #pragma unroll
     for (int u = 0; u < PD; ++u) {
-        const int s = s0 + u * kFlWaves;
+        const int s = s0 + u * NW;
         if (s < n_steps) process(s, set[u]);   // uniform over the wavefront
     }
 
@@ -284,11 +290,11 @@ __global__ __launch_bounds__(256, (FlBudget<OT, NT>::kWavesPerSimd)) void first_
             *reinterpret_cast<float4*>(&part[wave][16 * mt + 4 * q + r][4 * j]) =
                 make_float4(facc[mt][0][r], facc[mt][1][r], facc[mt][2][r], facc[mt][3][r]);
     __syncthreads();
-    for (int f = tid; f < Bp * (kColChunk / 4); f += 256) {
+    for (int f = tid; f < Bp * (kColChunk / 4); f += 64 * NW) {
         const int b = f / (kColChunk / 4), c4 = (f % (kColChunk / 4)) * 4;
         float4 z = *reinterpret_cast<const float4*>(&part[0][b][c4]);
 #pragma unroll
-        for (int wv = 1; wv < kFlWaves; ++wv) {
+        for (int wv = 1; wv < NW; ++wv) {
             const float4 o = *reinterpret_cast<const float4*>(&part[wv][b][c4]);
             z.x += o.x; z.y += o.y; z.z += o.z; z.w += o.w;
         }
@@ -303,7 +309,7 @@ __global__ __launch_bounds__(256, (FlBudget<OT, NT>::kWavesPerSimd)) void first_
     // 8 outputs per thread and pass, one vector store each: along the columns for the
     // batch-major copy, along the batch for the feature-major one; only batch rows below B
     // are written, so the zero padding of the buffers is preserved
-    for (int e = tid; e < Bp * (kColChunk / 8); e += 256) {
+    for (int e = tid; e < Bp * (kColChunk / 8); e += 64 * NW) {
         const int b = e / (kColChunk / 8), cl = (e % (kColChunk / 8)) * 8;
         if (b >= a.B) continue;
         float y[8];   // (columns that do not exist keep the zeros of the padding)
@@ -311,7 +317,7 @@ __global__ __launch_bounds__(256, (FlBudget<OT, NT>::kWavesPerSimd)) void first_
         for (int i = 0; i < 8; ++i) y[i] = (!RAG || c0 + cl + i < a.d_out) ? value(b, cl + i) : 0.f;
         store8(obm + static_cast<int64_t>(b) * a.dp_out + c0 + cl, y);
     }
-    for (int e = tid; e < kColChunk * (Bp / 8); e += 256) {
+    for (int e = tid; e < kColChunk * (Bp / 8); e += 64 * NW) {
         const int c = e / (Bp / 8), bl = (e % (Bp / 8)) * 8;
         if (bl >= a.B || (RAG && c0 + c >= a.d_out)) continue;
         float y[8];
@@ -578,18 +584,31 @@ __global__ __launch_bounds__(64 * kWideWaves) void first_layer_wide_kernel(First
 // whole 64-column chunks of 16-byte aligned rows, and whole 16-row steps
 bool whole_tiles(const FirstArgs& a) { return a.d_out % kColChunk == 0 && a.w_off % 4 == 0 && a.d_in % 16 == 0; }
 
-template <typename OT, int NT>
-void launch_fl_wm(const FirstArgs& a, bool stream_w, unsigned grid, hipStream_t st) {
+template <typename OT, int NT, int NW>
+void launch_fl_nw(const FirstArgs& a, bool stream_w, unsigned grid, hipStream_t st) {
+    const dim3 block(64 * NW);
     if constexpr (NT < 8) {   // (at 128 samples other layers go to the wide kernel)
         if (!whole_tiles(a)) {
-            hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWRagged, kWRagged>), dim3(grid), dim3(256), 0, st, a);
+            hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWRagged, kWRagged, NW>), dim3(grid), block, 0, st, a);
             return;
         }
     }
     if (stream_w && !a.shared_w)
-        hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWVectorStream, kWVectorStream>), dim3(grid), dim3(256), 0, st, a);
-    else if (stream_w) hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWVectorStream, kWVector>), dim3(grid), dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWVector, kWVector>), dim3(grid), dim3(256), 0, st, a);
+        hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWVectorStream, kWVectorStream, NW>), dim3(grid), block, 0, st, a);
+    else if (stream_w) hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWVectorStream, kWVector, NW>), dim3(grid), block, 0, st, a);
+    else hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWVector, kWVector, NW>), dim3(grid), block, 0, st, a);
+}
+
+template <typename OT, int NT>
+void launch_fl_wm(const FirstArgs& a, bool stream_w, unsigned grid, hipStream_t st) {
+    // (eight wavefronts: see kFlWaves)
+    if constexpr (NT == 4 && sizeof(OT) == 4) {
+        if (a.total_blocks <= compute_units() && a.d_in >= 256) {
+            launch_fl_nw<OT, NT, 2 * kFlWaves>(a, stream_w, grid, st);
+            return;
+        }
+    }
+    launch_fl_nw<OT, NT, kFlWaves>(a, stream_w, grid, st);
 }
 
 template <typename OT>
