@@ -29,10 +29,10 @@ namespace {
 
 // Wavefronts of a workgroup.  Up to 64 samples two workgroups share a CU; where the whole grid is no more than one
 // per CU, fp32 operands at 33 to 64 samples take twice as many, since such a wavefront requests nothing ahead (see
-// FlBudget) and its matrix instructions, 40 % of the time, need another one's loads under way beside them.  Five steps with
-// four and eight: 3072-1024-1024-10, 16 workers of 64, 1894 and 1817 us (the launch 211 and 194); 1500-800-800-10, 16 of 50,
-// 1255 and 1150; 784-1000-300-10, 14 of 64, 670 and 633; 300-1024-10, 12 of 60, 264 and 258; but 128 inputs, one step of the
-// walk per wavefront, 276 and 279.  bf16 operands and up to 32 samples, which have a step ahead: 0.99 to 1.04 times as fast.
+// FlBudget) and needs another one's loads under way beside its matrix instructions.  Five steps with four and eight
+// (the products on the fp32 instructions): 3072-1024-1024-10, 16 workers of 64, 1894 and 1817 us (the launch 211 and 194);
+// 1500-800-800-10, 16 of 50, 1255 and 1150; 784-1000-300-10, 14 of 64, 670 and 633; 300-1024-10, 12 of 60, 264 and 258; but
+// 128 inputs, one step of the walk per wavefront, 276 and 279.  bf16 operands and up to 32 samples, which have a step ahead: 0.99 to 1.04 times as fast.
 constexpr int kFlWaves = 4;
 
 struct FirstArgs {
@@ -88,20 +88,25 @@ struct FlBudget {
 // the weights read: cached where all replicas read one model, which the neighbouring blocks want in
 // the L2.  (A template parameter, not a run-time flag: with the choice made per load the compiler
 // waited for each load before it issued the next.)
-template <typename OT, int NT, int WM, int WMR, int NW>
+// SPLIT (fp32 operands, see split_products): all products of bf16 parts.
+template <typename OT, int NT, int WM, int WMR, int NW, bool SPLIT>
 __global__ __launch_bounds__(64 * NW, (FlBudget<OT, NT>::kWavesPerSimd)) void first_layer_kernel(FirstArgs a) {
-    constexpr int kPad = sizeof(OT) == 2 ? 8 : 4;
+    static_assert(!SPLIT || sizeof(OT) == 4, "see split_products");
+    using LT = std::conditional_t<SPLIT, bf16_t, OT>;   // what LDS holds
+    constexpr int NP = SPLIT ? 3 : 1;
+    constexpr int kPad = sizeof(LT) == 2 ? 8 : 4;
     constexpr int Bp = 16 * NT;
     constexpr int NS = Bp / 32;
     constexpr int PD = FlBudget<OT, NT>::kAhead;
     // the dZ^T slice during the walk; the wavefronts' partial Z_1' tiles after it
-    constexpr size_t kSliceBytes = sizeof(OT) * kColChunk * (Bp + kPad);
+    constexpr size_t kSliceBytes = sizeof(LT) * NP * kColChunk * (Bp + kPad);
     constexpr size_t kPartBytes = sizeof(float) * NW * Bp * (kColChunk + 4);
     __shared__ __attribute__((aligned(16))) char smem[kSliceBytes > kPartBytes ? kSliceBytes : kPartBytes];
     __shared__ float bias_s[kColChunk];
     // row (c % 4) * 16 + c / 4 holds column c0 + c: the 16 lanes of an operand read (columns
     // 4 j + t) then hit 16 consecutive LDS rows
-    OT (*dzt)[Bp + kPad] = reinterpret_cast<OT (*)[Bp + kPad]>(smem);
+    LT (*dzt)[kColChunk][Bp + kPad] = reinterpret_cast<LT (*)[kColChunk][Bp + kPad]>(smem);
+    __shared__ int huge_s[NW];   // by wavefront: it staged a delta above kMaxSplit
 
     const int64_t logical = xcd_logical_block(a.total_blocks);
     if (logical < 0) return;
@@ -177,23 +182,49 @@ __global__ __launch_bounds__(64 * NW, (FlBudget<OT, NT>::kWavesPerSimd)) void fi
     // first loads, then the staging of the slice (its own round trip overlaps with them)
 #pragma unroll
     for (int p = 0; p < PD; ++p) load_step(wave + p * NW, set[p]);
+    const OT* ZT = static_cast<const OT*>(a.dz_fm) + (static_cast<int64_t>(g) * a.dp_out + c0) * Bp;
     {
-        const OT* ZT = static_cast<const OT*>(a.dz_fm) + (static_cast<int64_t>(g) * a.dp_out + c0) * Bp;
+        float m = 0.f;
         for (int p = tid; p < kColChunk * (Bp / 8); p += 64 * NW) {
-            const int c = p / (Bp / 8), seg = p % (Bp / 8);
-            *reinterpret_cast<Frag<OT>*>(&dzt[(c & 3) * 16 + (c >> 2)][seg * 8]) = load8(ZT + static_cast<int64_t>(p) * 8);
+            const int c = p / (Bp / 8), seg = p % (Bp / 8), row = (c & 3) * 16 + (c >> 2);
+            const Frag<OT> f = load8(ZT + static_cast<int64_t>(p) * 8);
+            if constexpr (SPLIT) {
+                const Parts x = split8(f.v);
+#pragma unroll
+                for (int i = 0; i < 3; ++i) *reinterpret_cast<bf16x8*>(&dzt[i][row][seg * 8]) = x.p[i];
+                m = fmaxf(m, largest(f.v));
+            } else {
+                *reinterpret_cast<Frag<OT>*>(&dzt[0][row][seg * 8]) = f;
+            }
         }
+        const bool huge = __any(m > kMaxSplit);
+        if (SPLIT && lane == 0) huge_s[wave] = huge;
     }
     __syncthreads();
+    bool huge_dz = false;
+    if constexpr (SPLIT) {
+        int any = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) any |= huge_s[w];
+        huge_dz = __builtin_amdgcn_readfirstlane(any) != 0;
+    }
     // bias of these columns: db_1 = sum_b dZ_1, the same update; kept for the forward epilogue
     if (tid < kColChunk && (WM != kWRagged || c0 + tid < a.d_out)) {
         float* bx = a.X + g * a.x_stride + a.b_off + c0 + tid;
         const float x = a.Xr[g * a.xr_stride + a.b_off + c0 + tid];
         float vb0 = a.Aux[g * a.aux_stride + a.b_off + c0 + tid];
         if (a.imp_in) vb0 = (vb0 - x) * a.inv_lr;
-        const OT* zr = dzt[(tid & 3) * 16 + (tid >> 2)];
+        const int row = (tid & 3) * 16 + (tid >> 2);
         float sb = 0.f;
-        for (int b = 0; b < a.B; ++b) sb += to_f32(zr[b]);
+        if (SPLIT && huge_dz) {
+            for (int b = 0; b < a.B; ++b) sb += to_f32(ZT[tid * Bp + b]);
+        } else {
+            for (int b = 0; b < a.B; ++b) {
+                float z = to_f32(dzt[0][row][b]);
+                if constexpr (SPLIT) z = (z + to_f32(dzt[1][row][b])) + to_f32(dzt[2][row][b]);
+                sb += z;
+            }
+        }
         const float vb = a.beta * vb0 + (sb + a.wd * x);
         if (a.V) a.V[g * a.x_stride + a.b_off + c0 + tid] = vb;
         *bx = x - a.lr * vb;
@@ -213,13 +244,39 @@ __global__ __launch_bounds__(64 * NW, (FlBudget<OT, NT>::kWavesPerSimd)) void fi
         f32x4 acc[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        bool huge = huge_dz;
+        if constexpr (SPLIT) {
+            float m = 0.f;
 #pragma unroll
-        for (int st = 0; st < NS; ++st)
+            for (int st = 0; st < NS; ++st) m = fmaxf(m, largest(x.af[st].v));
+            huge = huge || __any(m > kMaxSplit);
+        }
+        if (SPLIT && huge) {
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const Frag<OT> zf = *reinterpret_cast<const Frag<OT>*>(&dzt[t * 16 + j][32 * st + 8 * q]);
-                acc[t] = mma8(x.af[st], zf, acc[t]);
+            for (int st = 0; st < NS; ++st)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) acc[t] = mma8(x.af[st], load8(ZT + (4 * j + t) * Bp + 32 * st + 8 * q), acc[t]);
+        } else {
+#pragma unroll
+            for (int st = 0; st < NS; ++st) {
+                if constexpr (SPLIT) {
+                    const Parts af = split8(x.af[st].v);
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        Parts zf;
+#pragma unroll
+                        for (int i = 0; i < 3; ++i) zf.p[i] = *reinterpret_cast<const bf16x8*>(&dzt[i][t * 16 + j][32 * st + 8 * q]);
+                        acc[t] = mma8(af, zf, acc[t]);
+                    }
+                } else {
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const Frag<OT> zf = *reinterpret_cast<const Frag<OT>*>(&dzt[0][t * 16 + j][32 * st + 8 * q]);
+                        acc[t] = mma8(x.af[st], zf, acc[t]);
+                    }
+                }
             }
+        }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             consume_here(x.w[r]);
@@ -247,6 +304,24 @@ __global__ __launch_bounds__(64 * NW, (FlBudget<OT, NT>::kWavesPerSimd)) void fi
             }
         }
         // Z_1' += A_0'[:, k0 .. k0+15] W_1[k0 .. k0+15, :] with the tile just updated
+        if constexpr (SPLIT) {
+            float m = 0.f;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) m = fmaxf(m, largest<4>({x.w[r].x, x.w[r].y, x.w[r].z, x.w[r].w}));
+#pragma unroll
+            for (int mt = 0; mt < NT; ++mt) m = fmaxf(m, largest(x.an[mt].v));
+            if (!__any(m > kMaxSplit)) {
+                const Parts4 wp[4] = {split4(x.w[0].x, x.w[1].x, x.w[2].x, x.w[3].x), split4(x.w[0].y, x.w[1].y, x.w[2].y, x.w[3].y),
+                                      split4(x.w[0].z, x.w[1].z, x.w[2].z, x.w[3].z), split4(x.w[0].w, x.w[1].w, x.w[2].w, x.w[3].w)};
+#pragma unroll
+                for (int mt = 0; mt < NT; ++mt) {
+                    const Parts4 an = split4(x.an[mt].v[0], x.an[mt].v[1], x.an[mt].v[2], x.an[mt].v[3]);
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) facc[mt][t] = mma4(an, wp[t], facc[mt][t]);
+                }
+                return;
+            }
+        }
         Frag4<OT> bf;
         pack4(bf, x.w[0].x, x.w[1].x, x.w[2].x, x.w[3].x);
 #pragma unroll
@@ -584,44 +659,45 @@ __global__ __launch_bounds__(64 * kWideWaves) void first_layer_wide_kernel(First
 // whole 64-column chunks of 16-byte aligned rows, and whole 16-row steps
 bool whole_tiles(const FirstArgs& a) { return a.d_out % kColChunk == 0 && a.w_off % 4 == 0 && a.d_in % 16 == 0; }
 
-template <typename OT, int NT, int NW>
+template <typename OT, int NT, int NW, bool SPLIT>
 void launch_fl_nw(const FirstArgs& a, bool stream_w, unsigned grid, hipStream_t st) {
     const dim3 block(64 * NW);
     if constexpr (NT < 8) {   // (at 128 samples other layers go to the wide kernel)
         if (!whole_tiles(a)) {
-            hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWRagged, kWRagged, NW>), dim3(grid), block, 0, st, a);
+            hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWRagged, kWRagged, NW, SPLIT>), dim3(grid), block, 0, st, a);
             return;
         }
     }
     if (stream_w && !a.shared_w)
-        hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWVectorStream, kWVectorStream, NW>), dim3(grid), block, 0, st, a);
-    else if (stream_w) hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWVectorStream, kWVector, NW>), dim3(grid), block, 0, st, a);
-    else hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWVector, kWVector, NW>), dim3(grid), block, 0, st, a);
+        hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWVectorStream, kWVectorStream, NW, SPLIT>), dim3(grid), block, 0, st, a);
+    else if (stream_w) hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWVectorStream, kWVector, NW, SPLIT>), dim3(grid), block, 0, st, a);
+    else hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWVector, kWVector, NW, SPLIT>), dim3(grid), block, 0, st, a);
 }
 
 template <typename OT, int NT>
-void launch_fl_wm(const FirstArgs& a, bool stream_w, unsigned grid, hipStream_t st) {
-    // (eight wavefronts: see kFlWaves)
+void launch_fl_wm(const FirstArgs& a, bool split, bool stream_w, unsigned grid, hipStream_t st) {
     if constexpr (NT == 4 && sizeof(OT) == 4) {
-        if (a.total_blocks <= compute_units() && a.d_in >= 256) {
-            launch_fl_nw<OT, NT, 2 * kFlWaves>(a, stream_w, grid, st);
-            return;
-        }
+        const bool eight = a.total_blocks <= compute_units() && a.d_in >= 256;   // (see kFlWaves)
+        if (eight && split) launch_fl_nw<OT, NT, 2 * kFlWaves, true>(a, stream_w, grid, st);
+        else if (eight) launch_fl_nw<OT, NT, 2 * kFlWaves, false>(a, stream_w, grid, st);
+        else if (split) launch_fl_nw<OT, NT, kFlWaves, true>(a, stream_w, grid, st);
+        else launch_fl_nw<OT, NT, kFlWaves, false>(a, stream_w, grid, st);
+    } else {
+        launch_fl_nw<OT, NT, kFlWaves, false>(a, stream_w, grid, st);
     }
-    launch_fl_nw<OT, NT, kFlWaves>(a, stream_w, grid, st);
 }
 
 template <typename OT>
-hipError_t launch_fl(const FirstArgs& a, int nt, bool stream_w, unsigned grid, hipStream_t st) {
-    if (nt == 2) launch_fl_wm<OT, 2>(a, stream_w, grid, st);
-    else if (nt == 4) launch_fl_wm<OT, 4>(a, stream_w, grid, st);
+hipError_t launch_fl(const FirstArgs& a, int nt, bool split, bool stream_w, unsigned grid, hipStream_t st) {
+    if (nt == 2) launch_fl_wm<OT, 2>(a, split, stream_w, grid, st);
+    else if (nt == 4) launch_fl_wm<OT, 4>(a, split, stream_w, grid, st);
     else if constexpr (sizeof(OT) == 2) {
         // 128 samples.  (Whole tiles whose height is no multiple of the 128 rows that the wide kernel's
         // wavefronts take together stay with the other one: cut off as ragged rows are, they run 0.94 ..
         // 1.0 times as fast up to 784 inputs of a cached state, 1.0 .. 1.03 from 1040 inputs on.)
         const dim3 block(64 * kWideWaves);
         if (!whole_tiles(a)) hipLaunchKernelGGL((first_layer_wide_kernel<OT, kWRagged, kWRagged>), dim3(grid), block, 0, st, a);
-        else if (a.d_in % (16 * kWideWaves) != 0) launch_fl_wm<OT, 8>(a, stream_w, grid, st);
+        else if (a.d_in % (16 * kWideWaves) != 0) launch_fl_wm<OT, 8>(a, split, stream_w, grid, st);
         else if (stream_w && !a.shared_w)
             hipLaunchKernelGGL((first_layer_wide_kernel<OT, kWVectorStream, kWVectorStream>), dim3(grid), block, 0, st, a);
         else if (stream_w) hipLaunchKernelGGL((first_layer_wide_kernel<OT, kWVectorStream, kWVector>), dim3(grid), block, 0, st, a);
@@ -709,8 +785,8 @@ hipError_t launch_first_layer(lc_handle* h) {
     a.total_blocks = static_cast<int64_t>(S.G) * a.n_chunks;
     const unsigned grid = static_cast<unsigned>((a.total_blocks + kXcds - 1) / kXcds * kXcds);
     timing_start(h, kTimeBwd, 1, kBwdFirstLayer);
-    const hipError_t e = bf16 ? launch_fl<bf16_t>(a, S.Bp / 16, h->stream_weights, grid, h->stream)
-                              : launch_fl<float>(a, S.Bp / 16, h->stream_weights, grid, h->stream);
+    const hipError_t e = bf16 ? launch_fl<bf16_t>(a, S.Bp / 16, false, h->stream_weights, grid, h->stream)
+                              : launch_fl<float>(a, S.Bp / 16, split_products(h), h->stream_weights, grid, h->stream);
     timing_stop(h, kTimeBwd, 1, kBwdFirstLayer);
     if (e == hipSuccess) h->imp[1] = sb.next;
     return e;
