@@ -809,10 +809,17 @@ struct BwdArgs {
 // SPLIT (fp32 operands, see split_products): the products are formed of bf16 parts.  The slices of dZ_l are split when they
 // are staged, the wavefront's rows of A_{l-1}^T once, and a W tile when it is parked, so that LDS holds three planes of each.
 template <typename OT, int NT, int WM, bool DAO = false, bool NDA = false, bool FRAGS = NDA, bool SPLIT = false>
-__global__ __launch_bounds__(256, NT == 8 && !NDA && !DAO ? 1 : 2) void backward_kernel(BwdArgs a) {
+__global__ __launch_bounds__(256, NT == 8 && !NDA && !DAO && (sizeof(OT) == 4 || WM == kWGeneric) ? 1 : 2) void backward_kernel(BwdArgs a) {
     static_assert(!SPLIT || (sizeof(OT) == 4 && NT >= 4 && WM != kWGeneric), "see split_products");
     using LT = std::conditional_t<SPLIT, bf16_t, OT>;    // what LDS holds
     constexpr int NP = SPLIT ? 3 : 1;
+    // 128 samples of bf16 operands, two workgroups per CU: the registers just suffice with addresses as in place(), and where
+    // rows do not stream (their instances have more to hold) with the wavefront's rows of A_{l-1}^T parked in LDS.  (With
+    // one, 384 row blocks of 1500x1000, 16 workers of 100 samples, went in two rounds of which the second was half empty.
+    // 5 steps with one and two: 3072-1500-1000-100 2526 and 2441 us; 1500-900-1600-100, 20 workers of 70, 2335 and 2225;
+    // 1024-2048-2048-10, 24 of 110, 3105 and 2991; 784-500-300-10, 16 of 100, 431 and 423; 300-704-500-20, 16 of 80, 461 and 460.)
+    constexpr bool kPair = NT == 8 && !NDA && !DAO && sizeof(OT) == 2 && WM != kWGeneric;
+    constexpr bool kLaneOffsets = SPLIT || kPair, kParkA = kPair && WM != kWVectorStream;
     constexpr int kPad = sizeof(LT) == 2 ? 8 : 4;
     constexpr int Bp = 16 * NT;
     constexpr int NS = NT / 2;                 // 32-wide steps over the batch; also staging pieces per thread
@@ -823,6 +830,7 @@ __global__ __launch_bounds__(256, NT == 8 && !NDA && !DAO ? 1 : 2) void backward
     // (the parts of W: no padding, so that two workgroups of 64 samples fit a CU, but the 16-byte pieces of a row
     // permuted by the row)
     __shared__ __attribute__((aligned(16))) LT wlds[NDA ? 1 : 4][NP][kRowsPerWave][kColChunk + (SPLIT ? 0 : kPad)];
+    __shared__ Frag<OT> a_lds[kParkA ? 4 : 1][NS][kParkA ? 64 : 1];   // (kParkA)
     __shared__ __attribute__((aligned(16))) int huge_s[4];   // by wavefront: it staged a delta above kMaxSplit
 
     const int64_t logical = xcd_logical_block(a.total_blocks);
@@ -831,7 +839,7 @@ __global__ __launch_bounds__(256, NT == 8 && !NDA && !DAO ? 1 : 2) void backward
     int g, rem;
     shared_order(logical, per_group, a.shared_w, g, rem);
     const int rb = rem / a.col_split, cs = rem % a.col_split;
-    const int tid = threadIdx.x, lane = tid & 63, wave = SPLIT ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = kLaneOffsets ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
     const int j = lane & 15, q = lane >> 4;
     const int k0 = (rb * 4 + wave) * kRowsPerWave;   // < dp_in: the grid covers dp_in / 64 row blocks exactly
     const bool vec = a.vec != 0;
@@ -842,9 +850,9 @@ __global__ __launch_bounds__(256, NT == 8 && !NDA && !DAO ? 1 : 2) void backward
     float* Vw = a.V ? a.V + g * a.x_stride + a.w_off : nullptr;
     const float* Va = DAO ? nullptr : a.Aux + g * a.aux_stride + a.w_off;
     // Place of row k0 + 4 q + r (past d_in: of the last row, which is read in its stead without a branch between the
-    // loads; such weights are zeroed when used and never stored), columns c0 + 4 j and on.  SPLIT: a base that is the same for
-    // the whole wavefront and byte offsets that a lane keeps for the walk, which leaves the registers the parts need.
-    // (The other instances gain nothing from that: whole steps 0.97 to 1.02 times as fast.)
+    // loads; such weights are zeroed when used and never stored), columns c0 + 4 j and on.  kLaneOffsets: a base that is the
+    // same for the whole wavefront and byte offsets that a lane keeps for the walk, which leaves registers free.  (Instances
+    // that do not need them gain nothing from that: whole steps 0.97 to 1.02 times as fast.)
     const int last = a.d_in - 1, back = k0 < last ? k0 : last;
     unsigned woff[4];
 #pragma unroll
@@ -853,7 +861,7 @@ __global__ __launch_bounds__(256, NT == 8 && !NDA && !DAO ? 1 : 2) void backward
         woff[r] = 4u * (static_cast<unsigned>((row < last ? row : last) - back) * static_cast<unsigned>(a.d_out) + 4u * j);
     }
     auto place = [&](auto* base, int r, int c0) {
-        if constexpr (SPLIT) {
+        if constexpr (kLaneOffsets) {
             using C = std::conditional_t<std::is_const_v<std::remove_pointer_t<decltype(base)>>, const char, char>;
             return reinterpret_cast<decltype(base)>(reinterpret_cast<C*>(base + static_cast<int64_t>(back) * a.d_out + c0) + woff[r]);
         } else {
@@ -903,6 +911,8 @@ __global__ __launch_bounds__(256, NT == 8 && !NDA && !DAO ? 1 : 2) void backward
             if constexpr (SPLIT) {
                 af[s] = split8(f[s].v);
                 huge_a = huge_a || largest(f[s].v) > kMaxSplit;
+            } else if constexpr (kParkA) {
+                a_lds[wave][s][lane] = f[s];
             } else {
                 af[s] = f[s];
             }
@@ -929,6 +939,7 @@ __global__ __launch_bounds__(256, NT == 8 && !NDA && !DAO ? 1 : 2) void backward
     float4 w[4], v[4], wn[4], vn[4];
     Frag<OT> st_t[NS], st_b[NS];   // staging registers for the dZ^T and dZ slices
 
+    const unsigned zoff = static_cast<unsigned>(tid >> 3) * a.dp_out + (tid & 7) * 8u;   // of 32 x 64 entries of dZ_l, a thread's 8
     auto issue_loads = [&](int cc, float4 (&ww)[4], float4 (&vv)[4]) {
         const int c0 = cc * kColChunk;
 #pragma unroll
@@ -948,13 +959,15 @@ __global__ __launch_bounds__(256, NT == 8 && !NDA && !DAO ? 1 : 2) void backward
             // the dZ^T slice is one contiguous run of 64 * Bp elements
             const OT* src_t = dZT + static_cast<int64_t>(c0) * Bp;
 #pragma unroll
-            for (int s = 0; s < NS; ++s) st_t[s] = load8(src_t + static_cast<int64_t>(tid + 256 * s) * 8);
+            for (int s = 0; s < NS; ++s)
+                st_t[s] = kLaneOffsets ? load8(src_t + 2048 * s + tid * 8u) : load8(src_t + static_cast<int64_t>(tid + 256 * s) * 8);
         }
         if (need_da) {
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
                 const int p = tid + 256 * s;
-                st_b[s] = load8(dZ + static_cast<int64_t>(p >> 3) * a.dp_out + c0 + (p & 7) * 8);
+                st_b[s] = kLaneOffsets ? load8(dZ + static_cast<int64_t>(32 * s) * a.dp_out + c0 + zoff)
+                                       : load8(dZ + static_cast<int64_t>(p >> 3) * a.dp_out + c0 + (p & 7) * 8);
             }
         }
     };
@@ -1063,6 +1076,7 @@ __global__ __launch_bounds__(256, NT == 8 && !NDA && !DAO ? 1 : 2) void backward
             } else {
 #pragma unroll
                 for (int s = 0; s < NS; ++s) {
+                    if constexpr (kParkA) af[s] = a_lds[wave][s][lane];
 #pragma unroll
                     for (int t = 0; t < 4; ++t) acc[t] = mma8(af[s], operand(dzt_lds, t * 16 + j, 32 * s + 8 * q), acc[t]);
                 }
