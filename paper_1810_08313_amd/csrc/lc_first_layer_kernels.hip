@@ -55,7 +55,8 @@ struct FirstArgs {
     const void* an_bm;    // A_0 of the next step, batch-major [G][Bp][dp_in]
     void* out_bm;         // A_1 of the next step [G][Bp][dp_out]
     void* out_fm;         //                      [G][dp_out][Bp]
-    int n_chunks;         // 64-column chunks per replica
+    int n_chunks;         // column chunks per replica
+    int chunk_cols;       // their width: 64, or 96 (see wide_columns)
     int64_t total_blocks;
 };
 
@@ -421,27 +422,30 @@ __global__ __launch_bounds__(64 * NW, (FlBudget<OT, NT>::kWavesPerSimd)) void fi
 // r - 1) after the barrier of round r, which every reader of round r - 1 has passed.
 constexpr int kWideWaves = 8;
 
-template <typename OT, int WM, int WMR, int PD = 1>
+// CPL: columns of a lane, four or (ragged rows, see wide_columns) six; the chunk is 16 CPL columns wide.
+template <typename OT, int WM, int WMR, int CPL = 4, int PD = 1>
 __global__ __launch_bounds__(64 * kWideWaves) void first_layer_wide_kernel(FirstArgs a) {
     static_assert(sizeof(OT) == 2, "operand fragments of fp32 do not fit the register budget here");
+    static_assert(CPL == 4 || (CPL == 6 && WM == kWRagged && WMR == kWRagged), "six columns: 16 and 8 bytes at any float address");
+    constexpr int NC = 16 * CPL, NH = CPL / 2;
     constexpr int kPad = 8;
     constexpr int Bp = 128, NS = Bp / 32, NTH = 64 * kWideWaves;
-    constexpr size_t kSliceBytes = sizeof(OT) * kColChunk * (Bp + kPad);
-    constexpr size_t kTileBytes = 2 * kWideWaves * 2 * 64 * sizeof(bf16x8);
-    constexpr size_t kPartBytes = sizeof(float) * Bp * (kColChunk + 4);
+    constexpr size_t kSliceBytes = sizeof(OT) * NC * (Bp + kPad);
+    constexpr size_t kTileBytes = 2 * kWideWaves * NH * 64 * sizeof(bf16x8);
+    constexpr size_t kPartBytes = sizeof(float) * Bp * (NC + 4);
     constexpr size_t kWalkBytes = kSliceBytes + kTileBytes;
     __shared__ __attribute__((aligned(16))) char smem[kWalkBytes > kPartBytes ? kWalkBytes : kPartBytes];
-    __shared__ float bias_s[kColChunk];
+    __shared__ float bias_s[NC];
     OT (*dzt)[Bp + kPad] = reinterpret_cast<OT (*)[Bp + kPad]>(smem);
-    // [buffer][wavefront][half][lane]: a lane's 4 x 4 block of the tile as 4 operand fragments
-    // (columns 4 j + t, rows 4 q ..), 16 bytes per lane and half: consecutive lanes, no bank conflicts
-    bf16x8 (*wt)[kWideWaves][2][64] = reinterpret_cast<bf16x8 (*)[kWideWaves][2][64]>(smem + kSliceBytes);
+    // [buffer][wavefront][pair][lane]: a lane's 4 x CPL block of the tile as CPL operand fragments
+    // (columns CPL j + t, rows 4 q ..), 16 bytes per lane and pair: consecutive lanes, no bank conflicts
+    bf16x8 (*wt)[kWideWaves][NH][64] = reinterpret_cast<bf16x8 (*)[kWideWaves][NH][64]>(smem + kSliceBytes);
 
     const int64_t logical = xcd_logical_block(a.total_blocks);
     if (logical < 0) return;
     int g, chunk;
     shared_order(logical, a.n_chunks, a.shared_w, g, chunk);
-    const int c0 = chunk * kColChunk;
+    const int c0 = chunk * NC;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane & 15, q = lane >> 4;
@@ -455,19 +459,17 @@ __global__ __launch_bounds__(64 * kWideWaves) void first_layer_wide_kernel(First
     const OT* AN = static_cast<const OT*>(a.an_bm) + (static_cast<int64_t>(g) * Bp + 16 * wave) * a.dp_in;
     constexpr bool RAG = WM == kWRagged;
     const int n_rounds = (a.d_in + 16 * kWideWaves - 1) / (16 * kWideWaves);   // (divides unless RAG)
-    const int left = RAG ? a.d_out - (c0 + 4 * j) : 4;   // columns that exist from this lane's first one on
-    auto past_end = [&](int row) { return row < a.d_in ? 0 : row - (a.d_in - 1); };   // rows back to the last one
+    const int left = RAG ? a.d_out - (c0 + CPL * j) : CPL;   // columns that exist from this lane's first one on
+    const int c_own = RAG && left < 1 ? a.d_out - 1 : c0 + CPL * j;   // (a lane without columns reads, and never uses, the last ones)
 
     struct Set {
-        float4 w[4], v[4];            // rows k0 + 4 q + r, columns c0 + 4 j ..
+        float w[4][CPL], v[4][CPL];   // rows k0 + 4 q + r, columns c0 + CPL j ..
         Frag<OT> af[NS];              // A_0^T tile of this wavefront's 16 rows
         Frag<OT> an[kWideWaves / 2];  // A_0' of this wavefront's samples, 4 entries for each of two tiles of the round
     };
     Set set[PD + 1];
 
-    unsigned woff[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) woff[r] = 4u * static_cast<unsigned>((4 * q + r) * a.d_out + c0 + 4 * j);
+    const unsigned woff = 4u * static_cast<unsigned>(4 * q * a.d_out + c_own);   // (row 4 q of a step; the others by their base)
     const unsigned atoff = static_cast<unsigned>(sizeof(OT)) * static_cast<unsigned>(8 * lane);   // in a fragment
     auto at_byte = [](auto* base, unsigned off) {
         using T = std::remove_pointer_t<decltype(base)>;
@@ -475,22 +477,44 @@ __global__ __launch_bounds__(64 * kWideWaves) void first_layer_wide_kernel(First
         return reinterpret_cast<T*>(reinterpret_cast<C*>(base) + off);
     };
 
+    typedef float f32x2_u __attribute__((ext_vector_type(2), aligned(4)));
+    auto load_columns = [&](auto mode, const float* p, float (&to)[CPL]) {
+        const float4 f = load_wm<decltype(mode)::value>(p, 0, a.d_out, true);
+        to[0] = f.x; to[1] = f.y; to[2] = f.z; to[3] = f.w;
+        if constexpr (CPL == 6) {
+            const f32x2_u g = *reinterpret_cast<const f32x2_u*>(p + 4);
+            to[4] = g[0]; to[5] = g[1];
+        }
+    };
+    auto store_columns = [&](float* p, const float (&from)[CPL]) {
+        store_wm<WM>(p, 0, left, true, make_float4(from[0], from[1], from[2], from[3]));
+        if constexpr (CPL == 6) {
+            if (left > 5) {
+                *reinterpret_cast<f32x2_u*>(p + 4) = f32x2_u{from[4], from[5]};
+            } else if (left > 4) {
+                p[4] = from[4];
+            }
+        }
+    };
+    constexpr std::integral_constant<int, WM> kState{};
+    constexpr std::integral_constant<int, WMR> kWeights{};
     auto load_round = [&](int r, Set& x) {
         // rounds past the end are never used: the last one is read for them (no branch between the loads)
         const int rr = r < n_rounds ? r : n_rounds - 1;
         const int k0 = 16 * (kWideWaves * rr + wave);
-        const float* wb = Wr + static_cast<int64_t>(k0) * a.d_out;
-        const float* vb = Va + static_cast<int64_t>(k0) * a.d_out;
+        const int kb = RAG && k0 > a.d_in - 1 ? a.d_in - 1 : k0;
+        const float* wb = Wr + static_cast<int64_t>(kb) * a.d_out;
+        const float* vb = Va + static_cast<int64_t>(kb) * a.d_out;
 #pragma unroll
         for (int r4 = 0; r4 < 4; ++r4) {
-            // (a row's distance from this step's first row may be negative: 64-bit, sign-extended)
-            if constexpr (RAG) {
-                const int64_t back = static_cast<int64_t>(past_end(k0 + 4 * q + r4)) * a.d_out;
-                x.w[r4] = load_wm<WMR>(at_byte(wb, woff[r4]) - back, 0, a.d_out, true);
-                x.v[r4] = load_wm<WM>(at_byte(vb, woff[r4]) - back, 0, a.d_out, true);
+            if constexpr (RAG) {   // (rows that do not exist: the last one)
+                const int row = k0 + 4 * q + r4, last = a.d_in - 1;
+                const unsigned at = 4u * (static_cast<unsigned>((row < last ? row : last) - kb) * static_cast<unsigned>(a.d_out) + c_own);
+                load_columns(kWeights, at_byte(wb, at), x.w[r4]);
+                load_columns(kState, at_byte(vb, at), x.v[r4]);
             } else {
-                x.w[r4] = load_wm<WMR>(at_byte(wb, woff[r4]), 0, a.d_out, true);
-                x.v[r4] = load_wm<WM>(at_byte(vb, woff[r4]), 0, a.d_out, true);
+                load_columns(kWeights, at_byte(wb + r4 * a.d_out, woff), x.w[r4]);
+                load_columns(kState, at_byte(vb + r4 * a.d_out, woff), x.v[r4]);
             }
         }
         // (inputs have dp_in rows and columns; a step beyond them reads the last 16 instead, for rows
@@ -511,18 +535,22 @@ __global__ __launch_bounds__(64 * kWideWaves) void first_layer_wide_kernel(First
     for (int p = 0; p < PD; ++p) load_round(p, set[p]);
     {
         const OT* ZT = static_cast<const OT*>(a.dz_fm) + (static_cast<int64_t>(g) * a.dp_out + c0) * Bp;
-        for (int p = tid; p < kColChunk * (Bp / 8); p += NTH) {
+        for (int p = tid; p < NC * (Bp / 8); p += NTH) {
             const int c = p / (Bp / 8), seg = p % (Bp / 8);
-            *reinterpret_cast<Frag<OT>*>(&dzt[(c & 3) * 16 + (c >> 2)][seg * 8]) = load8(ZT + static_cast<int64_t>(p) * 8);
+            // (six columns a lane: the last chunk may reach past the deltas' padded rows)
+            const bool in = CPL == 4 || c0 + c < a.dp_out;
+            Frag<OT> f = load8(ZT + (in ? static_cast<int64_t>(p) * 8 : 0));
+            if (!in) f.v = bf16x8{};
+            *reinterpret_cast<Frag<OT>*>(&dzt[c % CPL * 16 + c / CPL][seg * 8]) = f;
         }
     }
     __syncthreads();
-    if (tid < kColChunk && (WM != kWRagged || c0 + tid < a.d_out)) {
+    if (tid < NC && (WM != kWRagged || c0 + tid < a.d_out)) {
         float* bx = a.X + g * a.x_stride + a.b_off + c0 + tid;
         const float x = a.Xr[g * a.xr_stride + a.b_off + c0 + tid];
         float vb0 = a.Aux[g * a.aux_stride + a.b_off + c0 + tid];
         if (a.imp_in) vb0 = (vb0 - x) * a.inv_lr;
-        const OT* zr = dzt[(tid & 3) * 16 + (tid >> 2)];
+        const OT* zr = dzt[tid % CPL * 16 + tid / CPL];
         float sb = 0.f;
         for (int b = 0; b < a.B; ++b) sb += to_f32(zr[b]);
         const float vb = a.beta * vb0 + (sb + a.wd * x);
@@ -531,79 +559,77 @@ __global__ __launch_bounds__(64 * kWideWaves) void first_layer_wide_kernel(First
         bias_s[tid] = x - a.lr * vb;
     }
 
-    f32x4 facc[4];
+    f32x4 facc[CPL];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) facc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < CPL; ++t) facc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     auto process = [&](int r, Set& x) {
         const int64_t row0 = static_cast<int64_t>(16 * (kWideWaves * r + wave)) * a.d_out;
         float* ws = W + row0;
         float* vs = Vw ? Vw + row0 : nullptr;
-        f32x4 acc[4];
+        f32x4 acc[CPL];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < CPL; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int st = 0; st < NS; ++st)
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
+            for (int t = 0; t < CPL; ++t) {
                 const Frag<OT> zf = *reinterpret_cast<const Frag<OT>*>(&dzt[t * 16 + j][32 * st + 8 * q]);
                 acc[t] = mma8(x.af[st], zf, acc[t]);
             }
 #pragma unroll
         for (int r4 = 0; r4 < 4; ++r4) {
-            consume_here(x.w[r4]);
-            consume_here(x.v[r4]);
-            if (a.imp_in) {   // the tile holds the parameters of one step earlier: v = (x_prev - x) / lr
-                x.v[r4].x = (x.v[r4].x - x.w[r4].x) * a.inv_lr;
-                x.v[r4].y = (x.v[r4].y - x.w[r4].y) * a.inv_lr;
-                x.v[r4].z = (x.v[r4].z - x.w[r4].z) * a.inv_lr;
-                x.v[r4].w = (x.v[r4].w - x.w[r4].w) * a.inv_lr;
-            }
-            x.v[r4].x = a.beta * x.v[r4].x + (acc[0][r4] + a.wd * x.w[r4].x);
-            x.v[r4].y = a.beta * x.v[r4].y + (acc[1][r4] + a.wd * x.w[r4].y);
-            x.v[r4].z = a.beta * x.v[r4].z + (acc[2][r4] + a.wd * x.w[r4].z);
-            x.v[r4].w = a.beta * x.v[r4].w + (acc[3][r4] + a.wd * x.w[r4].w);
-            x.w[r4].x -= a.lr * x.v[r4].x;
-            x.w[r4].y -= a.lr * x.v[r4].y;
-            x.w[r4].z -= a.lr * x.v[r4].z;
-            x.w[r4].w -= a.lr * x.v[r4].w;
-            if (!RAG || 16 * (kWideWaves * r + wave) + 4 * q + r4 < a.d_in) {
-                if (vs) store_wm<WM>(at_byte(vs, woff[r4]), 0, left, true, x.v[r4]);
-                store_wm<WM>(at_byte(ws, woff[r4]), 0, left, true, x.w[r4]);
-            } else {
-                x.w[r4] = make_float4(0.f, 0.f, 0.f, 0.f);
-            }
-        }
-        // the updated tile, as the 4 operand fragments of this lane
-        Frag4<OT> b0, b1, b2, b3;
-        pack4(b0, x.w[0].x, x.w[1].x, x.w[2].x, x.w[3].x);
-        pack4(b1, x.w[0].y, x.w[1].y, x.w[2].y, x.w[3].y);
-        pack4(b2, x.w[0].z, x.w[1].z, x.w[2].z, x.w[3].z);
-        pack4(b3, x.w[0].w, x.w[1].w, x.w[2].w, x.w[3].w);
-        bf16x8 lo, hi;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            lo[e] = b0.v[e]; lo[4 + e] = b1.v[e];
-            hi[e] = b2.v[e]; hi[4 + e] = b3.v[e];
+            for (int t = 0; t < CPL; ++t) asm volatile("" : "+v"(x.w[r4][t]), "+v"(x.v[r4][t]));   // (see consume_here)
+#pragma unroll
+            for (int t = 0; t < CPL; ++t) {
+                float& w = x.w[r4][t];
+                float& v = x.v[r4][t];
+                if (a.imp_in) v = (v - w) * a.inv_lr;   // (v held the parameters of one step earlier: v = (x_prev - x) / lr)
+                v = a.beta * v + (acc[t][r4] + a.wd * w);
+                w -= a.lr * v;
+            }
+            if (!RAG || 16 * (kWideWaves * r + wave) + 4 * q + r4 < a.d_in) {
+                if (vs) store_columns(at_byte(vs + r4 * a.d_out, woff), x.v[r4]);
+                store_columns(at_byte(ws + r4 * a.d_out, woff), x.w[r4]);
+            } else {
+#pragma unroll
+                for (int t = 0; t < CPL; ++t) x.w[r4][t] = 0.f;
+            }
         }
-        wt[r & 1][wave][0][lane] = lo;
-        wt[r & 1][wave][1][lane] = hi;
+        // the updated tile, as the operand fragments of this lane, two together
+#pragma unroll
+        for (int h = 0; h < NH; ++h) {
+            Frag4<OT> b0, b1;
+            pack4(b0, x.w[0][2 * h], x.w[1][2 * h], x.w[2][2 * h], x.w[3][2 * h]);
+            pack4(b1, x.w[0][2 * h + 1], x.w[1][2 * h + 1], x.w[2][2 * h + 1], x.w[3][2 * h + 1]);
+            bf16x8 both;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                both[e] = b0.v[e];
+                both[4 + e] = b1.v[e];
+            }
+            wt[r & 1][wave][h][lane] = both;
+        }
         __syncthreads();
         // Z_1'[these 16 samples] += A_0'[.., the round's 128 rows] W_1[the round's 128 rows, :]
 #pragma unroll
         for (int u = 0; u < kWideWaves; ++u) {
-            const bf16x8 l2 = wt[r & 1][u][0][lane], h2 = wt[r & 1][u][1][lane];
-            Frag4<OT> an, f0, f1, f2, f3;
+            Frag4<OT> an;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                an.v[e] = x.an[u / 2].v[4 * (u % 2) + e];
-                f0.v[e] = l2[e]; f1.v[e] = l2[4 + e];
-                f2.v[e] = h2[e]; f3.v[e] = h2[4 + e];
+            for (int e = 0; e < 4; ++e) an.v[e] = x.an[u / 2].v[4 * (u % 2) + e];
+#pragma unroll
+            for (int h = 0; h < NH; ++h) {
+                const bf16x8 both = wt[r & 1][u][h][lane];
+                Frag4<OT> f0, f1;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    f0.v[e] = both[e];
+                    f1.v[e] = both[4 + e];
+                }
+                facc[2 * h] = mma4(an, f0, facc[2 * h]);
+                facc[2 * h + 1] = mma4(an, f1, facc[2 * h + 1]);
             }
-            facc[0] = mma4(an, f0, facc[0]);
-            facc[1] = mma4(an, f1, facc[1]);
-            facc[2] = mma4(an, f2, facc[2]);
-            facc[3] = mma4(an, f3, facc[3]);
         }
     };
 
@@ -623,26 +649,26 @@ __global__ __launch_bounds__(64 * kWideWaves) void first_layer_wide_kernel(First
 
     // A_1' = ReLU(Z_1' + b_1), through LDS for the two layouts of the stores
     __syncthreads();   // every wavefront is done with the slice and the tiles that share this memory
-    float (*part)[kColChunk + 4] = reinterpret_cast<float (*)[kColChunk + 4]>(smem);
+    float (*part)[NC + 4] = reinterpret_cast<float (*)[NC + 4]>(smem);
 #pragma unroll
-    for (int r4 = 0; r4 < 4; ++r4) {
-        float4 z = make_float4(facc[0][r4] + bias_s[4 * j], facc[1][r4] + bias_s[4 * j + 1], facc[2][r4] + bias_s[4 * j + 2],
-                               facc[3][r4] + bias_s[4 * j + 3]);
-        z = make_float4(z.x > 0.f ? z.x : 0.f, z.y > 0.f ? z.y : 0.f, z.z > 0.f ? z.z : 0.f, z.w > 0.f ? z.w : 0.f);
-        *reinterpret_cast<float4*>(&part[16 * wave + 4 * q + r4][4 * j]) = z;
-    }
+    for (int r4 = 0; r4 < 4; ++r4)
+#pragma unroll
+        for (int t = 0; t < CPL; ++t) {
+            const float z = facc[t][r4] + bias_s[CPL * j + t];
+            part[16 * wave + 4 * q + r4][CPL * j + t] = z > 0.f ? z : 0.f;
+        }
     __syncthreads();
     OT* obm = static_cast<OT*>(a.out_bm) + static_cast<int64_t>(g) * Bp * a.dp_out;
     OT* ofm = static_cast<OT*>(a.out_fm) + static_cast<int64_t>(g) * a.dp_out * Bp;
-    for (int e = tid; e < Bp * (kColChunk / 8); e += NTH) {
-        const int b = e / (kColChunk / 8), cl = (e % (kColChunk / 8)) * 8;
-        if (b >= a.B) continue;
+    for (int e = tid; e < Bp * (NC / 8); e += NTH) {
+        const int b = e / (NC / 8), cl = (e % (NC / 8)) * 8;
+        if (b >= a.B || (CPL != 4 && c0 + cl >= a.dp_out)) continue;
         float y[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) y[i] = (!RAG || c0 + cl + i < a.d_out) ? part[b][cl + i] : 0.f;
         store8(obm + static_cast<int64_t>(b) * a.dp_out + c0 + cl, y);
     }
-    for (int e = tid; e < kColChunk * (Bp / 8); e += NTH) {
+    for (int e = tid; e < NC * (Bp / 8); e += NTH) {
         const int c = e / (Bp / 8), bl = (e % (Bp / 8)) * 8;
         if (bl >= a.B || (RAG && c0 + c >= a.d_out)) continue;
         float y[8];
@@ -696,7 +722,8 @@ hipError_t launch_fl(const FirstArgs& a, int nt, bool split, bool stream_w, unsi
         // wavefronts take together stay with the other one: cut off as ragged rows are, they run 0.94 ..
         // 1.0 times as fast up to 784 inputs of a cached state, 1.0 .. 1.03 from 1040 inputs on.)
         const dim3 block(64 * kWideWaves);
-        if (!whole_tiles(a)) hipLaunchKernelGGL((first_layer_wide_kernel<OT, kWRagged, kWRagged>), dim3(grid), block, 0, st, a);
+        if (a.chunk_cols == 96) hipLaunchKernelGGL((first_layer_wide_kernel<OT, kWRagged, kWRagged, 6>), dim3(grid), block, 0, st, a);
+        else if (!whole_tiles(a)) hipLaunchKernelGGL((first_layer_wide_kernel<OT, kWRagged, kWRagged>), dim3(grid), block, 0, st, a);
         else if (a.d_in % (16 * kWideWaves) != 0) launch_fl_wm<OT, 8>(a, split, stream_w, grid, st);
         else if (stream_w && !a.shared_w)
             hipLaunchKernelGGL((first_layer_wide_kernel<OT, kWVectorStream, kWVectorStream>), dim3(grid), block, 0, st, a);
@@ -744,6 +771,19 @@ bool first_layer_kernel_ok(const lc_handle* h) {
     return 100 * blocks >= full * cus * rounds;
 }
 
+// Columns of a chunk: 96 instead of 64 in the 128-sample kernel on ragged rows where the rounds of workgroups then cost
+// less, a workgroup of 96 columns taking 1.5 times as long.  5 steps with 64 and 96: 3072-1500-1000-100, 16 workers of 100,
+// 384 workgroups in two rounds and 256 in one, 2408 and 2252 us; but 1500-1999-1000-10, 24 of 90, 768 in three and 504 in
+// two, 2837 and 2896; 2048-1001-300-10, 25 of 128, 400 and 275 in two, 1531 and 1790.
+static int wide_columns(const lc_handle* h) {
+    const LayerGeom& g = h->layer[1];
+    const bool whole = g.d_out % kColChunk == 0 && g.w_off % 4 == 0 && g.d_in % 16 == 0;
+    if (h->train.Bp != 128 || h->md.gemm != LC_GEMM_BF16 || whole) return kColChunk;
+    const int64_t cus = compute_units(), m = h->train.G;
+    const int64_t r64 = (m * ((g.d_out + 63) / 64) + cus - 1) / cus, r96 = (m * ((g.d_out + 95) / 96) + cus - 1) / cus;
+    return 6 * r96 < 4 * r64 ? 96 : kColChunk;
+}
+
 // Backward pass and update of layer 1 for the step in slot train.cur_slot, and A_1 of the step in
 // the next slot (which must have been gathered already).
 hipError_t launch_first_layer(lc_handle* h) {
@@ -781,7 +821,8 @@ hipError_t launch_first_layer(lc_handle* h) {
     a.an_bm = static_cast<const char*>(S.a_bm[0]) + static_cast<size_t>(S.cur_slot + 1) * slot_bytes;
     a.out_bm = S.a_bm[1];
     a.out_fm = S.a_fm[1];
-    a.n_chunks = g.dp_out / kColChunk;
+    a.chunk_cols = wide_columns(h);
+    a.n_chunks = (g.d_out + a.chunk_cols - 1) / a.chunk_cols;
     a.total_blocks = static_cast<int64_t>(S.G) * a.n_chunks;
     const unsigned grid = static_cast<unsigned>((a.total_blocks + kXcds - 1) / kXcds * kXcds);
     timing_start(h, kTimeBwd, 1, kBwdFirstLayer);

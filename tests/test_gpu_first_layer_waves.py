@@ -1,5 +1,5 @@
-"""The first-layer kernel with eight wavefronts per workgroup (fp32 operands, 33 to 64 samples, one workgroup per
-compute unit): calls of two to four steps against the oracle, with the bars of test_gpu_parity.py."""
+"""Workgroups of the first-layer kernel: eight wavefronts (fp32 operands, 33 to 64 samples, one workgroup per compute
+unit) and chunks of 96 columns.  Calls of two to four steps against the oracle, with the bars of test_gpu_parity.py."""
 import pytest
 
 from test_gpu_parity import pkg  # noqa: F401
@@ -15,3 +15,14 @@ pytestmark = pytest.mark.gpu
 ])
 def test_calls_of_several_steps_with_eight_wavefronts(pkg, orc, dims, m, B):
     _calls(pkg, orc, dims, m, B, False, 0)
+
+
+@pytest.mark.parametrize("implicit", [0, 2])
+@pytest.mark.parametrize("dims,m,B", [
+    ([97, 257, 24, 10], 85, 128),    # 65 columns in a last chunk of 96, one row in a last step
+    ([130, 285, 24, 10], 84, 100),   # three short of whole chunks
+    ([64, 90, 10], 210, 70),         # one chunk, two columns of a lane missing
+])
+def test_chunks_of_96_columns(pkg, orc, dims, m, B, implicit):
+    """bf16 operands, 65 to 128 samples, ragged rows: one round of workgroups instead of two."""
+    _calls(pkg, orc, dims, m, B, True, implicit)
