@@ -33,8 +33,6 @@
 
 #include <type_traits>
 
-#include <type_traits>
-
 namespace lc {
 
 namespace {
