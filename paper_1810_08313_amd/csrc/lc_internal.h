@@ -227,7 +227,9 @@ inline bool first_forward_reads_rows(const lc_handle* h) {
     return h->train.Bp == 128 && static_cast<int64_t>(h->train.G) * (h->layer[1].dp_out / kColChunk) >= 256;
 }
 // fp32 products of a step's launches per layer on the bf16 matrix cores (Parts in lc_mma.h), where they are what a kernel
-// waits for.  5 steps, fp32 instructions and parts: 3072-1024-1024-10, 16 workers of 64 samples, 1794 and 1661 us;
+// waits for.  Off unless LC_SPLIT_PRODUCTS asks for it: the rounding is another one, a ReLU gate that is met on one side only
+// is amplified over the steps of later calls, and of four large drawn models one differed by 1.0e-3 from the fp32 instructions in a
+// call's state after the third call, more than fp32 results may (both were 2e-7 from 64 bits after the first).  5 steps, fp32 instructions and parts: 3072-1024-1024-10, 16 workers of 64 samples, 1794 and 1661 us;
 // 2048-1500-1000-100, 12 of 100, 3610 and 3150; 784-500-300-10, 16 of 100, 693 and 647, 16 of 64, 502 and 488; tau = 1,
 // 3072-2048-2048-10, 16 of 64, an iteration 763 and 705.  Gradients are 0.86 times (0.66 to 1.00) as far from 64 bits (40
 // drawn models).  Not for

@@ -9,6 +9,12 @@ from test_gpu_summation_error import _error
 
 pytestmark = pytest.mark.gpu
 
+
+@pytest.fixture(autouse=True)
+def _parts(monkeypatch):
+    monkeypatch.setenv("LC_SPLIT_PRODUCTS", "1")
+
+
 # (64- and 128-sample kernels; whole and ragged rows; shared-out columns; the first-layer kernel with 4 and 8 wavefronts
 # does not run in a call of one step, see the calls of two below)
 SHAPES = [([784, 500, 300, 10], 16, 100), ([512, 512, 512, 10], 16, 64), ([300, 520, 136, 70], 40, 33), ([1025, 705, 321, 10], 12, 128),
