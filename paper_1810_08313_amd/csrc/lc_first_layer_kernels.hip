@@ -27,12 +27,13 @@ namespace lc {
 
 namespace {
 
-// Wavefronts of a workgroup.  Up to 64 samples two workgroups share a CU; where the whole grid is no more than one
-// per CU, fp32 operands at 33 to 64 samples take twice as many, since such a wavefront requests nothing ahead (see
-// FlBudget) and needs another one's loads under way beside its matrix instructions.  Five steps with four and eight
-// (the products on the fp32 instructions): 3072-1024-1024-10, 16 workers of 64, 1894 and 1817 us (the launch 211 and 194);
-// 1500-800-800-10, 16 of 50, 1255 and 1150; 784-1000-300-10, 14 of 64, 670 and 633; 300-1024-10, 12 of 60, 264 and 258; but
-// 128 inputs, one step of the walk per wavefront, 276 and 279.  bf16 operands and up to 32 samples, which have a step ahead: 0.99 to 1.04 times as fast.
+// Wavefronts of a workgroup, and partial sums of Z_1'.  Up to 64 samples two workgroups share a CU; where the whole grid is
+// no more than one per CU, fp32 operands at 33 to 64 samples take twice as many (PAIRS), since such a wavefront requests
+// nothing ahead (see FlBudget) and needs another one's loads under way beside its matrix instructions.  Five steps with
+// four and eight: 3072-1024-1024-10, 16 workers of 64, 1879 and 1797 us; 1500-800-800-10, 16 of 50, 1264 and 1141;
+// 784-1000-300-10, 14 of 64, 676 and 641; 2000-777-300-10, 18 of 40, 1337 and 1207; 300-1024-10, 12 of 60, 264 and 236.
+// Below 256 inputs, 14 of 60: 64-1024-10 160 and 164, 100 inputs 180 and 173, 160 200 and 203, 192 205 and 207, 224 224 and 220.
+// bf16 operands and up to 32 samples, which have a step ahead: 0.99 to 1.04 times as fast.
 constexpr int kFlWaves = 4;
 
 struct FirstArgs {
@@ -74,8 +75,8 @@ struct FlBudget {
     static constexpr int kAhead = (NT == 4 && sizeof(OT) == 4) ? 0 : 1;
 };
 
-// One workgroup = one replica x 64 columns of W_1; its NW wavefronts take the 16-row steps
-// wave, wave + NW, ... and never synchronise inside the walk: the dZ_1 slice is staged once, the
+// One workgroup = one replica x 64 columns of W_1; its 4 wavefronts take the 16-row steps
+// wave, wave + 4, ... and never synchronise inside the walk: the dZ_1 slice is staged once, the
 // A_0 tiles go from memory straight into operand registers.  The loads of a wavefront's next PD
 // steps are in flight while it works on the current one (PD + 1 register sets, addressed
 // statically); a step is small enough (about 20 memory instructions with its stores) that the
@@ -89,25 +90,38 @@ struct FlBudget {
 // the weights read: cached where all replicas read one model, which the neighbouring blocks want in
 // the L2.  (A template parameter, not a run-time flag: with the choice made per load the compiler
 // waited for each load before it issued the next.)
+// PAIRS: 8 wavefronts, of which u and u + 4 take the steps that wavefront u of four would take, in turn, and add up that
+// wavefront's share of Z_1' in the same order, each for half of the samples: the same bits.  (Eight shares, added up at the
+// end, round otherwise, and a ReLU gate that one of two such sums opens is amplified by later steps: the momentum of
+// 3072-1024-1024-10, 16 workers of 64, differed by up to 2.4e-3 after three calls of five steps.)  The updated tiles go
+// through LDS, 8 of them between two barriers; a wavefront then holds half of the sums, which leaves registers for a step
+// ahead.  (With a share of the columns for either half, rows whose length is no multiple of 32 floats have twice as many
+// cache lines that two wavefronts write in part: 2000-777-300-10 1430 us instead of 1207.)
 // SPLIT (fp32 operands, see split_products): all products of bf16 parts.
-template <typename OT, int NT, int WM, int WMR, int NW, bool SPLIT>
-__global__ __launch_bounds__(64 * NW, (FlBudget<OT, NT>::kWavesPerSimd)) void first_layer_kernel(FirstArgs a) {
-    static_assert(!SPLIT || sizeof(OT) == 4, "see split_products");
+template <typename OT, int NT, int WM, int WMR, bool PAIRS, bool SPLIT>
+__global__ __launch_bounds__(PAIRS ? 512 : 256, (FlBudget<OT, NT>::kWavesPerSimd)) void first_layer_kernel(FirstArgs a) {
+    static_assert(!SPLIT || (sizeof(OT) == 4 && !PAIRS), "see split_products");
+    constexpr int NW = PAIRS ? 2 * kFlWaves : kFlWaves;
+    constexpr int SW = NW / kFlWaves, MW = NT / SW;   // steps of a round and tiles of samples that a wavefront multiplies
     using LT = std::conditional_t<SPLIT, bf16_t, OT>;   // what LDS holds
     constexpr int NP = SPLIT ? 3 : 1;
     constexpr int kPad = sizeof(LT) == 2 ? 8 : 4;
     constexpr int Bp = 16 * NT;
     constexpr int NS = Bp / 32;
-    constexpr int PD = FlBudget<OT, NT>::kAhead;
+    constexpr int PD = PAIRS ? 1 : FlBudget<OT, NT>::kAhead;
     // the dZ^T slice during the walk; the wavefronts' partial Z_1' tiles after it
     constexpr size_t kSliceBytes = sizeof(LT) * NP * kColChunk * (Bp + kPad);
-    constexpr size_t kPartBytes = sizeof(float) * NW * Bp * (kColChunk + 4);
-    __shared__ __attribute__((aligned(16))) char smem[kSliceBytes > kPartBytes ? kSliceBytes : kPartBytes];
+    constexpr size_t kPartBytes = sizeof(float) * kFlWaves * Bp * (kColChunk + 4);
+    constexpr size_t kTileBytes = PAIRS ? 2 * NW * 4 * 64 * sizeof(Frag4<OT>) : 0;
+    constexpr size_t kWalkBytes = kSliceBytes + kTileBytes;
+    __shared__ __attribute__((aligned(16))) char smem[kWalkBytes > kPartBytes ? kWalkBytes : kPartBytes];
     __shared__ float bias_s[kColChunk];
     // row (c % 4) * 16 + c / 4 holds column c0 + c: the 16 lanes of an operand read (columns
     // 4 j + t) then hit 16 consecutive LDS rows
     LT (*dzt)[kColChunk][Bp + kPad] = reinterpret_cast<LT (*)[kColChunk][Bp + kPad]>(smem);
     __shared__ int huge_s[NW];   // by wavefront: it staged a delta above kMaxSplit
+    // PAIRS: [buffer][wavefront][t][lane], a lane's 4 x 4 block of an updated tile as operands (columns 4 j + t, rows 4 q ..)
+    Frag4<OT> (*wt)[NW][4][64] = reinterpret_cast<Frag4<OT> (*)[NW][4][64]>(smem + kSliceBytes);
 
     const int64_t logical = xcd_logical_block(a.total_blocks);
     if (logical < 0) return;
@@ -116,6 +130,7 @@ __global__ __launch_bounds__(64 * NW, (FlBudget<OT, NT>::kWavesPerSimd)) void fi
     const int c0 = chunk * kColChunk;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: step bases live in scalar registers
+    const int turn = wave % kFlWaves, mt0 = wave / kFlWaves * MW;
     const int j = lane & 15, q = lane >> 4;
 
     float* W = a.X + g * a.x_stride + a.w_off;
@@ -131,7 +146,7 @@ __global__ __launch_bounds__(64 * NW, (FlBudget<OT, NT>::kWavesPerSimd)) void fi
     struct Set {
         float4 w[4], v[4];      // rows k0 + 4 q + r, columns c0 + 4 j ..
         Frag<OT> af[NS];        // A_0^T tile of the 16 rows
-        Frag4<OT> an[NT];       // next step's A_0, 4 entries of each batch row
+        Frag4<OT> an[SW][MW];   // next step's A_0, 4 entries of each batch row
     };
     Set set[PD + 1];
 
@@ -175,9 +190,14 @@ __global__ __launch_bounds__(64 * NW, (FlBudget<OT, NT>::kWavesPerSimd)) void fi
                 x.af[st] = load8(at_byte(ab + kFragElems * st, atoff));
             }
         }
-        const OT* nb = AN + (k0 / 32) * kFragElems + (k0 / 16 % 2) * kHalf;
 #pragma unroll
-        for (int mt = 0; mt < NT; ++mt) x.an[mt] = load4(at_byte(nb + static_cast<int64_t>(16 * mt) * a.dp_in, atoff));
+        for (int i = 0; i < SW; ++i) {
+            const int si = s - wave + turn + i * kFlWaves, n0 = PAIRS ? (si < n_steps ? si : n_steps - 1) : k0 / 16;
+            const OT* nb = AN + (n0 / 2) * kFragElems + (n0 % 2) * kHalf;
+#pragma unroll
+            for (int mt = 0; mt < MW; ++mt)
+                x.an[i][mt] = load4(at_byte(nb + static_cast<int64_t>(16 * (mt0 + mt)) * a.dp_in, atoff));
+        }
     };
 
     // first loads, then the staging of the slice (its own round trip overlaps with them)
@@ -232,9 +252,9 @@ __global__ __launch_bounds__(64 * NW, (FlBudget<OT, NT>::kWavesPerSimd)) void fi
         bias_s[tid] = x - a.lr * vb;
     }
 
-    f32x4 facc[NT][4];
+    f32x4 facc[MW][4];
 #pragma unroll
-    for (int mt = 0; mt < NT; ++mt)
+    for (int mt = 0; mt < MW; ++mt)
 #pragma unroll
         for (int t = 0; t < 4; ++t) facc[mt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
 
@@ -296,7 +316,7 @@ __global__ __launch_bounds__(64 * NW, (FlBudget<OT, NT>::kWavesPerSimd)) void fi
             x.w[r].y -= a.lr * x.v[r].y;
             x.w[r].z -= a.lr * x.v[r].z;
             x.w[r].w -= a.lr * x.v[r].w;
-            const bool in = !RAG || 16 * s + 4 * q + r < a.d_in;
+            const bool in = RAG ? 16 * s + 4 * q + r < a.d_in : !PAIRS || s < n_steps;
             if (in) {
                 if (vs) store_wm<WM>(at_byte(vs, woff[r]), 0, left, true, x.v[r]);
                 store_wm<WM>(at_byte(ws, woff[r]), 0, left, true, x.w[r]);
@@ -310,38 +330,55 @@ __global__ __launch_bounds__(64 * NW, (FlBudget<OT, NT>::kWavesPerSimd)) void fi
 #pragma unroll
             for (int r = 0; r < 4; ++r) m = fmaxf(m, largest<4>({x.w[r].x, x.w[r].y, x.w[r].z, x.w[r].w}));
 #pragma unroll
-            for (int mt = 0; mt < NT; ++mt) m = fmaxf(m, largest(x.an[mt].v));
+            for (int mt = 0; mt < NT; ++mt) m = fmaxf(m, largest(x.an[0][mt].v));
             if (!__any(m > kMaxSplit)) {
                 const Parts4 wp[4] = {split4(x.w[0].x, x.w[1].x, x.w[2].x, x.w[3].x), split4(x.w[0].y, x.w[1].y, x.w[2].y, x.w[3].y),
                                       split4(x.w[0].z, x.w[1].z, x.w[2].z, x.w[3].z), split4(x.w[0].w, x.w[1].w, x.w[2].w, x.w[3].w)};
 #pragma unroll
                 for (int mt = 0; mt < NT; ++mt) {
-                    const Parts4 an = split4(x.an[mt].v[0], x.an[mt].v[1], x.an[mt].v[2], x.an[mt].v[3]);
+                    const float (&v)[4] = x.an[0][mt].v;
+                    const Parts4 an = split4(v[0], v[1], v[2], v[3]);
 #pragma unroll
                     for (int t = 0; t < 4; ++t) facc[mt][t] = mma4(an, wp[t], facc[mt][t]);
                 }
                 return;
             }
         }
-        Frag4<OT> bf;
-        pack4(bf, x.w[0].x, x.w[1].x, x.w[2].x, x.w[3].x);
+        Frag4<OT> bf[4];
+        pack4(bf[0], x.w[0].x, x.w[1].x, x.w[2].x, x.w[3].x);
+        pack4(bf[1], x.w[0].y, x.w[1].y, x.w[2].y, x.w[3].y);
+        pack4(bf[2], x.w[0].z, x.w[1].z, x.w[2].z, x.w[3].z);
+        pack4(bf[3], x.w[0].w, x.w[1].w, x.w[2].w, x.w[3].w);
+        if constexpr (PAIRS) {
+            // (the buffer's readers of two rounds ago have passed the barrier of the last one)
+            const int buf = s / NW % 2;
 #pragma unroll
-        for (int mt = 0; mt < NT; ++mt) facc[mt][0] = mma4(x.an[mt], bf, facc[mt][0]);
-        pack4(bf, x.w[0].y, x.w[1].y, x.w[2].y, x.w[3].y);
+            for (int t = 0; t < 4; ++t) wt[buf][wave][t][lane] = bf[t];
+            __syncthreads();
 #pragma unroll
-        for (int mt = 0; mt < NT; ++mt) facc[mt][1] = mma4(x.an[mt], bf, facc[mt][1]);
-        pack4(bf, x.w[0].z, x.w[1].z, x.w[2].z, x.w[3].z);
+            for (int i = 0; i < SW; ++i) {
+                if (s - wave + turn + i * kFlWaves >= n_steps) break;   // uniform over the wavefront
 #pragma unroll
-        for (int mt = 0; mt < NT; ++mt) facc[mt][2] = mma4(x.an[mt], bf, facc[mt][2]);
-        pack4(bf, x.w[0].w, x.w[1].w, x.w[2].w, x.w[3].w);
+                for (int t = 0; t < 4; ++t) {
+                    bf[t] = wt[buf][turn + i * kFlWaves][t][lane];
 #pragma unroll
-        for (int mt = 0; mt < NT; ++mt) facc[mt][3] = mma4(x.an[mt], bf, facc[mt][3]);
+                    for (int mt = 0; mt < MW; ++mt) facc[mt][t] = mma4(x.an[i][mt], bf[t], facc[mt][t]);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int mt = 0; mt < MW; ++mt) facc[mt][t] = mma4(x.an[0][mt], bf[t], facc[mt][t]);
+        }
     };
 
     // groups of PD + 1 steps without control flow in between (a branch would make the compiler
     // drain the loads in flight where the paths meet), then the steps whose loads are under way
+    // (PAIRS: as many rounds for every wavefront; steps past the end change nothing)
     int s0 = wave;
-    for (; s0 + PD * NW < n_steps; s0 += NW * (PD + 1)) {
+    const int s_end = PAIRS ? (n_steps + NW - 1) / NW * NW : n_steps;
+    for (; s0 + PD * NW < s_end; s0 += NW * (PD + 1)) {
 #pragma unroll
         for (int u = 0; u <= PD; ++u) {
             const int s = s0 + u * NW;
@@ -353,24 +390,24 @@ __global__ __launch_bounds__(64 * NW, (FlBudget<OT, NT>::kWavesPerSimd)) void fi
 #pragma unroll
     for (int u = 0; u < PD; ++u) {
         const int s = s0 + u * NW;
-        if (s < n_steps) process(s, set[u]);   // uniform over the wavefront
+        if (s < s_end) process(s, set[u]);   // uniform over the wavefront
     }
 
     // A_1' = ReLU(Z_1' + b_1): the wavefronts' partial tiles are added in wavefront order
     __syncthreads();   // every wavefront is done with the slice that shares this memory
     float (*part)[Bp][kColChunk + 4] = reinterpret_cast<float (*)[Bp][kColChunk + 4]>(smem);
 #pragma unroll
-    for (int mt = 0; mt < NT; ++mt)
+    for (int mt = 0; mt < MW; ++mt)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-            *reinterpret_cast<float4*>(&part[wave][16 * mt + 4 * q + r][4 * j]) =
+            *reinterpret_cast<float4*>(&part[turn][16 * (mt0 + mt) + 4 * q + r][4 * j]) =
                 make_float4(facc[mt][0][r], facc[mt][1][r], facc[mt][2][r], facc[mt][3][r]);
     __syncthreads();
     for (int f = tid; f < Bp * (kColChunk / 4); f += 64 * NW) {
         const int b = f / (kColChunk / 4), c4 = (f % (kColChunk / 4)) * 4;
         float4 z = *reinterpret_cast<const float4*>(&part[0][b][c4]);
 #pragma unroll
-        for (int wv = 1; wv < NW; ++wv) {
+        for (int wv = 1; wv < kFlWaves; ++wv) {
             const float4 o = *reinterpret_cast<const float4*>(&part[wv][b][c4]);
             z.x += o.x; z.y += o.y; z.z += o.z; z.w += o.w;
         }
@@ -685,31 +722,29 @@ __global__ __launch_bounds__(64 * kWideWaves) void first_layer_wide_kernel(First
 // whole 64-column chunks of 16-byte aligned rows, and whole 16-row steps
 bool whole_tiles(const FirstArgs& a) { return a.d_out % kColChunk == 0 && a.w_off % 4 == 0 && a.d_in % 16 == 0; }
 
-template <typename OT, int NT, int NW, bool SPLIT>
-void launch_fl_nw(const FirstArgs& a, bool stream_w, unsigned grid, hipStream_t st) {
-    const dim3 block(64 * NW);
+template <typename OT, int NT, bool PAIRS, bool SPLIT>
+void launch_fl_pairs(const FirstArgs& a, bool stream_w, unsigned grid, hipStream_t st) {
+    const dim3 block(PAIRS ? 512 : 256);
     if constexpr (NT < 8) {   // (at 128 samples other layers go to the wide kernel)
         if (!whole_tiles(a)) {
-            hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWRagged, kWRagged, NW, SPLIT>), dim3(grid), block, 0, st, a);
+            hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWRagged, kWRagged, PAIRS, SPLIT>), dim3(grid), block, 0, st, a);
             return;
         }
     }
     if (stream_w && !a.shared_w)
-        hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWVectorStream, kWVectorStream, NW, SPLIT>), dim3(grid), block, 0, st, a);
-    else if (stream_w) hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWVectorStream, kWVector, NW, SPLIT>), dim3(grid), block, 0, st, a);
-    else hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWVector, kWVector, NW, SPLIT>), dim3(grid), block, 0, st, a);
+        hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWVectorStream, kWVectorStream, PAIRS, SPLIT>), dim3(grid), block, 0, st, a);
+    else if (stream_w) hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWVectorStream, kWVector, PAIRS, SPLIT>), dim3(grid), block, 0, st, a);
+    else hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWVector, kWVector, PAIRS, SPLIT>), dim3(grid), block, 0, st, a);
 }
 
 template <typename OT, int NT>
 void launch_fl_wm(const FirstArgs& a, bool split, bool stream_w, unsigned grid, hipStream_t st) {
     if constexpr (NT == 4 && sizeof(OT) == 4) {
-        const bool eight = a.total_blocks <= compute_units() && a.d_in >= 256;   // (see kFlWaves)
-        if (eight && split) launch_fl_nw<OT, NT, 2 * kFlWaves, true>(a, stream_w, grid, st);
-        else if (eight) launch_fl_nw<OT, NT, 2 * kFlWaves, false>(a, stream_w, grid, st);
-        else if (split) launch_fl_nw<OT, NT, kFlWaves, true>(a, stream_w, grid, st);
-        else launch_fl_nw<OT, NT, kFlWaves, false>(a, stream_w, grid, st);
+        if (split) launch_fl_pairs<OT, NT, false, true>(a, stream_w, grid, st);
+        else if (a.total_blocks <= compute_units() && a.d_in >= 256) launch_fl_pairs<OT, NT, true, false>(a, stream_w, grid, st);   // (see kFlWaves)
+        else launch_fl_pairs<OT, NT, false, false>(a, stream_w, grid, st);
     } else {
-        launch_fl_nw<OT, NT, kFlWaves, false>(a, stream_w, grid, st);
+        launch_fl_pairs<OT, NT, false, false>(a, stream_w, grid, st);
     }
 }
 
