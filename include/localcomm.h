@@ -108,10 +108,11 @@ int64_t lc_row_stride(int64_t P);
  * mix = SplitMix64 output function, G = 0x9E3779B97F4A7C15 (sampling with
  * replacement from the whole set, an independent stream per worker).
  * The iteration counter starts at k = 0.  No device memory is touched.
- * Four environment variables are read here, for measurement runs only (results agree to rounding
+ * Five environment variables are read here, for measurement runs only (results agree to rounding
  * whatever they say): LC_AVG_CHUNK_MB (1..1024, column chunk of the two-kernel averaging step),
  * LC_AVG_TWO_PHASE (0: one averaging kernel at every size), LC_SHARED_W_ORDER (0: replica-major
- * block order everywhere; n: sets of n replicas, see lc_set_lazy_broadcast), LC_SYNC_FIRST_LAYER
+ * block order everywhere; n: sets of n replicas, see lc_set_lazy_broadcast), LC_GROUP_SHARED (0: steps
+ * that read one model for all replicas take the replicas' batches one by one), LC_SYNC_FIRST_LAYER
  * (0: no tile-owner kernels, 1: for the first layer only; see lc_set_deferred_update).
  * Errors: LC_ERR_ARG (m < 1, null), LC_ERR_MODEL (P != lc_param_count, bad dims,
  * B outside 1..128, E > N). */

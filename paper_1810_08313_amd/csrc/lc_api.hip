@@ -457,8 +457,6 @@ int lc_init(int m, int64_t P, const lc_model* md, uint64_t seed, lc_handle** out
     h->da_part = nullptr;
     h->a0_layout = kInputsPlain;
     h->net_ok = net_shape_ok(h);
-    h->split_on = false;   // see split_products()
-    if (const char* e = getenv("LC_SPLIT_PRODUCTS")) h->split_on = atoi(e) != 0;   // tuning knob for measurement runs
     h->res_on = true;
     h->res_fuse_always = false;
     h->fl_on = true;

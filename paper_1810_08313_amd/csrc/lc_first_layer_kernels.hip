@@ -97,20 +97,16 @@ struct FlBudget {
 // through LDS, 8 of them between two barriers; a wavefront then holds half of the sums, which leaves registers for a step
 // ahead.  (With a share of the columns for either half, rows whose length is no multiple of 32 floats have twice as many
 // cache lines that two wavefronts write in part: 2000-777-300-10 1430 us instead of 1207.)
-// SPLIT (fp32 operands, see split_products): all products of bf16 parts.
-template <typename OT, int NT, int WM, int WMR, bool PAIRS, bool SPLIT>
+template <typename OT, int NT, int WM, int WMR, bool PAIRS>
 __global__ __launch_bounds__(PAIRS ? 512 : 256, (FlBudget<OT, NT>::kWavesPerSimd)) void first_layer_kernel(FirstArgs a) {
-    static_assert(!SPLIT || (sizeof(OT) == 4 && !PAIRS), "see split_products");
     constexpr int NW = PAIRS ? 2 * kFlWaves : kFlWaves;
     constexpr int SW = NW / kFlWaves, MW = NT / SW;   // steps of a round and tiles of samples that a wavefront multiplies
-    using LT = std::conditional_t<SPLIT, bf16_t, OT>;   // what LDS holds
-    constexpr int NP = SPLIT ? 3 : 1;
-    constexpr int kPad = sizeof(LT) == 2 ? 8 : 4;
+    constexpr int kPad = sizeof(OT) == 2 ? 8 : 4;
     constexpr int Bp = 16 * NT;
     constexpr int NS = Bp / 32;
     constexpr int PD = PAIRS ? 1 : FlBudget<OT, NT>::kAhead;
     // the dZ^T slice during the walk; the wavefronts' partial Z_1' tiles after it
-    constexpr size_t kSliceBytes = sizeof(LT) * NP * kColChunk * (Bp + kPad);
+    constexpr size_t kSliceBytes = sizeof(OT) * kColChunk * (Bp + kPad);
     constexpr size_t kPartBytes = sizeof(float) * kFlWaves * Bp * (kColChunk + 4);
     constexpr size_t kTileBytes = PAIRS ? 2 * NW * 4 * 64 * sizeof(Frag4<OT>) : 0;
     constexpr size_t kWalkBytes = kSliceBytes + kTileBytes;
@@ -118,8 +114,7 @@ __global__ __launch_bounds__(PAIRS ? 512 : 256, (FlBudget<OT, NT>::kWavesPerSimd
     __shared__ float bias_s[kColChunk];
     // row (c % 4) * 16 + c / 4 holds column c0 + c: the 16 lanes of an operand read (columns
     // 4 j + t) then hit 16 consecutive LDS rows
-    LT (*dzt)[kColChunk][Bp + kPad] = reinterpret_cast<LT (*)[kColChunk][Bp + kPad]>(smem);
-    __shared__ int huge_s[NW];   // by wavefront: it staged a delta above kMaxSplit
+    OT (*dzt)[Bp + kPad] = reinterpret_cast<OT (*)[Bp + kPad]>(smem);
     // PAIRS: [buffer][wavefront][t][lane], a lane's 4 x 4 block of an updated tile as operands (columns 4 j + t, rows 4 q ..)
     Frag4<OT> (*wt)[NW][4][64] = reinterpret_cast<Frag4<OT> (*)[NW][4][64]>(smem + kSliceBytes);
 
@@ -203,49 +198,23 @@ __global__ __launch_bounds__(PAIRS ? 512 : 256, (FlBudget<OT, NT>::kWavesPerSimd
     // first loads, then the staging of the slice (its own round trip overlaps with them)
 #pragma unroll
     for (int p = 0; p < PD; ++p) load_step(wave + p * NW, set[p]);
-    const OT* ZT = static_cast<const OT*>(a.dz_fm) + (static_cast<int64_t>(g) * a.dp_out + c0) * Bp;
     {
-        float m = 0.f;
+        const OT* ZT = static_cast<const OT*>(a.dz_fm) + (static_cast<int64_t>(g) * a.dp_out + c0) * Bp;
         for (int p = tid; p < kColChunk * (Bp / 8); p += 64 * NW) {
-            const int c = p / (Bp / 8), seg = p % (Bp / 8), row = (c & 3) * 16 + (c >> 2);
-            const Frag<OT> f = load8(ZT + static_cast<int64_t>(p) * 8);
-            if constexpr (SPLIT) {
-                const Parts x = split8(f.v);
-#pragma unroll
-                for (int i = 0; i < 3; ++i) *reinterpret_cast<bf16x8*>(&dzt[i][row][seg * 8]) = x.p[i];
-                m = fmaxf(m, largest(f.v));
-            } else {
-                *reinterpret_cast<Frag<OT>*>(&dzt[0][row][seg * 8]) = f;
-            }
+            const int c = p / (Bp / 8), seg = p % (Bp / 8);
+            *reinterpret_cast<Frag<OT>*>(&dzt[(c & 3) * 16 + (c >> 2)][seg * 8]) = load8(ZT + static_cast<int64_t>(p) * 8);
         }
-        const bool huge = __any(m > kMaxSplit);
-        if (SPLIT && lane == 0) huge_s[wave] = huge;
     }
     __syncthreads();
-    bool huge_dz = false;
-    if constexpr (SPLIT) {
-        int any = 0;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) any |= huge_s[w];
-        huge_dz = __builtin_amdgcn_readfirstlane(any) != 0;
-    }
     // bias of these columns: db_1 = sum_b dZ_1, the same update; kept for the forward epilogue
     if (tid < kColChunk && (WM != kWRagged || c0 + tid < a.d_out)) {
         float* bx = a.X + g * a.x_stride + a.b_off + c0 + tid;
         const float x = a.Xr[g * a.xr_stride + a.b_off + c0 + tid];
         float vb0 = a.Aux[g * a.aux_stride + a.b_off + c0 + tid];
         if (a.imp_in) vb0 = (vb0 - x) * a.inv_lr;
-        const int row = (tid & 3) * 16 + (tid >> 2);
+        const OT* zr = dzt[(tid & 3) * 16 + (tid >> 2)];
         float sb = 0.f;
-        if (SPLIT && huge_dz) {
-            for (int b = 0; b < a.B; ++b) sb += to_f32(ZT[tid * Bp + b]);
-        } else {
-            for (int b = 0; b < a.B; ++b) {
-                float z = to_f32(dzt[0][row][b]);
-                if constexpr (SPLIT) z = (z + to_f32(dzt[1][row][b])) + to_f32(dzt[2][row][b]);
-                sb += z;
-            }
-        }
+        for (int b = 0; b < a.B; ++b) sb += to_f32(zr[b]);
         const float vb = a.beta * vb0 + (sb + a.wd * x);
         if (a.V) a.V[g * a.x_stride + a.b_off + c0 + tid] = vb;
         *bx = x - a.lr * vb;
@@ -265,39 +234,13 @@ __global__ __launch_bounds__(PAIRS ? 512 : 256, (FlBudget<OT, NT>::kWavesPerSimd
         f32x4 acc[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-        bool huge = huge_dz;
-        if constexpr (SPLIT) {
-            float m = 0.f;
 #pragma unroll
-            for (int st = 0; st < NS; ++st) m = fmaxf(m, largest(x.af[st].v));
-            huge = huge || __any(m > kMaxSplit);
-        }
-        if (SPLIT && huge) {
+        for (int st = 0; st < NS; ++st)
 #pragma unroll
-            for (int st = 0; st < NS; ++st)
-#pragma unroll
-                for (int t = 0; t < 4; ++t) acc[t] = mma8(x.af[st], load8(ZT + (4 * j + t) * Bp + 32 * st + 8 * q), acc[t]);
-        } else {
-#pragma unroll
-            for (int st = 0; st < NS; ++st) {
-                if constexpr (SPLIT) {
-                    const Parts af = split8(x.af[st].v);
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        Parts zf;
-#pragma unroll
-                        for (int i = 0; i < 3; ++i) zf.p[i] = *reinterpret_cast<const bf16x8*>(&dzt[i][t * 16 + j][32 * st + 8 * q]);
-                        acc[t] = mma8(af, zf, acc[t]);
-                    }
-                } else {
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        const Frag<OT> zf = *reinterpret_cast<const Frag<OT>*>(&dzt[0][t * 16 + j][32 * st + 8 * q]);
-                        acc[t] = mma8(x.af[st], zf, acc[t]);
-                    }
-                }
+            for (int t = 0; t < 4; ++t) {
+                const Frag<OT> zf = *reinterpret_cast<const Frag<OT>*>(&dzt[t * 16 + j][32 * st + 8 * q]);
+                acc[t] = mma8(x.af[st], zf, acc[t]);
             }
-        }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             consume_here(x.w[r]);
@@ -325,25 +268,6 @@ __global__ __launch_bounds__(PAIRS ? 512 : 256, (FlBudget<OT, NT>::kWavesPerSimd
             }
         }
         // Z_1' += A_0'[:, k0 .. k0+15] W_1[k0 .. k0+15, :] with the tile just updated
-        if constexpr (SPLIT) {
-            float m = 0.f;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) m = fmaxf(m, largest<4>({x.w[r].x, x.w[r].y, x.w[r].z, x.w[r].w}));
-#pragma unroll
-            for (int mt = 0; mt < NT; ++mt) m = fmaxf(m, largest(x.an[0][mt].v));
-            if (!__any(m > kMaxSplit)) {
-                const Parts4 wp[4] = {split4(x.w[0].x, x.w[1].x, x.w[2].x, x.w[3].x), split4(x.w[0].y, x.w[1].y, x.w[2].y, x.w[3].y),
-                                      split4(x.w[0].z, x.w[1].z, x.w[2].z, x.w[3].z), split4(x.w[0].w, x.w[1].w, x.w[2].w, x.w[3].w)};
-#pragma unroll
-                for (int mt = 0; mt < NT; ++mt) {
-                    const float (&v)[4] = x.an[0][mt].v;
-                    const Parts4 an = split4(v[0], v[1], v[2], v[3]);
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) facc[mt][t] = mma4(an, wp[t], facc[mt][t]);
-                }
-                return;
-            }
-        }
         Frag4<OT> bf[4];
         pack4(bf[0], x.w[0].x, x.w[1].x, x.w[2].x, x.w[3].x);
         pack4(bf[1], x.w[0].y, x.w[1].y, x.w[2].y, x.w[3].y);
@@ -722,36 +646,36 @@ __global__ __launch_bounds__(64 * kWideWaves) void first_layer_wide_kernel(First
 // whole 64-column chunks of 16-byte aligned rows, and whole 16-row steps
 bool whole_tiles(const FirstArgs& a) { return a.d_out % kColChunk == 0 && a.w_off % 4 == 0 && a.d_in % 16 == 0; }
 
-template <typename OT, int NT, bool PAIRS, bool SPLIT>
+template <typename OT, int NT, bool PAIRS>
 void launch_fl_pairs(const FirstArgs& a, bool stream_w, unsigned grid, hipStream_t st) {
     const dim3 block(PAIRS ? 512 : 256);
     if constexpr (NT < 8) {   // (at 128 samples other layers go to the wide kernel)
         if (!whole_tiles(a)) {
-            hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWRagged, kWRagged, PAIRS, SPLIT>), dim3(grid), block, 0, st, a);
+            hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWRagged, kWRagged, PAIRS>), dim3(grid), block, 0, st, a);
             return;
         }
     }
     if (stream_w && !a.shared_w)
-        hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWVectorStream, kWVectorStream, PAIRS, SPLIT>), dim3(grid), block, 0, st, a);
-    else if (stream_w) hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWVectorStream, kWVector, PAIRS, SPLIT>), dim3(grid), block, 0, st, a);
-    else hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWVector, kWVector, PAIRS, SPLIT>), dim3(grid), block, 0, st, a);
+        hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWVectorStream, kWVectorStream, PAIRS>), dim3(grid), block, 0, st, a);
+    else if (stream_w) hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWVectorStream, kWVector, PAIRS>), dim3(grid), block, 0, st, a);
+    else hipLaunchKernelGGL((first_layer_kernel<OT, NT, kWVector, kWVector, PAIRS>), dim3(grid), block, 0, st, a);
 }
 
 template <typename OT, int NT>
-void launch_fl_wm(const FirstArgs& a, bool split, bool stream_w, unsigned grid, hipStream_t st) {
+void launch_fl_wm(const FirstArgs& a, bool stream_w, unsigned grid, hipStream_t st) {
     if constexpr (NT == 4 && sizeof(OT) == 4) {
-        if (split) launch_fl_pairs<OT, NT, false, true>(a, stream_w, grid, st);
-        else if (a.total_blocks <= compute_units() && a.d_in >= 256) launch_fl_pairs<OT, NT, true, false>(a, stream_w, grid, st);   // (see kFlWaves)
-        else launch_fl_pairs<OT, NT, false, false>(a, stream_w, grid, st);
-    } else {
-        launch_fl_pairs<OT, NT, false, false>(a, stream_w, grid, st);
+        if (a.total_blocks <= compute_units() && a.d_in >= 256) {   // (see kFlWaves)
+            launch_fl_pairs<OT, NT, true>(a, stream_w, grid, st);
+            return;
+        }
     }
+    launch_fl_pairs<OT, NT, false>(a, stream_w, grid, st);
 }
 
 template <typename OT>
-hipError_t launch_fl(const FirstArgs& a, int nt, bool split, bool stream_w, unsigned grid, hipStream_t st) {
-    if (nt == 2) launch_fl_wm<OT, 2>(a, split, stream_w, grid, st);
-    else if (nt == 4) launch_fl_wm<OT, 4>(a, split, stream_w, grid, st);
+hipError_t launch_fl(const FirstArgs& a, int nt, bool stream_w, unsigned grid, hipStream_t st) {
+    if (nt == 2) launch_fl_wm<OT, 2>(a, stream_w, grid, st);
+    else if (nt == 4) launch_fl_wm<OT, 4>(a, stream_w, grid, st);
     else if constexpr (sizeof(OT) == 2) {
         // 128 samples.  (Whole tiles whose height is no multiple of the 128 rows that the wide kernel's
         // wavefronts take together stay with the other one: cut off as ragged rows are, they run 0.94 ..
@@ -759,7 +683,7 @@ hipError_t launch_fl(const FirstArgs& a, int nt, bool split, bool stream_w, unsi
         const dim3 block(64 * kWideWaves);
         if (a.chunk_cols == 96) hipLaunchKernelGGL((first_layer_wide_kernel<OT, kWRagged, kWRagged, 6>), dim3(grid), block, 0, st, a);
         else if (!whole_tiles(a)) hipLaunchKernelGGL((first_layer_wide_kernel<OT, kWRagged, kWRagged>), dim3(grid), block, 0, st, a);
-        else if (a.d_in % (16 * kWideWaves) != 0) launch_fl_wm<OT, 8>(a, split, stream_w, grid, st);
+        else if (a.d_in % (16 * kWideWaves) != 0) launch_fl_wm<OT, 8>(a, stream_w, grid, st);
         else if (stream_w && !a.shared_w)
             hipLaunchKernelGGL((first_layer_wide_kernel<OT, kWVectorStream, kWVectorStream>), dim3(grid), block, 0, st, a);
         else if (stream_w) hipLaunchKernelGGL((first_layer_wide_kernel<OT, kWVectorStream, kWVector>), dim3(grid), block, 0, st, a);
@@ -861,8 +785,8 @@ hipError_t launch_first_layer(lc_handle* h) {
     a.total_blocks = static_cast<int64_t>(S.G) * a.n_chunks;
     const unsigned grid = static_cast<unsigned>((a.total_blocks + kXcds - 1) / kXcds * kXcds);
     timing_start(h, kTimeBwd, 1, kBwdFirstLayer);
-    const hipError_t e = bf16 ? launch_fl<bf16_t>(a, S.Bp / 16, false, h->stream_weights, grid, h->stream)
-                              : launch_fl<float>(a, S.Bp / 16, split_products(h), h->stream_weights, grid, h->stream);
+    const hipError_t e = bf16 ? launch_fl<bf16_t>(a, S.Bp / 16, h->stream_weights, grid, h->stream)
+                              : launch_fl<float>(a, S.Bp / 16, h->stream_weights, grid, h->stream);
     timing_stop(h, kTimeBwd, 1, kBwdFirstLayer);
     if (e == hipSuccess) h->imp[1] = sb.next;
     return e;

@@ -147,7 +147,6 @@ struct lc_handle {
     float* res_a1x;         // [slots][m][dp1/16][Bp][16] exchange buffer of the resident kernel, by step of a launch; null when the shape does not qualify
     unsigned* res_ctr;      // error flag, counters and placement probe of the resident kernels, see kCtr* above
     unsigned res_arrivals;  // value of every counter once the queued launches have run (zeroed with the scratch at attach)
-    bool split_on;          // see split_products()
     bool net_ok;            // the model runs whole local steps on one compute unit per replica (net_kernel)
     float* da_part;         // shares of dA of the largest layer whose columns are shared out (see BwdArgs), or null
     float* res_avx;         // [2 parities][m][Ps] models handed over at averaging steps inside a launch
@@ -226,21 +225,6 @@ inline bool fetches_its_inputs(const lc_handle* h) { return h->res_on && h->res_
 inline bool first_forward_reads_rows(const lc_handle* h) {
     return h->train.Bp == 128 && static_cast<int64_t>(h->train.G) * (h->layer[1].dp_out / kColChunk) >= 256;
 }
-// fp32 products of a step's launches per layer on the bf16 matrix cores (Parts in lc_mma.h), where they are what a kernel
-// waits for.  Off unless LC_SPLIT_PRODUCTS asks for it: the rounding is another one, a ReLU gate that is met on one side only
-// is amplified over the steps of later calls, and of four large drawn models one differed by 1.0e-3 from the fp32 instructions in a
-// call's state after the third call, more than fp32 results may (both were 2e-7 from 64 bits after the first).  5 steps, fp32 instructions and parts: 3072-1024-1024-10, 16 workers of 64 samples, 1794 and 1661 us;
-// 2048-1500-1000-100, 12 of 100, 3610 and 3150; 784-500-300-10, 16 of 100, 693 and 647, 16 of 64, 502 and 488; tau = 1,
-// 3072-2048-2048-10, 16 of 64, an iteration 763 and 705.  Gradients are 0.86 times (0.66 to 1.00) as far from 64 bits (40
-// drawn models).  Not for
-//   up to 32 samples in the backward pass, fewer than 64 in a block of the forward pass: too few products for an operand
-//     that has to be split (784-500-300-10, 16 of 32, 385 and 397 us)
-//   rows of fewer than 64 columns (last layers), workgroups of one column chunk: latency (700-300-10, 12 of 110, 297 and 310)
-//   128 samples in layers that may go by tile (see launch_sync_nt)
-//   forward passes of fewer than 256 inputs: 1.02 times as fast, but a step of 40-200-512-10 that the tests take unforced
-//     then meets a gate
-//   models that have a kernel of their own on chip, whichever way they run
-inline bool split_products(const lc_handle* h) { return h->split_on && h->md.gemm != LC_GEMM_BF16; }
 // The layout of a call's mini-batches; more_steps: its periods have more than one step, so that the first layer's
 // kernel may run the next step's forward pass.
 inline InputLayout input_layout(const lc_handle* h, bool more_steps) {

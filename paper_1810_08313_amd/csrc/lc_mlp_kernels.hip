@@ -249,12 +249,8 @@ struct FwdArgs {
 //
 // FRAGS instances (layer 1 of most training steps, see input_layout) read the activations in fragment order.
 constexpr int kActRows = 0, kActFeatureMajor = 1, kActFragments = 2;
-//
-// SPLIT (fp32 operands, see split_products): a step's weights and activations are split into bf16 parts in registers.  A sum
-// that is not finite is formed again from the operands, so infinities and NaN come out as the fp32 instructions give them.
-template <typename OT, int MT, int NW, int PF, int WM, int AM, bool SPLIT = false>
+template <typename OT, int MT, int NW, int PF, int WM, int AM>
 __global__ __launch_bounds__(NW * 64) void forward_kernel(FwdArgs a) {
-    static_assert(!SPLIT || (sizeof(OT) == 4 && MT >= 4 && WM != kWGeneric), "see split_products");
     constexpr bool AFM = AM == kActFeatureMajor, FRAGS = AM == kActFragments;
     constexpr int VW = 16 / sizeof(OT);
     static_assert(!AFM || MT % VW == 0, "AFM needs whole groups of VW tiles");
@@ -413,24 +409,6 @@ __global__ __launch_bounds__(NW * 64) void forward_kernel(FwdArgs a) {
                 w[e].w = e < left ? w[e].w : 0.f;
             }
         }
-        if constexpr (SPLIT) {
-            auto column = [&](int t) {
-                float x[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) x[e] = t == 0 ? w[e].x : t == 1 ? w[e].y : t == 2 ? w[e].z : w[e].w;
-                return split8(x);
-            };
-            Parts wp[4];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) wp[t] = column(t);
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                const Parts ap = split8(f[mt].v);
-#pragma unroll
-                for (int t = 0; t < 4; ++t) acc[mt][t] = mma8(ap, wp[t], acc[mt][t]);
-            }
-            return;
-        }
         transpose_a_step(f);
         Frag<OT> bf;
         float x[8];
@@ -483,19 +461,6 @@ __global__ __launch_bounds__(NW * 64) void forward_kernel(FwdArgs a) {
         }
     }
 
-    // sample b of the block, column c of the chunk, from the operands
-    auto plain_sum = [&](int b, int c, float z) {
-        if (isfinite(z) || c0 + c >= a.d_out) return z;
-        z = 0.f;
-#pragma unroll 1
-        for (int k = 0; k < a.d_in; ++k) {
-            int64_t at = static_cast<int64_t>(b) * a.dp_in + k;
-            if constexpr (FRAGS)   // (fp32: see load_frag and InputLayout)
-                at = static_cast<int64_t>(b / 16 * 16) * a.dp_in + k / 32 * kFragElems + k % 32 / 16 * 256 + 4 * (k % 16 / 4 * 16 + b % 16) + k % 4;
-            z = fmaf(to_f32(A[at]), W[static_cast<int64_t>(k) * a.d_out + c0 + c], z);
-        }
-        return z;
-    };
     // combine the wavefronts' partial tiles: every wavefront parks its own, then all threads add
     // them up in wavefront order (the order fixes the rounding) into the first one
 #pragma unroll
@@ -517,17 +482,6 @@ __global__ __launch_bounds__(NW * 64) void forward_kernel(FwdArgs a) {
         for (int w = 1; w < NW; ++w) {
             const float4 o = *reinterpret_cast<const float4*>(&part[w][row][c4]);
             v.x = o.x + v.x; v.y = o.y + v.y; v.z = o.z + v.z; v.w = o.w + v.w;
-        }
-        if constexpr (SPLIT) {
-            if (!isfinite((v.x + v.y) + (v.z + v.w))) {   // (finite numbers that overflow here are formed again for nothing)
-                const int b = batch_row(row / 16, row % 16);   // (place c of a narrow tile is column c too)
-                if (row0 + b < a.B) {
-                    v.x = plain_sum(b, c4, v.x);
-                    v.y = plain_sum(b, c4 + 1, v.y);
-                    v.z = plain_sum(b, c4 + 2, v.z);
-                    v.w = plain_sum(b, c4 + 3, v.w);
-                }
-            }
         }
         *reinterpret_cast<float4*>(&part[0][row][c4]) = v;
     }
@@ -806,32 +760,24 @@ struct BwdArgs {
 // workgroups share a CU where one did (784x500 with 16 replicas of 100 samples, fp32: 43 -> 36 us).
 // FRAGS: they read their inputs in fragments.  (Chosen at run time it costs registers: 784x512, 32 replicas of 128
 // samples, fp32: 62 us instead of 55.)
-// SPLIT (fp32 operands, see split_products): the products are formed of bf16 parts.  The slices of dZ_l are split when they
-// are staged, the wavefront's rows of A_{l-1}^T once, and a W tile when it is parked, so that LDS holds three planes of each.
-template <typename OT, int NT, int WM, bool DAO = false, bool NDA = false, bool FRAGS = NDA, bool SPLIT = false>
+template <typename OT, int NT, int WM, bool DAO = false, bool NDA = false, bool FRAGS = NDA>
 __global__ __launch_bounds__(256, NT == 8 && !NDA && !DAO && (sizeof(OT) == 4 || WM == kWGeneric) ? 1 : 2) void backward_kernel(BwdArgs a) {
-    static_assert(!SPLIT || (sizeof(OT) == 4 && NT >= 4 && WM != kWGeneric), "see split_products");
-    using LT = std::conditional_t<SPLIT, bf16_t, OT>;    // what LDS holds
-    constexpr int NP = SPLIT ? 3 : 1;
     // 128 samples of bf16 operands, two workgroups per CU: the registers just suffice with addresses as in place(), and where
     // rows do not stream (their instances have more to hold) with the wavefront's rows of A_{l-1}^T parked in LDS.  (With
     // one, 384 row blocks of 1500x1000, 16 workers of 100 samples, went in two rounds of which the second was half empty.
     // 5 steps with one and two: 3072-1500-1000-100 2526 and 2441 us; 1500-900-1600-100, 20 workers of 70, 2335 and 2225;
     // 1024-2048-2048-10, 24 of 110, 3105 and 2991; 784-500-300-10, 16 of 100, 431 and 423; 300-704-500-20, 16 of 80, 461 and 460.)
     constexpr bool kPair = NT == 8 && !NDA && !DAO && sizeof(OT) == 2 && WM != kWGeneric;
-    constexpr bool kLaneOffsets = SPLIT || kPair, kParkA = kPair && WM != kWVectorStream;
-    constexpr int kPad = sizeof(LT) == 2 ? 8 : 4;
+    constexpr bool kParkA = kPair && WM != kWVectorStream;
+    constexpr int kPad = sizeof(OT) == 2 ? 8 : 4;
     constexpr int Bp = 16 * NT;
     constexpr int NS = NT / 2;                 // 32-wide steps over the batch; also staging pieces per thread
     // dZ^T slice: row (c % 4) * 16 + c / 4 holds column c0 + c, so that the 16 lanes
     // of a B-operand read (columns 4 j + t) hit 16 consecutive LDS rows
-    __shared__ __attribute__((aligned(16))) LT dzt_lds[NP][kColChunk][Bp + kPad];
-    __shared__ __attribute__((aligned(16))) LT dz_lds[NP][NDA ? 1 : Bp][kColChunk + kPad];
-    // (the parts of W: no padding, so that two workgroups of 64 samples fit a CU, but the 16-byte pieces of a row
-    // permuted by the row)
-    __shared__ __attribute__((aligned(16))) LT wlds[NDA ? 1 : 4][NP][kRowsPerWave][kColChunk + (SPLIT ? 0 : kPad)];
+    __shared__ __attribute__((aligned(16))) OT dzt_lds[kColChunk][Bp + kPad];
+    __shared__ __attribute__((aligned(16))) OT dz_lds[NDA ? 1 : Bp][kColChunk + kPad];
+    __shared__ __attribute__((aligned(16))) OT wlds[NDA ? 1 : 4][kRowsPerWave][kColChunk + kPad];
     __shared__ Frag<OT> a_lds[kParkA ? 4 : 1][NS][kParkA ? 64 : 1];   // (kParkA)
-    __shared__ __attribute__((aligned(16))) int huge_s[4];   // by wavefront: it staged a delta above kMaxSplit
 
     const int64_t logical = xcd_logical_block(a.total_blocks);
     if (logical < 0) return;
@@ -839,7 +785,7 @@ __global__ __launch_bounds__(256, NT == 8 && !NDA && !DAO && (sizeof(OT) == 4 ||
     int g, rem;
     shared_order(logical, per_group, a.shared_w, g, rem);
     const int rb = rem / a.col_split, cs = rem % a.col_split;
-    const int tid = threadIdx.x, lane = tid & 63, wave = kLaneOffsets ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = kPair ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
     const int j = lane & 15, q = lane >> 4;
     const int k0 = (rb * 4 + wave) * kRowsPerWave;   // < dp_in: the grid covers dp_in / 64 row blocks exactly
     const bool vec = a.vec != 0;
@@ -850,7 +796,7 @@ __global__ __launch_bounds__(256, NT == 8 && !NDA && !DAO && (sizeof(OT) == 4 ||
     float* Vw = a.V ? a.V + g * a.x_stride + a.w_off : nullptr;
     const float* Va = DAO ? nullptr : a.Aux + g * a.aux_stride + a.w_off;
     // Place of row k0 + 4 q + r (past d_in: of the last row, which is read in its stead without a branch between the
-    // loads; such weights are zeroed when used and never stored), columns c0 + 4 j and on.  kLaneOffsets: a base that is the
+    // loads; such weights are zeroed when used and never stored), columns c0 + 4 j and on.  kPair: a base that is the
     // same for the whole wavefront and byte offsets that a lane keeps for the walk, which leaves registers free.  (Instances
     // that do not need them gain nothing from that: whole steps 0.97 to 1.02 times as fast.)
     const int last = a.d_in - 1, back = k0 < last ? k0 : last;
@@ -861,7 +807,7 @@ __global__ __launch_bounds__(256, NT == 8 && !NDA && !DAO && (sizeof(OT) == 4 ||
         woff[r] = 4u * (static_cast<unsigned>((row < last ? row : last) - back) * static_cast<unsigned>(a.d_out) + 4u * j);
     }
     auto place = [&](auto* base, int r, int c0) {
-        if constexpr (kLaneOffsets) {
+        if constexpr (kPair) {
             using C = std::conditional_t<std::is_const_v<std::remove_pointer_t<decltype(base)>>, const char, char>;
             return reinterpret_cast<decltype(base)>(reinterpret_cast<C*>(base + static_cast<int64_t>(back) * a.d_out + c0) + woff[r]);
         } else {
@@ -896,28 +842,15 @@ __global__ __launch_bounds__(256, NT == 8 && !NDA && !DAO && (sizeof(OT) == 4 ||
     for (int nt = 0; nt < NT; ++nt) dacc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // this lane's A operands for the dW product: row k0 + j of A_{l-1}^T, all batch steps
-    auto load_a = [&](int s) {
-        return FRAGS ? load_frag(AT + static_cast<int64_t>(k0) * Bp + s * kFragElems, lane)
-                     : load8(AT + static_cast<int64_t>(k0 + j) * Bp + 32 * s + 8 * q);
-    };
-    std::conditional_t<SPLIT, Parts, Frag<OT>> af[NS];
-    bool huge_a = false;   // of the wavefront's rows
+    Frag<OT> af[NS];
     if constexpr (!DAO) {
-        Frag<OT> f[NS];
-#pragma unroll
-        for (int s = 0; s < NS; ++s) f[s] = load_a(s);
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-            if constexpr (SPLIT) {
-                af[s] = split8(f[s].v);
-                huge_a = huge_a || largest(f[s].v) > kMaxSplit;
-            } else if constexpr (kParkA) {
-                a_lds[wave][s][lane] = f[s];
-            } else {
-                af[s] = f[s];
-            }
+            const Frag<OT> f = FRAGS ? load_frag(AT + static_cast<int64_t>(k0) * Bp + s * kFragElems, lane)
+                                     : load8(AT + static_cast<int64_t>(k0 + j) * Bp + 32 * s + 8 * q);
+            if constexpr (kParkA) a_lds[wave][s][lane] = f;
+            else af[s] = f;
         }
-        huge_a = __any(huge_a);
     }
 
     // ReLU gates of this lane's dA entries, fetched now (one bit each) instead of after the walk
@@ -960,58 +893,32 @@ __global__ __launch_bounds__(256, NT == 8 && !NDA && !DAO && (sizeof(OT) == 4 ||
             const OT* src_t = dZT + static_cast<int64_t>(c0) * Bp;
 #pragma unroll
             for (int s = 0; s < NS; ++s)
-                st_t[s] = kLaneOffsets ? load8(src_t + 2048 * s + tid * 8u) : load8(src_t + static_cast<int64_t>(tid + 256 * s) * 8);
+                st_t[s] = kPair ? load8(src_t + 2048 * s + tid * 8u) : load8(src_t + static_cast<int64_t>(tid + 256 * s) * 8);
         }
         if (need_da) {
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
                 const int p = tid + 256 * s;
-                st_b[s] = kLaneOffsets ? load8(dZ + static_cast<int64_t>(32 * s) * a.dp_out + c0 + zoff)
-                                       : load8(dZ + static_cast<int64_t>(p >> 3) * a.dp_out + c0 + (p & 7) * 8);
+                st_b[s] = kPair ? load8(dZ + static_cast<int64_t>(32 * s) * a.dp_out + c0 + zoff)
+                                : load8(dZ + static_cast<int64_t>(p >> 3) * a.dp_out + c0 + (p & 7) * 8);
             }
         }
     };
     auto stage_to_lds = [&]() {
-        auto put = [](auto& tile, int row, int at, const Frag<OT>& f) {
-            if constexpr (SPLIT) {
-                const Parts x = split8(f.v);
-#pragma unroll
-                for (int i = 0; i < 3; ++i) *reinterpret_cast<bf16x8*>(&tile[i][row][at]) = x.p[i];
-            } else {
-                *reinterpret_cast<Frag<OT>*>(&tile[0][row][at]) = f;
-            }
-        };
         if constexpr (!DAO) {
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
                 const int p = tid + 256 * s;
                 const int c = p / (Bp / 8), seg = p % (Bp / 8);
-                put(dzt_lds, (c & 3) * 16 + (c >> 2), seg * 8, st_t[s]);
+                *reinterpret_cast<Frag<OT>*>(&dzt_lds[(c & 3) * 16 + (c >> 2)][seg * 8]) = st_t[s];
             }
         }
         if (need_da) {
 #pragma unroll
             for (int s = 0; s < NS; ++s) {
                 const int p = tid + 256 * s;
-                put(dz_lds, p >> 3, (p & 7) * 8, st_b[s]);
+                *reinterpret_cast<Frag<OT>*>(&dz_lds[p >> 3][(p & 7) * 8]) = st_b[s];
             }
-        }
-        if constexpr (SPLIT) {   // (both slices hold the same deltas)
-            float m = 0.f;
-#pragma unroll
-            for (int s = 0; s < NS; ++s) m = fmaxf(m, DAO ? largest(st_b[s].v) : largest(st_t[s].v));
-            const bool huge = __any(m > kMaxSplit);
-            if (lane == 0) huge_s[wave] = huge;
-        }
-    };
-    auto operand = [](const auto& tile, int row, int at) {
-        if constexpr (SPLIT) {
-            Parts x;
-#pragma unroll
-            for (int i = 0; i < 3; ++i) x.p[i] = *reinterpret_cast<const bf16x8*>(&tile[i][row][at]);
-            return x;
-        } else {
-            return *reinterpret_cast<const Frag<OT>*>(&tile[0][row][at]);
         }
     };
 
@@ -1023,11 +930,6 @@ __global__ __launch_bounds__(256, NT == 8 && !NDA && !DAO && (sizeof(OT) == 4 ||
         const int c0 = chunk_at(i) * kColChunk;
         const bool has_next = i + 1 < cc_n;
         if (has_next) issue_loads(chunk_at(i + 1), wn, vn);
-        bool huge_dz = false;
-        if constexpr (SPLIT) {
-            const int4 h = *reinterpret_cast<const int4*>(huge_s);
-            huge_dz = __builtin_amdgcn_readfirstlane(h.x | h.y | h.z | h.w) != 0;
-        }
 
         // bias of these 64 columns: db_l = sum_b dZ_l from the staged slice, then the same update
         // (one thread per column).  Every row block of the replica walks this chunk; the job goes
@@ -1037,20 +939,13 @@ __global__ __launch_bounds__(256, NT == 8 && !NDA && !DAO && (sizeof(OT) == 4 ||
             const float x = a.Xr[g * a.xr_stride + a.b_off + c0 + tid];   // requested before the sum below
             float v0 = a.Aux[g * a.aux_stride + a.b_off + c0 + tid];
             if (a.imp_in) v0 = (v0 - x) * a.inv_lr;
+            const OT* zr = dzt_lds[(tid & 3) * 16 + (tid >> 2)];
             float sb = 0.f;   // (batch entries beyond B are zeros; the order of the sum is the batch order)
-            if (SPLIT && huge_dz) {
-#pragma unroll 1
-                for (int b = 0; b < Bp; ++b) sb += to_f32(dZT[static_cast<int64_t>(c0 + tid) * Bp + b]);
-            } else {
 #pragma unroll
-                for (int b8 = 0; b8 < Bp; b8 += 8) {
-                    const auto f = operand(dzt_lds, (tid & 3) * 16 + (tid >> 2), b8);
+            for (int b8 = 0; b8 < Bp; b8 += 8) {
+                const Frag<OT> f = *reinterpret_cast<const Frag<OT>*>(zr + b8);
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        if constexpr (SPLIT) sb += (to_f32(f.p[0][e]) + to_f32(f.p[1][e])) + to_f32(f.p[2][e]);
-                        else sb += to_f32(f.v[e]);
-                    }
-                }
+                for (int e = 0; e < 8; ++e) sb += to_f32(f.v[e]);
             }
             const float vb = momentum_update(a.beta, v0, sb, a.wd, x);
             if (a.V) a.V[g * a.x_stride + a.b_off + c0 + tid] = vb;
@@ -1061,28 +956,16 @@ __global__ __launch_bounds__(256, NT == 8 && !NDA && !DAO && (sizeof(OT) == 4 ||
         if constexpr (!DAO) {
 #pragma unroll
             for (int t = 0; t < 4; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-            if (SPLIT && (huge_a || huge_dz)) {
-                int at = lane;   // (opaque: no address is to be held in registers across the walk)
-                asm volatile("" : "+v"(at));
-                const int j = at & 15, q = at >> 4;
-#pragma unroll 1
-                for (int b = 8 * q; b < Bp; b += (b & 7) == 7 ? 25 : 1) {   // 8 of every 32 samples, one instruction each
-                    const float x = AT[FRAGS ? static_cast<int64_t>(k0) * Bp + b / 32 * kFragElems + 64 * (b & 4) + 4 * at + (b & 3)
-                                             : static_cast<int64_t>(k0 + j) * Bp + b];
 #pragma unroll
-                    for (int t = 0; t < 4; ++t)
-                        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, dZT[static_cast<int64_t>(c0 + 4 * j + t) * Bp + b], acc[t], 0, 0, 0);
-                }
-            } else {
+            for (int s = 0; s < NS; ++s) {
+                if constexpr (kParkA) af[s] = a_lds[wave][s][lane];
 #pragma unroll
-                for (int s = 0; s < NS; ++s) {
-                    if constexpr (kParkA) af[s] = a_lds[wave][s][lane];
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) acc[t] = mma8(af[s], operand(dzt_lds, t * 16 + j, 32 * s + 8 * q), acc[t]);
+                for (int t = 0; t < 4; ++t) {
+                    const Frag<OT> bf = *reinterpret_cast<const Frag<OT>*>(&dzt_lds[t * 16 + j][32 * s + 8 * q]);
+                    acc[t] = mma8(af[s], bf, acc[t]);
                 }
             }
         }
-        bool huge_w = false;
         if (need_da) {
             // old weights, in operand precision, to LDS in natural column order
 #pragma unroll
@@ -1090,43 +973,8 @@ __global__ __launch_bounds__(256, NT == 8 && !NDA && !DAO && (sizeof(OT) == 4 ||
                 const bool in = WM == kWGeneric || k0 + 4 * q + r < a.d_in;
                 // (columns past the row end: what a ragged load found there)
                 const int left = WM == kWRagged ? a.d_out - (c0 + 4 * j) : 4;
-                const float x[4] = {in && left > 0 ? w[r].x : 0.f, in && left > 1 ? w[r].y : 0.f, in && left > 2 ? w[r].z : 0.f,
-                                    in && left > 3 ? w[r].w : 0.f};
-                if constexpr (SPLIT) {
-                    huge_w = huge_w || largest(x) > kMaxSplit;
-                    const Parts4 f = split4(x[0], x[1], x[2], x[3]);
-                    const int row = 4 * q + r, at = 8 * ((j >> 1) ^ (row & 7)) + 4 * (j & 1);
-#pragma unroll
-                    for (int i = 0; i < 3; ++i) *reinterpret_cast<bf16x4*>(&wlds[wave][i][row][at]) = f.p[i];
-                } else {
-                    store4<OT>(&wlds[wave][0][4 * q + r][4 * j], x[0], x[1], x[2], x[3]);
-                }
-            }
-            huge_w = SPLIT && __any(huge_w);
-        }
-        if constexpr (SPLIT && !NDA) {   // dA with the fp32 instructions, while the old weights are at hand
-            if (huge_w || huge_dz) {
-                int at = lane;   // (opaque, as above)
-                asm volatile("" : "+v"(at));
-                const int j = at & 15, q = at >> 4;
-                wave_sync_lds();
-                float* tile = reinterpret_cast<float*>(&wlds[wave][0][0][0]);   // (three planes: room for 16 x 64 floats)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const bool in = WM == kWGeneric || k0 + 4 * q + r < a.d_in;
-                    const int left = WM == kWRagged ? a.d_out - (c0 + 4 * j) : 4;
-                    store4<float>(tile + (4 * q + r) * kColChunk + 4 * j, in && left > 0 ? w[r].x : 0.f, in && left > 1 ? w[r].y : 0.f,
-                                  in && left > 2 ? w[r].z : 0.f, in && left > 3 ? w[r].w : 0.f);
-                }
-                wave_sync_lds();
-#pragma unroll 1
-                for (int c = 8 * q; c < kColChunk; c += (c & 7) == 7 ? 25 : 1) {
-                    const float x = tile[j * kColChunk + c];
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt)
-                        dacc[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, dZ[static_cast<int64_t>(16 * nt + j) * a.dp_out + c0 + c],
-                                                                        dacc[nt], 0, 0, 0);
-                }
+                store4<OT>(&wlds[wave][4 * q + r][4 * j], in && left > 0 ? w[r].x : 0.f, in && left > 1 ? w[r].y : 0.f,
+                           in && left > 2 ? w[r].z : 0.f, in && left > 3 ? w[r].w : 0.f);
             }
         }
         // update and store
@@ -1154,15 +1002,18 @@ __global__ __launch_bounds__(256, NT == 8 && !NDA && !DAO && (sizeof(OT) == 4 ||
                 if (!a.skip_x) store_wm<WM>(place(W, r, c0), 0, left, vec, w[r]);
             }
         }
-        if (need_da && !(SPLIT && (huge_w || huge_dz))) {
+        if (need_da) {
             wave_sync_lds();
             // dA^T[k][b] += sum_c W[k][c] dZ[b][c] over this chunk's 64 columns
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
                 if (sizeof(OT) == 4 && WM == kWGeneric && 32 * s >= a.d_out) break;   // (no columns; uniform)
-                const auto wf = operand(wlds[wave], j, SPLIT ? 8 * ((4 * s + q) ^ (j & 7)) : 32 * s + 8 * q);
+                const Frag<OT> wf = *reinterpret_cast<const Frag<OT>*>(&wlds[wave][j][32 * s + 8 * q]);
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt) dacc[nt] = add_mma8(wf, operand(dz_lds, 16 * nt + j, 32 * s + 8 * q), dacc[nt]);
+                for (int nt = 0; nt < NT; ++nt) {
+                    const Frag<OT> zf = *reinterpret_cast<const Frag<OT>*>(&dz_lds[16 * nt + j][32 * s + 8 * q]);
+                    dacc[nt] = mma8(wf, zf, dacc[nt]);
+                }
             }
         }
         if (has_next) {
@@ -1544,26 +1395,16 @@ int weight_mode(bool vec, bool stream, int d_out) {
 // The accumulators of a full 128-row batch leave no registers for prefetching at two
 // wavefronts per SIMD, so that case runs four wavefronts per block with a deeper queue.
 template <typename OT, int WM>
-hipError_t launch_fwd_cfg(const FwdArgs& a, int mt, bool wide, int am, bool split, unsigned grid, hipStream_t s) {
-#define LC_FWD(MT_, NW_, PF_, ...) \
-    hipLaunchKernelGGL((forward_kernel<OT, MT_, NW_, PF_, WM, __VA_ARGS__>), dim3(grid), dim3(NW_ * 64), 0, s, a)
-#define LC_FWD_BOTH(MT_, NW_, PF_, ...) \
-    if (am == kActFragments) LC_FWD(MT_, NW_, PF_, kActFragments, __VA_ARGS__); else LC_FWD(MT_, NW_, PF_, kActRows, __VA_ARGS__)
-    if constexpr (sizeof(OT) == 4 && WM != kWGeneric) {
-        if (split) {
-            switch (mt) {
-                case 4: if (wide) { LC_FWD_BOTH(4, 8, 1, true); } else { LC_FWD_BOTH(4, 4, 3, true); } break;
-                case 8: if (am == kActFeatureMajor) LC_FWD(8, 4, 1, kActFeatureMajor, true); else { LC_FWD_BOTH(8, 4, 1, true); } break;
-                default: return hipErrorInvalidValue;
-            }
-            return hipGetLastError();
-        }
-    }
+hipError_t launch_fwd_cfg(const FwdArgs& a, int mt, bool wide, int am, unsigned grid, hipStream_t s) {
+#define LC_FWD(MT_, NW_, PF_, AM_) \
+    hipLaunchKernelGGL((forward_kernel<OT, MT_, NW_, PF_, WM, AM_>), dim3(grid), dim3(NW_ * 64), 0, s, a)
+#define LC_FWD_BOTH(MT_, NW_, PF_) \
+    if (am == kActFragments) LC_FWD(MT_, NW_, PF_, kActFragments); else LC_FWD(MT_, NW_, PF_, kActRows)
     switch (mt) {
-        case 1: if (wide) { LC_FWD_BOTH(1, 8, 3, false); } else { LC_FWD_BOTH(1, 4, 3, false); } break;
-        case 2: if (wide) { LC_FWD_BOTH(2, 8, 3, false); } else { LC_FWD_BOTH(2, 4, 1, false); } break;   // many blocks: occupancy 3 beats a deeper queue
-        case 4: if (wide) { LC_FWD_BOTH(4, 8, 1, false); } else { LC_FWD_BOTH(4, 4, 3, false); } break;
-        case 8: if (am == kActFeatureMajor) LC_FWD(8, 4, 1, kActFeatureMajor, false); else { LC_FWD_BOTH(8, 4, 1, false); } break;
+        case 1: if (wide) { LC_FWD_BOTH(1, 8, 3); } else { LC_FWD_BOTH(1, 4, 3); } break;
+        case 2: if (wide) { LC_FWD_BOTH(2, 8, 3); } else { LC_FWD_BOTH(2, 4, 1); } break;   // many blocks: occupancy 3 beats a deeper queue
+        case 4: if (wide) { LC_FWD_BOTH(4, 8, 1); } else { LC_FWD_BOTH(4, 4, 3); } break;
+        case 8: if (am == kActFeatureMajor) LC_FWD(8, 4, 1, kActFeatureMajor); else { LC_FWD_BOTH(8, 4, 1); } break;
         default: return hipErrorInvalidValue;
     }
 #undef LC_FWD_BOTH
@@ -1571,61 +1412,43 @@ hipError_t launch_fwd_cfg(const FwdArgs& a, int mt, bool wide, int am, bool spli
     return hipGetLastError();
 }
 template <typename OT>
-hipError_t launch_fwd_wm(const FwdArgs& a, int mt, bool wide, int am, bool split, unsigned grid, hipStream_t s) {
+hipError_t launch_fwd_wm(const FwdArgs& a, int mt, bool wide, int am, unsigned grid, hipStream_t s) {
     switch (weight_mode(a.vec != 0, a.stream != 0, a.d_out)) {
-        case kWVector: return launch_fwd_cfg<OT, kWVector>(a, mt, wide, am, split, grid, s);
-        case kWVectorStream: return launch_fwd_cfg<OT, kWVectorStream>(a, mt, wide, am, split, grid, s);
-        case kWRagged: return launch_fwd_cfg<OT, kWRagged>(a, mt, wide, am, split, grid, s);
-        default: return launch_fwd_cfg<OT, kWGeneric>(a, mt, wide, am, false, grid, s);
+        case kWVector: return launch_fwd_cfg<OT, kWVector>(a, mt, wide, am, grid, s);
+        case kWVectorStream: return launch_fwd_cfg<OT, kWVectorStream>(a, mt, wide, am, grid, s);
+        case kWRagged: return launch_fwd_cfg<OT, kWRagged>(a, mt, wide, am, grid, s);
+        default: return launch_fwd_cfg<OT, kWGeneric>(a, mt, wide, am, grid, s);
     }
 }
 
-template <typename OT, int WM, bool SPLIT>
+template <typename OT, int WM>
 hipError_t launch_bwd_nt(const BwdArgs& a, int nt, unsigned grid, hipStream_t s) {
-#define LC_BWD(NT_, PAD_, ...) \
-    hipLaunchKernelGGL((backward_kernel<OT, NT_, WM, false, __VA_ARGS__, SPLIT>), dim3(grid), dim3(256), PAD_, s, a)
-    if constexpr (!SPLIT) {
-        if (nt == 2 && !a.dzp_bm) {
-            if (!a.frags) return hipErrorInvalidValue;   // (see first_forward_reads_rows)
-            // (where the weights stream a third workgroup per CU costs more than it hides: the unused LDS keeps it out)
-            LC_BWD(2, a.stream ? 55u * 1024 : 0, true, true);
-            return hipGetLastError();
-        }
-        if (nt == 2) {
-            LC_BWD(2, 0, false, false);
-            return hipGetLastError();
-        }
-    }
     if (!a.dzp_bm) {
-        if (!a.frags && nt != 8) return hipErrorInvalidValue;
+        if (!a.frags && nt != 8) return hipErrorInvalidValue;   // (see first_forward_reads_rows)
+        // (where the weights stream a third workgroup per CU costs more than it hides: the unused LDS keeps it out)
+        const unsigned pad = a.stream ? 55u * 1024 : 0;
         switch (nt) {
-            case 4: LC_BWD(4, 0, true, true); break;
+            case 2: hipLaunchKernelGGL((backward_kernel<OT, 2, WM, false, true>), dim3(grid), dim3(256), pad, s, a); break;
+            case 4: hipLaunchKernelGGL((backward_kernel<OT, 4, WM, false, true>), dim3(grid), dim3(256), 0, s, a); break;
             case 8:
-                if (a.frags) LC_BWD(8, 0, true, true);
-                else LC_BWD(8, 0, true, false);
+                if (a.frags) hipLaunchKernelGGL((backward_kernel<OT, 8, WM, false, true>), dim3(grid), dim3(256), 0, s, a);
+                else hipLaunchKernelGGL((backward_kernel<OT, 8, WM, false, true, false>), dim3(grid), dim3(256), 0, s, a);
                 break;
             default: return hipErrorInvalidValue;
         }
         return hipGetLastError();
     }
     switch (nt) {
-        case 4: LC_BWD(4, 0, false, false); break;
-        case 8: LC_BWD(8, 0, false, false); break;
+        case 2: hipLaunchKernelGGL((backward_kernel<OT, 2, WM>), dim3(grid), dim3(256), 0, s, a); break;
+        case 4: hipLaunchKernelGGL((backward_kernel<OT, 4, WM>), dim3(grid), dim3(256), 0, s, a); break;
+        case 8: hipLaunchKernelGGL((backward_kernel<OT, 8, WM>), dim3(grid), dim3(256), 0, s, a); break;
         default: return hipErrorInvalidValue;
     }
-#undef LC_BWD
     return hipGetLastError();
 }
 // dZ_{l-1} only (see backward_kernel); for layers with 16-byte aligned rows of a multiple of 64 columns
 template <typename OT>
-hipError_t launch_bwd_da_only(const BwdArgs& a, int nt, bool split, unsigned grid, hipStream_t s) {
-    if constexpr (sizeof(OT) == 4) {
-        if (split) {
-            if (nt != 4) return hipErrorInvalidValue;
-            hipLaunchKernelGGL((backward_kernel<OT, 4, kWVectorStream, true, false, false, true>), dim3(grid), dim3(256), 0, s, a);
-            return hipGetLastError();
-        }
-    }
+hipError_t launch_bwd_da_only(const BwdArgs& a, int nt, unsigned grid, hipStream_t s) {
     switch (nt) {
         case 2: hipLaunchKernelGGL((backward_kernel<OT, 2, kWVectorStream, true>), dim3(grid), dim3(256), 0, s, a); break;
         case 4: hipLaunchKernelGGL((backward_kernel<OT, 4, kWVectorStream, true>), dim3(grid), dim3(256), 0, s, a); break;
@@ -1635,22 +1458,12 @@ hipError_t launch_bwd_da_only(const BwdArgs& a, int nt, bool split, unsigned gri
     return hipGetLastError();
 }
 template <typename OT>
-hipError_t launch_bwd_wm(const BwdArgs& a, int nt, bool split, unsigned grid, hipStream_t s) {
-    const int wm = weight_mode(a.vec != 0, a.stream != 0, a.d_out);
-    if constexpr (sizeof(OT) == 4) {
-        if (split && wm != kWGeneric) {
-            switch (wm) {
-                case kWVector: return launch_bwd_nt<OT, kWVector, true>(a, nt, grid, s);
-                case kWVectorStream: return launch_bwd_nt<OT, kWVectorStream, true>(a, nt, grid, s);
-                default: return launch_bwd_nt<OT, kWRagged, true>(a, nt, grid, s);
-            }
-        }
-    }
-    switch (wm) {
-        case kWVector: return launch_bwd_nt<OT, kWVector, false>(a, nt, grid, s);
-        case kWVectorStream: return launch_bwd_nt<OT, kWVectorStream, false>(a, nt, grid, s);
-        case kWRagged: return launch_bwd_nt<OT, kWRagged, false>(a, nt, grid, s);
-        default: return launch_bwd_nt<OT, kWGeneric, false>(a, nt, grid, s);
+hipError_t launch_bwd_wm(const BwdArgs& a, int nt, unsigned grid, hipStream_t s) {
+    switch (weight_mode(a.vec != 0, a.stream != 0, a.d_out)) {
+        case kWVector: return launch_bwd_nt<OT, kWVector>(a, nt, grid, s);
+        case kWVectorStream: return launch_bwd_nt<OT, kWVectorStream>(a, nt, grid, s);
+        case kWRagged: return launch_bwd_nt<OT, kWRagged>(a, nt, grid, s);
+        default: return launch_bwd_nt<OT, kWGeneric>(a, nt, grid, s);
     }
 }
 
@@ -1859,8 +1672,8 @@ hipError_t launch_forward(lc_handle* h, bool eval, int l, int loss_offset) {
     const bool afm = in_fm != nullptr && !grouped && a.m_split == 1 && mt * 16 == S.Bp && mt == 8;
     const int am = frags ? kActFragments : afm ? kActFeatureMajor : kActRows;
     a.a_in_fm = in_fm;
-    if (bf16) e = launch_fwd_wm<bf16_t>(a, mt, wide, am, false, grid, h->stream);
-    else e = launch_fwd_wm<float>(a, mt, wide, am, !eval && split_products(h) && mt >= 4 && g.d_in >= 256, grid, h->stream);
+    if (bf16) e = launch_fwd_wm<bf16_t>(a, mt, wide, am, grid, h->stream);
+    else e = launch_fwd_wm<float>(a, mt, wide, am, grid, h->stream);
     if (!eval) timing_stop(h, kTimeFwd);
     return e;
 }
@@ -2062,17 +1875,14 @@ hipError_t launch_backward(lc_handle* h, int l, bool da_only) {
     const unsigned grid = xcd_grid(a.total_blocks);
     // (same conditions as the tile-owner kernel that follows; the columns are not shared out here)
     if (da_only && (l < 2 || !a.vec || g.d_out % kColChunk != 0 || !a.stream)) return hipErrorInvalidValue;
-    // (a layer that may go by tile rounds alike however it goes)
-    const int trips = (g.dp_out / kColChunk + a.col_split - 1) / a.col_split;
-    const bool split = split_products(h) && S.Bp >= 64 && (sync_layer_ok(h, l) ? S.Bp == 64 && n_groups == S.G : trips >= 2);
     timing_start(h, kTimeBwd, l, kBwdRowOwner);
     hipError_t e;
     if (da_only) {
-        e = bf16 ? launch_bwd_da_only<bf16_t>(a, a.Bp / 16, false, grid, h->stream)
-                 : launch_bwd_da_only<float>(a, a.Bp / 16, split, grid, h->stream);
+        e = bf16 ? launch_bwd_da_only<bf16_t>(a, a.Bp / 16, grid, h->stream)
+                 : launch_bwd_da_only<float>(a, a.Bp / 16, grid, h->stream);
     } else {
-        e = bf16 ? launch_bwd_wm<bf16_t>(a, S.Bp / 16, false, grid, h->stream)
-                 : launch_bwd_wm<float>(a, S.Bp / 16, split, grid, h->stream);
+        e = bf16 ? launch_bwd_wm<bf16_t>(a, S.Bp / 16, grid, h->stream)
+                 : launch_bwd_wm<float>(a, S.Bp / 16, grid, h->stream);
     }
     if (e == hipSuccess && shares > 1) {
         const CombineArgs c{a.da_part, a.part_stride, shares, g.dp_in, S.Bp, a.a_fm, a.dzp_bm, a.dzp_fm};

@@ -4,8 +4,6 @@
 #pragma once
 #include "lc_internal.h"
 
-#include <type_traits>
-
 namespace lc {
 namespace {
 
@@ -81,51 +79,6 @@ __device__ __forceinline__ f32x4 mma8(const Frag<bf16_t>& a, const Frag<bf16_t>&
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.v, b.v, c, 0, 0, 0);
 }
 
-// fp32 products on the bf16 matrix cores.  An fp32 number is the sum of three bf16 numbers exactly (8 + 8 + 8 of its 24
-// significant bits, each part rounded to nearest), products of bf16 numbers are exact in fp32, and of the nine products
-// of two such sums the three smallest reach 2^-24 of the whole together: less than one rounding of the result.  The other
-// six take 6 x 16 clocks per 32 reduction indices where the fp32 instructions take 8 x 32, they round the sum six times
-// where those round it eight times, and vector instructions run beside them: beside fp32 matrix instructions they do not
-// (four wavefronts on a SIMD, one matrix and four vector instructions in turn: 48 clocks with the fp32 instruction of 32,
-// 34 with a bf16 one of 32).
-// Operands above kMaxSplit go through the fp32 instructions: parts of such numbers, or their products, may be infinite
-// with either sign where the whole is not.
-struct Parts {
-    bf16x8 p[3];
-};
-constexpr float kMaxSplit = 1.152921504606846976e18f;   // 2^60
-__device__ __forceinline__ Parts split8(const float (&x)[8]) {
-    Parts f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        f.p[0][e] = static_cast<bf16_t>(x[e]);
-        const float r = x[e] - static_cast<float>(f.p[0][e]);
-        f.p[1][e] = static_cast<bf16_t>(r);
-        f.p[2][e] = static_cast<bf16_t>(r - static_cast<float>(f.p[1][e]));
-    }
-    return f;
-}
-__device__ __forceinline__ f32x4 mma8(const Parts& a, const Parts& b, f32x4 c) {
-#pragma unroll
-    for (int i = 2; i >= 0; --i)   // the small products first
-#pragma unroll
-        for (int k = 0; k <= i; ++k) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.p[i - k], b.p[k], c, 0, 0, 0);
-    return c;
-}
-// The same with one rounding of the whole sum instead of six, for long sums (vector instructions: 4 per product)
-template <typename F>
-__device__ __forceinline__ f32x4 add_mma8(const F& a, const F& b, f32x4 c) {
-    if constexpr (std::is_same_v<F, Parts>) return c + mma8(a, b, f32x4{0.f, 0.f, 0.f, 0.f});
-    else return mma8(a, b, c);
-}
-template <int N>
-__device__ __forceinline__ float largest(const float (&x)[N]) {   // of the magnitudes
-    float m = fabsf(x[0]);
-#pragma unroll
-    for (int e = 1; e < N; ++e) m = fmaxf(m, fabsf(x[e]));
-    return m;
-}
-
 // operand fragments of the 16-deep product: 4 consecutive reduction indices per lane
 template <typename OT>
 struct Frag4;
@@ -162,31 +115,6 @@ __device__ __forceinline__ f32x4 mma4(const Frag4<bf16_t>& a, const Frag4<bf16_t
     typedef short s16x4 __attribute__((ext_vector_type(4)));
     return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4, a.v), __builtin_bit_cast(s16x4, b.v), c,
                                                      0, 0, 0);
-}
-
-// parts of the operands of the 16-deep product
-struct Parts4 {
-    bf16x4 p[3];
-};
-__device__ __forceinline__ Parts4 split4(float a, float b, float c, float d) {
-    const float x[4] = {a, b, c, d};
-    Parts4 f;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        f.p[0][e] = static_cast<bf16_t>(x[e]);
-        const float r = x[e] - static_cast<float>(f.p[0][e]);
-        f.p[1][e] = static_cast<bf16_t>(r);
-        f.p[2][e] = static_cast<bf16_t>(r - static_cast<float>(f.p[1][e]));
-    }
-    return f;
-}
-__device__ __forceinline__ f32x4 mma4(const Parts4& a, const Parts4& b, f32x4 c) {
-    f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int i = 2; i >= 0; --i)
-#pragma unroll
-        for (int k = 0; k <= i; ++k) s = mma4(Frag4<bf16_t>{a.p[i - k]}, Frag4<bf16_t>{b.p[k]}, s);
-    return c + s;   // (in long sums, and where 16 products would be four fp32 roundings: one of the whole sum instead of six)
 }
 
 __device__ __forceinline__ float to_f32(float x) { return x; }

@@ -23,8 +23,6 @@
 #include "lc_internal.h"
 #include "lc_mma.h"
 
-#include <type_traits>
-
 namespace lc {
 
 namespace {
@@ -56,17 +54,13 @@ struct SyncArgs {
 // slice is staged in LDS in two buffers, one barrier per replica.
 // FRAGS is a template parameter: chosen per load, the form of the A operands costs the OWN instances 4 to 5 %
 // (3072x2048, 64 workers of 32 samples, bf16: 908 us a launch, 859 so; 2048x2048 596 and 573).
-// SPLIT: as in backward_kernel.
-template <typename OT, int NT, bool OWN, bool FRAGS, bool SPLIT>
+template <typename OT, int NT, bool OWN, bool FRAGS>
 __global__ __launch_bounds__(256) void sync_first_layer_kernel(SyncArgs a) {
-    using LT = std::conditional_t<SPLIT, bf16_t, OT>;
-    constexpr int NP = SPLIT ? 3 : 1;
-    constexpr int kPad = sizeof(LT) == 2 ? 8 : 4;
+    constexpr int kPad = sizeof(OT) == 2 ? 8 : 4;
     constexpr int Bp = 16 * NT;
     constexpr int NS = NT / 2;
     // row (c % 4) * 16 + c / 4 holds column c0 + c (the layout backward_kernel uses)
-    __shared__ __attribute__((aligned(16))) LT dzt_lds[2][NP][kColChunk][Bp + kPad];
-    __shared__ __attribute__((aligned(16))) int huge_s[2][4];   // by wavefront: it staged a delta above kMaxSplit
+    __shared__ __attribute__((aligned(16))) OT dzt_lds[2][kColChunk][Bp + kPad];
 
     const int64_t logical = xcd_logical_block(a.total_blocks);
     if (logical < 0) return;
@@ -127,32 +121,7 @@ __global__ __launch_bounds__(256) void sync_first_layer_kernel(SyncArgs a) {
         for (int s = 0; s < NS; ++s) {
             const int p = tid + 256 * s;
             const int c = p / (Bp / 8), seg = p % (Bp / 8);
-            const int row = (c & 3) * 16 + (c >> 2);
-            if constexpr (SPLIT) {
-                const Parts x = split8(st_t[s].v);
-#pragma unroll
-                for (int i = 0; i < 3; ++i) *reinterpret_cast<bf16x8*>(&dzt_lds[buf][i][row][seg * 8]) = x.p[i];
-            } else {
-                *reinterpret_cast<Frag<OT>*>(&dzt_lds[buf][0][row][seg * 8]) = st_t[s];
-            }
-        }
-        if constexpr (SPLIT) {
-            float m = 0.f;
-#pragma unroll
-            for (int s = 0; s < NS; ++s) m = fmaxf(m, largest(st_t[s].v));
-            const bool huge = __any(m > kMaxSplit);
-            if (lane == 0) huge_s[buf][wave] = huge;
-        }
-    };
-
-    auto operand = [&](int buf, int row, int at) {
-        if constexpr (SPLIT) {
-            Parts x;
-#pragma unroll
-            for (int i = 0; i < 3; ++i) x.p[i] = *reinterpret_cast<const bf16x8*>(&dzt_lds[buf][i][row][at]);
-            return x;
-        } else {
-            return *reinterpret_cast<const Frag<OT>*>(&dzt_lds[buf][0][row][at]);
+            *reinterpret_cast<Frag<OT>*>(&dzt_lds[buf][(c & 3) * 16 + (c >> 2)][seg * 8]) = st_t[s];
         }
     };
 
@@ -165,12 +134,6 @@ __global__ __launch_bounds__(256) void sync_first_layer_kernel(SyncArgs a) {
         const int buf = g & 1;
         const bool has_next = g + 1 < a.G;
         if (has_next) issue_loads(g + 1, vn, wn);
-        const OT* dZT = static_cast<const OT*>(a.dz_fm) + (static_cast<int64_t>(g) * a.dp_out + c0) * Bp;   // (the slice in memory)
-        bool huge_dz = false;
-        if constexpr (SPLIT) {
-            const int4 h = *reinterpret_cast<const int4*>(huge_s[buf]);
-            huge_dz = __builtin_amdgcn_readfirstlane(h.x | h.y | h.z | h.w) != 0;
-        }
 
         // bias of these 64 columns for replica g (one thread per column): the momentum entry is
         // updated here, the averaging kernels form x_bar - lr v from it like for every other layer
@@ -184,20 +147,13 @@ __global__ __launch_bounds__(256) void sync_first_layer_kernel(SyncArgs a) {
             } else {
                 v0 = *bv;
             }
+            const OT* zr = dzt_lds[buf][(tid & 3) * 16 + (tid >> 2)];
             float sb = 0.f;
-            if (SPLIT && huge_dz) {
-                for (int b = 0; b < Bp; ++b) sb += to_f32(dZT[static_cast<int64_t>(tid) * Bp + b]);
-            } else {
-                const int row = (tid & 3) * 16 + (tid >> 2);
 #pragma unroll
-                for (int b8 = 0; b8 < Bp; b8 += 8) {
-                    const auto f = operand(buf, row, b8);
+            for (int b8 = 0; b8 < Bp; b8 += 8) {
+                const Frag<OT> f = *reinterpret_cast<const Frag<OT>*>(zr + b8);
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        if constexpr (SPLIT) sb += (to_f32(f.p[0][e]) + to_f32(f.p[1][e])) + to_f32(f.p[2][e]);
-                        else sb += to_f32(f.v[e]);
-                    }
-                }
+                for (int e = 0; e < 8; ++e) sb += to_f32(f.v[e]);
             }
             const float vb = momentum_update(a.beta, v0, sb, a.wd, xb);
             *bv = vb;
@@ -207,30 +163,12 @@ __global__ __launch_bounds__(256) void sync_first_layer_kernel(SyncArgs a) {
         f32x4 acc[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-        bool huge = huge_dz;
-        if constexpr (SPLIT) {
-            float m = 0.f;
 #pragma unroll
-            for (int s = 0; s < NS; ++s) m = fmaxf(m, largest(af[s].v));
-            huge = huge || __any(m > kMaxSplit);
-        }
-        if (SPLIT && huge) {
+        for (int s = 0; s < NS; ++s) {
 #pragma unroll
-            for (int s = 0; s < NS; ++s)
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    acc[t] = mma8(af[s], load8(dZT + static_cast<int64_t>(4 * j + t) * Bp + 32 * s + 8 * q), acc[t]);
-        } else {
-#pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                if constexpr (SPLIT) {
-                    const Parts x = split8(af[s].v);
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) acc[t] = mma8(x, operand(buf, t * 16 + j, 32 * s + 8 * q), acc[t]);
-                } else {
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) acc[t] = mma8(af[s], operand(buf, t * 16 + j, 32 * s + 8 * q), acc[t]);
-                }
+            for (int t = 0; t < 4; ++t) {
+                const Frag<OT> bf = *reinterpret_cast<const Frag<OT>*>(&dzt_lds[buf][t * 16 + j][32 * s + 8 * q]);
+                acc[t] = mma8(af[s], bf, acc[t]);
             }
         }
         if (has_next) load_rows(g + 1);   // (the operand registers are free again; no second set)
@@ -280,24 +218,16 @@ __global__ __launch_bounds__(256) void sync_first_layer_kernel(SyncArgs a) {
 }
 
 template <typename OT, bool OWN, bool FRAGS>
-hipError_t launch_sync_nt(const SyncArgs& a, bool split, int nt, unsigned grid, hipStream_t st) {
-    if constexpr (sizeof(OT) == 4) {
-        // (128 samples: two slices in parts leave room for one workgroup per CU.  3072-2048-2048-10, 16 workers of 100
-        // samples, tau = 1: an iteration 1227 us with the fp32 instructions, 1407 with parts)
-        if (split && nt == 4) {
-            hipLaunchKernelGGL((sync_first_layer_kernel<OT, 4, OWN, FRAGS, true>), dim3(grid), dim3(256), 0, st, a);
-            return hipGetLastError();
-        }
-    }
-    if (nt == 2) hipLaunchKernelGGL((sync_first_layer_kernel<OT, 2, OWN, FRAGS, false>), dim3(grid), dim3(256), 0, st, a);
-    else if (nt == 4) hipLaunchKernelGGL((sync_first_layer_kernel<OT, 4, OWN, FRAGS, false>), dim3(grid), dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((sync_first_layer_kernel<OT, 8, OWN, FRAGS, false>), dim3(grid), dim3(256), 0, st, a);
+hipError_t launch_sync_nt(const SyncArgs& a, int nt, unsigned grid, hipStream_t st) {
+    if (nt == 2) hipLaunchKernelGGL((sync_first_layer_kernel<OT, 2, OWN, FRAGS>), dim3(grid), dim3(256), 0, st, a);
+    else if (nt == 4) hipLaunchKernelGGL((sync_first_layer_kernel<OT, 4, OWN, FRAGS>), dim3(grid), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((sync_first_layer_kernel<OT, 8, OWN, FRAGS>), dim3(grid), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 template <typename OT>
-hipError_t launch_sync1(const SyncArgs& a, bool own, bool frags, bool split, int nt, unsigned grid, hipStream_t st) {
-    if (own) return frags ? launch_sync_nt<OT, true, true>(a, split, nt, grid, st) : launch_sync_nt<OT, true, false>(a, split, nt, grid, st);
-    return frags ? launch_sync_nt<OT, false, true>(a, split, nt, grid, st) : launch_sync_nt<OT, false, false>(a, split, nt, grid, st);
+hipError_t launch_sync1(const SyncArgs& a, bool own, bool frags, int nt, unsigned grid, hipStream_t st) {
+    if (own) return frags ? launch_sync_nt<OT, true, true>(a, nt, grid, st) : launch_sync_nt<OT, true, false>(a, nt, grid, st);
+    return frags ? launch_sync_nt<OT, false, true>(a, nt, grid, st) : launch_sync_nt<OT, false, false>(a, nt, grid, st);
 }
 
 }  // namespace
@@ -367,8 +297,8 @@ hipError_t launch_sync_layer(lc_handle* h, int l) {
     const unsigned grid = static_cast<unsigned>((a.total_blocks + kXcds - 1) / kXcds * kXcds);
     const bool frags = l == 1 && h->a0_layout == kInputsLayers;
     timing_start(h, kTimeBwd, l, kBwdTileOwner);
-    const hipError_t e = bf16 ? launch_sync1<bf16_t>(a, own, frags, false, S.Bp / 16, grid, h->stream)
-                              : launch_sync1<float>(a, own, frags, split_products(h), S.Bp / 16, grid, h->stream);
+    const hipError_t e = bf16 ? launch_sync1<bf16_t>(a, own, frags, S.Bp / 16, grid, h->stream)
+                              : launch_sync1<float>(a, own, frags, S.Bp / 16, grid, h->stream);
     timing_stop(h, kTimeBwd, l, kBwdTileOwner);
     if (e == hipSuccess && own) h->imp[l] = sb.next;   // (explicit again: v is in V; the rows of X wait for the broadcast)
     return e;
