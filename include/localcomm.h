@@ -305,6 +305,12 @@ int lc_set_fused_averaging(lc_handle* h, int mode);
  * the resident step kernel runs the steps); negative on error. */
 int lc_implicit_momentum_layers(const lc_handle* h);
 
+/* Columns and wavefronts of a workgroup of the kernel that runs the first layer's backward pass together
+ * with the next step's forward pass (lc_set_first_layer_fusion), where the steps are taken layer by layer;
+ * 0 and 0 for models and settings that keep the separate launches.  Device memory need not be attached.
+ * Errors: LC_ERR_ARG (null). */
+int lc_first_layer_workgroup(const lc_handle* h, int32_t* columns, int32_t* wavefronts);
+
 /* 1 if lc_local_steps() of this (attached) handle takes the resident step kernel, else 0. */
 int lc_resident_active(const lc_handle* h);
 

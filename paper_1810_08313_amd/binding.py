@@ -95,6 +95,8 @@ def lib() -> C.CDLL:
     L.lc_set_fused_averaging.argtypes = [vp, C.c_int]
     L.lc_implicit_momentum_layers.restype = C.c_int
     L.lc_implicit_momentum_layers.argtypes = [vp]
+    L.lc_first_layer_workgroup.restype = C.c_int
+    L.lc_first_layer_workgroup.argtypes = [vp, C.POINTER(C.c_int32), C.POINTER(C.c_int32)]
     L.lc_resident_active.restype = C.c_int
     L.lc_resident_active.argtypes = [vp]
     L.lc_xcd_local_exchange_active.restype = C.c_int
@@ -339,6 +341,12 @@ class LocalSGD:
         rc = self._L.lc_implicit_momentum_layers(self._h)
         self._check(min(rc, 0), "lc_implicit_momentum_layers")
         return rc
+
+    def first_layer_workgroup(self) -> Tuple[int, int]:
+        """Columns and wavefronts of a workgroup of the first-layer kernel; (0, 0): separate launches."""
+        c, w = C.c_int32(), C.c_int32()
+        self._check(self._L.lc_first_layer_workgroup(self._h, C.byref(c), C.byref(w)), "lc_first_layer_workgroup")
+        return c.value, w.value
 
     def resident_active(self) -> bool:
         rc = self._L.lc_resident_active(self._h)

@@ -57,7 +57,7 @@ struct FirstArgs {
     void* out_bm;         // A_1 of the next step [G][Bp][dp_out]
     void* out_fm;         //                      [G][dp_out][Bp]
     int n_chunks;         // column chunks per replica
-    int chunk_cols;       // their width: 64, or 96 (see wide_columns)
+    int chunk_cols, wavefronts;   // see FirstLayerPlan
     int64_t total_blocks;
 };
 
@@ -664,7 +664,7 @@ void launch_fl_pairs(const FirstArgs& a, bool stream_w, unsigned grid, hipStream
 template <typename OT, int NT>
 void launch_fl_wm(const FirstArgs& a, bool stream_w, unsigned grid, hipStream_t st) {
     if constexpr (NT == 4 && sizeof(OT) == 4) {
-        if (a.total_blocks <= compute_units() && a.d_in >= 256) {   // (see kFlWaves)
+        if (a.wavefronts == 2 * kFlWaves) {
             launch_fl_pairs<OT, NT, true>(a, stream_w, grid, st);
             return;
         }
@@ -677,13 +677,10 @@ hipError_t launch_fl(const FirstArgs& a, int nt, bool stream_w, unsigned grid, h
     if (nt == 2) launch_fl_wm<OT, 2>(a, stream_w, grid, st);
     else if (nt == 4) launch_fl_wm<OT, 4>(a, stream_w, grid, st);
     else if constexpr (sizeof(OT) == 2) {
-        // 128 samples.  (Whole tiles whose height is no multiple of the 128 rows that the wide kernel's
-        // wavefronts take together stay with the other one: cut off as ragged rows are, they run 0.94 ..
-        // 1.0 times as fast up to 784 inputs of a cached state, 1.0 .. 1.03 from 1040 inputs on.)
         const dim3 block(64 * kWideWaves);
         if (a.chunk_cols == 96) hipLaunchKernelGGL((first_layer_wide_kernel<OT, kWRagged, kWRagged, 6>), dim3(grid), block, 0, st, a);
         else if (!whole_tiles(a)) hipLaunchKernelGGL((first_layer_wide_kernel<OT, kWRagged, kWRagged>), dim3(grid), block, 0, st, a);
-        else if (a.d_in % (16 * kWideWaves) != 0) launch_fl_wm<OT, 8>(a, stream_w, grid, st);
+        else if (a.wavefronts == kFlWaves) launch_fl_wm<OT, 8>(a, stream_w, grid, st);
         else if (stream_w && !a.shared_w)
             hipLaunchKernelGGL((first_layer_wide_kernel<OT, kWVectorStream, kWVectorStream>), dim3(grid), block, 0, st, a);
         else if (stream_w) hipLaunchKernelGGL((first_layer_wide_kernel<OT, kWVectorStream, kWVector>), dim3(grid), block, 0, st, a);
@@ -696,19 +693,33 @@ hipError_t launch_fl(const FirstArgs& a, int nt, bool stream_w, unsigned grid, h
 
 }  // namespace
 
+// Columns of a chunk: 96 instead of 64 in the 128-sample kernel on ragged rows where the rounds of workgroups then cost
+// less, a workgroup of 96 columns taking 1.5 times as long.  5 steps with 64 and 96: 3072-1500-1000-100, 16 workers of 100,
+// 384 workgroups in two rounds and 256 in one, 2408 and 2252 us; but 1500-1999-1000-10, 24 of 90, 768 in three and 504 in
+// two, 2837 and 2896; 2048-1001-300-10, 25 of 128, 400 and 275 in two, 1531 and 1790.
+static int wide_columns(const lc_handle* h, bool whole) {
+    const LayerGeom& g = h->layer[1];
+    if (h->train.Bp != 128 || h->md.gemm != LC_GEMM_BF16 || whole) return kColChunk;
+    const int64_t cus = compute_units(), m = h->train.G;
+    const int64_t r64 = (m * ((g.d_out + 63) / 64) + cus - 1) / cus, r96 = (m * ((g.d_out + 95) / 96) + cus - 1) / cus;
+    return 6 * r96 < 4 * r64 ? 96 : kColChunk;
+}
+
 // The kernel serves layer 1 of models with at least two layers whose first-layer rows are at least one
 // column chunk long, when there are enough (replica, column chunk) pairs to fill the chip; everything
 // else keeps the row-owner backward kernel and the separate forward launch.
-bool first_layer_kernel_ok(const lc_handle* h) {
-    if (h->md.kind != LC_KIND_MLP || h->L < 2) return false;
+FirstLayerPlan first_layer_plan(const lc_handle* h) {
+    const FirstLayerPlan none{0, 0};
+    if (h->md.kind != LC_KIND_MLP || h->L < 2) return none;
     const LayerGeom& g = h->layer[1];
     const ActSet& S = h->train;
-    if (g.d_out < kColChunk) return false;
-    if (S.Bp != 32 && S.Bp != 64 && S.Bp != 128) return false;
-    if (g.d_in < 16 * kFlWaves) return false;
+    const bool bf16 = h->md.gemm == LC_GEMM_BF16;
+    if (g.d_out < kColChunk) return none;
+    if (S.Bp != 32 && S.Bp != 64 && S.Bp != 128) return none;
+    if (g.d_in < 16 * kFlWaves) return none;
     // fp32 operands at 128 samples: the operand fragments of two steps and the 32 accumulator tiles
     // do not fit the register file
-    if (h->md.gemm != LC_GEMM_BF16 && S.Bp == 128) return false;
+    if (!bf16 && S.Bp == 128) return none;
     // Every workgroup walks a whole column chunk, so a last round of few workgroups takes as long as a
     // full one (3072x1024, batch 128: 147 us a step with 16 replicas = 256 workgroups, 250 with 20, 288
     // with 32).  How many times as fast whole runs are than with the separate launches, median (least)
@@ -721,26 +732,20 @@ bool first_layer_kernel_ok(const lc_handle* h) {
     //   and cached 0.97), above 0.99 .. 1.11
     const int64_t blocks = static_cast<int64_t>(S.G) * (g.dp_out / kColChunk);
     const int64_t cus = compute_units(), rounds = (blocks + cus - 1) / cus;
-    if (blocks < 192) return false;
-    if (rounds == 1) return true;
     const bool whole = g.d_out % kColChunk == 0 && g.w_off % 4 == 0 && g.d_in % 16 == 0;
+    if (blocks < 192) return none;
     int full = 0;   // per cent
-    if (S.Bp == 128) full = whole || h->stream_weights ? 75 : 80;
-    else if (!whole && h->stream_weights) full = h->md.gemm == LC_GEMM_BF16 ? 70 : 85;
-    return 100 * blocks >= full * cus * rounds;
-}
-
-// Columns of a chunk: 96 instead of 64 in the 128-sample kernel on ragged rows where the rounds of workgroups then cost
-// less, a workgroup of 96 columns taking 1.5 times as long.  5 steps with 64 and 96: 3072-1500-1000-100, 16 workers of 100,
-// 384 workgroups in two rounds and 256 in one, 2408 and 2252 us; but 1500-1999-1000-10, 24 of 90, 768 in three and 504 in
-// two, 2837 and 2896; 2048-1001-300-10, 25 of 128, 400 and 275 in two, 1531 and 1790.
-static int wide_columns(const lc_handle* h) {
-    const LayerGeom& g = h->layer[1];
-    const bool whole = g.d_out % kColChunk == 0 && g.w_off % 4 == 0 && g.d_in % 16 == 0;
-    if (h->train.Bp != 128 || h->md.gemm != LC_GEMM_BF16 || whole) return kColChunk;
-    const int64_t cus = compute_units(), m = h->train.G;
-    const int64_t r64 = (m * ((g.d_out + 63) / 64) + cus - 1) / cus, r96 = (m * ((g.d_out + 95) / 96) + cus - 1) / cus;
-    return 6 * r96 < 4 * r64 ? 96 : kColChunk;
+    if (rounds == 1) full = 0;
+    else if (S.Bp == 128) full = whole || h->stream_weights ? 75 : 80;
+    else if (!whole && h->stream_weights) full = bf16 ? 70 : 85;
+    if (100 * blocks < full * cus * rounds) return none;
+    FirstLayerPlan p{wide_columns(h, whole), kFlWaves};
+    // 128 samples: the wide kernel.  (Whole tiles whose height is no multiple of the 128 rows that its wavefronts
+    // take together stay with the other one: cut off as ragged rows are, they run 0.94 .. 1.0 times as fast up
+    // to 784 inputs of a cached state, 1.0 .. 1.03 from 1040 inputs on.)
+    if (S.Bp == 128 && !(whole && g.d_in % (16 * kWideWaves) != 0)) p.wavefronts = kWideWaves;
+    if (S.Bp == 64 && !bf16 && blocks <= cus && g.d_in >= 256) p.wavefronts = 2 * kFlWaves;   // (see kFlWaves)
+    return p;
 }
 
 // Backward pass and update of layer 1 for the step in slot train.cur_slot, and A_1 of the step in
@@ -751,7 +756,8 @@ hipError_t launch_first_layer(lc_handle* h) {
     const bool bf16 = h->md.gemm == LC_GEMM_BF16;
     const size_t es = bf16 ? 2 : 4;
     const size_t slot_bytes = static_cast<size_t>(S.G) * S.Bp * g.dp_in * es;
-    if (!first_layer_kernel_ok(h)) return hipErrorInvalidValue;
+    const FirstLayerPlan plan = first_layer_plan(h);
+    if (!plan.columns) return hipErrorInvalidValue;
     if (S.cur_slot + 1 >= S.slots || h->a0_layout != kInputsLayers) return hipErrorInvalidValue;
     FirstArgs a;
     const StepBufs sb = plan_step_buffers(h, 1);
@@ -780,7 +786,8 @@ hipError_t launch_first_layer(lc_handle* h) {
     a.an_bm = static_cast<const char*>(S.a_bm[0]) + static_cast<size_t>(S.cur_slot + 1) * slot_bytes;
     a.out_bm = S.a_bm[1];
     a.out_fm = S.a_fm[1];
-    a.chunk_cols = wide_columns(h);
+    a.chunk_cols = plan.columns;
+    a.wavefronts = plan.wavefronts;
     a.n_chunks = (g.d_out + a.chunk_cols - 1) / a.chunk_cols;
     a.total_blocks = static_cast<int64_t>(S.G) * a.n_chunks;
     const unsigned grid = static_cast<unsigned>((a.total_blocks + kXcds - 1) / kXcds * kXcds);
