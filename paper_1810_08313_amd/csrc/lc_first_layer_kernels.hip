@@ -694,9 +694,14 @@ hipError_t launch_fl(const FirstArgs& a, int nt, bool stream_w, unsigned grid, h
 }  // namespace
 
 // Columns of a chunk: 96 instead of 64 in the 128-sample kernel on ragged rows where the rounds of workgroups then cost
-// less, a workgroup of 96 columns taking 1.5 times as long.  5 steps with 64 and 96: 3072-1500-1000-100, 16 workers of 100,
-// 384 workgroups in two rounds and 256 in one, 2408 and 2252 us; but 1500-1999-1000-10, 24 of 90, 768 in three and 504 in
-// two, 2837 and 2896; 2048-1001-300-10, 25 of 128, 400 and 275 in two, 1531 and 1790.
+// less, a workgroup of 96 columns taking 1.5 times as long.  5 steps of 7238 drawn models (64 .. 3072 inputs, 65 .. 4096
+// columns, 8 .. 250 workers of 65 .. 128 samples), times as fast as with 64 columns by rounds, median (least .. most), state
+// that streams / cached:
+//   2 -> 1   1.107 (1.056 .. 1.163) / 1.045 (0.988 .. 1.112)      2 -> 2   0.85 (0.81 .. 0.91) / 0.90 (0.82 .. 0.97)
+//   4 -> 2   1.06 (1.04 .. 1.08) / 1.02 (1.02 .. 1.04)            3 -> 2   0.991 (0.92 .. 1.016) / 0.99 (0.95 .. 1.02)
+//   5 -> 3   1.02 (0.96 .. 1.04) / 1.00 (0.98 .. 1.03)            4 -> 3   0.95 (0.92 .. 0.98) / 0.97 (0.94 .. 1.00)
+//   8 -> 5, 11 -> 7, 14 -> 9   1.00 .. 1.01 (0.99 .. 1.02)        6 -> 4, 9 -> 6, 12 -> 8   0.99 (0.95 .. 1.01)
+// 3072-1500-1000-100, 16 of 100, two rounds of 64 columns, one of 96: 2408 and 2252 us.
 static int wide_columns(const lc_handle* h, bool whole) {
     const LayerGeom& g = h->layer[1];
     if (h->train.Bp != 128 || h->md.gemm != LC_GEMM_BF16 || whole) return kColChunk;
@@ -730,16 +735,19 @@ FirstLayerPlan first_layer_plan(const lc_handle* h) {
     //   90 %; bf16 0.90 .. 1.01 (0.89) below 70 %, 1.04 up to 80 %
     //   128 samples: below 70 % 0.84 .. 1.01 (0.84), to 75 % 0.95 .. 1.02, to 80 % 0.97 .. 1.03 (ragged
     //   and cached 0.97), above 0.99 .. 1.11
-    const int64_t blocks = static_cast<int64_t>(S.G) * (g.dp_out / kColChunk);
-    const int64_t cus = compute_units(), rounds = (blocks + cus - 1) / cus;
+    // Counted are the workgroups that will be launched.  Where those have 96 columns, whole runs are 1.14 times as fast as
+    // with the separate launches with a state that streams (median of 1265 models, least 1.04) and 1.13 cached (2093 models,
+    // least 1.00); of the rounds of 64 columns 706 and 2008 of these models would fill less than 75 and 80 %.
     const bool whole = g.d_out % kColChunk == 0 && g.w_off % 4 == 0 && g.d_in % 16 == 0;
+    FirstLayerPlan p{wide_columns(h, whole), kFlWaves};
+    const int64_t blocks = static_cast<int64_t>(S.G) * ((g.d_out + p.columns - 1) / p.columns);
+    const int64_t cus = compute_units(), rounds = (blocks + cus - 1) / cus;
     if (blocks < 192) return none;
     int full = 0;   // per cent
     if (rounds == 1) full = 0;
     else if (S.Bp == 128) full = whole || h->stream_weights ? 75 : 80;
     else if (!whole && h->stream_weights) full = bf16 ? 70 : 85;
     if (100 * blocks < full * cus * rounds) return none;
-    FirstLayerPlan p{wide_columns(h, whole), kFlWaves};
     // 128 samples: the wide kernel.  (Whole tiles whose height is no multiple of the 128 rows that its wavefronts
     // take together stay with the other one: cut off as ragged rows are, they run 0.94 .. 1.0 times as fast up
     // to 784 inputs of a cached state, 1.0 .. 1.03 from 1040 inputs on.)

@@ -35,6 +35,12 @@ def _plan(dims, m, B, bf16):
     ([97, 257, 24, 10], 85, 128, True, (96, 8)),      # a round less with chunks of 96
     ([130, 285, 24, 10], 84, 100, True, (96, 8)),
     ([64, 90, 10], 210, 70, True, (96, 8)),
+    ([97, 673, 24, 10], 94, 70, True, (96, 8)),       # five become three
+    ([130, 290, 24, 10], 52, 100, True, (96, 8)),     # one full round where two of 64 columns would be half empty
+    ([100, 1500, 24, 10], 12, 128, True, (96, 8)),
+    ([3072, 1400, 1000, 10], 16, 100, True, (96, 8)),
+    ([64, 90, 10], 191, 70, True, (0, 0)),            # 191 workgroups of 96 columns
+    ([1500, 1999, 1000, 10], 24, 90, True, (64, 8)),  # three would become two
     ([301, 450, 24, 10], 32, 128, True, (64, 8)),     # one round
     ([1024, 1024, 64, 10], 24, 128, True, (64, 8)),   # whole tiles
     ([1040, 1024, 64, 10], 24, 128, True, (64, 4)),   # ... not of 128 rows

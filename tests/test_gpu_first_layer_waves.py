@@ -54,3 +54,12 @@ def test_a_worker_does_not_depend_on_how_many_there_are(pkg, dims, few, many, B)
     assert np.isfinite(out[0][0]).all()
     for a, b in zip(*out):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("dims,m,B", [
+    ([97, 673, 24, 10], 94, 70),     # five rounds become three; 96 columns reach 64 past the padded 704 of the deltas, 31 of the last 32 do not exist
+    ([130, 290, 24, 10], 52, 100),   # two become one, which 64 columns would have filled to a half; ... past 320
+    ([100, 1500, 24, 10], 12, 128),  # 192 workgroups
+])
+def test_last_chunks_of_96_columns_past_the_padding(pkg, orc, dims, m, B):
+    _calls(pkg, orc, dims, m, B, True, 2)
