@@ -1008,7 +1008,8 @@ __global__ __launch_bounds__(256, NT == 8 && !NDA && !DAO && (sizeof(OT) == 4 ||
             // dA^T[k][b] += sum_c W[k][c] dZ[b][c] over this chunk's 64 columns
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
-                if (sizeof(OT) == 4 && WM == kWGeneric && 32 * s >= a.d_out) break;   // (no columns; uniform)
+                // (no columns; uniform.  bf16 products are too short for this to show: 7 models 0.98 to 1.00 times as fast)
+                if (sizeof(OT) == 4 && WM == kWGeneric && 32 * s >= a.d_out) break;
                 const Frag<OT> wf = *reinterpret_cast<const Frag<OT>*>(&wlds[wave][j][32 * s + 8 * q]);
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) {
@@ -1768,6 +1769,10 @@ hipError_t launch_softmax(lc_handle* h, bool eval, int loss_offset) {
 // 128-512-192-10, 24 replicas of 100, fp32: 103 -> 118 us; 64-448-192-10, 16 of 64, bf16: 40 -> 43;
 // 64-768-300-10, 13 of 128, bf16: 69 -> 79.  Where more is saved: 64-256-1024-10, 16 of 16, bf16:
 // 60 -> 50; 128-256-1024-10, 16 of 100, fp32: 178 -> 108.
+// At 128 samples one workgroup per CU is counted as a place.  With fp32 operands the kernel's tiles leave room for no more; two
+// with bf16 operands fit, but a chunk then takes each of them about twice as long (2.5 us of a step alone, 4.7 to 5.4 beside
+// another: 11856 shared walks of 2988 drawn models).  2302 models of 64 .. 1024 inputs, 64 .. 2048 and 129 .. 2048 units, 2 .. 40
+// workers, 5 steps, times as fast as without shares, mean (least): one place 1.101 (0.92), two 1.104 (0.87).
 int backward_shares(const lc_handle* h, int l) {
     if (h->stream_weights || l < 2) return 1;
     const LayerGeom& g = h->layer[l];
@@ -1775,7 +1780,7 @@ int backward_shares(const lc_handle* h, int l) {
     const int64_t base = static_cast<int64_t>(h->m) * (g.dp_in / 64);
     const int64_t cus = compute_units();
     if (base >= cus || n_cc < 3) return 1;
-    const int64_t slots = h->train.Bp == 128 ? cus : 2 * cus;   // (at 128 samples the kernel's tiles leave room for one per CU)
+    const int64_t slots = h->train.Bp == 128 ? cus : 2 * cus;
     const int64_t want = (slots + base - 1) / base;
     const int64_t per = (n_cc + want - 1) / want;   // chunks per workgroup
     const int64_t shares = (n_cc + per - 1) / per, blocks = base * shares;
