@@ -795,10 +795,14 @@ __global__ __launch_bounds__(256, NT == 8 && !NDA && !DAO && (sizeof(OT) == 4 ||
     const float* Wr = a.Xr + g * a.xr_stride + a.w_off;
     float* Vw = a.V ? a.V + g * a.x_stride + a.w_off : nullptr;
     const float* Va = DAO ? nullptr : a.Aux + g * a.aux_stride + a.w_off;
-    // kPair: place of row k0 + 4 q + r (past d_in: of the last row), columns c0 + 4 j and on, as a base that is the same for the
-    // whole wavefront and byte offsets that a lane keeps for the walk.  (The other instances gain nothing from that, whole
-    // steps 0.97 to 1.02 times as fast, and the first layer's at 128 bf16 samples lose a workgroup per CU: 184 registers, 168 without.
-    // One step of 784-512-512-10, 8 workers of 128: 75.4 and 73.7 us; 5 of 1024-704-256-10, 12 of 128: 464 and 457.)
+    // Place of row k0 + 4 q + r (past d_in: of the last row), columns c0 + 4 j and on.  kPair: a base that is the same for the
+    // whole wavefront and byte offsets that a lane keeps for the walk, which leaves registers free.  (Instances that do not
+    // need them gain nothing from that: whole steps 0.97 to 1.02 times as fast.)
+    // Not for the first layer's whole rows at 128 bf16 samples (kRowBases: a pointer to the row, and the column beside it), which
+    // hold 184 registers with such places and 168 without, so that three workgroups share a CU: one step of 784-512-512-10,
+    // 8 workers of 128, 75.6 and 74.8 us; 5 of 1024-704-256-10, 12 of 128, 465 and 460.  The others are faster with them: 5
+    // steps of 2048-1500-1000-100, fp32, 12 of 100, 3573 us, 3626 without; 784-500-300-10, 16 of 100, 678 and 682.
+    constexpr bool kRowBases = NDA && NT == 8 && sizeof(OT) == 2 && (WM == kWVector || WM == kWVectorStream);
     const int last = a.d_in - 1, back = k0 < last ? k0 : last;
     unsigned woff[4];
 #pragma unroll
@@ -807,8 +811,15 @@ __global__ __launch_bounds__(256, NT == 8 && !NDA && !DAO && (sizeof(OT) == 4 ||
         woff[r] = 4u * (static_cast<unsigned>((row < last ? row : last) - back) * static_cast<unsigned>(a.d_out) + 4u * j);
     }
     auto place = [&](auto* base, int r, int c0) {
-        using C = std::conditional_t<std::is_const_v<std::remove_pointer_t<decltype(base)>>, const char, char>;
-        return reinterpret_cast<decltype(base)>(reinterpret_cast<C*>(base + static_cast<int64_t>(back) * a.d_out + c0) + woff[r]);
+        if constexpr (kPair) {
+            using C = std::conditional_t<std::is_const_v<std::remove_pointer_t<decltype(base)>>, const char, char>;
+            return reinterpret_cast<decltype(base)>(reinterpret_cast<C*>(base + static_cast<int64_t>(back) * a.d_out + c0) + woff[r]);
+        } else {
+            const int row = k0 + 4 * q + r;
+            auto* p = base + static_cast<int64_t>(row < a.d_in ? row : last) * a.d_out;
+            if constexpr (kRowBases) return p;
+            else return p + c0 + 4 * j;
+        }
     };
     const OT* AT = static_cast<const OT*>(a.a_fm) + static_cast<int64_t>(g) * a.dp_in * Bp;
     const OT* dZ = static_cast<const OT*>(a.dz_bm) + static_cast<int64_t>(g) * Bp * a.dp_out;
@@ -879,14 +890,11 @@ __global__ __launch_bounds__(256, NT == 8 && !NDA && !DAO && (sizeof(OT) == 4 ||
             } else {
                 // rows past d_in read the last row instead (no branch between the loads); their
                 // weights are zeroed when used and they are never stored
-                const int rr = row < a.d_in ? row : a.d_in - 1;
-                const float* wp = kPair ? place(Wr, r, c0) : Wr + static_cast<int64_t>(rr) * a.d_out;
-                const float* vp = kPair ? place(Va, r, c0) : Va + static_cast<int64_t>(rr) * a.d_out;
-                const int at = kPair ? 0 : c0 + 4 * j;
+                const int at = kRowBases ? c0 + 4 * j : 0;
                 // (weights that all replicas share are wanted in the L2 by the neighbouring blocks)
-                if (WM == kWVectorStream && a.shared_w) ww[r] = load_wm<kWVector>(wp, at, a.d_out, vec);
-                else ww[r] = load_wm<WM>(wp, at, a.d_out, vec);
-                if constexpr (!DAO) vv[r] = load_wm<WM>(vp, at, a.d_out, vec);
+                if (WM == kWVectorStream && a.shared_w) ww[r] = load_wm<kWVector>(place(Wr, r, c0), at, a.d_out, vec);
+                else ww[r] = load_wm<WM>(place(Wr, r, c0), at, a.d_out, vec);
+                if constexpr (!DAO) vv[r] = load_wm<WM>(place(Va, r, c0), at, a.d_out, vec);
             }
         }
         if constexpr (!DAO) {
@@ -998,9 +1006,9 @@ __global__ __launch_bounds__(256, NT == 8 && !NDA && !DAO && (sizeof(OT) == 4 ||
             w[r].z = weight_update(w[r].z, a.lr, v[r].z);
             w[r].w = weight_update(w[r].w, a.lr, v[r].w);
             if (row < a.d_in) {
-                const int at = kPair ? 0 : c0 + 4 * j, end = kPair ? a.d_out - (c0 + 4 * j) : a.d_out;
-                if (Vw) store_wm<WM>(kPair ? place(Vw, r, c0) : Vw + static_cast<int64_t>(row) * a.d_out, at, end, vec, v[r]);
-                if (!a.skip_x) store_wm<WM>(kPair ? place(W, r, c0) : W + static_cast<int64_t>(row) * a.d_out, at, end, vec, w[r]);
+                const int at = kRowBases ? c0 + 4 * j : 0, end = kRowBases ? a.d_out : a.d_out - (c0 + 4 * j);
+                if (Vw) store_wm<WM>(place(Vw, r, c0), at, end, vec, v[r]);
+                if (!a.skip_x) store_wm<WM>(place(W, r, c0), at, end, vec, w[r]);
             }
         }
         if (need_da) {
