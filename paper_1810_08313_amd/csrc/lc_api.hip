@@ -651,14 +651,6 @@ int lc_implicit_momentum_layers(const lc_handle* h) {
     return n;
 }
 
-int lc_first_layer_workgroup(const lc_handle* h, int32_t* columns, int32_t* wavefronts) {
-    if (!h || !columns || !wavefronts) return LC_ERR_ARG;
-    const FirstLayerPlan p = h->fl_on ? first_layer_plan(h) : FirstLayerPlan{0, 0};
-    *columns = p.columns;
-    *wavefronts = p.wavefronts;
-    return LC_OK;
-}
-
 int lc_set_deferred_update(lc_handle* h, int on) {
     if (!h) return LC_ERR_ARG;
     h->defer_x_on = on != 0;

@@ -710,10 +710,14 @@ static int wide_columns(const lc_handle* h, bool whole) {
     return 6 * r96 < 4 * r64 ? 96 : kColChunk;
 }
 
+struct FirstLayerPlan {
+    int columns, wavefronts;   // of a workgroup; 0: the layer keeps the separate launches
+};
+
 // The kernel serves layer 1 of models with at least two layers whose first-layer rows are at least one
 // column chunk long, when there are enough (replica, column chunk) pairs to fill the chip; everything
 // else keeps the row-owner backward kernel and the separate forward launch.
-FirstLayerPlan first_layer_plan(const lc_handle* h) {
+static FirstLayerPlan first_layer_plan(const lc_handle* h) {
     const FirstLayerPlan none{0, 0};
     if (h->md.kind != LC_KIND_MLP || h->L < 2) return none;
     const LayerGeom& g = h->layer[1];
@@ -755,6 +759,8 @@ FirstLayerPlan first_layer_plan(const lc_handle* h) {
     if (S.Bp == 64 && !bf16 && blocks <= cus && g.d_in >= 256) p.wavefronts = 2 * kFlWaves;   // (see kFlWaves)
     return p;
 }
+
+bool first_layer_kernel_ok(const lc_handle* h) { return first_layer_plan(h).columns != 0; }
 
 // Backward pass and update of layer 1 for the step in slot train.cur_slot, and A_1 of the step in
 // the next slot (which must have been gathered already).
@@ -808,3 +814,11 @@ hipError_t launch_first_layer(lc_handle* h) {
 }
 
 }  // namespace lc
+
+extern "C" int lc_first_layer_workgroup(const lc_handle* h, int32_t* columns, int32_t* wavefronts) {
+    if (!h || !columns || !wavefronts) return LC_ERR_ARG;
+    const lc::FirstLayerPlan p = h->fl_on ? lc::first_layer_plan(h) : lc::FirstLayerPlan{0, 0};
+    *columns = p.columns;
+    *wavefronts = p.wavefronts;
+    return LC_OK;
+}

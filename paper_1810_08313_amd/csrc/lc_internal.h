@@ -193,11 +193,7 @@ bool forward_fuses_softmax(const lc_handle* h);  // last layer's kernel also doe
 hipError_t launch_softmax(lc_handle* h, bool eval, int loss_offset);
 hipError_t launch_backward(lc_handle* h, int l, bool da_only = false);   // da_only: dZ_{l-1} only, no update
 size_t backward_share_floats(const lc_handle* h);   // scratch for the shares of dA of layers whose columns are shared out
-struct FirstLayerPlan {
-    int columns, wavefronts;   // of a workgroup; 0: the layer keeps the separate launches
-};
-FirstLayerPlan first_layer_plan(const lc_handle* h);   // layer 1: backward kernel that also runs the next step's forward
-inline bool first_layer_kernel_ok(const lc_handle* h) { return first_layer_plan(h).columns != 0; }
+bool first_layer_kernel_ok(const lc_handle* h);   // layer 1: backward kernel that also runs the next step's forward
 hipError_t launch_first_layer(lc_handle* h);
 bool implicit_layer_ok(const lc_handle* h, int l);   // layer l may keep its momentum implicitly inside a period
 void layer_weights(const lc_handle* h, int l, const float** base, int64_t* stride);   // where layer l's current parameters are read
