@@ -388,19 +388,21 @@ template <typename OT, int WM, int WMR, int CPL = 4, int PD = 1>
 __global__ __launch_bounds__(64 * kWideWaves) void first_layer_wide_kernel(FirstArgs a) {
     static_assert(sizeof(OT) == 2, "operand fragments of fp32 do not fit the register budget here");
     static_assert(CPL == 4 || (CPL == 6 && WM == kWRagged && WMR == kWRagged), "six columns: 16 and 8 bytes at any float address");
-    constexpr int NC = 16 * CPL, NH = CPL / 2;
+    constexpr int NC = 16 * CPL;
     constexpr int kPad = 8;
     constexpr int Bp = 128, NS = Bp / 32, NTH = 64 * kWideWaves;
     constexpr size_t kSliceBytes = sizeof(OT) * NC * (Bp + kPad);
-    constexpr size_t kTileBytes = 2 * kWideWaves * NH * 64 * sizeof(bf16x8);
+    constexpr size_t kTileBytes = 2 * kWideWaves * CPL * 64 * sizeof(Frag4<OT>);
     constexpr size_t kPartBytes = sizeof(float) * Bp * (NC + 4);
     constexpr size_t kWalkBytes = kSliceBytes + kTileBytes;
     __shared__ __attribute__((aligned(16))) char smem[kWalkBytes > kPartBytes ? kWalkBytes : kPartBytes];
     __shared__ float bias_s[NC];
     OT (*dzt)[Bp + kPad] = reinterpret_cast<OT (*)[Bp + kPad]>(smem);
-    // [buffer][wavefront][pair][lane]: a lane's 4 x CPL block of the tile as CPL operand fragments
-    // (columns CPL j + t, rows 4 q ..), 16 bytes per lane and pair: consecutive lanes, no bank conflicts
-    bf16x8 (*wt)[kWideWaves][NH][64] = reinterpret_cast<bf16x8 (*)[kWideWaves][NH][64]>(smem + kSliceBytes);
+    // [buffer][wavefront][pair][lane]: a lane's 4 x 4 block of the tile as 4 operand fragments
+    // (columns 4 j + t, rows 4 q ..), 16 bytes per lane and pair: consecutive lanes, no bank conflicts
+    bf16x8 (*wt)[kWideWaves][2][64] = reinterpret_cast<bf16x8 (*)[kWideWaves][2][64]>(smem + kSliceBytes);
+    // six columns: [buffer][pair of wavefronts][t][lane], rows 4 q .. of the first's tile and of the second's
+    bf16x8 (*wt32)[kWideWaves / 2][CPL][64] = reinterpret_cast<bf16x8 (*)[kWideWaves / 2][CPL][64]>(smem + kSliceBytes);
 
     const int64_t logical = xcd_logical_block(a.total_blocks);
     if (logical < 0) return;
@@ -558,38 +560,63 @@ __global__ __launch_bounds__(64 * kWideWaves) void first_layer_wide_kernel(First
                 for (int t = 0; t < CPL; ++t) x.w[r4][t] = 0.f;
             }
         }
-        // the updated tile, as the operand fragments of this lane, two together
-#pragma unroll
-        for (int h = 0; h < NH; ++h) {
-            Frag4<OT> b0, b1;
-            pack4(b0, x.w[0][2 * h], x.w[1][2 * h], x.w[2][2 * h], x.w[3][2 * h]);
-            pack4(b1, x.w[0][2 * h + 1], x.w[1][2 * h + 1], x.w[2][2 * h + 1], x.w[3][2 * h + 1]);
-            bf16x8 both;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                both[e] = b0.v[e];
-                both[4 + e] = b1.v[e];
-            }
-            wt[r & 1][wave][h][lane] = both;
-        }
-        __syncthreads();
+        // the updated tile as operand fragments of this lane, then
         // Z_1'[these 16 samples] += A_0'[.., the round's 128 rows] W_1[the round's 128 rows, :]
+        if constexpr (CPL == 6) {
+            // 32-deep products of two tiles at a time, each round's sum formed from zero.  (In one sum over all inputs, as below,
+            // X and V were 1.024 and 1.038 times as far from 64 bits as with the launches per layer, 1.03 and 1.05 from 1700
+            // inputs on; now 0.996 and 0.993, 0.985 and 0.982: 300 drawn models, two seeds.  3072-1500-1000-100, 16 workers of 100,
+            // 5 steps: 2254 us either way.  Sums of four rounds added up in LDS: no nearer, 2264 us.)
 #pragma unroll
-        for (int u = 0; u < kWideWaves; ++u) {
-            Frag4<OT> an;
+            for (int t = 0; t < CPL; ++t) {
+                Frag4<OT> b;
+                pack4(b, x.w[0][t], x.w[1][t], x.w[2][t], x.w[3][t]);
+                reinterpret_cast<bf16x4*>(&wt32[r & 1][wave / 2][t][lane])[wave % 2] = b.v;
+            }
+            __syncthreads();
 #pragma unroll
-            for (int e = 0; e < 4; ++e) an.v[e] = x.an[u / 2].v[4 * (u % 2) + e];
+            for (int t = 0; t < CPL; t += 2) {
+                f32x4 z0{}, z1{};
 #pragma unroll
-            for (int h = 0; h < NH; ++h) {
-                const bf16x8 both = wt[r & 1][u][h][lane];
-                Frag4<OT> f0, f1;
+                for (int u = 0; u < kWideWaves / 2; ++u) {
+                    z0 = mma8(x.an[u], Frag<OT>{wt32[r & 1][u][t][lane]}, z0);
+                    z1 = mma8(x.an[u], Frag<OT>{wt32[r & 1][u][t + 1][lane]}, z1);
+                }
+                facc[t] += z0;
+                facc[t + 1] += z1;
+            }
+        } else {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                Frag4<OT> b0, b1;
+                pack4(b0, x.w[0][2 * h], x.w[1][2 * h], x.w[2][2 * h], x.w[3][2 * h]);
+                pack4(b1, x.w[0][2 * h + 1], x.w[1][2 * h + 1], x.w[2][2 * h + 1], x.w[3][2 * h + 1]);
+                bf16x8 both;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    f0.v[e] = both[e];
-                    f1.v[e] = both[4 + e];
+                    both[e] = b0.v[e];
+                    both[4 + e] = b1.v[e];
                 }
-                facc[2 * h] = mma4(an, f0, facc[2 * h]);
-                facc[2 * h + 1] = mma4(an, f1, facc[2 * h + 1]);
+                wt[r & 1][wave][h][lane] = both;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < kWideWaves; ++u) {
+                Frag4<OT> an;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) an.v[e] = x.an[u / 2].v[4 * (u % 2) + e];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const bf16x8 both = wt[r & 1][u][h][lane];
+                    Frag4<OT> f0, f1;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        f0.v[e] = both[e];
+                        f1.v[e] = both[4 + e];
+                    }
+                    facc[2 * h] = mma4(an, f0, facc[2 * h]);
+                    facc[2 * h + 1] = mma4(an, f1, facc[2 * h + 1]);
+                }
             }
         }
     };

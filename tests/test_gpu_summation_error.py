@@ -70,3 +70,53 @@ def test_forward_products_of_many_workers(pkg, dims, m, B):
     few, many = _error(pkg, dims, 4, B, 4, set_resident=False), _error(pkg, dims, m, B, 4, set_resident=False)
     _say(f"error dims={dims} B={B}: 4 workers {few:.3e}, {m} workers {many:.3e}")
     assert many < 1.1 * few
+
+
+def _forward_errors(pkg, dims, m, B, calls, positive):
+    """How far the last layer's weight gradient of a call's second step is from 64 bits, with the first layer's kernel and with
+    the launches per layer, rms over several calls.  bf16 models of two layers whose weights do not move (a rate of 1e-12,
+    no momentum): what differs are activations of the first layer that a sum just beside them rounds the other way."""
+    import torch
+    N, sl = 1000, dict(_blocks(dims))
+    rng, bf16 = np.random.default_rng(7), synth.bf16_representable
+    labels = rng.integers(0, dims[-1], N).astype(np.int32)
+    data, x1 = bf16(rng.random((N, dims[0]), dtype=np.float32)), bf16(synth.init_params(9, dims))
+    if positive:
+        x1[sl["W1"]] = bf16(rng.random(dims[0] * dims[1], dtype=np.float32) * (4.0 / dims[0]))
+    model = pkg.make_model(pkg.KIND_MLP, dims, B=B, N=N, E=64, lr=1e-12, beta=0.0, bf16=True)
+    runs = [pkg.LocalSGD(m, model, 9, x1, data, labels) for _ in range(2)]
+    for run, fused in zip(runs, (True, False)):
+        run.set_resident(False)
+        run.set_first_layer_fusion(fused)
+    assert [run.first_layer_workgroup() for run in runs] == [(96, 8), (0, 0)]
+    x = torch.from_numpy(x1).cuda().double()
+    W1, W2 = x[sl["W1"]].view(dims[0], dims[1]), x[sl["W2"]].view(dims[1], dims[2])
+    data, labels = torch.from_numpy(data).cuda().double(), torch.from_numpy(labels).cuda().long()
+    err = [0.0, 0.0]
+    for _ in range(calls):
+        for run in runs:
+            run.local_steps(2)
+        idx, V = runs[0].last_indices(), [run.V[:, sl["W2"]].double() for run in runs]
+        for i in range(m):
+            at = torch.from_numpy(np.asarray(idx[i], np.int64)).cuda()
+            a = torch.relu(data[at] @ W1 + x[sl["b1"]]).float().bfloat16().double()
+            dz = torch.softmax(a @ W2 + x[sl["b2"]], 1)
+            dz[torch.arange(B), labels[at]] -= 1.0
+            g = (a.t() @ (dz / B).float().bfloat16().double()).reshape(-1)
+            for r in range(2):
+                err[r] += float(((V[r][i] - g).norm() / g.norm()) ** 2) / (m * calls)
+    for run in runs:
+        run.close()
+    return np.sqrt(err)
+
+
+def test_first_layer_with_chunks_of_96_columns(pkg):
+    """Geometric mean over six models, since one sum beside a rounding step moves all deltas of a sample.  Positive products, of
+    which every further one makes the sum larger, tell long chains best.  (One sum over all inputs: 1.22.)"""
+    ratios = []
+    for dims, m, B in [([3072, 1500, 10], 12, 128), ([3072, 1400, 100], 16, 100), ([784, 673, 10], 32, 70)]:
+        for positive in (False, True):
+            on, off = _forward_errors(pkg, dims, m, B, 12, positive)
+            _say(f"error dims={dims} B={B} positive={positive}: chunks of 96 columns {on:.3e}, launches per layer {off:.3e}")
+            ratios.append(on / off)
+    assert np.exp(np.mean(np.log(ratios))) < 1.1, ratios
