@@ -622,9 +622,10 @@ __global__ __launch_bounds__(kResThreads) void resident_kernel(ResArgs args) {
 //   one wavefront per batch tile: softmax cross-entropy and dZ; all: a batch that was requested a step ago
 //     into LDS, and another one requested
 //   dW = A_0^T dZ and the update of the own tile
-// What bounds it is latency: 64-10, 4 workers, batch 32, one period of 4 steps, 14.2 us -- before the first
-// step 4 us (the indices' hash, one round trip for rows, state and labels), 1.6 us a step, 3 us for the averaging
-// step in the launch.  With a gather kernel before it, W in LDS only and the softmax through LDS it was 18.2 us.
+// What bounds it is latency: 64-10, 4 workers, batch 32, one period of 4 steps, 14.2 us -- 1.7 us a step (1 to 16
+// steps: 9.1 to 34.7 us), 2.5 us for the averaging step in the launch (1 to 4 periods: 14.2 to 42.3 us), 4.9 us for the
+// launch itself, the indices' hash and one round trip for rows, state and labels.  With a gather kernel before it, W in
+// LDS only and the softmax through LDS it was 18.2 us.
 struct Res1Args {
     float* X;
     float* V;
